@@ -76,6 +76,19 @@ def test_hadamard_rotation_bit_exact(rows, K, block):
     assert torch.equal(y, got)
 
 
+@pytest.mark.parametrize("rows,K,block", [(1, 8, 8), (3, 24, 8), (1, 4104, 8), (257, 16, 16), (33, 128, 128), (7, 2048, 2048),
+                                          (3, 12288, 4096), (3, 24576, 8192), (5, 20, 4), (3, 5, 1)])
+def test_hadamard_segment_edges_bit_exact(rows, K, block):
+    """Tensors that end inside a segment of the kernel, every group of stages present and absent, and tensors that are no
+    whole number of 16-byte chunks; exact, because FP64 sums of FP16 numbers are."""
+    x = wl.make_activations(rows, K, 70 + block % 89, DEV)
+    ref = tr.rotate_fp16(x.cpu().numpy(), block)
+    assert np.array_equal(_bits(api.hadamard_rotate(x, block).cpu().numpy()), _bits(ref))
+    odd = torch.empty(rows * K + 1, dtype=torch.float16, device=DEV)[1:].view(rows, K)      # 2-byte aligned only
+    odd.copy_(x)
+    assert np.array_equal(_bits(api.hadamard_rotate(odd, block, out=odd).cpu().numpy()), _bits(ref))
+
+
 def test_rotated_layer_matches_the_oracle_and_the_unrotated_product():
     M, K, N = 33, 1024, 128
     x = wl.make_activations(M, K, 64, DEV)
