@@ -4,6 +4,8 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "qoq_internal.h"
 
 namespace qoq {
@@ -39,133 +41,177 @@ __device__ inline uint16_t make_scale(double range, double steps)
 
 __device__ inline int round_half_away(double v) { return (int)round(v); }
 
-__device__ inline float wave_max(float v)
+__device__ inline void write_header(const BlobLayout& L, uint8_t* blob)
 {
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ inline float wave_min(float v)
-{
-    for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ inline int wave_max_i(int v)
-{
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ inline int wave_min_i(int v)
-{
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-    return v;
+    BlobHeader h;
+    h.magic = kMagic; h.version = kVersion; h.N = L.N; h.K = L.K; h.mode = L.mode; h.group = kGroup;
+    h.codes_off = L.codes_off; h.meta_off = L.meta_off; h.scale_off = L.scale_off;
+    h.zero_off = L.zero_off; h.total = L.total;
+    *reinterpret_cast<BlobHeader*>(blob) = h;
 }
 
-// Row-wide min and max of an FP16 row, result broadcast to every thread of the block.
-__device__ inline void row_min_max(const __half* row, int64_t K, float& lo, float& hi)
+typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
+
+// Cross-lane steps inside a row of 16 lanes: after a rotation by 8 and one by 4, the four lanes 4 apart agree.
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v)
 {
-    __shared__ float s_lo[kThreads / 64], s_hi[kThreads / 64];
-    float mn = 0.f, mx = 0.f;  // the range always contains 0
-    for (int64_t k = (int64_t)threadIdx.x * 2; k < K; k += kThreads * 2) {
-        const __half2 v = *reinterpret_cast<const __half2*>(row + k);
-        const float a = __low2float(v), b = __high2float(v);
-        mn = fminf(mn, fminf(a, b));
-        mx = fmaxf(mx, fmaxf(a, b));
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+constexpr int kRowRor4 = 0x124, kRowRor8 = 0x128;
+__device__ __forceinline__ float quarter_max(float v)
+{
+    v = fmaxf(v, dpp_f32<kRowRor8>(v));
+    return fmaxf(v, dpp_f32<kRowRor4>(v));
+}
+__device__ __forceinline__ float quarter_min(float v)
+{
+    v = fminf(v, dpp_f32<kRowRor8>(v));
+    return fminf(v, dpp_f32<kRowRor4>(v));
+}
+
+// FP16 weights -> packed layer, group or per-channel mode.  One workgroup per four adjacent output channels (rows i ..
+// i + 3 of one 16-row fragment, whose 16-byte code words are adjacent in memory); thread (row r, k-block kb, group q) of
+// the workgroup owns, per group of 128 channels, the 32 weights whose codes make up one 16-byte lane word: it reads four
+// 16-byte chunks and writes the word whole.  The row is read once and kept in registers (CH groups per thread) between
+// the pass that finds its range and the pass that quantizes; rows of more than 256 groups are read twice (CH = 0).
+//
+// Every decision is taken in FP32 and is the one exact arithmetic takes:
+//   level 1   round_half_away(w / s0) of two FP16 numbers: |w / s0| < 256 is on a midpoint or at least 2^-12 away from
+//             every one; w * fl(1 / s0) is within 3e-5 of it, and pushed 1e-4 away from zero it lands on the same side
+//             (the argument of the activation quantizer).  Per-channel codes are the same quotient plus an integer.
+//   level 2   quotients of small integers by s1 <= 16 (by 15 for s1 itself): multiples of 1/32 (1/15), nudged by 1e-3.
+// Bound by HBM: 22016 x 4096 in group mode in 54 us (226 MB, 4.2 TB/s; a copy moves them in 42 us).  One division of
+// doubles per weight and 4-byte stores 16 bytes apart kept one row per workgroup at 213 us, and it wrote the header by
+// a launch of its own.
+template <bool GROUP, int CH>
+__global__ __launch_bounds__(1024) void pack_kernel(const __half* __restrict__ w, BlobLayout L, uint8_t* __restrict__ blob)
+{
+    __shared__ float s_lo[16][4], s_hi[16][4];
+    __shared__ float s_scale[4], s_zero[4];
+    const int tid = threadIdx.x, r = tid & 3, kb = (tid >> 2) & 3, q = tid >> 4;
+    const int G = (int)L.G, gstep = (int)blockDim.x >> 4;
+    // Workgroups go round the eight XCDs; the four that share 256-byte runs of codes (channels 16 apart) follow each
+    // other on one of them, so that its L2 puts whole lines together.
+    int64_t id = blockIdx.x;
+    if (id < (int64_t)(gridDim.x & ~31u)) id = ((id >> 5) << 5) + ((id & 7) << 2) + ((id >> 3) & 3);
+    const int64_t nf = id >> 2;
+    const int ib = (int)(id & 3);
+    const int64_t n = (nf >> 2) * 64 + 16 * ib + 4 * (nf & 3) + r;
+    const int i = 4 * ib + r;
+    const uint4* row = reinterpret_cast<const uint4*>(w + n * L.K);
+    uint4 v[CH > 0 ? CH : 1][4];
+    auto load = [&](uint4 (&x)[4], int g) __attribute__((always_inline)) {
+        const uint4* src = row + (g < G ? g : 0) * 16 + kb * 2;          // past the end: values that are not used
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] = src[(c >> 1) * 8 + (c & 1)];
+    };
+    hv2 mn2 = {(_Float16)0.f, (_Float16)0.f}, mx2 = mn2;                 // the range always contains 0
+    auto scan = [&](const uint4 (&x)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t u[4] = {x[c].x, x[c].y, x[c].z, x[c].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const hv2 p = __builtin_bit_cast(hv2, u[e]);
+                mn2 = __builtin_elementwise_min(mn2, p);
+                mx2 = __builtin_elementwise_max(mx2, p);
+            }
+        }
+    };
+    if constexpr (CH > 0) {
+#pragma unroll
+        for (int c = 0; c < CH; ++c) load(v[c], q + c * gstep);
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+            if (q + c * gstep < G) scan(v[c]);
+    } else {
+        for (int g = q; g < G; g += gstep) { load(v[0], g); scan(v[0]); }
     }
-    mn = wave_min(mn);
-    mx = wave_max(mx);
-    if ((threadIdx.x & 63) == 0) { s_lo[threadIdx.x >> 6] = mn; s_hi[threadIdx.x >> 6] = mx; }
+    float lo = quarter_min(fminf((float)mn2.x, (float)mn2.y)), hi = quarter_max(fmaxf((float)mx2.x, (float)mx2.y));
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) { lo = fminf(lo, __shfl_xor(lo, o, 64)); hi = fmaxf(hi, __shfl_xor(hi, o, 64)); }
+    if ((tid & 63) < 4) { s_lo[tid >> 6][r] = lo; s_hi[tid >> 6][r] = hi; }
     __syncthreads();
-    lo = s_lo[0]; hi = s_hi[0];
-    for (int w = 1; w < kThreads / 64; ++w) { lo = fminf(lo, s_lo[w]); hi = fmaxf(hi, s_hi[w]); }
-}
-
-// Place this lane's two adjacent codes (k_local = 2*lane, 2*lane+1) into their packed dword,
-// combine the four lanes that share a dword, and let the first of them store it.
-__device__ inline void store_group_codes(uint8_t* codes, int64_t nf, int i, int64_t g, int64_t G, int lane,
-                                         int code_a, int code_b)
-{
-    int sh_a, sh_b;
-    const size_t off = code_dword_offset(nf, i, g, G, 2 * lane, sh_a);
-    (void)code_dword_offset(nf, i, g, G, 2 * lane + 1, sh_b);
-    uint32_t v = ((uint32_t)code_a << sh_a) | ((uint32_t)code_b << sh_b);
-    v |= __shfl_xor(v, 1, 64);
-    v |= __shfl_xor(v, 2, 64);
-    if ((lane & 3) == 0) *reinterpret_cast<uint32_t*>(codes + off) = v;
-}
-
-// One block per logical output channel; each wave quantizes one group of 128 at a time.
-__global__ __launch_bounds__(kThreads) void pack_group_kernel(const __half* __restrict__ w, BlobLayout L,
-                                                              uint8_t* __restrict__ blob)
-{
-    const int64_t n = blockIdx.x;
-    const __half* row = w + n * L.K;
-    float lo, hi;
-    row_min_max(row, L.K, lo, hi);
-    const double absmax = fmax((double)hi, -(double)lo);
-    const uint16_t s0_bits = make_scale(absmax, 119.0);  // level 1, protective range (Eq. 3)
-    const double s0 = (double)half_bits_to_float(s0_bits);
-    if (threadIdx.x == 0) reinterpret_cast<uint16_t*>(blob + L.scale_off)[n] = s0_bits;
-
-    int64_t nf; int i;
-    phys_row(n, nf, i);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint8_t* codes = blob + L.codes_off;
+    if (tid < 4) {                                                       // thread r settles row r
+        for (int x = 1; x < ((int)blockDim.x + 63) >> 6; ++x) { lo = fminf(lo, s_lo[x][r]); hi = fmaxf(hi, s_hi[x][r]); }
+        // level 1 with the protective range (Eq. 3), or the per-channel 4-bit scale
+        const uint16_t bits = GROUP ? make_scale(fmax((double)hi, -(double)lo), 119.0) : make_scale((double)hi - (double)lo, 15.0);
+        const float sc = half_bits_to_float(bits);
+        s_scale[r] = sc;
+        reinterpret_cast<uint16_t*>(blob + L.scale_off)[n] = bits;
+        if (!GROUP) {
+            const int z = max(0, min(15, round_half_away(-(double)lo / (double)sc)));
+            s_zero[r] = (float)z;
+            (blob + L.zero_off)[n] = (uint8_t)z;
+        }
+    }
+    if (blockIdx.x == 0 && tid == 4) write_header(L, blob);
+    __syncthreads();
+    const float inv = 1.0f / s_scale[r];
+    const float half_up = GROUP ? 0.f : s_zero[r] + (0.5f + 1e-4f);
+    uint4* codes = reinterpret_cast<uint4*>(blob + L.codes_off);
     uint16_t* meta = reinterpret_cast<uint16_t*>(blob + L.meta_off);
-    for (int64_t g = wave; g < L.G; g += kThreads / 64) {
-        const __half2 v = *reinterpret_cast<const __half2*>(row + g * kGroup + 2 * lane);
-        int qa = round_half_away((double)__low2float(v) / s0);
-        int qb = round_half_away((double)__high2float(v) / s0);
-        qa = max(-119, min(119, qa));
-        qb = max(-119, min(119, qb));
-        // level 2 (Eq. 4): asymmetric UINT4 on the INT8 intermediates, range widened to hold 0
-        const int gmin = wave_min_i(min(min(qa, qb), 0));
-        const int gmax = wave_max_i(max(max(qa, qb), 0));
-        const int s1 = max(1, (gmax - gmin + 14) / 15);
-        const int z = min(15, (2 * (-gmin) + s1) / (2 * s1));
-        const int na = 2 * qa + (2 * z + 1) * s1, nb = 2 * qb + (2 * z + 1) * s1;
-        const int ca = na <= 0 ? 0 : min(15, na / (2 * s1));
-        const int cb = nb <= 0 ? 0 : min(15, nb / (2 * s1));
-        store_group_codes(codes, nf, i, g, L.G, lane, ca, cb);
-        if (lane == 0)
-            meta[meta_offset(nf, i, g, L.N / 16) / 2] = (uint16_t)(s1 | (((128 - z * s1) & 0xFF) << 8));
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void pack_channel_kernel(const __half* __restrict__ w, BlobLayout L,
-                                                                uint8_t* __restrict__ blob)
-{
-    const int64_t n = blockIdx.x;
-    const __half* row = w + n * L.K;
-    float lo, hi;
-    row_min_max(row, L.K, lo, hi);
-    const uint16_t sw_bits = make_scale((double)hi - (double)lo, 15.0);
-    const double sw = (double)half_bits_to_float(sw_bits);
-    const int z = max(0, min(15, round_half_away(-(double)lo / sw)));
-    if (threadIdx.x == 0) {
-        reinterpret_cast<uint16_t*>(blob + L.scale_off)[n] = sw_bits;
-        (blob + L.zero_off)[n] = (uint8_t)z;
-    }
-    int64_t nf; int i;
-    phys_row(n, nf, i);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint8_t* codes = blob + L.codes_off;
-    for (int64_t g = wave; g < L.G; g += kThreads / 64) {
-        const __half2 v = *reinterpret_cast<const __half2*>(row + g * kGroup + 2 * lane);
-        const int ca = max(0, min(15, round_half_away((double)__low2float(v) / sw + (double)z)));
-        const int cb = max(0, min(15, round_half_away((double)__high2float(v) / sw + (double)z)));
-        store_group_codes(codes, nf, i, g, L.G, lane, ca, cb);
+    auto quantize = [&](const uint4 (&x)[4], int g) __attribute__((always_inline)) {
+        float f[32];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t u[4] = {x[c].x, x[c].y, x[c].z, x[c].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const hv2 p = __builtin_bit_cast(hv2, u[e]);
+                f[8 * c + 2 * e] = (float)p.x;
+                f[8 * c + 2 * e + 1] = (float)p.y;
+            }
+        }
+        float scale2 = inv, offset = half_up;                            // code = floor(f * scale2 + offset), clamped
+        if constexpr (GROUP) {
+            float gmin = 0.f, gmax = 0.f;
+#pragma unroll
+            for (int e = 0; e < 32; ++e) {
+                const float t = f[e] * inv;
+                f[e] = __builtin_amdgcn_fmed3f(truncf(t + copysignf(0.5f + 1e-4f, t)), -119.f, 119.f);
+                gmin = fminf(gmin, f[e]);
+                gmax = fmaxf(gmax, f[e]);
+            }
+            // level 2 (Eq. 4): asymmetric UINT4 on the INT8 intermediates, range widened to hold 0
+            gmin = quarter_min(gmin);
+            gmax = quarter_max(gmax);
+            const float s1 = fmaxf(1.f, truncf((gmax - gmin + 14.01f) * (1.f / 15.f)));   // ceil(range / 15)
+            scale2 = __builtin_amdgcn_rcpf(s1);
+            const float z = fminf(15.f, truncf(fmaf(-gmin, scale2, 0.5f + 1e-3f)));
+            offset = z + (0.5f + 1e-3f);
+            if (kb == 0 && g < G) {
+                const int s = (int)s1, zs = (int)z * s;
+                meta[meta_offset(nf, i, g, L.N / 16) / 2] = (uint16_t)(s | (((128 - zs) & 0xFF) << 8));
+            }
+        }
+        uint32_t d[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {                                    // chunk c = k-step c / 2, half c % 2 of its 16 codes
+            d[c] = 0;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const uint32_t code = (uint32_t)(int)__builtin_amdgcn_fmed3f(fmaf(f[8 * c + t], scale2, offset), 0.f, 15.f);
+                d[c] |= code << (8 * (t & 3) + 4 * (t >> 2));
+            }
+        }
+        if (g < G) codes[(nf * G + g) * 64 + kb * 16 + i] = make_uint4(d[0], d[1], d[2], d[3]);
+    };
+    if constexpr (CH > 0) {
+#pragma unroll
+        for (int c = 0; c < CH; ++c) quantize(v[c], q + c * gstep);
+    } else {
+        for (int g0 = 0; g0 < G; g0 += gstep) {                          // all lanes of a row of 16 stay together
+            load(v[0], g0 + q);
+            quantize(v[0], g0 + q);
+        }
     }
 }
 
 __global__ void write_header_kernel(BlobLayout L, uint8_t* blob)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        BlobHeader h;
-        h.magic = kMagic; h.version = kVersion; h.N = L.N; h.K = L.K; h.mode = L.mode; h.group = kGroup;
-        h.codes_off = L.codes_off; h.meta_off = L.meta_off; h.scale_off = L.scale_off;
-        h.zero_off = L.zero_off; h.total = L.total;
-        *reinterpret_cast<BlobHeader*>(blob) = h;
-    }
+    if (threadIdx.x == 0 && blockIdx.x == 0) write_header(L, blob);
 }
 
 // One thread per packed dword: gathers its 8 codes from the logical [N, K] byte tensor.
@@ -238,13 +284,24 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(const uint8_t* __restr
 
 }  // namespace
 
+// As few groups per thread as 1024 threads allow (64 groups at a time): short rows then leave registers for more waves.
+template <bool GROUP>
+static void launch_pack(const __half* w, const BlobLayout& L, uint8_t* blob, hipStream_t s)
+{
+    const int64_t per = L.G <= 64 ? 1 : L.G <= 128 ? 2 : 4;
+    const int64_t groups = std::min<int64_t>(64, (L.G + per - 1) / per);
+    const dim3 grid((unsigned)(L.N / 4)), block((unsigned)((groups * 16 + 63) / 64 * 64));
+    if (L.G <= 64) pack_kernel<GROUP, 1><<<grid, block, 0, s>>>(w, L, blob);
+    else if (L.G <= 128) pack_kernel<GROUP, 2><<<grid, block, 0, s>>>(w, L, blob);
+    else if (L.G <= 256) pack_kernel<GROUP, 4><<<grid, block, 0, s>>>(w, L, blob);
+    else pack_kernel<GROUP, 0><<<grid, block, 0, s>>>(w, L, blob);
+}
+
 hipError_t launch_pack_weights(const void* w_fp16, const BlobLayout& L, uint8_t* blob, hipStream_t s)
 {
-    write_header_kernel<<<1, 64, 0, s>>>(L, blob);
-    if (L.mode == 0)
-        pack_group_kernel<<<dim3((unsigned)L.N), kThreads, 0, s>>>(static_cast<const __half*>(w_fp16), L, blob);
-    else
-        pack_channel_kernel<<<dim3((unsigned)L.N), kThreads, 0, s>>>(static_cast<const __half*>(w_fp16), L, blob);
+    const __half* w = static_cast<const __half*>(w_fp16);
+    if (L.mode == 0) launch_pack<true>(w, L, blob, s);
+    else launch_pack<false>(w, L, blob, s);
     return hipGetLastError();
 }
 

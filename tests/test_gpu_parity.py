@@ -72,6 +72,32 @@ def test_pack_per_channel_matches_oracle(api, N, K):
     assert (_np(q).astype(np.int64) == code).all()
 
 
+@pytest.mark.parametrize("N,K", [(64, 8192), (192, 8320), (64, 16512), (64, 32768), (128, 33024)])
+def test_pack_register_and_reread_rows(api, N, K):
+    """Rows of one, two and four groups per thread, with idle threads, and rows that are read twice; channels with ties on
+    rounding midpoints of both levels, subnormal values and scales, a single nonzero weight, one sign.  Whole numbers
+    and one correctly rounded quotient: exact."""
+    w, _ = rand_inputs(0, N, K, seed=N + K)
+    w[9] = (torch.arange(K, device=DEV) % 239 - 119).to(torch.float16) * 0.5            # level-1 midpoints at s0 = 1
+    w[9, 1] = 119.0
+    w[10] = (torch.arange(K, device=DEV) % 31).to(torch.float16) * 0.5                  # per-channel midpoints at sw = 1
+    w[11] = w[12] * 2.0 ** -14                                                          # subnormal weights and scale
+    w[13] = 0
+    w[13, K - 1] = 2.0 ** -24                                                           # the scale rounds to zero
+    w[14] = -w[14].abs()
+    blob = api.pack_weights(w, api.QOQ_GROUP128)
+    q, s1, z, s0 = api.unpack_weights(blob, N, K, api.QOQ_GROUP128)
+    ref = qq.progressive_quant(_np(w))
+    assert (_np(s0).view(np.uint16) == ref["s0"].view(np.uint16)).all()
+    assert (_np(s1).astype(np.int64) == ref["s1"]).all() and (_np(z).astype(np.int64) == ref["z"]).all()
+    assert (_np(q).astype(np.int64) == ref["Q"]).all()
+    blob = api.pack_weights(w, api.QOQ_PER_CHANNEL)
+    q, _, z, sw = api.unpack_weights(blob, N, K, api.QOQ_PER_CHANNEL)
+    code, zr, swr = qq.per_channel_quant(_np(w))
+    assert (_np(sw).view(np.uint16) == swr.view(np.uint16)).all()
+    assert (_np(z).astype(np.int64) == zr).all() and (_np(q).astype(np.int64) == code).all()
+
+
 def test_pack_quantized_roundtrip(api):
     rng = np.random.default_rng(3)
     N, K = 128, 384
