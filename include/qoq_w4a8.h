@@ -194,6 +194,9 @@ int qoq_w4a8_linear(const void* x_fp16, const void* packed, int64_t M, int64_t N
  *   qoq_channel_absmax     x_fp16 [M, K] device -> absmax [K] FP32 device (overwritten).  K % 8 == 0.
  *   qoq_channel_order_host salience [K] FP32 HOST -> perm [K] INT32 HOST: new channel j = old channel perm[j].
  *                          Every salience must be finite (a NaN has no place in an order): else QOQ_ERR_SHAPE.
+ *   qoq_channel_order      the same order computed on the device: salience [K] FP32 device -> perm [K] INT32 device,
+ *                          K <= 32768; nonfinite [1] INT32 device receives 1 if some salience is not finite (perm is
+ *                          then meaningless), else 0.
  *   qoq_gather_channels    dst[r, j] = src[r, perm[j]], FP16 [rows, K] device, perm [K] INT32 device, not in place.
  *   qoq_quant_act_per_token_reordered   qoq_quant_act_per_token of x[:, perm] in one pass (K <= 32768).
  * perm entries outside [0, K) are clamped (a kernel cannot report them).
@@ -204,6 +207,7 @@ int qoq_w4a8_linear(const void* x_fp16, const void* packed, int64_t M, int64_t N
  * Errors as above (QOQ_ERR_SHAPE, QOQ_ERR_NULL, QOQ_ERR_ALIGN, QOQ_ERR_ARCH, QOQ_ERR_HIP). */
 int qoq_channel_absmax(const void* x_fp16, int64_t M, int64_t K, float* absmax, void* stream);
 int qoq_channel_order_host(const float* salience_host, int64_t K, int32_t* perm_host);
+int qoq_channel_order(const float* salience, int64_t K, int32_t* perm, int32_t* nonfinite, void* stream);
 int qoq_gather_channels(const void* src_fp16, const int32_t* perm, int64_t rows, int64_t K, void* dst_fp16, void* stream);
 int qoq_quant_act_per_token_reordered(const void* x_fp16, const int32_t* perm, int64_t M, int64_t K, int8_t* qx,
                                       void* sx_fp16, int32_t* rowsum, float* tx, void* stream);

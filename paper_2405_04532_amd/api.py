@@ -17,6 +17,7 @@ QOQ_PER_CHANNEL = 1
 # qoq_status
 QOQ_OK, QOQ_ERR_NULL, QOQ_ERR_SHAPE, QOQ_ERR_ALIGN, QOQ_ERR_BLOB, QOQ_ERR_WORKSPACE, QOQ_ERR_ARCH, QOQ_ERR_HIP = range(8)
 GROUP = 128
+DEVICE_ORDER_MAX = 32768          # channels that qoq_channel_order sorts
 
 _lib = None
 
@@ -60,6 +61,7 @@ _SIGNATURES = {
                                              ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]),
     "qoq_channel_absmax": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]),
     "qoq_channel_order_host": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]),
+    "qoq_channel_order": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]),
     "qoq_gather_channels": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p,
                                            ctypes.c_void_p]),
     "qoq_quant_act_per_token_reordered": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64,
@@ -384,7 +386,16 @@ def channel_absmax(x):
 
 
 def channel_order(salience):
-    """Permutation (INT32, on the device of `salience`): most salient channel first; sorted on the host."""
+    """Permutation (INT32, on the device of `salience`): most salient channel first.  Sorted where `salience` is, up to
+    DEVICE_ORDER_MAX channels; longer ones on the host.  A salience that is not finite raises QoqError either way."""
+    if salience.is_cuda and 0 < salience.numel() <= DEVICE_ORDER_MAX:
+        sal = salience.detach().to(torch.float32).contiguous()
+        perm = torch.empty(sal.numel(), dtype=torch.int32, device=sal.device)
+        nonfinite = torch.empty(1, dtype=torch.int32, device=sal.device)
+        _check(lib().qoq_channel_order(_ptr(sal), sal.numel(), _ptr(perm), _ptr(nonfinite), _stream(sal.device)))
+        if nonfinite.item():
+            _check(QOQ_ERR_SHAPE)
+        return perm
     host = salience.detach().to("cpu", torch.float32).contiguous()
     perm = torch.empty(host.numel(), dtype=torch.int32)
     _check(lib().qoq_channel_order_host(host.data_ptr(), host.numel(), perm.data_ptr()))

@@ -282,6 +282,15 @@ int qoq_channel_order_host(const float* salience_host, int64_t K, int32_t* perm_
     return QOQ_OK;
 }
 
+int qoq_channel_order(const float* salience, int64_t K, int32_t* perm, int32_t* nonfinite, void* stream)
+{
+    if (K <= 0 || K > qoq::channel_order_max_k()) return QOQ_ERR_SHAPE;
+    if (!salience || !perm || !nonfinite) return QOQ_ERR_NULL;
+    if (!aligned4(salience) || !aligned4(perm) || !aligned4(nonfinite)) return QOQ_ERR_ALIGN;
+    if (!arch_ok()) return QOQ_ERR_ARCH;
+    return qoq::launch_channel_order(salience, K, perm, nonfinite, static_cast<hipStream_t>(stream)) == hipSuccess ? QOQ_OK : QOQ_ERR_HIP;
+}
+
 int qoq_gather_channels(const void* src_fp16, const int32_t* perm, int64_t rows, int64_t K, void* dst_fp16, void* stream)
 {
     if (rows < 0 || rows > (1 << 24) || K <= 0 || (K % 8) != 0 || K > (1 << 24)) return QOQ_ERR_SHAPE;

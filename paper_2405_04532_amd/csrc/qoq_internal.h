@@ -53,6 +53,8 @@ hipError_t launch_zero(void* dst, size_t bytes, hipStream_t s);
 hipError_t launch_act_quant_reordered(const void* x_fp16, const int32_t* perm, int64_t M, int64_t K, int8_t* qx, void* sx,
                                       int32_t* rowsum, float* tx, hipStream_t s);
 hipError_t launch_channel_absmax(const void* x, int64_t M, int64_t K, float* absmax, hipStream_t s);
+int channel_order_max_k();
+hipError_t launch_channel_order(const float* salience, int64_t K, int32_t* perm, int32_t* bad, hipStream_t s);
 hipError_t launch_gather_channels(const void* src, const int32_t* perm, int64_t rows, int64_t K, void* dst, hipStream_t s);
 hipError_t launch_hadamard(const void* src, int64_t rows, int64_t K, int64_t block, void* dst, hipStream_t s);
 int hadamard_max_block();

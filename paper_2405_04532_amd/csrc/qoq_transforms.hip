@@ -18,30 +18,137 @@
 namespace qoq {
 namespace {
 
-constexpr int kRowsPerSlab = 64;
-
 // salience[k] = max_m |x[m, k]| (Section 4.3: the magnitude of the input activations decides a channel's
-// salience).  One thread per 8 channels and slab of rows; non-negative floats order like their bit patterns,
-// so the slabs meet with an integer atomic maximum on a zero-filled array.
-__global__ __launch_bounds__(256) void channel_absmax_kernel(const __half* __restrict__ x, int64_t M, int64_t K, int* __restrict__ out_bits)
+// salience).  A workgroup takes 256 channels x 128 rows: thread (8-channel chunk c, row group q of 8) has the 16 loads of
+// its rows in flight together, maxima of FP16 pairs, the eight row groups meet in LDS and one of them goes on;
+// non-negative floats order like their bit patterns, so the slabs of rows meet with an integer atomic maximum on a
+// zero-filled array.  Bound by HBM latency and bandwidth: 1024 x 14336 (29 MB) in 8 us; with one thread per 8 channels
+// and 64 rows one after the other, 112 workgroups in all, it was 33 us.
+constexpr int kAbsmaxRows = 128;
+__global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* __restrict__ x, int64_t M, int chunks, int* __restrict__ out_bits)
 {
-    const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (c >= K / 8) return;
-    const int64_t r0 = (int64_t)blockIdx.y * kRowsPerSlab, r1 = min(M, r0 + kRowsPerSlab);
-    float mx[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int64_t r = r0; r < r1; ++r) {
-        const uint4 v = reinterpret_cast<const uint4*>(x + r * K)[c];
-        const __half* h = reinterpret_cast<const __half*>(&v);
+    __shared__ uint4 s_max[8][32];
+    const int cl = threadIdx.x & 31, q = threadIdx.x >> 5;
+    const int c = (int)blockIdx.x * 32 + cl;
+    const int64_t r0 = (int64_t)blockIdx.y * kAbsmaxRows + q;
+    const uint4* col = x + min(c, chunks - 1);
+    uint4 v[16];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) mx[j] = fmaxf(mx[j], fabsf(__half2float(h[j])));
-    }
+    for (int j = 0; j < 16; ++j) v[j] = col[min(r0 + 8 * j, M - 1) * chunks];   // past the end: the last row once more
+    auto pair_max = [](uint32_t a, uint32_t b) {         // of FP16 pairs; a NaN is not taken
+        typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(hv2, a), __builtin_bit_cast(hv2, b & 0x7FFF7FFFu)));
+    };
+    uint4 mx = make_uint4(0u, 0u, 0u, 0u);
+    auto take = [&](const uint4& t) { mx.x = pair_max(mx.x, t.x); mx.y = pair_max(mx.y, t.y); mx.z = pair_max(mx.z, t.z); mx.w = pair_max(mx.w, t.w); };
 #pragma unroll
-    for (int j = 0; j < 8; ++j) atomicMax(out_bits + c * 8 + j, __float_as_int(mx[j]));
+    for (int j = 0; j < 16; ++j) take(v[j]);
+    s_max[q][cl] = mx;
+    __syncthreads();
+    if (q != 0 || c >= chunks) return;
+#pragma unroll
+    for (int j = 1; j < 8; ++j) take(s_max[j][cl]);
+    const uint32_t w[4] = {mx.x, mx.y, mx.z, mx.w};
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        atomicMax(out_bits + (int64_t)c * 8 + j, __float_as_int(__half2float(__ushort_as_half((unsigned short)(w[j >> 1] >> (16 * (j & 1)))))));
 }
 
-// dst[r, j] = src[r, perm[j]]; one thread per 8 output channels.  Indices are clamped to the row.
-__global__ __launch_bounds__(256) void gather_channels_kernel(const __half* __restrict__ src, const int32_t* __restrict__ perm,
-                                                              int64_t rows, int64_t K, __half* __restrict__ dst)
+// Sorting by rank: new place of channel k = how many channels come before it (larger salience, or equal and a smaller
+// index).  A workgroup settles 64 channels, one per lane; its sixteen waves count over sixteen parts of the channels (two
+// vector instructions per pair) and meet in LDS.  K^2 work, for K <= kRankMaxK: 14336 channels in 27 us, where the copy to the
+// host, the sort there and the copy back took 0.7 ms.  bad[0] = 1 if some salience is not finite (the order is then
+// meaningless), else 0.
+constexpr int kRankMaxK = 32768, kRankTile = 8192;
+__global__ __launch_bounds__(1024) void channel_order_kernel(const float* __restrict__ salience, int K, int32_t* __restrict__ perm,
+                                                             int32_t* __restrict__ bad)
+{
+    __shared__ __attribute__((aligned(16))) uint32_t s_key[kRankTile];
+    __shared__ uint32_t s_rank[64];
+    __shared__ int s_bad;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto key_of = [](float f) {                          // unsigned integers in the order of the floats, -0 = +0
+        const uint32_t b = __float_as_uint(f + 0.0f);
+        return b & 0x80000000u ? ~b : b | 0x80000000u;
+    };
+    const int k0 = (int)blockIdx.x * 64, k = k0 + lane;
+    const uint32_t mine = k < K ? key_of(salience[k]) : 0u;
+    if (threadIdx.x < 64) s_rank[threadIdx.x] = 0;
+    if (threadIdx.x == 64) s_bad = 0;
+    uint32_t rank = 0;
+    bool nonfinite = false;
+    for (int j0 = 0; j0 < K; j0 += kRankTile) {
+        __syncthreads();
+        for (int j = threadIdx.x; j < kRankTile; j += 1024) {
+            const float f = j0 + j < K ? salience[j0 + j] : 0.f;
+            nonfinite |= !(fabsf(f) < __builtin_inff());
+            s_key[j] = j0 + j < K ? key_of(f) : 0u;      // past the end: before nobody (a finite float's key is not 0)
+        }
+        __syncthreads();
+        for (int blk = wave; blk < kRankTile / 64; blk += 16) {              // 64 keys that every lane compares its own with
+            const int j = j0 + blk * 64;
+            if (j >= K) break;
+            const uint4* keys = reinterpret_cast<const uint4*>(s_key + blk * 64);
+            // ties count in blocks before this workgroup's own channels, not behind; a key above mine - 1 is one of at least mine
+            const uint32_t floor_key = j < k0 ? mine - 1 : mine;
+            uint32_t n[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const uint4 t = keys[e];
+                n[0] += t.x > floor_key;
+                n[1] += t.y > floor_key;
+                n[2] += t.z > floor_key;
+                n[3] += t.w > floor_key;
+            }
+            rank += (n[0] + n[1]) + (n[2] + n[3]);
+            if (j == k0)                                                     // its own 64: equal keys in front of its own
+                for (int e = 0; e < 63; ++e) rank += e < lane && s_key[blk * 64 + e] == mine;
+        }
+    }
+    atomicAdd(&s_rank[lane], rank);
+    if (nonfinite) s_bad = 1;
+    __syncthreads();
+    if (threadIdx.x < 64 && k < K) perm[min((int)s_rank[lane], K - 1)] = k;   // (the bound only matters for NaNs)
+    if (blockIdx.x == 0 && threadIdx.x == 0) bad[0] = s_bad;
+}
+
+// dst[r, j] = src[r, perm[j]].  A workgroup brings `rows_per` rows into LDS as whole lines and gathers there: thread t makes
+// 8 output channels at a time, whose indices it fetches once for all its rows.  Two-byte gathers from memory, the first
+// version, took 134 us for 4096 x 14336 (117 MB each way; a copy takes 44 us), this one 49 us.  Indices are clamped to
+// the row.
+constexpr int kGatherThreads = 512;
+constexpr int64_t kGatherLds = 64 << 10;
+template <int ROWS>
+__global__ __launch_bounds__(kGatherThreads) void gather_channels_kernel(const uint4* __restrict__ src, const int4* __restrict__ perm,
+                                                                         int64_t rows, int K, uint4* __restrict__ dst)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned short s_row[];   // ROWS x K
+    const int chunks = K / 8;
+    const int64_t r0 = (int64_t)blockIdx.x * ROWS;
+    const int here = (int)min((int64_t)ROWS, rows - r0);
+    for (int c = threadIdx.x; c < here * chunks; c += kGatherThreads) reinterpret_cast<uint4*>(s_row)[c] = src[r0 * chunks + c];
+    __syncthreads();
+    for (int c = threadIdx.x; c < chunks; c += kGatherThreads) {
+        const int4 p0 = perm[2 * c], p1 = perm[2 * c + 1];
+        const int idx[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
+        int at[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) at[j] = min(max(idx[j], 0), K - 1);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            if (r < here) {
+                uint32_t w[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) w[j] = (uint32_t)s_row[r * K + at[2 * j]] | ((uint32_t)s_row[r * K + at[2 * j + 1]] << 16);
+                dst[(r0 + r) * chunks + c] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+        }
+    }
+}
+
+// Rows too long for LDS: one thread per 8 output channels, gathers from memory.
+__global__ __launch_bounds__(256) void gather_long_kernel(const __half* __restrict__ src, const int32_t* __restrict__ perm,
+                                                          int64_t rows, int64_t K, __half* __restrict__ dst)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t chunks = K / 8;
@@ -199,17 +306,39 @@ hipError_t launch_channel_absmax(const void* x, int64_t M, int64_t K, float* abs
 {
     hipError_t e = launch_zero(absmax, (size_t)K * sizeof(float), s);
     if (e != hipSuccess || M == 0) return e;
-    const dim3 grid((unsigned)((K / 8 + 255) / 256), (unsigned)((M + kRowsPerSlab - 1) / kRowsPerSlab));
-    channel_absmax_kernel<<<grid, 256, 0, s>>>(static_cast<const __half*>(x), M, K, reinterpret_cast<int*>(absmax));
+    const int64_t chunks = K / 8;
+    for (int64_t m0 = 0; m0 < M; m0 += (int64_t)65535 * kAbsmaxRows) {       // at most 65535 slabs in a launch
+        const int64_t rows = std::min<int64_t>(M - m0, (int64_t)65535 * kAbsmaxRows);
+        const dim3 grid((unsigned)((chunks + 31) / 32), (unsigned)((rows + kAbsmaxRows - 1) / kAbsmaxRows));
+        channel_absmax_kernel<<<grid, 256, 0, s>>>(static_cast<const uint4*>(x) + m0 * chunks, rows, (int)chunks, reinterpret_cast<int*>(absmax));
+    }
+    return hipGetLastError();
+}
+
+int channel_order_max_k() { return kRankMaxK; }
+
+hipError_t launch_channel_order(const float* salience, int64_t K, int32_t* perm, int32_t* bad, hipStream_t s)
+{
+    channel_order_kernel<<<(unsigned)((K + 63) / 64), 1024, 0, s>>>(salience, (int)K, perm, bad);
     return hipGetLastError();
 }
 
 hipError_t launch_gather_channels(const void* src, const int32_t* perm, int64_t rows, int64_t K, void* dst, hipStream_t s)
 {
+    if (rows == 0) return hipSuccess;
+    if (2 * K <= kGatherLds) {
+        // as many rows as fit 64 KiB (two workgroups of 512 threads per compute unit), at most four
+        const uint4* from = static_cast<const uint4*>(src);
+        const int4* p = reinterpret_cast<const int4*>(perm);
+        uint4* to = static_cast<uint4*>(dst);
+        auto blocks = [&](int per) { return dim3((unsigned)((rows + per - 1) / per)); };
+        if (8 * K <= kGatherLds) gather_channels_kernel<4><<<blocks(4), kGatherThreads, (size_t)K * 8, s>>>(from, p, rows, (int)K, to);
+        else if (4 * K <= kGatherLds) gather_channels_kernel<2><<<blocks(2), kGatherThreads, (size_t)K * 4, s>>>(from, p, rows, (int)K, to);
+        else gather_channels_kernel<1><<<blocks(1), kGatherThreads, (size_t)K * 2, s>>>(from, p, rows, (int)K, to);
+        return hipGetLastError();
+    }
     const int64_t n = rows * (K / 8);
-    if (n == 0) return hipSuccess;
-    gather_channels_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(static_cast<const __half*>(src), perm, rows, K,
-                                                                        static_cast<__half*>(dst));
+    gather_long_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(static_cast<const __half*>(src), perm, rows, K, static_cast<__half*>(dst));
     return hipGetLastError();
 }
 

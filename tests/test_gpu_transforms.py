@@ -30,6 +30,33 @@ def test_salience_and_order(M, K):
     assert not api.channel_absmax(x[:0]).any()                   # no tokens: zeros
 
 
+@pytest.mark.parametrize("K", [1, 63, 64, 65, 8191, 8193, 14336, 32768, 32776])
+def test_channel_order_on_the_device(K):
+    """Ranks at the edges of a workgroup's 64 channels and of a tile of keys, many ties, both zeros, negative numbers; the
+    last size is sorted on the host."""
+    s = torch.randint(-3, 40, (K,), generator=torch.Generator().manual_seed(K)).to(torch.float32) * 0.25
+    s[::7] = -0.0
+    perm = api.channel_order(s.to(DEV))
+    assert perm.dtype == torch.int32 and perm.is_cuda
+    assert np.array_equal(perm.cpu().numpy(), tr.channel_order(s.numpy()))
+    for bad in (float("nan"), float("inf"), float("-inf")):
+        t = s.clone()
+        t[K // 2] = bad
+        with pytest.raises(api.QoqError):
+            api.channel_order(t.to(DEV))
+
+
+@pytest.mark.parametrize("rows,K", [(1, 8), (5, 8192), (3, 8200), (7, 16392), (2, 32768), (2, 32776)])
+def test_gather_and_salience_edges(rows, K):
+    """Four, two and one rows in LDS with a remainder, and rows that do not fit; row slabs of the salience."""
+    x = wl.make_activations(rows, K, 71, DEV)
+    perm = torch.randperm(K, generator=torch.Generator().manual_seed(K)).to(torch.int32).to(DEV)
+    got = api.gather_channels(x, perm).cpu().numpy()
+    assert np.array_equal(_bits(got), _bits(tr.reorder_channels(x.cpu().numpy(), perm.cpu().numpy())))
+    y = wl.make_activations(128 * rows + 1, 264, 72, DEV)
+    assert np.array_equal(api.channel_absmax(y).cpu().numpy(), tr.channel_salience(y.cpu().numpy()))
+
+
 def test_gather_and_reordered_quantizer_bit_exact():
     M, K, N = 70, 2048, 192
     x = wl.make_activations(M, K, 61, DEV)
