@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqoq_w4a8.so")
 PROBE_LIB = os.path.join(HERE, "libqoq_probe.so")     # measurement probes of the benchmark (plain streaming read, matrix-core ceiling)
-SOURCES = ["qoq_api.hip", "qoq_pack.hip", "qoq_act.hip", "qoq_gemm.hip", "qoq_gemm_astat.hip", "qoq_kv4.hip", "qoq_transforms.hip"]
+SOURCES = ["qoq_api.hip", "qoq_pack.hip", "qoq_act.hip", "qoq_gemm.hip", "qoq_gemm_astat.hip", "qoq_gemm_mma16.hip", "qoq_kv4.hip", "qoq_transforms.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed FP32 instructions off (they have produced wrong results on these machines)
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -73,7 +73,7 @@ def _check_astat_prologue(path):
 def build(extra_flags=(), verbose=False):
     os.makedirs(OBJ, exist_ok=True)
     extra = list(extra_flags)
-    with ThreadPoolExecutor(max_workers=7) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(lambda s: _compile(s, extra), SOURCES))
     subprocess.check_call(["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs)
     subprocess.check_call(["hipcc", "-shared", os.path.join(CSRC, "probe_read.hip"), os.path.join(CSRC, "probe_mfma.hip"),

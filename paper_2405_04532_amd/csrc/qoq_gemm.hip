@@ -58,17 +58,6 @@ namespace {
 // iteration, the group of parity e of a pair of consecutive groups.
 // ------------------------------------------------------------------------------------------
 
-// Write-through store / cache-bypassing load of 16 bytes (device-coherent without fences).
-// A store of more than 8 bytes reads its data registers over several cycles after issue; the instruction that
-// follows must not write them (a documented wait-state requirement the compiler honours for its own stores but
-// cannot for inline assembly, which it does not know to be a store: partial sums whose registers were reused at
-// once came out corrupted in a few lanes).  Hence the idle cycles inside the store statements.  The streaming
-// kernel goes further and keeps its stores out of the loop altogether (below): they go out after the last copy,
-// together with the wait for their completion, from registers the same statement keeps alive.
-__device__ __forceinline__ void store_sc1(int4* ptr, v4i v)
-{
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 3" :: "v"(ptr), "v"(v) : "memory");
-}
 template <int CNT>
 __device__ __forceinline__ void store_sc1_and_wait(int4* ptr, int stride, const v4i (&v)[CNT])
 {
@@ -94,15 +83,6 @@ __device__ __forceinline__ void store_sc1_and_wait(int4* ptr, int stride, const 
                      :: "v"(ptr), "v"(ptr + stride), "v"(ptr + 2 * stride), "v"(ptr + 3 * stride), "v"(v[0]), "v"(v[1]), "v"(v[2]),
                      "v"(v[3]) : "memory");
 }
-__device__ __forceinline__ void load_sc1_nowait(v4i& v, const int4* ptr)
-{
-    asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(ptr) : "memory");
-}
-__device__ __forceinline__ void wait_loads(v4i& a, v4i& b, v4i& c, v4i& d)
-{
-    asm volatile("s_waitcnt vmcnt(0)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) :: "memory");
-}
-
 constexpr int kStreamThreads = 768;  // eight consumer waves + four producer waves
 
 // Blocks shared with other workgroups: this workgroup has written its partial tiles (at most two) to the
@@ -956,7 +936,8 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
 // 128 tokens x (32 * CF) channels in 4 x CF accumulator tiles of v_mfma_i32_32x32x32_i8 (CF = 4: 256
 // accumulator registers per lane).  Four workgroup shapes share the code:
 //     CF = 4, waves 2 x 2 : 256 tokens x 256 channels  (large problems: fewest bytes per MFMA)
-//     CF = 2, waves 1 x 4 : 128 tokens x 256 channels  (few tokens)
+//     CF = 2, waves 1 x 4 : 128 tokens x 256 channels  (few tokens; with more of these tiles than compute units the
+//                           16x16x64 kernel of qoq_gemm_mma16.hip takes over, two workgroups per compute unit)
 //     CF = 2, waves 2 x 2 : 256 tokens x 128 channels  (few channels)
 //     CF = 3, waves 2 x 2 : 256 tokens x 192 channels  (tile counts that fill the CUs where 256 x 256 leaves a
 //                           quarter idle, e.g. N = 12288).  A wave's three 32-row fragments are then every second
@@ -978,17 +959,16 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
 // ------------------------------------------------------------------------------------------
 typedef int v16i __attribute__((ext_vector_type(16)));
 constexpr int kMmaThreads = 256;
-// Ring depth (template parameter DEPTH): slabs of one quantization group each -- activations (tokens of the tile x
-// 128 k), weights (channels of the tile x 128 k, 1 KiB per 16 channels), metadata.  3 = one workgroup per compute
-// unit that hides the memory latency by its own lead of two groups; 2 = rings small enough for two workgroups per
-// compute unit (two waves per SIMD: while one waits for its copies or at its barrier, the other one's matrix
-// instructions keep the pipe busy).
+// Ring depth: slabs of one quantization group each -- activations (tokens of the tile x 128 k), weights (channels of the
+// tile x 128 k, 1 KiB per 16 channels), metadata.  Three: one workgroup per compute unit hides the memory latency by its
+// own lead of two groups.
+constexpr int kMmaDepth = 3;
 constexpr int kMSlotBytes = 1024;                   // metadata: 256 B per copying wave
 
-template <bool GROUP, int OUT, int CF, int WM, int DEPTH>
-__global__ __launch_bounds__(kMmaThreads, DEPTH == 2 ? 2 : 1) void mma_kernel(GemmDev p)
+template <bool GROUP, int OUT, int CF, int WM>
+__global__ __launch_bounds__(kMmaThreads, 1) void mma_kernel(GemmDev p)
 {
-    static_assert(DEPTH == 2 || DEPTH == 3, "ring depth");
+    constexpr int DEPTH = kMmaDepth;
     constexpr int kASlots = DEPTH, kWSlots = DEPTH;
     constexpr int WN = 4 / WM;                      // waves along the channels
     constexpr int TMt = 128 * WM, TNt = 32 * CF * WN;   // tile: tokens x channels
@@ -1498,18 +1478,18 @@ void launch_stream(const GemmDev& p, bool fp16, dim3 grid, hipStream_t s)
     }
 }
 
-template <bool GROUP, int CF, int WM, int DEPTH = 3>
+template <bool GROUP, int CF, int WM>
 void launch_mma(const GemmDev& p, bool fp16, hipStream_t s)
 {
     constexpr int TMt = 128 * WM, TNt = 32 * CF * (4 / WM);
     const dim3 grid((unsigned)(((p.N + TNt - 1) / TNt) * ((p.M + TMt - 1) / TMt)), (unsigned)p.S);
-    if (fp16) mma_kernel<GROUP, OUT_FP16, CF, WM, DEPTH><<<grid, kMmaThreads, 0, s>>>(p);
-    else mma_kernel<GROUP, OUT_I32, CF, WM, DEPTH><<<grid, kMmaThreads, 0, s>>>(p);
+    if (fp16) mma_kernel<GROUP, OUT_FP16, CF, WM><<<grid, kMmaThreads, 0, s>>>(p);
+    else mma_kernel<GROUP, OUT_I32, CF, WM><<<grid, kMmaThreads, 0, s>>>(p);
 }
 
 // tile_m selects the kernel and its shape: 16 / 32 / 64 = streaming kernel with that many tokens per tile;
 // 128 = compute-bound kernel, 256 tokens x 256 channels; 129 = 128 tokens x 256 channels; 130 = 256 x 128;
-// 131 = 256 x 192.
+// 131 = 256 x 192; 132 = 128 x 256, two workgroups per compute unit.
 template <bool GROUP>
 void launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStream_t s)
 {
@@ -1543,8 +1523,7 @@ void launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStream_t s)
     } else if (tile_m == 131) {
         launch_mma<GROUP, 3, 2>(p, fp16, s);
     } else if (tile_m == 132) {
-        launch_mma<GROUP, 2, 1, 2>(p, fp16, s);
-
+        (void)launch_mma16(p, GROUP, fp16, s);
     } else {
         launch_mma<GROUP, 4, 2>(p, fp16, s);
     }

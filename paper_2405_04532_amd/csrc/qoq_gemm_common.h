@@ -94,6 +94,26 @@ __device__ __forceinline__ void wait_vmcnt()
 // position.  (Measured: swizzles that only use r & 7 leave two-way conflicts on every such read.)
 __device__ __forceinline__ int row_swizzle(int r) { return (r >> 1) & 7; }   // r = row % 16
 
+// Write-through store / cache-bypassing load of 16 bytes (device-coherent without fences).
+// A store of more than 8 bytes reads its data registers over several cycles after issue; the instruction that
+// follows must not write them (a documented wait-state requirement the compiler honours for its own stores but
+// cannot for inline assembly, which it does not know to be a store: partial sums whose registers were reused at
+// once came out corrupted in a few lanes).  Hence the idle cycles inside the store statements.  The streaming
+// kernel goes further and keeps its stores out of the loop altogether (below): they go out after the last copy,
+// together with the wait for their completion, from registers the same statement keeps alive.
+__device__ __forceinline__ void store_sc1(int4* ptr, v4i v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 3" :: "v"(ptr), "v"(v) : "memory");
+}
+__device__ __forceinline__ void load_sc1_nowait(v4i& v, const int4* ptr)
+{
+    asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(ptr) : "memory");
+}
+__device__ __forceinline__ void wait_loads(v4i& a, v4i& b, v4i& c, v4i& d)
+{
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) :: "memory");
+}
+
 // Compiler-visible write-through store / cache-bypassing load (two relaxed device-scope 8-byte atomics each): the
 // compiler tracks their registers and waits itself.  For code with no copy queue to preserve, and wherever
 // control flow lies between a load and its use (the compiler may copy a register it believes already loaded).
@@ -152,5 +172,8 @@ __device__ __forceinline__ void finish4(const GemmDev& p, int m, int n0, v4i v, 
 hipError_t launch_astat(const GemmDev& p, int tile_m, int nwg, bool group, bool fp16, hipStream_t s);
 // Largest number of quantization groups one workgroup of that kernel can keep resident for `tile` tokens.
 int astat_max_groups(int tile);
+
+// qoq_gemm_mma16.hip: the compute-bound kernel with 16x16x64 matrix instructions (tile_m code 132).
+hipError_t launch_mma16(const GemmDev& p, bool group, bool fp16, hipStream_t s);
 
 }  // namespace qoq

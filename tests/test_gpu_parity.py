@@ -346,6 +346,25 @@ def test_group_compute_kernel_shapes_ragged(api, tile_m, split_k):
     run_group_case(api, 389, 1472, 2176, seed=13, tile_m=tile_m, split_k=split_k)
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M,N,K,split_k", [(1, 64, 128, 1), (127, 320, 256, 1), (129, 256, 384, 1), (257, 576, 128, 1), (130, 320, 1152, 4)])
+def test_two_per_unit_tile_edges(api, mode, M, N, K, split_k):
+    """The 128 x 256 tile with two workgroups per compute unit: one to three groups (rings shorter than their lead), one
+    token, one block, one past a tile on either axis, slices of unequal length; exact accumulators."""
+    w, x = rand_inputs(M, N, K, seed=61 + M + N)
+    ref = (ogemm.forward_per_channel if mode else ogemm.forward_group)(_np(w), _np(x))
+    blob = api.pack_weights(w, mode)
+    qx, sx, rowsum, _ = api.quant_act_per_token(x)
+    api.set_gemm_config(132, split_k)
+    try:
+        acc = api.w4a8_gemm_i32(qx, blob, N, mode, rowsum=rowsum if mode else None)
+        out = api.w4a8_gemm(qx, sx, blob, N, mode, rowsum=rowsum if mode else None)
+    finally:
+        api.set_gemm_config()
+    assert (_np(acc).astype(np.int64) == ref["acc"]).all()
+    check_fp16(out, ref["out64"])
+
+
 def _pack_logical(api, code, s1, z, s0):
     t = lambda a, dt: torch.from_numpy(np.ascontiguousarray(a.astype(dt))).to(DEV)
     return api.pack_quantized(t(code, np.uint8), t(s1, np.uint8), t(z, np.uint8), t(s0, np.float16))
