@@ -1,16 +1,20 @@
-"""Thin ctypes binding of libqoq_w4a8.so (same names as include/qoq_w4a8.h).
+"""Thin binding of libqoq_w4a8.so (same names as include/qoq_w4a8.h).
 
 Argument marshalling only: torch owns device memory and streams, every step of the path
-runs in the library's HIP kernels.  There is no fallback: if the library is not built or
-a call fails, an exception is raised.
+runs in the library's HIP kernels.  The calls a serving loop makes per layer go through the native module _qoq_py.so
+(csrc/qoq_py.cpp), the others through ctypes.  There is no fallback: if the libraries are not built or a call fails, an
+exception is raised.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libqoq_w4a8.so")
+NATIVE_PATH = os.path.join(_HERE, "_qoq_py.so")
 
 QOQ_GROUP128 = 0
 QOQ_PER_CHANNEL = 1
@@ -118,6 +122,25 @@ def _check(status):
         raise QoqError(status, status_string(status))
 
 
+_native = None
+
+
+def _load_native():
+    """The native half of this module (raises if it has not been built)."""
+    global _native
+    if _native is None:
+        lib()
+        if not os.path.exists(NATIVE_PATH):
+            raise RuntimeError(f"{NATIVE_PATH} is missing: run `python -m paper_2405_04532_amd.build` first")
+        spec = importlib.util.spec_from_file_location("_qoq_py", NATIVE_PATH,
+                                                      loader=importlib.machinery.ExtensionFileLoader("_qoq_py", NATIVE_PATH))
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.set_raise_status(_check)
+        _native = module
+    return _native
+
+
 def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
@@ -192,14 +215,7 @@ def unpack_weights(blob, N, K, mode=QOQ_GROUP128):
 
 def quant_act_per_token(x, want_rowsum=True, want_tx=False):
     """FP16 activations [M, K] -> (qx int8 [M,K], sx FP16 [M], rowsum int32 [M] | None, tx FP32 [M] | None)."""
-    _dev(x, torch.float16, "x")
-    M, K = x.shape
-    qx = torch.empty((M, K), dtype=torch.int8, device=x.device)
-    sx = torch.empty(M, dtype=torch.float16, device=x.device)
-    rowsum = torch.empty(M, dtype=torch.int32, device=x.device) if want_rowsum else None
-    tx = torch.empty(M, dtype=torch.float32, device=x.device) if want_tx else None
-    _check(lib().qoq_quant_act_per_token(_ptr(x), M, K, _ptr(qx), _ptr(sx), _ptr(rowsum), _ptr(tx), _stream(x.device)))
-    return qx, sx, rowsum, tx
+    return (_native or _load_native()).quant_act(x, want_rowsum, want_tx)
 
 
 def new_workspace(nbytes, device):
@@ -219,25 +235,13 @@ def _workspace(M, N, K, mode, device, workspace):
 
 def w4a8_gemm(qx, sx, packed, N, mode=QOQ_GROUP128, rowsum=None, out=None, workspace=None):
     """out[M, N] FP16 = W4A8 GEMM of INT8 activations with a packed weight blob."""
-    _dev(qx, torch.int8, "qx")
-    M, K = qx.shape
-    if out is None:
-        out = torch.empty((M, N), dtype=torch.float16, device=qx.device)
-    workspace, ws_bytes = _workspace(M, N, K, mode, qx.device, workspace)
-    _check(lib().qoq_w4a8_gemm(_ptr(qx), _ptr(sx), _ptr(rowsum), _ptr(packed), M, N, K, mode, _ptr(out),
-                               _ptr(workspace), ws_bytes, _stream(qx.device)))
-    return out
+    return (_native or _load_native()).w4a8_gemm(qx, sx, packed, N, mode, rowsum, out, workspace)
 
 
 def w4a8_gemm_noalloc(qx, sx, packed, N, out, mode=QOQ_GROUP128, rowsum=None):
     """qoq_w4a8_gemm_noalloc: the same GEMM with the library's own per-GPU scratch array; `out` [M, N] FP16 is the
     caller's (nothing is allocated on the way, here or in the library)."""
-    _dev(qx, torch.int8, "qx")
-    _dev(out, torch.float16, "out")
-    M, K = qx.shape
-    _check(lib().qoq_w4a8_gemm_noalloc(_ptr(qx), _ptr(sx), _ptr(rowsum), _ptr(packed), M, N, K, mode, _ptr(out),
-                                       _stream(qx.device)))
-    return out
+    return (_native or _load_native()).w4a8_gemm_noalloc(qx, sx, packed, N, out, mode, rowsum)
 
 
 def w4a8_gemm_i32(qx, packed, N, mode=QOQ_GROUP128, rowsum=None, out=None, workspace=None):
@@ -254,65 +258,22 @@ def w4a8_gemm_i32(qx, packed, N, mode=QOQ_GROUP128, rowsum=None, out=None, works
 
 def w4a8_linear(x, packed, N, mode=QOQ_GROUP128, out=None, qx=None, sx=None, rowsum=None, workspace=None):
     """Activation quantization + GEMM in one call; returns (out FP16 [M,N], qx, sx, rowsum)."""
-    _dev(x, torch.float16, "x")
-    M, K = x.shape
-    dev = x.device
-    if out is None:
-        out = torch.empty((M, N), dtype=torch.float16, device=dev)
-    if qx is None:
-        qx = torch.empty((M, K), dtype=torch.int8, device=dev)
-    if sx is None:
-        sx = torch.empty(M, dtype=torch.float16, device=dev)
-    if rowsum is None:
-        rowsum = torch.empty(M, dtype=torch.int32, device=dev)
-    workspace, ws_bytes = _workspace(M, N, K, mode, dev, workspace)
-    _check(lib().qoq_w4a8_linear(_ptr(x), _ptr(packed), M, N, K, mode, _ptr(out), _ptr(qx), _ptr(sx), _ptr(rowsum),
-                                 _ptr(workspace), ws_bytes, _stream(dev)))
-    return out, qx, sx, rowsum
+    return (_native or _load_native()).w4a8_linear(x, packed, N, mode, out, qx, sx, rowsum, workspace)
 
 
 def w4a8_gemm_token_sum(qx, sx, tx, packed, N, out=None, workspace=None):
     """Per-channel GEMM with the token-sum (subtraction after multiplication) epilogue; tx = FP32 [M]."""
-    _dev(qx, torch.int8, "qx")
-    _dev(tx, torch.float32, "tx")
-    M, K = qx.shape
-    if out is None:
-        out = torch.empty((M, N), dtype=torch.float16, device=qx.device)
-    workspace, ws_bytes = _workspace(M, N, K, QOQ_PER_CHANNEL, qx.device, workspace)
-    _check(lib().qoq_w4a8_gemm_token_sum(_ptr(qx), _ptr(sx), _ptr(tx), _ptr(packed), M, N, K, _ptr(out),
-                                         _ptr(workspace), ws_bytes, _stream(qx.device)))
-    return out
-
-
-def _quant_outputs(M, K, dev, want_y, want_rowsum, want_tx):
-    y = torch.empty((M, K), dtype=torch.float16, device=dev) if want_y else None
-    qx = torch.empty((M, K), dtype=torch.int8, device=dev)
-    sx = torch.empty(M, dtype=torch.float16, device=dev)
-    rowsum = torch.empty(M, dtype=torch.int32, device=dev) if want_rowsum else None
-    tx = torch.empty(M, dtype=torch.float32, device=dev) if want_tx else None
-    return y, qx, sx, rowsum, tx
+    return (_native or _load_native()).w4a8_gemm_token_sum(qx, sx, tx, packed, N, out, workspace)
 
 
 def rmsnorm_quant(x, gamma, eps, want_y=True, want_rowsum=True, want_tx=False):
     """RMSNorm with the per-token quantization fused in; returns (y FP16 | None, qx, sx, rowsum | None, tx | None)."""
-    _dev(x, torch.float16, "x")
-    _dev(gamma, torch.float16, "gamma")
-    M, K = x.shape
-    y, qx, sx, rowsum, tx = _quant_outputs(M, K, x.device, want_y, want_rowsum, want_tx)
-    _check(lib().qoq_rmsnorm_quant(_ptr(x), _ptr(gamma), float(eps), M, K, _ptr(y), _ptr(qx), _ptr(sx), _ptr(rowsum),
-                                   _ptr(tx), _stream(x.device)))
-    return y, qx, sx, rowsum, tx
+    return (_native or _load_native()).rmsnorm_quant(x, gamma, eps, want_y, want_rowsum, want_tx)
 
 
 def silu_mul_quant(gate_up, want_y=True, want_rowsum=True, want_tx=False):
     """SiLU(gate) * up on a fused [M, 2K] tensor with the per-token quantization fused in."""
-    _dev(gate_up, torch.float16, "gate_up")
-    M, K2 = gate_up.shape
-    K = K2 // 2
-    y, qx, sx, rowsum, tx = _quant_outputs(M, K, gate_up.device, want_y, want_rowsum, want_tx)
-    _check(lib().qoq_silu_mul_quant(_ptr(gate_up), M, K, _ptr(y), _ptr(qx), _ptr(sx), _ptr(rowsum), _ptr(tx),
-                                    _stream(gate_up.device)))
-    return y, qx, sx, rowsum, tx
+    return (_native or _load_native()).silu_mul_quant(gate_up, want_y, want_rowsum, want_tx)
 
 
 # ---------------------------------------------------------------------------------------
@@ -332,11 +293,7 @@ def kv4_new_cache(B, Hkv, S_max, device, D=128):
 
 def kv4_append(cache, k, v, positions, S_max):
     """Quantize k, v [B, T, Hkv, D] FP16 and write them at token positions positions[b] .. + T - 1."""
-    _dev(k, torch.float16, "k")
-    _dev(v, torch.float16, "v")
-    _dev(positions, torch.int32, "positions")
-    B, T, Hkv, D = k.shape
-    _check(lib().qoq_kv4_append(_ptr(k), _ptr(v), _ptr(positions), B, T, Hkv, D, S_max, _ptr(cache), _stream(k.device)))
+    return (_native or _load_native()).kv4_append(cache, k, v, positions, S_max)
 
 
 def kv4_attention_workspace_bytes(B, H, Hkv, S_max, D=128):
@@ -347,18 +304,7 @@ def kv4_attention_decode(q, cache, seq_lens, Hkv, S_max, out=None, workspace=Non
     """out[b, h] = softmax(q[b, h] . K^ / sqrt(D)) V^ over the first seq_lens[b] tokens of the cache.
     With a `workspace` (uint8 tensor of kv4_attention_workspace_bytes) the library may split long sequences
     over several workgroups."""
-    _dev(q, torch.float16, "q")
-    _dev(seq_lens, torch.int32, "seq_lens")
-    B, H, D = q.shape
-    if out is None:
-        out = torch.empty((B, H, D), dtype=torch.float16, device=q.device)
-    if workspace is None:
-        _check(lib().qoq_kv4_attention_decode(_ptr(q), _ptr(cache), _ptr(seq_lens), B, H, Hkv, D, S_max, _ptr(out),
-                                              _stream(q.device)))
-    else:
-        _check(lib().qoq_kv4_attention_decode_split(_ptr(q), _ptr(cache), _ptr(seq_lens), B, H, Hkv, D, S_max, _ptr(out),
-                                                    _ptr(workspace), workspace.numel(), _stream(q.device)))
-    return out
+    return (_native or _load_native()).kv4_attention_decode(q, cache, seq_lens, Hkv, S_max, out, workspace)
 
 
 def kv4_unpack(cache, B, Hkv, S_max, D=128):
@@ -413,13 +359,7 @@ def gather_channels(src, perm):
 
 def quant_act_per_token_reordered(x, perm, want_rowsum=True, want_tx=False):
     """quant_act_per_token of x[:, perm] in one pass."""
-    _dev(x, torch.float16, "x")
-    _dev(perm, torch.int32, "perm")
-    M, K = x.shape
-    _, qx, sx, rowsum, tx = _quant_outputs(M, K, x.device, False, want_rowsum, want_tx)
-    _check(lib().qoq_quant_act_per_token_reordered(_ptr(x), _ptr(perm), M, K, _ptr(qx), _ptr(sx), _ptr(rowsum), _ptr(tx),
-                                                   _stream(x.device)))
-    return qx, sx, rowsum, tx
+    return (_native or _load_native()).quant_act_reordered(x, perm, want_rowsum, want_tx)
 
 
 def hadamard_rotate(src, block=None, out=None):

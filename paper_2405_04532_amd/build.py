@@ -1,4 +1,5 @@
-"""Build the C-ABI library libqoq_w4a8.so (and the benchmark's read probe libqoq_probe.so) from csrc/*.hip with hipcc for gfx950.
+"""Build the C-ABI library libqoq_w4a8.so (and the benchmark's read probe libqoq_probe.so) from csrc/*.hip with hipcc for
+gfx950, and the native half of the Python binding, _qoq_py.so, from csrc/qoq_py.cpp.
 
 Usage: python -m paper_2405_04532_amd.build   (cross-compiles; no GPU needed)
 """
@@ -12,6 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqoq_w4a8.so")
 PROBE_LIB = os.path.join(HERE, "libqoq_probe.so")     # measurement probes of the benchmark (plain streaming read, matrix-core ceiling)
+PY_LIB = os.path.join(HERE, "_qoq_py.so")             # native argument marshalling of api.py's hot calls (host code only)
 SOURCES = ["qoq_api.hip", "qoq_pack.hip", "qoq_act.hip", "qoq_gemm.hip", "qoq_gemm_astat.hip", "qoq_gemm_mma16.hip", "qoq_kv4.hip", "qoq_transforms.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed FP32 instructions off (they have produced wrong results on these machines)
@@ -70,14 +72,32 @@ def _check_astat_prologue(path):
         raise RuntimeError("no activation-stationary kernel found in " + path)
 
 
+def _compile_binding():
+    """Host C++ against the headers of the torch that is installed; linked to the library beside it."""
+    import sysconfig
+    from torch.utils.cpp_extension import include_paths
+    obj = os.path.join(OBJ, "qoq_py.o")
+    inc = [f"-I{d}" for d in include_paths() + [sysconfig.get_paths()["include"]]]
+    subprocess.check_call(["hipcc", "-c", os.path.join(CSRC, "qoq_py.cpp"), "-o", obj, "-O2", "-std=c++17", "-fPIC", "-DUSE_ROCM=1"] + inc)
+    return obj
+
+
+def _link_binding(obj):
+    from torch.utils.cpp_extension import library_paths
+    libs = [f"-L{d}" for d in library_paths() + [HERE]] + ["-lqoq_w4a8", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    subprocess.check_call(["hipcc", "-shared", "-fPIC", obj, "-o", PY_LIB, "-Wl,-rpath,$ORIGIN"] + libs)
+
+
 def build(extra_flags=(), verbose=False):
     os.makedirs(OBJ, exist_ok=True)
     extra = list(extra_flags)
-    with ThreadPoolExecutor(max_workers=8) as ex:
+    with ThreadPoolExecutor(max_workers=9) as ex:
+        binding = ex.submit(_compile_binding)
         objs = list(ex.map(lambda s: _compile(s, extra), SOURCES))
     subprocess.check_call(["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs)
     subprocess.check_call(["hipcc", "-shared", os.path.join(CSRC, "probe_read.hip"), os.path.join(CSRC, "probe_mfma.hip"),
                            "-o", PROBE_LIB] + FLAGS + extra)
+    _link_binding(binding.result())
     if verbose:
         print("built", LIB)
     return LIB
