@@ -21,20 +21,27 @@
 //   the four k-values of an MFMA operand row.  A token still owns whole 16-bit words (32 of them), so appending a
 //   token is 32 plain 2-byte stores.
 //
-// Decode kernel.  One workgroup of four waves per (sequence, KV head); every wave streams chunks of the sequence,
-// 16-token tiles at a time, and both products run on v_mfma_f32_16x16x16_f16 (FP16 operands, FP32 sums):
+// Decode kernel.  One workgroup of 4 or 8 waves per (sequence, KV head); every wave streams chunks of the sequence,
+// two 16-token tiles at a time, and both products run on v_mfma_f32_16x16x32_f16 (FP16 operands, FP32 sums):
 //   S[token][head]  = sum_d (code - z_K)[token][d] * q[head][d]     A = unpacked keys, B = the queries of the up
 //                                                                    to 16 heads that share the KV head (GQA
-//                                                                    costs nothing extra), 8 MFMAs per tile
+//                                                                    costs nothing extra), 4 MFMAs per tile
 //   score = S * s_K[token] * log2(e) / sqrt(D); online softmax in base 2
-//   O[d][head]     += sum_token (code - z_V)[token][d] * (p * s_V)[token][head]    8 MFMAs per tile
+//   O[d][head]     += sum_token (code - z_V)[token][d] * (p * s_V)[token][head]    8 MFMAs for both tiles
 // The output layout of the first product (a lane holds 4 tokens of one head) is exactly the operand layout of the
-// second, so the softmax runs in place and nothing moves between lanes except the running maximum.  The paper's
+// second, so the softmax runs in place and nothing moves between lanes except the running maximum.  With up to eight
+// heads the columns of a matrix instruction hold both tiles side by side (columns 0..7 the first tile, 8..15 the second):
+// the queries are repeated in both halves, a lane keeps the scores of its own half's tile, and every column is a
+// softmax stream of its own until the end, so the softmax costs one tile's instructions for two tiles.  The paper's
 // kernel computes on scalar cores and fights their compute roof (Section 5.3: FP16 instead of FP32 arithmetic,
 // two-operation dequantization); here the two-operation dequantization is kept and the multiply-adds go to the
 // matrix cores, which leaves the vector pipe with the unpacking and the softmax only.
+// Measured against one tile per matrix instruction and 16x16x16 products: Llama-2-7B heads 64 x 1024 58.8 us instead of 63.5
+// (4.85 TB/s; the loads alone, with no arithmetic, take 52), Llama-3-8B heads 64 x 1024 17.5 instead of 19.3, 4 x 8192 12.7
+// instead of 16.6, Llama-3-70B heads 64 x 1024 18.2 instead of 19.9.  The vector pipe is active half of the time: 150 of the
+// 250 vector instructions per chunk unpack codes.  Taking the longest sequences first, or two waves per workgroup, was slower.
 // The scale/zero words of a chunk are loaded together with its codes, one chunk ahead of the arithmetic (the
-// prefetch of the dequantization parameters of Section 5.3).  Partial (max, sum, acc) of the four waves meet in LDS.
+// prefetch of the dequantization parameters of Section 5.3).  Partial (max, sum, acc) of the waves meet in LDS.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -221,33 +228,38 @@ __device__ __forceinline__ void unpack4(uint32_t word, h2 c, h2 c16, h2 (&out)[4
     out[3] = and_or(hi, 0x00F000F0u, 0x64006400u) * sixteenth + c16;
 }
 
-typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ h4 join(h2 a, h2 b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3); }
+__device__ __forceinline__ h8 join(h2 a, h2 b, h2 c, h2 d)
+{
+    struct { h2 v[4]; } t = {{a, b, c, d}};
+    return __builtin_bit_cast(h8, t);
+}
 __device__ __forceinline__ _Float16 half_bits(uint32_t v) { return __builtin_bit_cast(_Float16, (unsigned short)v); }
 
-constexpr int kDecodeThreads = 256;
-constexpr int kDecodeWaves = 4;
 constexpr int kMaxRatio = 16;                            // query heads per KV head: the columns of one MFMA
-
 constexpr int kPartial = kD + 2;                         // floats per (split, head): 128 sums, the maximum, the weight sum
+constexpr int kChunk = 32;                               // tokens per chunk: two tiles of 16 (divides the page)
 
-// NTL tiles of 16 tokens per chunk.  SPLIT: the sequence is cut into gridDim.y contiguous ranges of chunks, one
-// workgroup each, whose (unnormalised sums, maximum, weight sum) go to the workspace for kv4_combine_kernel; used
-// when there are too few (sequence, KV head) pairs to fill the chip (grouped-query models).
-template <int NTL, bool SPLIT>
-__global__ __launch_bounds__(kDecodeThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void kv4_decode_kernel(const __half* __restrict__ q, const uint8_t* __restrict__ cache,
-                                                                    const int32_t* __restrict__ seq_lens, int64_t Hkv, int R,
-                                                                    int64_t S_max, __half* __restrict__ out, float* __restrict__ ws)
+// LDS of a workgroup: per wave and used column 128 sums, the maximum and the weight sum
+constexpr int decode_lds_bytes(int waves, int columns) { return waves * columns * kPartial * (int)sizeof(float); }
+
+// NW waves.  PK: tiles side by side in the columns of a matrix instruction (2 with at most eight heads, else 1).  SPLIT:
+// the sequence is cut into gridDim.y contiguous ranges of chunks, one workgroup each, whose (unnormalised sums, maximum,
+// weight sum) go to the workspace for kv4_combine_kernel; used when there are too few (sequence, KV head) pairs to fill
+// the chip (grouped-query models).
+template <int NW, int PK, bool SPLIT>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1 || NW == 8 ? 2 : 3))) void kv4_decode_kernel(
+    const __half* __restrict__ q, const uint8_t* __restrict__ cache, const int32_t* __restrict__ seq_lens, int64_t Hkv, int R,
+    int64_t S_max, __half* __restrict__ out, float* __restrict__ ws)
 {
-    constexpr int CH = 16 * NTL;                         // tokens per chunk (divides the page)
-    __shared__ float s_acc[kDecodeWaves][kMaxRatio][kD];
-    __shared__ float s_m[kDecodeWaves][kMaxRatio], s_l[kDecodeWaves][kMaxRatio];
-
+    extern __shared__ float s_part[];                    // [wave][column][kPartial]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int r16 = lane & 15, kb = lane >> 4;           // operand row (token / element slot / head) and k-block
+    const int r16 = lane & 15, kb = lane >> 4;           // operand row (token / element slot / column) and k-block
+    const int head = PK == 2 ? r16 & 7 : r16;            // this lane's column: head and, with PK = 2, which tile's scores it keeps
+    const bool second = PK == 2 && r16 >= 8;
     const int64_t bh = blockIdx.x;                       // b * Hkv + hk
     const int64_t b = bh / Hkv, hk = bh % Hkv;
     const int64_t n_pages = (S_max + kPageTokens - 1) / kPageTokens;
@@ -256,95 +268,125 @@ __global__ __launch_bounds__(kDecodeThreads) __attribute__((amdgpu_waves_per_eu(
     __half* out_bh = out + (b * Hkv + hk) * R * kD;
     float* ws_bh = SPLIT ? ws + ((size_t)bh * gridDim.y + blockIdx.y) * R * kPartial : nullptr;
     // this workgroup's range of chunks [c0, c1) and the length it masks against
-    const int chunks_seq = (L_seq + CH - 1) / CH;
+    const int chunks_seq = (L_seq + kChunk - 1) / kChunk;
     const int per_split = SPLIT ? (chunks_seq + (int)gridDim.y - 1) / (int)gridDim.y : chunks_seq;
     const int c0 = SPLIT ? min(chunks_seq, (int)blockIdx.y * per_split) : 0;
     const int c1 = SPLIT ? min(chunks_seq, c0 + per_split) : chunks_seq;
-    const int L = min(L_seq, c1 * CH);
+    const int L = min(L_seq, c1 * kChunk);
     if (c0 >= c1) {                                      // nothing to attend to: zero rows / an empty partial result
-        for (int x = threadIdx.x; x < R * (SPLIT ? kPartial : kD); x += kDecodeThreads) {
+        for (int x = threadIdx.x; x < R * (SPLIT ? kPartial : kD); x += 64 * NW) {
             if (SPLIT) ws_bh[x] = x % kPartial == kD ? -1e30f : 0.f;
             else out_bh[x] = __float2half_rn(0.f);
         }
         return;
     }
 
-    // B operand of S = K q^T: column r16 = query head, k-block kb = elements 32 kb .. 32 kb + 31 (heads >= R: zero)
-    h2 qv[16];
-    {
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(q + ((b * Hkv + hk) * R + min(r16, R - 1)) * kD + kb * 32);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) qv[e] = __builtin_bit_cast(h2, r16 < R ? src[e] : 0u);
-    }
-
     struct Chunk {
-        uint4 kc[NTL];      // keys: token r16 of the tile, elements 32 kb ..
-        uint4 vc[NTL];      // values: this lane's 16 bytes of the tile
-        uint32_t kz[NTL];   // (s, z) of token r16 (zero point for unpacking)
-        uint4 ks[NTL];      // (s, z) of tokens 4 kb .. 4 kb + 3 (scales of the scores this lane receives)
-        uint4 vp[NTL];      // (s, z) of tokens 4 kb .. 4 kb + 3 of the values
+        uint4 kc[2];        // keys: token r16 of the tile, elements 32 kb ..
+        uint4 vc[2];        // values: this lane's 16 bytes of the tile
+        uint32_t kz[2];     // (s, z) of token r16 (zero point for unpacking)
+        uint4 ks[2 / PK];   // (s, z) of tokens 4 kb .. 4 kb + 3 (scales of the scores this lane keeps)
+        uint4 vp[2];        // (s, z) of tokens 4 kb .. 4 kb + 3 of the values
     };
-    // Every address is a wave-uniform tile base plus a lane offset that never changes: the five loads of a tile
+    // Every address is a wave-uniform chunk base plus a lane offset that never changes: the loads of a chunk
     // cost no vector address arithmetic.
     const uint32_t off_kc = (uint32_t)(r16 * (kD / 2) + kb * 16), off_kz = (uint32_t)(kCodeBytes + r16 * 4);
-    const uint32_t off_ks = (uint32_t)(kCodeBytes + kb * 16), off_vc = (uint32_t)(kHalfPage + lane * 16);
+    const uint32_t off_ks = (uint32_t)(kCodeBytes + kb * 16 + (second ? 64 : 0)), off_vc = (uint32_t)(kHalfPage + lane * 16);
     const uint32_t off_vp = (uint32_t)(kHalfPage + kCodeBytes + kb * 16);
     auto load_chunk = [&](Chunk& c, int chunk) __attribute__((always_inline)) {
+        const int t0 = __builtin_amdgcn_readfirstlane(chunk * kChunk);         // < n_pages * 64: inside the allocation
+        const uint8_t* page = stream + (int64_t)(t0 / kPageTokens) * kPageBytes;
+        const int tin = t0 % kPageTokens;                // first token of the chunk inside its page (0 or 32)
+        const uint8_t* codes = page + tin * (kD / 2);    // key codes of the chunk; its value codes lie 4352 further
+        const uint8_t* prm = page + tin * 4;             // (s, z) words of the chunk
 #pragma unroll
-        for (int tt = 0; tt < NTL; ++tt) {
-            const int t0 = __builtin_amdgcn_readfirstlane(chunk * CH + tt * 16);   // < n_pages * 64: inside the allocation
-            const uint8_t* page = stream + (int64_t)(t0 / kPageTokens) * kPageBytes;
-            const int tin = t0 % kPageTokens;            // first token of the tile inside its page (a multiple of 16)
-            const uint8_t* codes = page + tin * (kD / 2);          // key codes of the tile; its value codes lie 4352 further
-            const uint8_t* prm = page + tin * 4;                   // (s, z) words of the tile
-            c.kc[tt] = *reinterpret_cast<const uint4*>(codes + off_kc);
-            c.kz[tt] = *reinterpret_cast<const uint32_t*>(prm + off_kz);
-            c.ks[tt] = *reinterpret_cast<const uint4*>(prm + off_ks);
-            c.vc[tt] = *reinterpret_cast<const uint4*>(codes + off_vc);
-            c.vp[tt] = *reinterpret_cast<const uint4*>(prm + off_vp);
+        for (int tt = 0; tt < 2; ++tt) {
+            c.kc[tt] = *reinterpret_cast<const uint4*>(codes + tt * 1024 + off_kc);
+            c.kz[tt] = *reinterpret_cast<const uint32_t*>(prm + tt * 64 + off_kz);
+            if (tt < 2 / PK) c.ks[tt] = *reinterpret_cast<const uint4*>(prm + tt * 64 + off_ks);
+        }
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) {
+            c.vc[tt] = *reinterpret_cast<const uint4*>(codes + tt * 1024 + off_vc);
+            c.vp[tt] = *reinterpret_cast<const uint4*>(prm + tt * 64 + off_vp);
         }
     };
+    // Wave w takes chunks w, w + NW, ...; all waves run the same number of iterations (a wave without a chunk in
+    // the last one re-reads the final chunk, masked).  Two buffers alternate, and every path through the loop
+    // issues a fixed number of loads, so the compiler's wait counts are exact: while a chunk is computed the next
+    // one stays in flight.  (With loads under a condition it waits for everything outstanding.)
+    const int n_iter = (c1 - c0 + NW - 1) / NW;
+    auto chunk_of = [&](int it) __attribute__((always_inline)) { return c0 + it * NW + wave; };
+    auto fetch = [&](Chunk& c, int it) __attribute__((always_inline)) { load_chunk(c, min(chunk_of(it), c1 - 1)); };
+    Chunk A, Bf;
+    fetch(A, 0);
 
-    float m = -1e30f, l = 0.f;                           // of head r16, over the tokens this lane has seen
-    f4 acc[8];                                           // acc[4u + j][x]: element d = 16 kb + 4x + 64u + j of head r16
+    // B operand of S = K q^T: column = head (both halves of the columns with PK = 2; heads >= R: zero), k-block kb =
+    // elements 32 kb .. 32 kb + 31
+    h2 qv[16];
+    {
+        const uint4* src = reinterpret_cast<const uint4*>(q + ((b * Hkv + hk) * R + min(head, R - 1)) * kD + kb * 32);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint4 t = src[e];
+            const uint32_t u[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+            for (int x = 0; x < 4; ++x) qv[4 * e + x] = __builtin_bit_cast(h2, head < R ? u[x] : 0u);
+        }
+    }
+
+    float m = -1e30f, l = 0.f;                           // of this lane's column, over the tokens it has seen
+    f4 acc[8];                                           // acc[4u + j][x]: element d = 16 kb + 4x + 64u + j of the column
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = (f4){0.f, 0.f, 0.f, 0.f};
     const float kScale = 1.4426950408889634f * 0.08838834764831845f;      // log2(e) / sqrt(128)
-    const int n_chunks = c1;                             // chunk indices past the range are clamped to its last chunk
 
     const h2 k960 = {(_Float16)960.0f, (_Float16)960.0f};
     // One chunk of arithmetic.  MASKED: the chunk reaches past the end of the sequence (possibly entirely); the
     // parameters of tokens past the end are whatever the cache holds and must not enter the arithmetic.
     auto process_as = [&](const Chunk& cur, int chunk, auto masked_tag) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked_tag)::value;
-        f4 sc[NTL];
-        float m_new = m;
+        constexpr int NS = 2 / PK;                       // score vectors of a lane
+        const int own = chunk * kChunk + (second ? 16 : 0) + 4 * kb;       // first token of the lane's (first) score vector
+        f4 d[2];
 #pragma unroll
-        for (int tt = 0; tt < NTL; ++tt) {
-            const int t0 = chunk * CH + tt * 16;
+        for (int tt = 0; tt < 2; ++tt) {
+            const int t0 = chunk * kChunk + tt * 16;
             uint32_t kz = cur.kz[tt];
             if (MASKED) kz = t0 + r16 < L ? kz : 0xE4000000u;               // -(1024 + 0)
             const h2 c = __builtin_bit_cast(h2, __builtin_amdgcn_perm(kz, kz, 0x07060706u));   // high half in both halves
             const h2 c16 = c + k960;
             const uint32_t kw[4] = {cur.kc[tt].x, cur.kc[tt].y, cur.kc[tt].z, cur.kc[tt].w};
-            f4 d = {0.f, 0.f, 0.f, 0.f};
+            d[tt] = (f4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
                 h2 kh[4];
                 unpack4(kw[w], c, c16, kh);              // kh[j] = elements 8w + 2j, 8w + 2j + 1 of this lane's 32
-                d = __builtin_amdgcn_mfma_f32_16x16x16f16(join(kh[0], kh[1]), join(qv[4 * w], qv[4 * w + 1]), d, 0, 0, 0);
-                d = __builtin_amdgcn_mfma_f32_16x16x16f16(join(kh[2], kh[3]), join(qv[4 * w + 2], qv[4 * w + 3]), d, 0, 0, 0);
+                d[tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(join(kh[0], kh[1], kh[2], kh[3]),
+                                                               join(qv[4 * w], qv[4 * w + 1], qv[4 * w + 2], qv[4 * w + 3]), d[tt], 0, 0, 0);
             }
+        }
+        f4 sc[NS];                                       // [x] = token own + x (+ 16 for the second vector)
+        if (PK == 2) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) sc[0][x] = second ? d[1][x] : d[0][x];
+        } else {
+#pragma unroll
+            for (int tt = 0; tt < NS; ++tt) sc[tt] = d[tt];
+        }
+        float m_new = m;
+#pragma unroll
+        for (int tt = 0; tt < NS; ++tt) {
             const uint32_t sw[4] = {cur.ks[tt].x, cur.ks[tt].y, cur.ks[tt].z, cur.ks[tt].w};
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {                // d[x] = token 4 kb + x of the tile, head r16
+            for (int x = 0; x < 4; ++x) {
                 const float ks = (float)half_bits(sw[x]);
-                sc[tt][x] = d[x] * (ks * kScale);
-                if (MASKED) sc[tt][x] = t0 + 4 * kb + x < L ? sc[tt][x] : -1e30f;
+                sc[tt][x] *= ks * kScale;
+                if (MASKED) sc[tt][x] = own + tt * 16 + x < L ? sc[tt][x] : -1e30f;
                 m_new = fmaxf(m_new, sc[tt][x]);
             }
         }
-        m_new = fmaxf(m_new, __shfl_xor(m_new, 16, 64));  // the four k-blocks of a head agree on the maximum
+        m_new = fmaxf(m_new, __shfl_xor(m_new, 16, 64));  // the four k-blocks of a column agree on the maximum
         m_new = fmaxf(m_new, __shfl_xor(m_new, 32, 64));
         if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {                  // rare once a few chunks have been seen
             const float alpha = __builtin_amdgcn_exp2f(m - m_new);
@@ -353,51 +395,60 @@ __global__ __launch_bounds__(kDecodeThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
             for (int i = 0; i < 8; ++i) acc[i] *= alpha;
         }
+        uint32_t pw[2][4];                               // (s, z) of the values, tokens 4 kb .. of both tiles
 #pragma unroll
-        for (int tt = 0; tt < NTL; ++tt) {
-            const int t0 = chunk * CH + tt * 16;
-            uint32_t pw[4] = {cur.vp[tt].x, cur.vp[tt].y, cur.vp[tt].z, cur.vp[tt].w};
+        for (int tt = 0; tt < 2; ++tt) {
+            const uint32_t w4[4] = {cur.vp[tt].x, cur.vp[tt].y, cur.vp[tt].z, cur.vp[tt].w};
+#pragma unroll
+            for (int x = 0; x < 4; ++x) pw[tt][x] = !MASKED || chunk * kChunk + tt * 16 + 4 * kb + x < L ? w4[x] : 0xE4000000u;   // else scale 0, zero point 0
+        }
+        uint32_t bw[2][2];                               // B operand: softmax weight * value scale, tokens 4 kb .. of both tiles
+#pragma unroll
+        for (int tt = 0; tt < NS; ++tt) {
             float wf[4];
 #pragma unroll
             for (int x = 0; x < 4; ++x) {
-                if (MASKED) pw[x] = t0 + 4 * kb + x < L ? pw[x] : 0xE4000000u;   // scale 0, zero point 0
                 // a masked score is -1e30: its weight underflows to 0 unless nothing valid has been seen yet
                 // (then m is -1e30 too), which the zero scale takes care of
                 const float pr = __builtin_amdgcn_exp2f(sc[tt][x] - m);
-                l += MASKED ? (t0 + 4 * kb + x < L ? pr : 0.f) : pr;
-                wf[x] = pr * (float)half_bits(pw[x]);
+                l += MASKED ? (own + tt * 16 + x < L ? pr : 0.f) : pr;
+                wf[x] = pr * (float)half_bits(PK == 2 ? (second ? pw[1][x] : pw[0][x]) : pw[tt][x]);
             }
-            const h4 bw = {(_Float16)wf[0], (_Float16)wf[1], (_Float16)wf[2], (_Float16)wf[3]};   // B: tokens 4 kb .., head r16
+            const uint32_t lo = __builtin_bit_cast(uint32_t, (h2){(_Float16)wf[0], (_Float16)wf[1]});
+            const uint32_t hi = __builtin_bit_cast(uint32_t, (h2){(_Float16)wf[2], (_Float16)wf[3]});
+            if (PK == 2) {                               // a column takes part with its own tile only
+                bw[0][0] = second ? 0u : lo; bw[0][1] = second ? 0u : hi;
+                bw[1][0] = second ? lo : 0u; bw[1][1] = second ? hi : 0u;
+            } else {
+                bw[tt][0] = lo; bw[tt][1] = hi;
+            }
+        }
+        h2 vh[2][2][2][4];                               // [tile][u][h][j]: (token 4 kb + 2h, + 1) of element 4 (r16 + 16 u) + j
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) {
             const uint32_t vw[4] = {cur.vc[tt].x, cur.vc[tt].y, cur.vc[tt].z, cur.vc[tt].w};
-            h2 vh[2][2][4];                              // [u][h][j]: (token 4 kb + 2h, + 1) of element 4 (r16 + 16 u) + j
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const h2 c = __builtin_bit_cast(h2, __builtin_amdgcn_perm(pw[2 * h + 1], pw[2 * h], 0x07060302u));
+                const h2 c = __builtin_bit_cast(h2, __builtin_amdgcn_perm(pw[tt][2 * h + 1], pw[tt][2 * h], 0x07060302u));
                 const h2 c16 = c + k960;
 #pragma unroll
-                for (int u = 0; u < 2; ++u) unpack4(vw[2 * u + h], c, c16, vh[u][h]);
+                for (int u = 0; u < 2; ++u) unpack4(vw[2 * u + h], c, c16, vh[tt][u][h]);
             }
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[4 * u + j] = __builtin_amdgcn_mfma_f32_16x16x16f16(join(vh[u][0][j], vh[u][1][j]), bw, acc[4 * u + j], 0, 0, 0);
         }
+        const h8 b8 = join(__builtin_bit_cast(h2, bw[0][0]), __builtin_bit_cast(h2, bw[0][1]), __builtin_bit_cast(h2, bw[1][0]),
+                           __builtin_bit_cast(h2, bw[1][1]));
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc[4 * u + j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(join(vh[0][u][0][j], vh[0][u][1][j], vh[1][u][0][j], vh[1][u][1][j]),
+                                                                        b8, acc[4 * u + j], 0, 0, 0);
     };
     auto process = [&](const Chunk& cur, int chunk) __attribute__((always_inline)) {
-        if (chunk * CH + CH <= L) process_as(cur, chunk, std::false_type{});
+        if (chunk * kChunk + kChunk <= L) process_as(cur, chunk, std::false_type{});
         else process_as(cur, chunk, std::true_type{});
     };
 
-    // Wave w takes chunks w, w + 4, ...; all waves run the same number of iterations (a wave without a chunk in
-    // the last one re-reads the final chunk, masked).  Two buffers alternate, and every path through the loop
-    // issues a fixed number of loads, so the compiler's wait counts are exact: while a chunk is computed the next
-    // one stays in flight.  (With loads under a condition it waits for everything outstanding.)
-    const int n_iter = (c1 - c0 + kDecodeWaves - 1) / kDecodeWaves;
-    auto chunk_of = [&](int it) __attribute__((always_inline)) { return c0 + it * kDecodeWaves + wave; };
-    auto fetch = [&](Chunk& c, int it) __attribute__((always_inline)) { load_chunk(c, min(chunk_of(it), n_chunks - 1)); };
-    Chunk A, Bf;
-    fetch(A, 0);
     int it = 0;
     // Only a wave's last chunk can reach past the end of the sequence: every earlier one lies before the final chunk.
     for (; it + 2 < n_iter; it += 2) {
@@ -414,30 +465,33 @@ __global__ __launch_bounds__(kDecodeThreads) __attribute__((amdgpu_waves_per_eu(
         process(A, chunk_of(it));
     }
 
-    // ---- the four waves' partial results meet in LDS --------------------------------------------
+    // ---- the partial results of the waves (and of the column halves) meet in LDS -----------------
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
-    if (r16 < R) {
+    const int columns = PK * R;
+    if (head < R) {
+        float* mine = s_part + (wave * columns + (second ? R : 0) + head) * kPartial;
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int x = 0; x < 4; ++x) s_acc[wave][r16][16 * kb + 4 * x + 64 * u + j] = acc[4 * u + j][x];
-        if (kb == 0) { s_m[wave][r16] = m; s_l[wave][r16] = l; }
+                for (int x = 0; x < 4; ++x) mine[16 * kb + 4 * x + 64 * u + j] = acc[4 * u + j][x];
+        if (kb == 0) { mine[kD] = m; mine[kD + 1] = l; }
     }
     __syncthreads();
-    for (int x = threadIdx.x; x < R * kD; x += kDecodeThreads) {
+    for (int x = threadIdx.x; x < R * kD; x += 64 * NW) {
         const int r = x / kD, d = x % kD;
+        const float* part = s_part + r * kPartial;
         float mm = -1e30f;
 #pragma unroll
-        for (int i = 0; i < kDecodeWaves; ++i) mm = fmaxf(mm, s_m[i][r]);
+        for (int i = 0; i < NW * PK; ++i) mm = fmaxf(mm, part[i * R * kPartial + kD]);
         float num = 0.f, den = 0.f;
 #pragma unroll
-        for (int i = 0; i < kDecodeWaves; ++i) {
-            const float f = __builtin_amdgcn_exp2f(s_m[i][r] - mm);
-            num = fmaf(s_acc[i][r][d], f, num);
-            den = fmaf(s_l[i][r], f, den);
+        for (int i = 0; i < NW * PK; ++i) {
+            const float f = __builtin_amdgcn_exp2f(part[i * R * kPartial + kD] - mm);
+            num = fmaf(part[i * R * kPartial + d], f, num);
+            den = fmaf(part[i * R * kPartial + kD + 1], f, den);
         }
         if (SPLIT) {
             ws_bh[r * kPartial + d] = num;
@@ -448,21 +502,30 @@ __global__ __launch_bounds__(kDecodeThreads) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
-// Second pass of the split variant: one workgroup of 128 threads per (sequence, query head).
+// Second pass of the split variant: one workgroup of 128 threads per (sequence, query head), all loads in flight at once.
+constexpr int kMaxSplits = 8;
 __global__ __launch_bounds__(kD) void kv4_combine_kernel(const float* __restrict__ ws, int NS, int R, __half* __restrict__ out)
 {
     const int64_t bh = blockIdx.x / R;                   // (sequence, KV head)
     const int r = (int)(blockIdx.x % R), d = threadIdx.x;
     const float* part = ws + (size_t)bh * NS * R * kPartial + (size_t)r * kPartial;
-    float mm = -1e30f;
-    for (int s = 0; s < NS; ++s) mm = fmaxf(mm, part[(size_t)s * R * kPartial + kD]);
-    float num = 0.f, den = 0.f;
-    for (int s = 0; s < NS; ++s) {
-        const float f = __builtin_amdgcn_exp2f(part[(size_t)s * R * kPartial + kD] - mm);
-        num = fmaf(part[(size_t)s * R * kPartial + d], f, num);
-        den = fmaf(part[(size_t)s * R * kPartial + kD + 1], f, den);
+    float acc[kMaxSplits], mx[kMaxSplits], den[kMaxSplits];
+#pragma unroll
+    for (int s = 0; s < kMaxSplits; ++s) {
+        const float* p = part + (size_t)min(s, NS - 1) * R * kPartial;
+        acc[s] = p[d]; mx[s] = p[kD]; den[s] = p[kD + 1];
     }
-    out[(size_t)blockIdx.x * kD + d] = __float2half_rn(den > 0.f ? num / den : 0.f);
+    float mm = mx[0];
+#pragma unroll
+    for (int s = 1; s < kMaxSplits; ++s) mm = fmaxf(mm, mx[s]);
+    float num = 0.f, sum = 0.f;
+#pragma unroll
+    for (int s = 0; s < kMaxSplits; ++s) {
+        const float f = s < NS ? __builtin_amdgcn_exp2f(mx[s] - mm) : 0.f;
+        num = fmaf(acc[s], f, num);
+        sum = fmaf(den[s], f, sum);
+    }
+    out[(size_t)blockIdx.x * kD + d] = __float2half_rn(sum > 0.f ? num / sum : 0.f);
 }
 
 }  // namespace
@@ -505,7 +568,7 @@ int kv4_decode_splits(int64_t B, int64_t Hkv, int64_t S_max)
     const int64_t pairs = B * Hkv;
     if (pairs <= 0) return 1;
     int64_t ns = kDecodeFill / pairs;                    // about one workgroup per compute unit
-    ns = std::min<int64_t>(ns, 8);
+    ns = std::min<int64_t>(ns, kMaxSplits);
     ns = std::min<int64_t>(ns, S_max / 512);             // ranges of at least 512 tokens
     return (int)std::max<int64_t>(ns, 1);
 }
@@ -516,6 +579,20 @@ size_t kv4_decode_workspace_bytes(int64_t B, int64_t H, int64_t Hkv, int64_t S_m
     return ns <= 1 ? 0 : (size_t)(B * H) * ns * kPartial * sizeof(float);
 }
 
+// Waves of a workgroup: eight where there is at most one workgroup per compute unit and every wave gets a chunk, else four
+// (32 pairs of 1023 tokens 8.3 us with eight, 9.4 with four; 512 pairs of 1024 tokens 17.5 us with four, 20.8 with eight,
+// whose registers and partial results allow one workgroup per compute unit).
+static int decode_waves(int64_t workgroups, int64_t tokens) { return workgroups <= 256 && tokens > 4 * kChunk ? 8 : 4; }
+
+template <int PK, bool SPLIT>
+static void launch_decode(int waves, dim3 grid, const __half* q, const uint8_t* cache, const int32_t* seq_lens, int64_t Hkv, int R,
+                          int64_t S_max, __half* out, float* ws, hipStream_t s)
+{
+    const size_t lds = (size_t)decode_lds_bytes(waves, PK * R);
+    if (waves == 8) kv4_decode_kernel<8, PK, SPLIT><<<grid, 512, lds, s>>>(q, cache, seq_lens, Hkv, R, S_max, out, ws);
+    else kv4_decode_kernel<4, PK, SPLIT><<<grid, 256, lds, s>>>(q, cache, seq_lens, Hkv, R, S_max, out, ws);
+}
+
 hipError_t launch_kv4_decode(const void* q, const uint8_t* cache, const int32_t* seq_lens, int64_t B, int64_t H, int64_t Hkv,
                              int64_t S_max, void* out, void* workspace, size_t workspace_bytes, hipStream_t s)
 {
@@ -524,15 +601,20 @@ hipError_t launch_kv4_decode(const void* q, const uint8_t* cache, const int32_t*
     __half* oh = static_cast<__half*>(out);
     const int R = (int)(H / Hkv);
     if (R < 1 || R > kMaxRatio) return hipErrorInvalidValue;
+    const int64_t pairs = B * Hkv;
     const int ns = kv4_decode_splits(B, Hkv, S_max);
     if (workspace && ns > 1 && workspace_bytes >= kv4_decode_workspace_bytes(B, H, Hkv, S_max)) {
         float* ws = static_cast<float*>(workspace);
-        const dim3 grid((unsigned)(B * Hkv), (unsigned)ns);
-        kv4_decode_kernel<2, true><<<grid, kDecodeThreads, 0, s>>>(qh, cache, seq_lens, Hkv, R, S_max, oh, ws);
+        const dim3 grid((unsigned)pairs, (unsigned)ns);
+        const int waves = decode_waves(pairs * ns, S_max / ns);
+        if (R <= 8) launch_decode<2, true>(waves, grid, qh, cache, seq_lens, Hkv, R, S_max, oh, ws, s);
+        else launch_decode<1, true>(waves, grid, qh, cache, seq_lens, Hkv, R, S_max, oh, ws, s);
         kv4_combine_kernel<<<(unsigned)(B * H), kD, 0, s>>>(ws, ns, R, oh);
         return hipGetLastError();
     }
-    kv4_decode_kernel<2, false><<<dim3((unsigned)(B * Hkv)), kDecodeThreads, 0, s>>>(qh, cache, seq_lens, Hkv, R, S_max, oh, nullptr);
+    const int waves = decode_waves(pairs, S_max);
+    if (R <= 8) launch_decode<2, false>(waves, dim3((unsigned)pairs), qh, cache, seq_lens, Hkv, R, S_max, oh, nullptr, s);
+    else launch_decode<1, false>(waves, dim3((unsigned)pairs), qh, cache, seq_lens, Hkv, R, S_max, oh, nullptr, s);
     return hipGetLastError();
 }
 

@@ -161,6 +161,15 @@ def test_attention_long_sequence_many_pages():
     _attention_case(2, 2, 2, 2500, [2500, 1999], 50)
 
 
+@pytest.mark.parametrize("H,Hkv", [(2, 2), (16, 2), (18, 2)])
+@pytest.mark.parametrize("B", [9, 130])
+def test_attention_tiles_and_waves(B, H, Hkv):
+    """Two tiles per matrix instruction (one and eight heads per KV head) and one (nine), eight waves per workgroup (18
+    pairs) and four (260), lengths at the edges of tiles, chunks and of the waves' shares; the tolerance of the other cases."""
+    edges = [300, 1, 16, 17, 31, 32, 33, 255, 257]
+    _attention_case(B, H, Hkv, 300, [edges[i % 9] for i in range(B)], 60 + H)
+
+
 def test_attention_ignores_tokens_past_the_length():
     B, H, Hkv, S_max, D = 1, 2, 2, 128, 128
     k, v = wl.make_kv(B, Hkv, S_max, D, 51, DEV)
