@@ -223,6 +223,34 @@ def test_kv4_argument_validation():
     assert api.kv4_cache_bytes(2, 4, 65) == 2 * 4 * 2 * 8704
 
 
+@pytest.mark.parametrize("T,p0", [(24, 0), (1, 3), (3, 2), (9, 61)])
+def test_append_rounding_ties(T, p0):
+    """Values on rounding midpoints of both signs (scale 1), ranges whose scale lies on an FP16 midpoint or right beside
+    one, subnormal ranges, one-signed and zero vectors; whole and partly covered quads.  Exact."""
+    rows = torch.zeros(24, 128, dtype=torch.float64)
+    half = torch.arange(128, dtype=torch.float64) % 16 - 7.5
+    rows[0], rows[1], rows[2] = half, half * 2.0 ** -10, half * 2.0 ** 8
+    for i, d in enumerate((0.0, 2.0 ** -10, -2.0 ** -10)):                      # (hi - lo) / 15 = 1 + 2^-11 and its neighbours
+        rows[3 + i, 0], rows[3 + i, 1], rows[3 + i, 2:] = 15.0, -15.0 / 2048 * (1 + d), half[2:].abs()
+    rows[6] = (torch.arange(128) % 33 - 16).double() * 2.0 ** -24               # subnormal range
+    rows[7], rows[8] = half.abs() + 1, -half.abs() - 1
+    rows[9, 5] = 2.0 ** -24                                                     # scale rounds to zero
+    rows[10, 7] = 60000.0
+    rows[11, 7], rows[11, 8] = 65504.0, -65504.0
+    rows[12:] = torch.randn(12, 128, generator=torch.Generator().manual_seed(3)).double() * torch.logspace(-4, 3, 12, dtype=torch.float64)[:, None]
+    x = rows.to(torch.float16)
+    k = torch.stack([x, x.roll(5, 0)])[:, None, :T].to(DEV)                     # [B = 2, Hkv = 1, T, D]
+    v = k.flip(0).contiguous()
+    S = 80
+    cache = api.kv4_new_cache(2, 1, S, DEV)
+    api.kv4_append(cache, k.permute(0, 2, 1, 3).contiguous(), v.permute(0, 2, 1, 3).contiguous(),
+                   torch.full((2,), p0, dtype=torch.int32, device=DEV), S)
+    full = lambda t: np.concatenate([np.zeros((2, 1, p0, 128), np.float16), t.cpu().numpy(), np.zeros((2, 1, S - p0 - T, 128), np.float16)], 2)
+    wrote = np.zeros((2, S), dtype=bool)
+    wrote[:, p0:p0 + T] = True
+    _check_cache(cache, 2, 1, S, full(k), full(v), wrote)
+
+
 def test_append_many_vectors_bit_exact():
     """Sixteen million elements (131072 key and value vectors), all codes, scales and zeros compared; half of the
     vectors are scaled to magnitudes between 1e-3 and 1e3 so that many exponents of x / s occur."""
