@@ -13,23 +13,35 @@
 
 namespace qoq {
 
+// two FP32 numbers as a word of two FP16 ones: by P::half2_bits where P has it, else one at a time
+template <class P>
+QOQ_HD auto pair_bits(float a, float b, int) -> decltype(P::half2_bits(a, b)) { return P::half2_bits(a, b); }
+template <class P>
+QOQ_HD uint32_t pair_bits(float a, float b, long) { return P::half_bits(a) | (P::half_bits(b) << 16); }
+
+// FP16 bits of two producer outputs, each known to lie between two FP32 numbers: rounding to FP16 is monotonic, so where
+// the two round to the same FP16 number, everything between them does.  Result as in half2_bits_from_bounds.
+template <class P>
+QOQ_HD uint32_t half2_bits_between(float a0, float b0, float a1, float b1, uint32_t& word)
+{
+    word = pair_bits<P>(P::keep(a0), P::keep(a1), 0);
+    return word ^ pair_bits<P>(P::keep(b0), P::keep(b1), 0);
+}
+
 // FP16 bits of two producer outputs from FP32 evaluations p0, p1 of them and factors below < 1 < above such that the
 // FP64 value that defines each result lies between fl32(p below) and fl32(p above).  Rounding to FP16 is monotonic,
 // so where the two bounds round to the same FP16 number, every value between them does, the FP64 one included:
 // subnormal and overflowing results need no case of their own.  word = the two results (element 0 in the low
 // half); the return value is zero if both are decided and has a bit set in the half of an element that is not (a
 // rounding midpoint lies between the two bounds: about 1 element in 1000 for factors 1 -+ 4 * 2^-23), which the
-// caller evaluates more precisely.  Five instructions per element and no branch: a wave alone on its SIMD pays
+// caller evaluates more precisely.  Four instructions per element and no branch: a wave alone on its SIMD pays
 // every instruction and every taken branch in full, and a test with comparisons per case cost more than the rest
 // of the kernel.  keep() stops the compiler from merging a product with the conversion after it into one
 // mixed-precision multiply-add with a zero addend, which turns a product of -0 into +0.
 template <class P>
 QOQ_HD uint32_t half2_bits_from_bounds(float p0, float p1, float below, float above, uint32_t& word)
 {
-    const uint32_t lo = P::half_bits(P::keep(p0 * below)) | (P::half_bits(P::keep(p1 * below)) << 16);
-    const uint32_t hi = P::half_bits(P::keep(p0 * above)) | (P::half_bits(P::keep(p1 * above)) << 16);
-    word = lo;
-    return lo ^ hi;
+    return half2_bits_between<P>(p0 * below, p0 * above, p1 * below, p1 * above, word);
 }
 
 // The same decision from a value known much more precisely: hi + lo with |lo| of the order of an FP32 unit in the

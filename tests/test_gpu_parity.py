@@ -632,3 +632,59 @@ def test_act_quant_without_token_sums(api):
     qx1, sx1, rs1, tx1 = api.quant_act_per_token(x, want_rowsum=False, want_tx=False)
     assert rs1 is None and tx1 is None
     assert torch.equal(qx0, qx1) and torch.equal(sx0, sx1)
+
+
+# Rows at the edges of the launcher's choices (threads per row, 16-byte chunks per thread) and values at the edges of the
+# code decision: a subnormal scale (|x / s| beyond 127), FP16's smallest numbers (scale 1), infinities and NaN (code 0).
+@pytest.mark.parametrize("M,K", [(3, 128), (2, 8192), (2, 8320), (1, 16384), (1, 16512), (1, 32768),
+                                 (512, 8320), (513, 8320), (1023, 4224), (1024, 4224), (1024, 8192), (1024, 8320)])
+def test_act_quant_launch_edges(api, M, K):
+    x = wl.make_activations(M, K, 3 * M + K, DEV, outlier_count=max(1, K // 100))
+    perm = torch.randperm(K, generator=torch.Generator().manual_seed(K)).to(torch.int32).to(DEV)
+    for order in (None, perm):
+        qx, sx, rowsum, tx = (api.quant_act_per_token(x, want_rowsum=True, want_tx=True) if order is None else
+                              api.quant_act_per_token_reordered(x, order, want_rowsum=True, want_tx=True))
+        rqx, rsx, rrow, rtx = qq.act_quant(_np(x if order is None else x[:, order.long()]))
+        assert (_np(qx).astype(np.int64) == rqx).all() and (_np(sx).view(np.uint16) == rsx.view(np.uint16)).all()
+        assert (_np(rowsum).astype(np.int64) == rrow).all()
+        assert np.allclose(_np(tx), rtx, rtol=1e-4, atol=1e-2)
+
+
+def test_act_quant_subnormal_scales_and_special_values(api):
+    K = 512
+    rng = np.random.default_rng(5)
+    rows = []
+    for amax in (2.0 ** -24, 2.0 ** -19, 3e-6, 1e-5, 1e-4, 7.74e-3, 7.76e-3, 65504.0):   # 127 * 2^-14 = 7.75e-3
+        rows.append(np.clip(rng.standard_normal(K) * amax / 2, -amax, amax))
+        rows[-1][7] = amax
+    x = np.stack(rows).astype(np.float16)
+    qx, sx, rowsum, _ = api.quant_act_per_token(torch.from_numpy(x).to(DEV), want_rowsum=True)
+    rqx, rsx, rrow, _ = qq.act_quant(x)
+    assert (_np(qx).astype(np.int64) == rqx).all() and (_np(sx).view(np.uint16) == rsx.view(np.uint16)).all()
+    assert (_np(rowsum).astype(np.int64) == rrow).all()
+    assert (np.abs(rqx[:5]) == 127).sum() > 20                           # the clamp does act at these scales
+    y = x.copy()
+    y[:, 11] = np.nan                                                    # not part of the maximum; its own code is 0
+    y[4, 12] = np.inf
+    qy, sy, _, _ = api.quant_act_per_token(torch.from_numpy(y).to(DEV))
+    z = x.copy()
+    z[:, 11] = 0
+    rqz, rsz, _, _ = qq.act_quant(z)
+    rqz[4], rsz[4] = 0, np.float16(np.inf)                               # an infinite scale: every code is 0
+    assert (_np(qy).astype(np.int64) == rqz).all() and (_np(sy).view(np.uint16) == rsz.view(np.uint16)).all()
+
+
+def test_silu_mul_quant_every_gate_value(api):
+    """Every finite FP16 gate, with up values of every magnitude: the FP32 sigmoid must stay inside its error bound."""
+    K = 8192
+    gate = np.arange(1 << 16, dtype=np.uint16)
+    gate = gate[(gate & 0x7C00) != 0x7C00]
+    gate = np.concatenate([gate, np.zeros(-len(gate) % K, np.uint16)]).reshape(-1, K)
+    for seed in range(6):
+        rng = np.random.default_rng(seed)
+        up = (rng.choice([-1.0, 1.0], gate.shape) * np.exp2(rng.uniform(-14, 8, gate.shape))).astype(np.float16)
+        gu = np.concatenate([gate.view(np.float16), up], axis=1)
+        y, _, _, _, _ = api.silu_mul_quant(torch.from_numpy(gu).to(DEV), want_y=True, want_rowsum=False)
+        with np.errstate(over="ignore"):
+            ry = qq.silu_mul_fp16(gu)
+        assert (_np(y).view(np.uint16) == ry.view(np.uint16)).all()

@@ -97,3 +97,14 @@ def test_fp32_decisions_match_fp64_rounding(tmp_path, force_pair):
     assert (~decided).sum() <= 8                                  # within 2^-36 of a midpoint: a handful in millions
     # the sample does exercise what it is meant to: subnormal, zero, ordinary and overflowing results
     assert ((want & 0x7FFF) == 0x7C00).sum() > 1000 and ((want & 0x7C00) == 0).sum() > 1000 and (want == 0x8000).sum() >= 400
+
+
+def test_normalisation_bounds_enclose_the_fp64_product():
+    """RMSNorm's fast path: the exact FP32 product x * gamma times the FP32 roundings of r (1 -+ 1.5 * 2^-23)."""
+    x, g, r = _triples(30, 4_000_000)
+    xf, gf = x.view(np.float16).astype(np.float32), g.view(np.float16).astype(np.float32)
+    p = xf * gf
+    assert (p.astype(np.float64) == xf.astype(np.float64) * gf.astype(np.float64)).all()
+    below, above = (r * (1.0 - 1.5 * 2.0 ** -23)).astype(np.float32), (r * (1.0 + 1.5 * 2.0 ** -23)).astype(np.float32)
+    exact = np.abs(xf.astype(np.float64) * r * gf.astype(np.float64))
+    assert (np.abs(p * below) <= exact).all() and (np.abs(p * above) >= exact).all()
