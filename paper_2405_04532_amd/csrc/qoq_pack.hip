@@ -170,7 +170,8 @@ __global__ __launch_bounds__(1024) void pack_kernel(const __half* __restrict__ w
 #pragma unroll
             for (int e = 0; e < 32; ++e) {
                 const float t = f[e] * inv;
-                f[e] = __builtin_amdgcn_fmed3f(truncf(t + copysignf(0.5f + 1e-4f, t)), -119.f, 119.f);
+                // through an integer: its conversion takes NaN to 0
+                f[e] = __builtin_amdgcn_fmed3f((float)(int)(t + copysignf(0.5f + 1e-4f, t)), -119.f, 119.f);
                 gmin = fminf(gmin, f[e]);
                 gmax = fmaxf(gmax, f[e]);
             }

@@ -72,6 +72,17 @@ def test_pack_per_channel_matches_oracle(api, N, K):
     assert (_np(q).astype(np.int64) == code).all()
 
 
+def test_pack_nan_weights(api):
+    """NaN weights in group mode neither take part in a range nor disturb their group: they are packed as zeros would be.  Exact."""
+    N, K = 64, 512
+    w, _ = rand_inputs(0, N, K, seed=17)
+    w[5, 7] = w[6, ::3] = w[7, 128:256] = w[8, K - 1] = float("nan")
+    q, s1, z, s0 = [_np(t) for t in api.unpack_weights(api.pack_weights(w, api.QOQ_GROUP128), N, K, api.QOQ_GROUP128)]
+    ref = qq.progressive_quant(np.where(np.isnan(_np(w)), np.float16(0), _np(w)))
+    assert (s0.view(np.uint16) == ref["s0"].view(np.uint16)).all()
+    assert (s1 == ref["s1"]).all() and (z == ref["z"]).all() and (q == ref["Q"]).all()
+
+
 @pytest.mark.parametrize("N,K", [(64, 8192), (192, 8320), (64, 16512), (64, 32768), (128, 33024)])
 def test_pack_register_and_reread_rows(api, N, K):
     """Rows of one, two and four groups per thread, with idle threads, and rows that are read twice; channels with ties on
