@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void kv4_append_kernel(const __half* __restric
 
 #pragma unroll
     for (int which = 0; which < 2; ++which) {
-        const uint32_t rw[4] = {raws[which].x, raws[which].y, raws[which].z, raws[which].w};
+        uint32_t rw[4] = {raws[which].x, raws[which].y, raws[which].z, raws[which].w};
         h2 mn = {(_Float16)0.f, (_Float16)0.f}, mx = mn;                   // the range is widened to contain 0
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -157,6 +157,14 @@ __global__ __launch_bounds__(256) void kv4_append_kernel(const __half* __restric
         const float inv = 1.0f / __half2float(__ushort_as_half(s_bits));
         const float z = __builtin_amdgcn_fmed3f(floorf(fmaf(-lo, inv, 0.5f + 1e-4f)), 0.f, 15.f);
         const float offset = z + (0.5f + 1e-4f);
+        // NaN, and infinity over an infinite scale, are quotient 0 (code z); times zero they leave NaN in the sum
+        float bad = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bad = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, rw[e]), (h2){(_Float16)0.f, (_Float16)0.f}, bad, false);
+        if (bad != bad)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if ((~(rw[e >> 1] >> (16 * (e & 1))) & 0x7C00u) == 0) rw[e >> 1] &= 0xFFFFu << (16 * (~e & 1));
         uint32_t c[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {

@@ -264,3 +264,21 @@ def test_append_many_vectors_bit_exact():
                    torch.zeros(B, dtype=torch.int32, device=DEV), S)
     torch.cuda.synchronize()
     _check_cache(cache, B, Hkv, S, k.cpu().numpy(), v.cpu().numpy(), np.ones((B, S), dtype=bool))
+
+
+def test_append_values_that_are_not_finite():
+    """NaN elements neither take part in the range nor disturb their neighbours: they are stored as zeros would be.  A vector
+    with an infinity has an infinite scale and codes 0.  Exact."""
+    x = torch.randn(8, 128, generator=torch.Generator().manual_seed(5)).to(torch.float16) + 0.5
+    x[0, 3] = x[1, 0::2] = x[2, :] = x[3, 127] = float("nan")
+    x[5, 9], x[6, 10], x[7, 11], x[7, 12] = float("inf"), float("-inf"), float("inf"), float("nan")
+    k = x[None, None].to(DEV)                                                   # [B = 1, Hkv = 1, T = 8, D]
+    cache = api.kv4_new_cache(1, 1, 8, DEV)
+    t = k.permute(0, 2, 1, 3).contiguous()
+    api.kv4_append(cache, t, t.clone(), torch.zeros(1, dtype=torch.int32, device=DEV), 8)
+    zeroed = np.where(np.isnan(x.numpy()), np.float16(0), x.numpy())
+    ref_c, ref_s, ref_z = kv4.kv4_quantize(zeroed[:5])
+    got = [g.cpu().numpy()[0, 0] for g in api.kv4_unpack(cache, 1, 1, 8)]
+    for c, s, z in (got[:3], got[3:]):
+        assert (c[:5] == ref_c).all() and (s[:5] == ref_s).all() and (z[:5] == ref_z).all()
+        assert np.isinf(s[5:]).all() and (z[5:] == 0).all() and (c[5:] == 0).all()
