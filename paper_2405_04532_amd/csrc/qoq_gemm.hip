@@ -1568,12 +1568,15 @@ static double mma_cost(int64_t M, int64_t N, int64_t G, int tile_m, int& S)
     S = mma_split(M, N, G, tile_m, 0);
     const int64_t wgs = mma_tiles(M, N, tile_m) * S;
     if (tile_m == 132) {
-        // two workgroups per compute unit (128 x 256 tiles, shallower rings): worth it only when the compute units
-        // really get two each; a pair then takes about 1.85 times one workgroup's time per group at full load
-        if (S > 1 || wgs < 384) return 1e30;
+        // two workgroups per compute unit (128 x 256 tiles, shallower rings): worth it only when some compute units
+        // really get two; a pair then takes about 1.85 times one workgroup's time per group at full load
+        // (4096 x 28672 at 300 tokens, 336 tiles: 51.6 us, the estimate 51.5; activation-stationary tiles 56)
+        if (S > 1 || wgs <= 256) return 1e30;
         // whole rounds of 512 workgroups at full load; what is left over runs two per compute unit if it is more
         // than 256 workgroups, else alone (at the pace of the 128 x 256 tile; measured on Llama-3-70B QKV at 2048
-        // tokens, 640 tiles: 154 us, against 165 us for the 256 x 192 tile the coarser estimate preferred)
+        // tokens, 640 tiles: 154 us, against 165 us for the 256 x 192 tile the coarser estimate preferred), without
+        // a start of its own behind a full round: it fills the places that the round's first workgroups leave
+        // (4096 x 22016 at 700 tokens, 516 tiles: 79.5 us, the estimate 80.8; 256 x 192 tiles 86.3; per channel 69 and 88)
         const int64_t full = wgs / 512, rem = wgs - full * 512;
         double t = (double)full * (8.0 + 1.14 * 1.45 * (double)G);
         if (rem > 256) {
@@ -1581,7 +1584,7 @@ static double mma_cost(int64_t M, int64_t N, int64_t G, int tile_m, int& S)
             t += 8.0 + 1.14 * (1.0 + 0.45 * l * l) * (double)G;
         } else if (rem > 0) {
             const double l = (double)rem / 256.0;
-            t += 8.0 + 0.62 * (1.0 + 0.45 * l * l) * (double)G;
+            t += 0.62 * (1.0 + 0.45 * l * l) * (double)G;
         }
         return t;
     }
@@ -1683,6 +1686,12 @@ static int64_t astat_nwg(int64_t M, int64_t N, int64_t G, int tile_m, int64_t fo
     int64_t S, gps;
     astat_slices(G, tile_m, S, gps);
     int64_t nwg = forced_nwg > 0 ? forced_nwg : std::max<int64_t>(1, 256 / (m_tiles * S));
+    // Consecutive workgroups go to consecutive XCDs: with a multiple of eight per token tile the workgroups of one fragment
+    // run sit on the same XCD in every tile and share its weights through that L2.  Taken where it costs at most 8% of the
+    // workgroups.  64-token tiles at 130 tokens, 80 instead of 85 workgroups: 4096 x 12288 19.9 -> 18.0 us, per channel
+    // 17.8 -> 16.1, 4096 x 6144 12.9 -> 11.4; 32-token tiles, 8192 x 10240 per channel at 65 tokens 22.2 -> 15.2.
+    const int64_t even = nwg / 8 * 8;
+    if (forced_nwg <= 0 && m_tiles > 1 && 100 * even >= 92 * nwg) nwg = even;
     nwg = std::min(nwg, frags);
     if (S > 1) nwg = std::max(nwg, (frags + 127) / 128);   // at most 128 fragments per workgroup when slices meet in the workspace
     return nwg;
@@ -1692,7 +1701,6 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
 {
     const int64_t G = K / kGroup;
     const bool pairs_ok = N % 128 == 0;                // the pair-streaming kernel takes whole block pairs
-    (void)mode;
     const int natural = M <= 16 ? 16 : M <= 32 ? 32 : 64;   // smallest streaming tile that holds min(M, 64) tokens
     int stream_tile = natural;
     StreamPlan plan = stream_plan(M, N, G, natural, 0);
@@ -1768,18 +1776,39 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
         const double stream_cost = pair_wins ? lock_cost : plan.cost;
         double chosen = best;
         if (stream_cost < (pair_wins ? 0.95 : 0.9) * best) { tile_m = pair_wins ? lock : stream_tile; chosen = stream_cost; }
-        // Or 64-token activation-stationary tiles side by side, all token tiles together on the 256 compute units
-        // (K <= 4096: one workgroup holds all of K; measured 6.5 us + 1.15 ... 1.5 us per fragment of a workgroup's
-        // run on the Llama-2-7B and Llama-3-8B layers at 96 ... 512 tokens: QKV at M = 128 15.5 us against 18.4 us,
-        // gate+up 22.5 against 27.8, Llama-3-8B QKV at M = 384 18.7 against 23.0).
+        // Or activation-stationary tiles side by side, all token tiles together on the 256 compute units, where one
+        // workgroup holds all of K (K <= 4096 with 64-token tiles, <= 8192 with 32-token tiles): a start plus a time per
+        // fragment f of a workgroup's run, within 8% of measurements at 65 ... 300 tokens (per channel in brackets):
+        // 64 tokens 6.0 + 1.2 f (5.0 + 1.07 f), or 6.5 + 1.4 f for short K and where the token tiles do not share an L2;
+        // 32 tokens and K <= 4096 4.4 + 0.8 f (3.9 + 0.74 f) up to f = 8, 5.0 + 0.95 f (4.3 + 0.85 f) beyond, and
+        // 5.2 + 1.7 f (5.5 + 1.13 f) above K = 4096.  32-token tiles against the plans below: 4096 x 6144 at 65 tokens
+        // 8.4 us instead of 9.3, 8192 x 10240 19.2 instead of 25.5, per channel at 130 tokens 21.3 instead of 25.8.
+        int astat = 0;
+        const bool pc = mode != 0;
+        auto run = [&](int tile, bool& shared) {
+            const int64_t n = astat_nwg(M, N, G, tile, 0);
+            shared = n % 8 == 0;
+            return (double)((N / 16 + n - 1) / n);
+        };
+        bool shared;
         if (G <= 32 && M <= 512) {
-            const int64_t m_tiles = (M + 63) / 64, n = std::max<int64_t>(1, 256 / m_tiles);
-            const double c = 6.5 + 1.4 * (double)((N / 16 + n - 1) / n);
-            if (c < 0.97 * chosen) {
-                tile_m = 71;
-                split_k = (int)astat_nwg(M, N, G, tile_m, 0);
-                return;
-            }
+            const double f = run(71, shared);
+            const bool fitted = shared && G == 32;
+            const double c = !fitted ? 6.5 + 1.4 * f : pc ? 5.0 + 1.07 * f : 6.0 + 1.2 * f;
+            if (c < (fitted ? 0.92 : 0.97) * chosen) { astat = 71; chosen = c; }
+        }
+        if (G >= 32 && G <= 64 && M <= 320) {
+            const double f = run(70, shared);
+            const double c = G > 32 ? (pc ? 5.5 + 1.13 * f : 5.2 + 1.7 * f)
+                             : f <= 8 ? (pc ? 3.9 + 0.74 * f : 4.4 + 0.8 * f) : (pc ? 4.3 + 0.85 * f : 5.0 + 0.95 * f);
+            // (the margin covers how far the other plans' estimates are off at these sizes; long runs at K > 4096 take longer)
+            const double margin = G <= 32 ? 0.97 : pc ? 0.9 : 0.8;
+            if (shared && c < margin * chosen && (G <= 32 || f <= 28)) astat = 70;
+        }
+        if (astat) {
+            tile_m = astat;
+            split_k = (int)astat_nwg(M, N, G, tile_m, 0);
+            return;
         }
         if (tile_m == 65 || tile_m == 66) {
             split_k = (int)pair_plan(M, N, G, 0, tile_m == 65 ? 2 : 4).nwg;
