@@ -1489,12 +1489,13 @@ void launch_mma(const GemmDev& p, bool fp16, hipStream_t s)
 
 // tile_m selects the kernel and its shape: 16 / 32 / 64 = streaming kernel with that many tokens per tile;
 // 128 = compute-bound kernel, 256 tokens x 256 channels; 129 = 128 tokens x 256 channels; 130 = 256 x 128;
-// 131 = 256 x 192; 132 = 128 x 256, two workgroups per compute unit.
+// 131 = 256 x 192; 132 = 128 x 256, two workgroups per compute unit.  The error of a launch is read, and thereby cleared,
+// once: by the launcher of another file that made it, or here.
 template <bool GROUP>
-void launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStream_t s)
+hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStream_t s)
 {
     if (tile_m >= 69 && tile_m <= 71) {
-        (void)launch_astat(p, tile_m, nwg, GROUP, fp16, s);
+        return launch_astat(p, tile_m, nwg, GROUP, fp16, s);
     } else if (tile_m == 66) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 63) / 64));
         if (fp16) lockstep_kernel<4, 4, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
@@ -1523,10 +1524,11 @@ void launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStream_t s)
     } else if (tile_m == 131) {
         launch_mma<GROUP, 3, 2>(p, fp16, s);
     } else if (tile_m == 132) {
-        (void)launch_mma16(p, GROUP, fp16, s);
+        return launch_mma16(p, GROUP, fp16, s);
     } else {
         launch_mma<GROUP, 4, 2>(p, fp16, s);
     }
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -1908,9 +1910,8 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         counters = align256((size_t)mma_tiles(a.M, a.N, a.tile_m) * sizeof(int));
     }
     p.parts = reinterpret_cast<int4*>(reinterpret_cast<uint8_t*>(a.workspace) + (a.parts_offset ? a.parts_offset : counters));
-    if (a.mode == 0) launch_any<true>(p, a.tile_m, nwg, a.out_fp16 != nullptr, s);
-    else launch_any<false>(p, a.tile_m, nwg, a.out_fp16 != nullptr, s);
-    return hipGetLastError();
+    return a.mode == 0 ? launch_any<true>(p, a.tile_m, nwg, a.out_fp16 != nullptr, s)
+                       : launch_any<false>(p, a.tile_m, nwg, a.out_fp16 != nullptr, s);
 }
 
 namespace {

@@ -221,3 +221,45 @@ int main() {
                            str(src), "-o", str(exe)])
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout
+
+
+LAUNCH_ERRORS = r"""
+#include <cstdio>
+#include "qoq_internal.h"
+static hipError_t g_last, g_next;
+extern "C" {                                    // these stand in front of the runtime's: nothing reaches a device
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return g_last = g_next; }
+hipError_t hipGetLastError() { const hipError_t e = g_last; g_last = hipSuccess; return e; }
+hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+}
+static int run(int tile, int64_t M, int64_t N, int64_t K, int mode, int split, hipError_t next) {
+    qoq::GemmArgs a{};
+    a.M = M; a.N = N; a.K = K; a.mode = mode; a.tile_m = tile; a.split_k = split; a.out_fp16 = &a;
+    g_last = hipSuccess; g_next = next;
+    return (int)qoq::launch_gemm(a, nullptr);
+}
+int main() {
+    for (int tile : {16, 32, 64, 65, 66, 67, 68, 69, 70, 71, 128, 129, 130, 131, 132})
+        for (int mode = 0; mode < 2; ++mode)
+            printf("%d %d %d\n", tile, run(tile, 256, 256, 256, mode, 1, hipSuccess), run(tile, 256, 256, 256, mode, 1, hipErrorLaunchFailure));
+    // two k-slices and more fragments than a workgroup can hand over: refused before any launch
+    printf("70 0 %d\n", run(70, 32, 4096, 16384, 0, 1, hipSuccess));
+    return 0;
+}
+"""
+
+
+def test_a_failed_gemm_launch_is_reported(api, tmp_path):
+    """Every kernel family: the error of a launch that fails, or that its launcher refuses, is what the call returns."""
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    pkg = os.path.dirname(api.LIB_PATH)
+    src, exe = tmp_path / "launch.cpp", tmp_path / "launch"
+    src.write_text(LAUNCH_ERRORS)
+    subprocess.check_call(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-rdynamic", "-I", os.path.join(rocm, "include"),
+                           "-I", os.path.join(pkg, "csrc"), str(src), "-o", str(exe), "-L", pkg, "-lqoq_w4a8",
+                           f"-Wl,-rpath,{pkg}", "-Wl,--allow-shlib-undefined"])
+    out = subprocess.run([str(exe)], capture_output=True, text=True, check=True)
+    rows = [[int(v) for v in line.split()] for line in out.stdout.splitlines()]
+    assert len(rows) == 31
+    assert all(good == 0 and bad != 0 for _, good, bad in rows), [r for r in rows if r[1] != 0 or r[2] == 0]
