@@ -65,6 +65,23 @@ bool integer(PyObject* o, int64_t* v)
     return !(*v == -1 && PyErr_Occurred());
 }
 
+// a truth value, as `if o:` takes it; false with the exception set if it has none
+bool flag(PyObject* o, bool* v)
+{
+    const int t = PyObject_IsTrue(o);
+    *v = t == 1;
+    return t >= 0;
+}
+
+bool number(PyObject* o, double* v)             // as float(o) takes it
+{
+    PyObject* f = PyNumber_Float(o);
+    if (!f) return false;
+    *v = PyFloat_AS_DOUBLE(f);
+    Py_DECREF(f);
+    return true;
+}
+
 void* stream_of(const at::Tensor& t) { return c10::hip::getCurrentHIPStream(t.get_device()).stream(); }
 
 at::Tensor new_like(const at::Tensor& on, at::IntArrayRef shape, at::ScalarType dtype)
@@ -119,9 +136,10 @@ PyObject* quant_act(PyObject*, PyObject* const* a, Py_ssize_t n)    // x, want_r
     HANDLE_TH_ERRORS
     if (!counted(n, 3)) return nullptr;
     const at::Tensor* x = dev_tensor(a[0], at::kHalf, "x");
-    if (!x || !has_dims(*x, 2, "x")) return nullptr;
+    bool want_rowsum, want_tx;
+    if (!x || !has_dims(*x, 2, "x") || !flag(a[1], &want_rowsum) || !flag(a[2], &want_tx)) return nullptr;
     const int64_t M = x->size(0), K = x->size(1);
-    const Quantized q(*x, M, K, false, PyObject_IsTrue(a[1]) == 1, PyObject_IsTrue(a[2]) == 1);
+    const Quantized q(*x, M, K, false, want_rowsum, want_tx);
     void* s = stream_of(*x);
     const void* xp = x->data_ptr();
     if (!call([&] { return qoq_quant_act_per_token(xp, M, K, q.qx_ptr(), q.sx_ptr(), q.rowsum_ptr(), q.tx_ptr(), s); })) return nullptr;
@@ -136,9 +154,10 @@ PyObject* quant_act_reordered(PyObject*, PyObject* const* a, Py_ssize_t n)    //
     const at::Tensor* x = dev_tensor(a[0], at::kHalf, "x");
     if (!x) return nullptr;
     const at::Tensor* perm = dev_tensor(a[1], at::kInt, "perm");
-    if (!perm || !has_dims(*x, 2, "x")) return nullptr;
+    bool want_rowsum, want_tx;
+    if (!perm || !has_dims(*x, 2, "x") || !flag(a[2], &want_rowsum) || !flag(a[3], &want_tx)) return nullptr;
     const int64_t M = x->size(0), K = x->size(1);
-    const Quantized q(*x, M, K, false, PyObject_IsTrue(a[2]) == 1, PyObject_IsTrue(a[3]) == 1);
+    const Quantized q(*x, M, K, false, want_rowsum, want_tx);
     void* s = stream_of(*x);
     const void* xp = x->data_ptr();
     const int32_t* pp = static_cast<const int32_t*>(perm->data_ptr());
@@ -155,11 +174,12 @@ PyObject* rmsnorm_quant(PyObject*, PyObject* const* a, Py_ssize_t n)    // x, ga
     const at::Tensor* x = dev_tensor(a[0], at::kHalf, "x");
     if (!x) return nullptr;
     const at::Tensor* gamma = dev_tensor(a[1], at::kHalf, "gamma");
-    if (!gamma || !has_dims(*x, 2, "x")) return nullptr;
-    const double eps = PyFloat_AsDouble(a[2]);
-    if (eps == -1.0 && PyErr_Occurred()) return nullptr;
+    bool want_y, want_rowsum, want_tx;
+    double eps;
+    if (!gamma || !has_dims(*x, 2, "x") || !number(a[2], &eps) || !flag(a[3], &want_y) || !flag(a[4], &want_rowsum) || !flag(a[5], &want_tx))
+        return nullptr;
     const int64_t M = x->size(0), K = x->size(1);
-    const Quantized q(*x, M, K, PyObject_IsTrue(a[3]) == 1, PyObject_IsTrue(a[4]) == 1, PyObject_IsTrue(a[5]) == 1);
+    const Quantized q(*x, M, K, want_y, want_rowsum, want_tx);
     void* s = stream_of(*x);
     const void *xp = x->data_ptr(), *gp = gamma->data_ptr();
     if (!call([&] { return qoq_rmsnorm_quant(xp, gp, eps, M, K, q.y_ptr(), q.qx_ptr(), q.sx_ptr(), q.rowsum_ptr(), q.tx_ptr(), s); }))
@@ -173,9 +193,10 @@ PyObject* silu_mul_quant(PyObject*, PyObject* const* a, Py_ssize_t n)    // gate
     HANDLE_TH_ERRORS
     if (!counted(n, 4)) return nullptr;
     const at::Tensor* x = dev_tensor(a[0], at::kHalf, "gate_up");
-    if (!x || !has_dims(*x, 2, "gate_up")) return nullptr;
+    bool want_y, want_rowsum, want_tx;
+    if (!x || !has_dims(*x, 2, "gate_up") || !flag(a[1], &want_y) || !flag(a[2], &want_rowsum) || !flag(a[3], &want_tx)) return nullptr;
     const int64_t M = x->size(0), K = x->size(1) / 2;
-    const Quantized q(*x, M, K, PyObject_IsTrue(a[1]) == 1, PyObject_IsTrue(a[2]) == 1, PyObject_IsTrue(a[3]) == 1);
+    const Quantized q(*x, M, K, want_y, want_rowsum, want_tx);
     void* s = stream_of(*x);
     const void* xp = x->data_ptr();
     if (!call([&] { return qoq_silu_mul_quant(xp, M, K, q.y_ptr(), q.qx_ptr(), q.sx_ptr(), q.rowsum_ptr(), q.tx_ptr(), s); })) return nullptr;
