@@ -1699,6 +1699,62 @@ static int64_t astat_nwg(int64_t M, int64_t N, int64_t G, int tile_m, int64_t fo
     return nwg;
 }
 
+// Plans at 65 to 512 tokens are compared by two fits to 9000 times of 3300 shapes (K = 512 ... 14336, 25 values that are and
+// are not multiples of 512 or 1024; 1024 ... 28672 channels; both modes; weights from memory), in microseconds.
+//
+// Activation-stationary tiles side by side, one workgroup holding all of K: a start (the activations' way into the
+// registers), a time per fragment of a workgroup's run, and the weights' way from memory, which token tiles that do not share
+// an L2 (astat_nwg) go once more each.  The kernel of a tile is compiled for J groups per wave (eight waves) and a
+// fragment costs J units whatever K asks of them, so the constants belong to J; what a unit does for a group grows with
+// K itself.  Root mean square error 3 to 4%.
+static double astat_cost(int64_t M, int64_t N, int64_t G, int tile_m, int mode)
+{
+    struct Fit { double start, fragment, fragment_group, per_mb, per_mb_again; };
+    static const Fit fits[5][2] = {                          // [kernel][mode]
+        {{4.75, 0.824, 0.0035, 0.089, 0.003}, {4.82, 0.800, 0.0054, 0.069, 0.001}},    // 64 tokens, J = 2
+        {{5.04, 0.971, 0.0028, 0.075, 0.008}, {4.89, 0.905, 0.0033, 0.073, 0.007}},    //            J = 3
+        {{5.78, 1.099, 0.0031, 0.072, 0.018}, {5.55, 0.820, 0.0069, 0.074, 0.020}},    //            J = 4
+        {{3.96, 0.855, 0.0028, 0.077, 0.003}, {3.68, 0.712, 0.0052, 0.072, 0.004}},    // 32 tokens, J = 4
+        {{5.59, 1.274, 0.0058, 0.053, 0.0}, {5.15, 0.808, 0.0056, 0.075, 0.0}}};     //            J = 8
+    const int64_t n = astat_nwg(M, N, G, tile_m, 0), tile = astat_tile(tile_m), per_wave = (G + 7) / 8;
+    const int kernel = tile_m == 71 ? (per_wave <= 2 ? 0 : (int)per_wave - 2) : per_wave <= 4 ? 3 : 4;
+    const Fit& t = fits[kernel][mode != 0];
+    const double f = (double)((N / 16 + n - 1) / n), mb = (double)N * (double)G * (double)kGroup / 2.0e6;
+    if (kernel == 4 && n % 8 != 0) return 1e30;              // scattered: up to 15% slower than the fit
+    const double again = n % 8 == 0 ? 0.0 : (double)((M + tile - 1) / tile - 1);
+    return t.start + (t.fragment + t.fragment_group * (double)G) * f + (t.per_mb + t.per_mb_again * again) * mb;
+}
+
+// The other plans' times from their estimates, which rank these plans among each other but were fitted elsewhere (whole
+// layers in group mode): off by up to 40% for small tiles per channel, 3 to 6% after this (9% for 32-token tiles).
+static double measured_cost(int64_t N, int64_t G, int tile_m, int mode, double estimate)
+{
+    struct Fit { double start, scale, per_mb; };
+    static const Fit fits[8][2] = {                          // [tile][mode]
+        {{-1.33, 0.915, 0.184}, {-0.24, 0.688, 0.120}},      // 16
+        {{-0.91, 0.988, 0.054}, {-0.36, 0.865, 0.059}},      // 32
+        {{0.79, 0.772, 0.060}, {1.25, 0.676, 0.059}},        // 64
+        {{1.37, 0.824, 0.048}, {2.14, 0.711, 0.044}},        // 65
+        {{2.45, 0.782, 0.082}, {2.95, 0.698, 0.071}},        // 66
+        {{0.55, 0.894, 0.049}, {3.64, 0.784, 0.051}},        // 129
+        {{2.85, 0.933, 0.0}, {8.02, 0.838, 0.0}},            // 131
+        {{1.74, 1.03, 0.0}, {2.75, 0.973, 0.0}}};            // 132
+    int row;
+    switch (tile_m) {
+        case 16: row = 0; break;
+        case 32: row = 1; break;
+        case 64: row = 2; break;
+        case 65: row = 3; break;
+        case 66: row = 4; break;
+        case 129: row = 5; break;
+        case 131: row = 6; break;
+        case 132: row = 7; break;
+        default: return estimate;                            // 128, 130: hardly ever the best at these sizes
+    }
+    const Fit& t = fits[row][mode != 0];
+    return t.start + t.scale * estimate + t.per_mb * (double)N * (double)G * (double)kGroup / 2.0e6;
+}
+
 void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTuning& forced, int& tile_m, int& split_k)
 {
     const int64_t G = K / kGroup;
@@ -1779,38 +1835,23 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
         double chosen = best;
         if (stream_cost < (pair_wins ? 0.95 : 0.9) * best) { tile_m = pair_wins ? lock : stream_tile; chosen = stream_cost; }
         // Or activation-stationary tiles side by side, all token tiles together on the 256 compute units, where one
-        // workgroup holds all of K (K <= 4096 with 64-token tiles, <= 8192 with 32-token tiles): a start plus a time per
-        // fragment f of a workgroup's run, within 8% of measurements at 65 ... 300 tokens (per channel in brackets):
-        // 64 tokens 6.0 + 1.2 f (5.0 + 1.07 f), or 6.5 + 1.4 f for short K and where the token tiles do not share an L2;
-        // 32 tokens and K <= 4096 4.4 + 0.8 f (3.9 + 0.74 f) up to f = 8, 5.0 + 0.95 f (4.3 + 0.85 f) beyond, and
-        // 5.2 + 1.7 f (5.5 + 1.13 f) above K = 4096.  32-token tiles against the plans below: 4096 x 6144 at 65 tokens
-        // 8.4 us instead of 9.3, 8192 x 10240 19.2 instead of 25.5, per channel at 130 tokens 21.3 instead of 25.8.
-        int astat = 0;
-        const bool pc = mode != 0;
-        auto run = [&](int tile, bool& shared) {
-            const int64_t n = astat_nwg(M, N, G, tile, 0);
-            shared = n % 8 == 0;
-            return (double)((N / 16 + n - 1) / n);
-        };
-        bool shared;
-        if (G <= 32 && M <= 512) {
-            const double f = run(71, shared);
-            const bool fitted = shared && G == 32;
-            const double c = !fitted ? 6.5 + 1.4 * f : pc ? 5.0 + 1.07 * f : 6.0 + 1.2 * f;
-            if (c < (fitted ? 0.92 : 0.97) * chosen) { astat = 71; chosen = c; }
-        }
-        if (G >= 32 && G <= 64 && M <= 320) {
-            const double f = run(70, shared);
-            const double c = G > 32 ? (pc ? 5.5 + 1.13 * f : 5.2 + 1.7 * f)
-                             : f <= 8 ? (pc ? 3.9 + 0.74 * f : 4.4 + 0.8 * f) : (pc ? 4.3 + 0.85 * f : 5.0 + 0.95 * f);
-            // (the margin covers how far the other plans' estimates are off at these sizes; long runs at K > 4096 take longer)
-            const double margin = G <= 32 ? 0.97 : pc ? 0.9 : 0.8;
-            if (shared && c < margin * chosen && (G <= 32 || f <= 28)) astat = 70;
-        }
-        if (astat) {
-            tile_m = astat;
-            split_k = (int)astat_nwg(M, N, G, tile_m, 0);
-            return;
+        // workgroup holds all of K (K <= 4096 with 64-token tiles, <= 8192 with 32-token tiles).  They are given 1%, which
+        // they gain, more or less, where the weights are still in a cache.  Of the 3300 shapes the choice is within 0.4% of the
+        // fastest plan on average; against the best without these tiles it gains 5% on average and is more than 2% slower for
+        // 45, the worst by 7% (6528 x 20480 at 72 tokens, 34.5 us, 32.0 without).
+        if (M <= 512) {
+            chosen = 1.01 * measured_cost(N, G, tile_m, mode, chosen);
+            int astat = 0;
+            for (const int cand : {71, 70}) {
+                if (G > astat_max_groups(astat_tile(cand))) continue;
+                const double c = astat_cost(M, N, G, cand, mode);
+                if (c < chosen) { astat = cand; chosen = c; }
+            }
+            if (astat) {
+                tile_m = astat;
+                split_k = (int)astat_nwg(M, N, G, tile_m, 0);
+                return;
+            }
         }
         if (tile_m == 65 || tile_m == 66) {
             split_k = (int)pair_plan(M, N, G, 0, tile_m == 65 ? 2 : 4).nwg;

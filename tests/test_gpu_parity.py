@@ -376,6 +376,22 @@ def test_two_per_unit_tile_edges(api, mode, M, N, K, split_k):
     check_fp16(out, ref["out64"])
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(65, 1024, 6528), (100, 1024, 2304), (130, 512, 3328), (200, 512, 3328), (257, 448, 2304), (389, 1024, 3328)])
+def test_side_by_side_plans_at_odd_widths(api, mode, M, N, K):
+    """Plans of 65 to 512 tokens where K is no multiple of 512: token tiles that share an L2 and that do not, a last tile of
+    one, two and five tokens, waves without a group of their own.  Exact accumulators."""
+    w, x = rand_inputs(M, N, K, seed=M + K)
+    ref = (ogemm.forward_per_channel if mode else ogemm.forward_group)(_np(w), _np(x))
+    blob = api.pack_weights(w, mode)
+    qx, sx, rowsum, _ = api.quant_act_per_token(x)
+    acc = api.w4a8_gemm_i32(qx, blob, N, mode, rowsum=rowsum if mode else None)
+    out = api.w4a8_gemm(qx, sx, blob, N, mode, rowsum=rowsum if mode else None)
+    assert api.query_gemm_config(M, N, K, mode)[0] in (70, 71)
+    assert (_np(acc).astype(np.int64) == ref["acc"]).all()
+    check_fp16(out, ref["out64"])
+
+
 def _pack_logical(api, code, s1, z, s0):
     t = lambda a, dt: torch.from_numpy(np.ascontiguousarray(a.astype(dt))).to(DEV)
     return api.pack_quantized(t(code, np.uint8), t(s1, np.uint8), t(z, np.uint8), t(s0, np.float16))

@@ -291,9 +291,10 @@ def test_the_checker_catches_a_planted_overrun(tmp_path):
 
 
 @pytest.mark.parametrize("M,N,K,mode,tile,nwg", [(130, 12288, 4096, 0, 71, 80), (65, 10240, 8192, 0, 70, 80), (100, 10240, 8192, 1, 70, 64),
-                                                 (300, 8192, 8192, 1, 70, 24), (700, 22016, 4096, 0, 132, 1)])
+                                                 (300, 8192, 8192, 1, 70, 24), (700, 22016, 4096, 0, 132, 1),
+                                                 (130, 4096, 3968, 0, 70, 48), (65, 6144, 3968, 0, 70, 80), (130, 6144, 3584, 0, 70, 48)])
 def test_side_by_side_tiles_share_an_xcd(M, N, K, mode, tile, nwg):
     """Activation-stationary tiles side by side get a multiple of eight workgroups each (the same XCD for a fragment run in
-    every token tile) and hold all of K; a small remainder behind a full round stays with the two-per-CU tile."""
+    every token tile) and hold all of K, whatever K is; a small remainder behind a full round stays with the two-per-CU tile."""
     from paper_2405_04532_amd import api
     assert api.query_gemm_config(M, N, K, mode) == (tile, nwg)
