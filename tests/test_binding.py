@@ -42,3 +42,113 @@ def test_a_flag_without_a_truth_value_raises_its_own_error():
         api.rmsnorm_quant(x, gamma, "small")
     for eps in ("1e-5", np.float32(1e-5), torch.tensor(1e-5)):                   # whatever float() takes
         assert len(api.rmsnorm_quant(x, gamma, eps)) == 5
+
+
+def _inputs(dev):
+    """One valid argument list per entry point, as keyword arguments of the public functions."""
+    g = torch.Generator().manual_seed(11)
+    half = lambda *s: torch.randn(s, generator=g).to(torch.float16).to(dev)
+    ints = lambda hi, *s: torch.randint(0, hi, s, generator=g, dtype=torch.int32).to(dev)
+    x, qx = half(M, K), torch.randint(-127, 128, (M, K), generator=g, dtype=torch.int8).to(dev)
+    sx, rowsum = half(M).abs() + 0.01, qx.sum(1, dtype=torch.int32)
+    packed = torch.zeros(max(1, api.packed_bytes(N, K)), dtype=torch.uint8, device=dev)
+    cache = api.kv4_new_cache(B, HKV, S, dev)
+    return {
+        "quant_act_per_token": dict(x=x),
+        "quant_act_per_token_reordered": dict(x=x, perm=torch.randperm(K, generator=g).to(torch.int32).to(dev)),
+        "rmsnorm_quant": dict(x=x, gamma=half(K), eps=1e-5),
+        "silu_mul_quant": dict(gate_up=x),
+        "w4a8_gemm": dict(qx=qx, sx=sx, packed=packed, N=N),
+        "w4a8_gemm_noalloc": dict(qx=qx, sx=sx, packed=packed, N=N, out=half(M, N)),
+        "w4a8_gemm_token_sum": dict(qx=qx, sx=sx, tx=half(M).float(), packed=packed, N=N),
+        "w4a8_linear": dict(x=x, packed=packed, N=N),
+        "kv4_append": dict(cache=cache, k=half(B, T, HKV, D), v=half(B, T, HKV, D), positions=ints(S - T, B), S_max=S),
+        "kv4_attention_decode": dict(q=half(B, H, D), cache=cache, seq_lens=ints(S, B) + 1, Hkv=HKV, S_max=S),
+    }
+
+
+# the tensors whose type, layout and place are checked
+CHECKED = {"quant_act_per_token": ["x"], "quant_act_per_token_reordered": ["x", "perm"], "rmsnorm_quant": ["x", "gamma"],
+           "silu_mul_quant": ["gate_up"], "w4a8_gemm": ["qx"], "w4a8_gemm_noalloc": ["qx", "out"], "w4a8_gemm_token_sum": ["qx", "tx"],
+           "w4a8_linear": ["x"], "kv4_append": ["k", "v", "positions"], "kv4_attention_decode": ["q", "seq_lens"]}
+NATIVE = {"quant_act_per_token": ("quant_act", 3), "quant_act_per_token_reordered": ("quant_act_reordered", 4), "rmsnorm_quant": ("rmsnorm_quant", 6),
+          "silu_mul_quant": ("silu_mul_quant", 4), "w4a8_gemm": ("w4a8_gemm", 8), "w4a8_gemm_noalloc": ("w4a8_gemm_noalloc", 7),
+          "w4a8_gemm_token_sum": ("w4a8_gemm_token_sum", 7), "w4a8_linear": ("w4a8_linear", 9), "kv4_append": ("kv4_append", 5),
+          "kv4_attention_decode": ("kv4_attention_decode", 7)}
+
+
+@pytest.mark.parametrize("name", sorted(CHECKED))
+def test_a_tensor_on_the_host_and_a_wrong_argument_count_are_refused(name):
+    with pytest.raises(TypeError, match="on the GPU"):
+        getattr(api, name)(**_inputs("cpu")[name])
+    first = next(iter(k for k in _inputs("cpu")[name] if k in CHECKED[name]))
+    with pytest.raises(TypeError, match="tensor"):
+        getattr(api, name)(**{**_inputs("cpu")[name], first: [1.0, 2.0]})
+    entry, count = NATIVE[name]
+    for n in (count - 1, count + 1):
+        with pytest.raises(TypeError, match=f"expected {count} arguments, got {n}"):
+            getattr(api._load_native(), entry)(*[None] * n)
+
+
+@gpu
+@pytest.mark.parametrize("name", sorted(CHECKED))
+def test_wrong_types_layouts_and_shapes_are_refused(name):
+    good = _inputs(DEV)[name]
+    call = getattr(api, name)
+    for arg in CHECKED[name]:
+        t = good[arg]
+        with pytest.raises(TypeError, match=arg):
+            call(**{**good, arg: t.cpu()})
+        with pytest.raises(TypeError, match=arg):
+            call(**{**good, arg: t.double()})
+        if t.dim() >= 2:
+            wide = torch.empty((*t.shape[:-1], 2 * t.shape[-1]), dtype=t.dtype, device=DEV)[..., ::2]
+            with pytest.raises(TypeError, match=arg):
+                call(**{**good, arg: wide})
+    first = CHECKED[name][0]
+    for shape in ((-1,), (1, 1, 1, 1, -1)):
+        with pytest.raises(ValueError, match="dimensions"):
+            call(**{**good, first: good[first].reshape(shape)})
+    if "N" in good:
+        with pytest.raises(TypeError):
+            call(**{**good, "N": 1.5})
+        with pytest.raises(api.QoqError):                                        # a status of the library, as its exception
+            call(**{**good, "N": 100, **({"out": torch.empty((M, 100), dtype=torch.float16, device=DEV)} if name == "w4a8_gemm_noalloc" else {})})
+
+
+@gpu
+@pytest.mark.parametrize("name", sorted(CHECKED))
+def test_calls_run_on_the_current_stream(name):
+    """The input of a call is finished late on a side stream: a launch anywhere else would read what was there before.  Only
+    that stream is waited for."""
+    good = _inputs(DEV)[name]
+    if "packed" in good:
+        mode = api.QOQ_PER_CHANNEL if name == "w4a8_gemm_token_sum" else api.QOQ_GROUP128
+        good["packed"] = api.pack_weights(wl.make_weights(N, K, 3, DEV), mode)
+    if name == "kv4_attention_decode":
+        src = _inputs(DEV)["kv4_append"]
+        long = {a: torch.randn(B, S, HKV, D, generator=torch.Generator().manual_seed(i)).to(torch.float16).to(DEV) for i, a in enumerate("kv")}
+        api.kv4_append(good["cache"], long["k"], long["v"], torch.zeros_like(src["positions"]), S)
+    call = getattr(api, name)
+
+    def outputs():
+        r = call(**good)
+        r = good["cache"] if r is None else r
+        return [t for t in (r if isinstance(r, tuple) else (r,)) if t is not None]
+
+    first = CHECKED[name][0]
+    real = good[first].clone()
+    want = [t.clone() for t in outputs()]
+    if name == "kv4_append":
+        good["cache"].zero_()
+    late = torch.zeros_like(real)
+    good[first] = late
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(20_000_000)
+        late.copy_(real)
+        got = outputs()
+    side.synchronize()
+    assert len(got) == len(want) and all(torch.equal(a, b) for a, b in zip(got, want))
+    assert any(bool(t.view(torch.uint8).any()) for t in want)
