@@ -40,6 +40,8 @@
 // (4.85 TB/s; the loads alone, with no arithmetic, take 52), Llama-3-8B heads 64 x 1024 17.5 instead of 19.3, 4 x 8192 12.7
 // instead of 16.6, Llama-3-70B heads 64 x 1024 18.2 instead of 19.9.  The vector pipe is active half of the time: 150 of the
 // 250 vector instructions per chunk unpack codes.  Taking the longest sequences first, or two waves per workgroup, was slower.
+// Relative error of the output against FP64 on the same cache (1 to 64 sequences, 64 to 8192 tokens, 1 to 16 heads per KV head):
+// 2.0e-4 to 2.4e-4, the FP16 softmax weights' own; 3% less than with one tile per instruction on average, nowhere more.
 // The scale/zero words of a chunk are loaded together with its codes, one chunk ahead of the arithmetic (the
 // prefetch of the dequantization parameters of Section 5.3).  Partial (max, sum, acc) of the waves meet in LDS.
 #include <hip/hip_fp16.h>
@@ -279,6 +281,11 @@ __device__ __forceinline__ h8 join(h2 a, h2 b, h2 c, h2 d)
 constexpr int kMaxRatio = 16;                            // query heads per KV head: the columns of one MFMA
 constexpr int kPartial = kD + 2;                         // floats per (split, head): 128 sums, the maximum, the weight sum
 constexpr int kChunk = 32;                               // tokens per chunk: two tiles of 16 (divides the page)
+// Chunks up to which four waves attend to a sequence, also in a workgroup of eight: three each.  Four waves more merge four
+// (eight) partial results more, 0.7 us, and save a chunk per wave, 0.75 us, for every eight: 32 pairs of 128 tokens in a cache
+// for 700 3.6 us (4.3 with eight waves at work), 300 tokens 4.8 (5.5), 512 tokens 5.6 with eight (one tile per
+// instruction and four waves 5.8).
+constexpr int kFewChunks = 12;
 
 // LDS of a workgroup: per wave and used column 128 sums, the maximum and the weight sum
 constexpr int decode_lds_bytes(int waves, int columns) { return waves * columns * kPartial * (int)sizeof(float); }
@@ -349,12 +356,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1
             c.vp[tt] = *reinterpret_cast<const uint4*>(prm + tt * 64 + off_vp);
         }
     };
-    // Wave w takes chunks w, w + NW, ...; all waves run the same number of iterations (a wave without a chunk in
-    // the last one re-reads the final chunk, masked).  Two buffers alternate, and every path through the loop
+    // Wave w of the nw that attend takes chunks w, w + nw, ...; they all run the same number of iterations (a wave without a
+    // chunk in the last one re-reads the final chunk, masked).  Two buffers alternate, and every path through the loop
     // issues a fixed number of loads, so the compiler's wait counts are exact: while a chunk is computed the next
     // one stays in flight.  (With loads under a condition it waits for everything outstanding.)
-    const int n_iter = (c1 - c0 + NW - 1) / NW;
-    auto chunk_of = [&](int it) __attribute__((always_inline)) { return c0 + it * NW + wave; };
+    const int nw = NW > 4 && c1 - c0 <= kFewChunks ? 4 : NW;
+    const int n_iter = wave < nw ? (c1 - c0 + nw - 1) / nw : 0;
+    auto chunk_of = [&](int it) __attribute__((always_inline)) { return c0 + it * nw + wave; };
     auto fetch = [&](Chunk& c, int it) __attribute__((always_inline)) { load_chunk(c, min(chunk_of(it), c1 - 1)); };
     Chunk A, Bf;
     fetch(A, 0);
@@ -499,15 +507,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1
         fetch(Bf, it + 1);
         process_as(A, chunk_of(it), std::false_type{});
         process(Bf, chunk_of(it + 1));
-    } else {
+    } else if (n_iter > 0) {
         process(A, chunk_of(it));
     }
 
-    // ---- the partial results of the waves (and of the column halves) meet in LDS -----------------
+    // ---- the partial results of the nw waves (and of the column halves) meet in LDS --------------
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
     const int columns = PK * R;
-    if (head < R) {
+    if (head < R && n_iter > 0) {
         float* mine = s_part + (wave * columns + (second ? R : 0) + head) * kPartial;
 #pragma unroll
         for (int u = 0; u < 2; ++u)
@@ -518,26 +526,31 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1
         if (kb == 0) { mine[kD] = m; mine[kD + 1] = l; }
     }
     __syncthreads();
-    for (int x = threadIdx.x; x < R * kD; x += 64 * NW) {
-        const int r = x / kD, d = x % kD;
-        const float* part = s_part + r * kPartial;
-        float mm = -1e30f;
+    auto merge = [&](auto n_) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_)::value;           // partial results of a head
+        for (int x = threadIdx.x; x < R * kD; x += 64 * NW) {
+            const int r = x / kD, d = x % kD;
+            const float* part = s_part + r * kPartial;
+            float mm = -1e30f;
 #pragma unroll
-        for (int i = 0; i < NW * PK; ++i) mm = fmaxf(mm, part[i * R * kPartial + kD]);
-        float num = 0.f, den = 0.f;
+            for (int i = 0; i < N; ++i) mm = fmaxf(mm, part[i * R * kPartial + kD]);
+            float num = 0.f, den = 0.f;
 #pragma unroll
-        for (int i = 0; i < NW * PK; ++i) {
-            const float f = __builtin_amdgcn_exp2f(part[i * R * kPartial + kD] - mm);
-            num = fmaf(part[i * R * kPartial + d], f, num);
-            den = fmaf(part[i * R * kPartial + kD + 1], f, den);
+            for (int i = 0; i < N; ++i) {
+                const float f = __builtin_amdgcn_exp2f(part[i * R * kPartial + kD] - mm);
+                num = fmaf(part[i * R * kPartial + d], f, num);
+                den = fmaf(part[i * R * kPartial + kD + 1], f, den);
+            }
+            if (SPLIT) {
+                ws_bh[r * kPartial + d] = num;
+                if (d == 0) { ws_bh[r * kPartial + kD] = mm; ws_bh[r * kPartial + kD + 1] = den; }
+            } else {
+                out_bh[r * kD + d] = __float2half_rn(num / den);
+            }
         }
-        if (SPLIT) {
-            ws_bh[r * kPartial + d] = num;
-            if (d == 0) { ws_bh[r * kPartial + kD] = mm; ws_bh[r * kPartial + kD + 1] = den; }
-        } else {
-            out_bh[r * kD + d] = __float2half_rn(num / den);
-        }
-    }
+    };
+    if (NW > 4 && nw == 4) merge(std::integral_constant<int, 4 * PK>());
+    else merge(std::integral_constant<int, NW * PK>());
 }
 
 // Second pass of the split variant: one workgroup of 128 threads per (sequence, query head), all loads in flight at once.
@@ -617,10 +630,11 @@ size_t kv4_decode_workspace_bytes(int64_t B, int64_t H, int64_t Hkv, int64_t S_m
     return ns <= 1 ? 0 : (size_t)(B * H) * ns * kPartial * sizeof(float);
 }
 
-// Waves of a workgroup: eight where there is at most one workgroup per compute unit and every wave gets a chunk, else four
-// (32 pairs of 1023 tokens 8.3 us with eight, 9.4 with four; 512 pairs of 1024 tokens 17.5 us with four, 20.8 with eight,
-// whose registers and partial results allow one workgroup per compute unit).
-static int decode_waves(int64_t workgroups, int64_t tokens) { return workgroups <= 256 && tokens > 4 * kChunk ? 8 : 4; }
+// Waves of a workgroup: eight where there is at most one workgroup per compute unit and a sequence that fills the cache (its
+// share of the ranges) has more chunks than four waves are given, else four (32 pairs of 1023 tokens 8.3 us with eight, 9.4
+// with four; 512 pairs of 1024 tokens 17.5 us with four, 20.8 with eight, whose registers and partial results allow one
+// workgroup per compute unit).  Of the eight, shorter sequences use four.
+static int decode_waves(int64_t workgroups, int64_t tokens) { return workgroups <= 256 && tokens > kFewChunks * kChunk ? 8 : 4; }
 
 template <int PK, bool SPLIT>
 static void launch_decode(int waves, dim3 grid, const __half* q, const uint8_t* cache, const int32_t* seq_lens, int64_t Hkv, int R,

@@ -170,6 +170,14 @@ def test_attention_tiles_and_waves(B, H, Hkv):
     _attention_case(B, H, Hkv, 300, [edges[i % 9] for i in range(B)], 60 + H)
 
 
+@pytest.mark.parametrize("H,Hkv", [(2, 2), (16, 2), (18, 2)])
+def test_attention_short_sequences_in_a_large_cache(H, Hkv):
+    """Workgroups of eight waves: sequences that four of them attend to (up to twelve chunks of 32 tokens) beside longer
+    ones, whole and cut into ranges on either side of that; the tolerance of the other cases."""
+    _attention_case(9, H, Hkv, 700, [700, 1, 32, 97, 353, 383, 384, 385, 416], 80 + H)
+    _attention_case(4, H, Hkv, 1024, [1024, 30, 768, 770], 90 + H, split=True)
+
+
 def test_attention_ignores_tokens_past_the_length():
     B, H, Hkv, S_max, D = 1, 2, 2, 128, 128
     k, v = wl.make_kv(B, Hkv, S_max, D, 51, DEV)
