@@ -112,7 +112,7 @@ __global__ __launch_bounds__(1024) void channel_order_kernel(const float* __rest
     if (blockIdx.x == 0 && threadIdx.x == 0) bad[0] = s_bad;
 }
 
-// dst[r, j] = src[r, perm[j]].  A workgroup brings `rows_per` rows into LDS as whole lines and gathers there: thread t makes
+// dst[r, j] = src[r, perm[j]].  A workgroup brings ROWS rows into LDS as whole lines and gathers there: thread t makes
 // 8 output channels at a time, whose indices it fetches once for all its rows.  Two-byte gathers from memory, the first
 // version, took 134 us for 4096 x 14336 (117 MB each way; a copy takes 44 us), this one 49 us.  Indices are clamped to
 // the row.
@@ -146,8 +146,8 @@ __global__ __launch_bounds__(kGatherThreads) void gather_channels_kernel(const u
     }
 }
 
-// Rows too long for LDS: one thread per 8 output channels, gathers from memory.
-__global__ __launch_bounds__(256) void gather_long_kernel(const __half* __restrict__ src, const int32_t* __restrict__ perm,
+// Rows too long for LDS, short ones and few: one thread per 8 output channels, gathers from memory.
+__global__ __launch_bounds__(256) void gather_direct_kernel(const __half* __restrict__ src, const int32_t* __restrict__ perm,
                                                           int64_t rows, int64_t K, __half* __restrict__ dst)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -326,19 +326,23 @@ hipError_t launch_channel_order(const float* salience, int64_t K, int32_t* perm,
 hipError_t launch_gather_channels(const void* src, const int32_t* perm, int64_t rows, int64_t K, void* dst, hipStream_t s)
 {
     if (rows == 0) return hipSuccess;
-    if (2 * K <= kGatherLds) {
-        // as many rows as fit 64 KiB (two workgroups of 512 threads per compute unit), at most four
+    // Gathers from memory are ahead where a row is a few cache lines (65536 x 128: 8.8 us, through LDS 11.3; x 320 20.2 and 16.6)
+    // and where long rows are few, since all of a workgroup's threads first wait for its row (64 x 11008: 3.1 and 3.9 us,
+    // 32 x 28672 3.9 and 4.9, 128 x 11008 4.0 and 3.4).
+    if (2 * K <= kGatherLds && K > 256 && (K < 8192 || rows * K >= (int64_t)5 << 18)) {
+        // as many rows as fit 64 KiB (two workgroups of 512 threads per compute unit), at most four, and no more than leave
+        // a workgroup for every compute unit (256 x 4096: 2.6 us with one row each, 3.4 with four)
         const uint4* from = static_cast<const uint4*>(src);
         const int4* p = reinterpret_cast<const int4*>(perm);
         uint4* to = static_cast<uint4*>(dst);
         auto blocks = [&](int per) { return dim3((unsigned)((rows + per - 1) / per)); };
-        if (8 * K <= kGatherLds) gather_channels_kernel<4><<<blocks(4), kGatherThreads, (size_t)K * 8, s>>>(from, p, rows, (int)K, to);
-        else if (4 * K <= kGatherLds) gather_channels_kernel<2><<<blocks(2), kGatherThreads, (size_t)K * 4, s>>>(from, p, rows, (int)K, to);
+        if (8 * K <= kGatherLds && rows >= 2048) gather_channels_kernel<4><<<blocks(4), kGatherThreads, (size_t)K * 8, s>>>(from, p, rows, (int)K, to);
+        else if (4 * K <= kGatherLds && rows >= 512) gather_channels_kernel<2><<<blocks(2), kGatherThreads, (size_t)K * 4, s>>>(from, p, rows, (int)K, to);
         else gather_channels_kernel<1><<<blocks(1), kGatherThreads, (size_t)K * 2, s>>>(from, p, rows, (int)K, to);
         return hipGetLastError();
     }
     const int64_t n = rows * (K / 8);
-    gather_long_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(static_cast<const __half*>(src), perm, rows, K, static_cast<__half*>(dst));
+    gather_direct_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(static_cast<const __half*>(src), perm, rows, K, static_cast<__half*>(dst));
     return hipGetLastError();
 }
 

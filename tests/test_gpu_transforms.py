@@ -57,6 +57,15 @@ def test_gather_and_salience_edges(rows, K):
     assert np.array_equal(api.channel_absmax(y).cpu().numpy(), tr.channel_salience(y.cpu().numpy()))
 
 
+@pytest.mark.parametrize("rows,K", [(3, 256), (3, 264), (511, 264), (513, 264), (2047, 264), (2050, 264), (513, 8184), (159, 8192), (160, 8192),
+                                    (81, 16392), (41, 32768)])
+def test_gather_on_either_side_of_its_rules(rows, K):
+    """Short rows and few long ones gathered from memory, the others through LDS with one, two and four rows at a time."""
+    x = wl.make_activations(rows, K, 73, DEV)
+    perm = torch.randperm(K, generator=torch.Generator().manual_seed(K)).to(torch.int32).to(DEV)
+    assert torch.equal(api.gather_channels(x, perm), x[:, perm.long()])
+
+
 def test_gather_and_reordered_quantizer_bit_exact():
     M, K, N = 70, 2048, 192
     x = wl.make_activations(M, K, 61, DEV)
