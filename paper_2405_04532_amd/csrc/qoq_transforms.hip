@@ -22,7 +22,7 @@ namespace {
 // salience).  A workgroup takes 256 channels x 128 rows: thread (8-channel chunk c, row group q of 8) has the 16 loads of
 // its rows in flight together, maxima of FP16 pairs, the eight row groups meet in LDS and one of them goes on;
 // non-negative floats order like their bit patterns, so the slabs of rows meet with an integer atomic maximum on a
-// zero-filled array.  Bound by HBM latency and bandwidth: 1024 x 14336 (29 MB) in 8 us; with one thread per 8 channels
+// zero-filled array; a slab alone stores its maxima, and nothing is filled (1 x 14336: 3.2 us instead of 4.9).  Bound by HBM latency and bandwidth: 1024 x 14336 (29 MB) in 8 us; with one thread per 8 channels
 // and 64 rows one after the other, 112 workgroups in all, it was 33 us.
 constexpr int kAbsmaxRows = 128;
 __global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* __restrict__ x, int64_t M, int chunks, int* __restrict__ out_bits)
@@ -50,8 +50,11 @@ __global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* __rest
     for (int j = 1; j < 8; ++j) take(s_max[j][cl]);
     const uint32_t w[4] = {mx.x, mx.y, mx.z, mx.w};
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-        atomicMax(out_bits + (int64_t)c * 8 + j, __float_as_int(__half2float(__ushort_as_half((unsigned short)(w[j >> 1] >> (16 * (j & 1)))))));
+    for (int j = 0; j < 8; ++j) {
+        const int bits = __float_as_int(__half2float(__ushort_as_half((unsigned short)(w[j >> 1] >> (16 * (j & 1))))));
+        if (gridDim.y == 1) out_bits[(int64_t)c * 8 + j] = bits;
+        else atomicMax(out_bits + (int64_t)c * 8 + j, bits);
+    }
 }
 
 // Sorting by rank: new place of channel k = how many channels come before it (larger salience, or equal and a smaller
@@ -304,8 +307,10 @@ __global__ __launch_bounds__(256) void hadamard_unaligned_kernel(const __half* _
 
 hipError_t launch_channel_absmax(const void* x, int64_t M, int64_t K, float* absmax, hipStream_t s)
 {
-    hipError_t e = launch_zero(absmax, (size_t)K * sizeof(float), s);
-    if (e != hipSuccess || M == 0) return e;
+    if (M == 0 || M > kAbsmaxRows) {
+        const hipError_t e = launch_zero(absmax, (size_t)K * sizeof(float), s);
+        if (e != hipSuccess || M == 0) return e;
+    }
     const int64_t chunks = K / 8;
     for (int64_t m0 = 0; m0 < M; m0 += (int64_t)65535 * kAbsmaxRows) {       // at most 65535 slabs in a launch
         const int64_t rows = std::min<int64_t>(M - m0, (int64_t)65535 * kAbsmaxRows);

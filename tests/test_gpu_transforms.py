@@ -57,6 +57,18 @@ def test_gather_and_salience_edges(rows, K):
     assert np.array_equal(api.channel_absmax(y).cpu().numpy(), tr.channel_salience(y.cpu().numpy()))
 
 
+@pytest.mark.parametrize("K", [8, 256, 264, 4104])
+@pytest.mark.parametrize("M", [1, 2, 127, 128, 129, 257])
+def test_salience_of_one_slab_of_rows_and_of_several(M, K):
+    """One slab of rows stores every channel itself, whatever the output held; a channel of NaNs and one of zeros are 0."""
+    x = wl.make_activations(M, K, 74, DEV)
+    x[:, 3], x[:, 5], x[M - 1, 6] = float("nan"), 0.0, float("inf")
+    out = torch.full((K,), float("nan"), device=DEV)
+    ref = np.nan_to_num(np.abs(x.float().cpu().numpy()), nan=0.0, posinf=np.inf).max(axis=0)
+    assert api.lib().qoq_channel_absmax(x.data_ptr(), M, K, out.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    assert np.array_equal(out.cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("rows,K", [(3, 256), (3, 264), (511, 264), (513, 264), (2047, 264), (2050, 264), (513, 8184), (159, 8192), (160, 8192),
                                     (81, 16392), (41, 32768)])
 def test_gather_on_either_side_of_its_rules(rows, K):
