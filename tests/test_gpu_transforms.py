@@ -125,10 +125,12 @@ def test_hadamard_rotation_bit_exact(rows, K, block):
 
 
 @pytest.mark.parametrize("rows,K,block", [(1, 8, 8), (3, 24, 8), (1, 4104, 8), (257, 16, 16), (33, 128, 128), (7, 2048, 2048),
-                                          (3, 12288, 4096), (3, 24576, 8192), (5, 20, 4), (3, 5, 1)])
+                                          (3, 12288, 4096), (3, 24576, 8192), (5, 20, 4), (3, 5, 1),
+                                          (512, 8, 8), (513, 8, 8), (514, 32, 16), (600, 128, 128), (2, 65536, 128), (2, 65792, 256), (1, 4104, 4),
+                                          (2, 512, 512)])
 def test_hadamard_segment_edges_bit_exact(rows, K, block):
-    """Tensors that end inside a segment of the kernel, every group of stages present and absent, and tensors that are no
-    whole number of 16-byte chunks; exact, because FP64 sums of FP16 numbers are."""
+    """Tensors that end inside a segment of the kernel, every group of stages present and absent, few short blocks, and tensors
+    that are no whole number of 16-byte chunks; exact, because FP64 sums of FP16 numbers are."""
     x = wl.make_activations(rows, K, 70 + block % 89, DEV)
     ref = tr.rotate_fp16(x.cpu().numpy(), block)
     assert np.array_equal(_bits(api.hadamard_rotate(x, block).cpu().numpy()), _bits(ref))
