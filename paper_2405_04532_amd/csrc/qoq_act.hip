@@ -630,9 +630,12 @@ __global__ __launch_bounds__(kWide) void silu_mul_quant_kernel(const __half* __r
 // per compute unit and repeat the per-row work (reductions, scale) in fewer waves (RMSNorm 4096 x 4096: 14.7 us with 256, 21
 // with 512; 1024 x 4096: 7.4 and 8.4; quantizer 4096 x 4096 9.9 and 10.5); with few, a row's own time counts and 256 is
 // slower (64 x 4096 SiLU.up 4.3 us against 3.7).  few_rows_wide: 1024 threads for long rows where the chip has room for them
-// and the work per element is long (SiLU.up 64 x 11008 6.0 us with 1024, 6.5 with 512; the others are no faster).
+// and the work per element is long (SiLU.up 64 x 11008 6.0 us with 1024, 6.5 with 512; the others are no faster).  Rows of up to
+// 512 elements are one chunk for each lane of one wave, which then has no other to wait for (quantizer with sums 4096 x 512
+// 3.7 us with 64 threads, 6.0 with 256, 4096 x 128 3.6 and 5.9).
 static int64_t row_threads(int64_t M, int64_t K, bool few_rows_wide = false)
 {
+    if (K <= 512) return 64;
     if (M >= 1024 && K <= (int64_t)256 * kCache * 8) return 256;
     if (M <= 512 && K > (int64_t)8192 && few_rows_wide) return kWide;
     return K <= (int64_t)512 * kCache * 8 ? 512 : kWide;

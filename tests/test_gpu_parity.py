@@ -715,3 +715,21 @@ def test_silu_mul_quant_every_gate_value(api):
         with np.errstate(over="ignore"):
             ry = qq.silu_mul_fp16(gu)
         assert (_np(y).view(np.uint16) == ry.view(np.uint16)).all()
+
+
+@pytest.mark.parametrize("M,K", [(1, 128), (5, 384), (3, 512), (3, 640), (1024, 512), (2049, 128)])
+def test_rows_of_one_wave(api, M, K):
+    """Rows short enough for a single wave, and the first that are not: quantizer, reordered quantizer and both producers."""
+    x, gamma = _producer_inputs(M, K, seed=M + K)
+    perm = torch.randperm(K, generator=torch.Generator().manual_seed(K)).to(torch.int32).to(DEV)
+    gate_up = torch.cat([x, x.flip(0)], dim=1).contiguous()
+    eps = 1e-5
+    for ry, got in ((_np(x), api.quant_act_per_token(x, want_tx=True)),
+                    (_np(x[:, perm.long()]), api.quant_act_per_token_reordered(x, perm, want_tx=True)),
+                    (qq.rmsnorm_fp16(_np(x), _np(gamma), eps), api.rmsnorm_quant(x, gamma, eps, want_y=False, want_tx=True)[1:]),
+                    (qq.silu_mul_fp16(_np(gate_up)), api.silu_mul_quant(gate_up, want_y=False, want_tx=True)[1:])):
+        qx, sx, rowsum, tx = got
+        rqx, rsx, rrow, rtx = qq.act_quant(ry)
+        assert (_np(qx).astype(np.int64) == rqx).all() and (_np(sx).view(np.uint16) == rsx.view(np.uint16)).all()
+        assert (_np(rowsum).astype(np.int64) == rrow).all()
+        assert np.allclose(_np(tx), rtx, rtol=1e-4, atol=1e-2)
