@@ -1323,14 +1323,18 @@ __global__ __launch_bounds__(kMmaThreads, 1) void mma_kernel(GemmDev p)
         if (!s_last) return;
         for (int s2 = 0; s2 < p.S; ++s2) {
             if (s2 == slice) continue;
-            const int4* theirs = p.parts + ((size_t)(tile_id * p.S + s2) * NJ) * kMmaThreads + threadIdx.x;
+            const int4* base = p.parts + ((size_t)(tile_id * p.S + s2) * NJ) * kMmaThreads;
+            const auto theirs = part_rsrc(base, NJ * kMmaThreads * 16);
 #pragma unroll
-            for (int j0 = 0; j0 < NJ; j0 += 16) {          // sixteen loads in flight: the sum is pure load latency
+            for (int j0 = 0; j0 < NJ; j0 += 16) {          // sixteen (four) loads in flight: the sum is pure load latency
                 v4i t[16];
+                if constexpr (CF == 4) {
 #pragma unroll
-                for (int x = 0; x < 16; ++x) load_sc1_nowait(t[x], theirs + (size_t)(j0 + x) * kMmaThreads);
+                    for (int x = 0; x < 16; x += 4) load_sc1_and_wait(&t[x], base + threadIdx.x + (size_t)(j0 + x) * kMmaThreads, kMmaThreads);
+                } else {
 #pragma unroll
-                for (int x = 0; x < 16; x += 4) wait_loads(t[x], t[x + 1], t[x + 2], t[x + 3]);
+                    for (int x = 0; x < 16; ++x) t[x] = load_sc1(theirs, (int)threadIdx.x * 16, (j0 + x) * kMmaThreads * 16);
+                }
 #pragma unroll
                 for (int x = 0; x < 16; ++x) {
                     const int j = j0 + x, cf = j >> 4, tf = (j >> 2) & 3, qd = j & 3;
@@ -1339,6 +1343,7 @@ __global__ __launch_bounds__(kMmaThreads, 1) void mma_kernel(GemmDev p)
                     acc[cf][tf][4 * qd + 2] += t[x].z;
                     acc[cf][tf][4 * qd + 3] += t[x].w;
                 }
+                __builtin_amdgcn_sched_barrier(0);         // or the loads of all the groups are moved together
             }
         }
     }

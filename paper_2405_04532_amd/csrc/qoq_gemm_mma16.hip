@@ -323,12 +323,10 @@ __global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(GemmDev p)
             if (s2 == slice) continue;
             const int4* theirs = p.parts + ((size_t)(tile_id * p.S + s2) * NJ) * kMmaThreads + threadIdx.x;
 #pragma unroll
-            for (int j0 = 0; j0 < NJ; j0 += 16) {          // sixteen loads in flight: the sum is pure load latency
+            for (int j0 = 0; j0 < NJ; j0 += 16) {          // four loads in flight: no plan cuts this kernel, only a forced one
                 v4i t[16];
 #pragma unroll
-                for (int x = 0; x < 16; ++x) load_sc1_nowait(t[x], theirs + (size_t)(j0 + x) * kMmaThreads);
-#pragma unroll
-                for (int x = 0; x < 16; x += 4) wait_loads(t[x], t[x + 1], t[x + 2], t[x + 3]);
+                for (int x = 0; x < 16; x += 4) load_sc1_and_wait(&t[x], theirs + (size_t)(j0 + x) * kMmaThreads, kMmaThreads);
 #pragma unroll
                 for (int x = 0; x < 16; ++x) acc[(j0 + x) >> 3][(j0 + x) & 7] += t[x];
             }

@@ -263,3 +263,15 @@ def test_a_failed_gemm_launch_is_reported(api, tmp_path):
     rows = [[int(v) for v in line.split()] for line in out.stdout.splitlines()]
     assert len(rows) == 31
     assert all(good == 0 and bad != 0 for _, good, bad in rows), [r for r in rows if r[1] != 0 or r[2] == 0]
+
+
+def test_no_register_load_in_inline_assembly():
+    """The compiler takes an output register of inline assembly as written: a load there may still be on its way.  Copies to LDS
+    have no such output."""
+    csrc = os.path.join(ROOT, "paper_2405_04532_amd", "csrc")
+    for name in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, name)).read()
+        for m in re.finditer(r"asm\s*(?:volatile)?\s*\((.*?)\);", text, flags=re.S):
+            loads = re.search(r"(global|buffer|flat|scratch|ds|s)_(load|read)\w*", m.group(1))
+            if loads and "_lds_" not in loads.group(0):
+                assert "waitcnt" in m.group(1), (name, m.group(0))
