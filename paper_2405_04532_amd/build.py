@@ -3,6 +3,7 @@ gfx950, and the native half of the Python binding, _qoq_py.so, from csrc/qoq_py.
 
 Usage: python -m paper_2405_04532_amd.build   (cross-compiles; no GPU needed)
 """
+import importlib.util
 import os
 import subprocess
 import sys
@@ -91,13 +92,17 @@ def _link_binding(obj):
 def build(extra_flags=(), verbose=False):
     os.makedirs(OBJ, exist_ok=True)
     extra = list(extra_flags)
+    with_binding = importlib.util.find_spec("torch") is not None      # the C library needs no torch, its Python binding does
     with ThreadPoolExecutor(max_workers=9) as ex:
-        binding = ex.submit(_compile_binding)
+        binding = ex.submit(_compile_binding) if with_binding else None
         objs = list(ex.map(lambda s: _compile(s, extra), SOURCES))
     subprocess.check_call(["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs)
     subprocess.check_call(["hipcc", "-shared", os.path.join(CSRC, "probe_read.hip"), os.path.join(CSRC, "probe_mfma.hip"),
                            "-o", PROBE_LIB] + FLAGS + extra)
-    _link_binding(binding.result())
+    if with_binding:
+        _link_binding(binding.result())
+    else:
+        print("no torch: the Python binding is not built")
     if verbose:
         print("built", LIB)
     return LIB

@@ -26,6 +26,20 @@ class NoTruth:
         raise ValueError("no truth value")
 
 
+def test_the_c_library_is_built_without_torch(monkeypatch, tmp_path, capsys):
+    import sys
+
+    from paper_2405_04532_amd import build
+    ran = []
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    monkeypatch.setattr(build, "_compile", lambda source, extra: source)
+    monkeypatch.setattr(build.subprocess, "check_call", lambda command, **kw: ran.append(command))
+    monkeypatch.setitem(sys.modules, "torch", None)
+    assert build.build() == build.LIB
+    assert [c for c in ran if build.LIB in c] and not [c for c in ran if build.PY_LIB in c]
+    assert "not built" in capsys.readouterr().out
+
+
 @gpu
 def test_a_flag_without_a_truth_value_raises_its_own_error():
     x, gamma = torch.ones((M, K), dtype=torch.float16, device=DEV), torch.ones(K, dtype=torch.float16, device=DEV)
