@@ -126,7 +126,7 @@ _native = None
 
 
 def _load_native():
-    """The native half of this module (raises if it has not been built)."""
+    """The native half of this module (raises if it has not been built, or for another torch)."""
     global _native
     if _native is None:
         lib()
@@ -136,6 +136,9 @@ def _load_native():
                                                       loader=importlib.machinery.ExtensionFileLoader("_qoq_py", NATIVE_PATH))
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)
+        if module.torch_version != torch.__version__:
+            raise RuntimeError(f"{NATIVE_PATH} was built for torch {module.torch_version}, this is {torch.__version__}: "
+                               "run `python -m paper_2405_04532_amd.build` again")
         module.set_raise_status(_check)
         _native = module
     return _native

@@ -76,10 +76,12 @@ def _check_astat_prologue(path):
 def _compile_binding():
     """Host C++ against the headers of the torch that is installed; linked to the library beside it."""
     import sysconfig
+    import torch
     from torch.utils.cpp_extension import include_paths
     obj = os.path.join(OBJ, "qoq_py.o")
     inc = [f"-I{d}" for d in include_paths() + [sysconfig.get_paths()["include"]]]
-    subprocess.check_call(["hipcc", "-c", os.path.join(CSRC, "qoq_py.cpp"), "-o", obj, "-O2", "-std=c++17", "-fPIC", "-DUSE_ROCM=1"] + inc)
+    subprocess.check_call(["hipcc", "-c", os.path.join(CSRC, "qoq_py.cpp"), "-o", obj, "-O2", "-std=c++17", "-fPIC", "-DUSE_ROCM=1",
+                           f'-DQOQ_TORCH_VERSION="{torch.__version__}"'] + inc)
     return obj
 
 

@@ -401,4 +401,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_qoq_py", nullptr, -1, methods, nu
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__qoq_py(void) { return PyModule_Create(&module); }
+// torch_version: the torch whose classes this was compiled against; api.py refuses any other.
+PyMODINIT_FUNC PyInit__qoq_py(void)
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", QOQ_TORCH_VERSION) != 0) Py_CLEAR(m);
+    return m;
+}

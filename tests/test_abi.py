@@ -14,7 +14,7 @@ HEADER = os.path.join(ROOT, "include", "qoq_w4a8.h")
 @pytest.fixture(scope="module")
 def api():
     from paper_2405_04532_amd import api as a
-    if not os.path.exists(a.LIB_PATH):
+    if not (os.path.exists(a.LIB_PATH) and os.path.exists(a.NATIVE_PATH)):
         from paper_2405_04532_amd import build
         build.build()
     return a

@@ -26,6 +26,14 @@ class NoTruth:
         raise ValueError("no truth value")
 
 
+def test_a_binding_of_another_torch_is_refused(monkeypatch):
+    assert api._load_native().torch_version == torch.__version__
+    monkeypatch.setattr(api, "_native", None)
+    monkeypatch.setattr(torch, "__version__", "0.0")
+    with pytest.raises(RuntimeError, match="built for torch"):
+        api._load_native()
+
+
 def test_the_c_library_is_built_without_torch(monkeypatch, tmp_path, capsys):
     import sys
 
