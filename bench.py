@@ -67,37 +67,41 @@ def load_read_probe():
     lib = ctypes.CDLL(qbuild.PROBE_LIB)
     lib.qoq_probe_read.restype = ctypes.c_int
     lib.qoq_probe_read.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]
-    lib.qoq_probe_mfma.restype = ctypes.c_int
-    lib.qoq_probe_mfma.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+    for probe in (lib.qoq_probe_mfma, lib.qoq_probe_mfma16):
+        probe.restype = ctypes.c_int
+        probe.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
     return lib
 
 
 def mfma_ceiling(dev):
     """What the INT8 matrix cores sustain on this machine, with no memory traffic at all (csrc/probe_mfma.hip): one
-    wave per SIMD issuing nothing but the compute-bound kernel's matrix instruction, about 3 ms per mode so that the
-    clock settles.  Fractions of the published peak."""
+    wave per SIMD issuing nothing but the compute-bound kernels' matrix instruction, 32x32x32 with one workgroup per
+    compute unit and 16x16x64 with two, about 3 ms per mode so that the clock settles.  Fractions of the published peak."""
     import torch
     probe = load_read_probe()
     sink = torch.zeros(16, dtype=torch.int32, device=dev)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     stream = torch.cuda.current_stream().cuda_stream
-    out = {}
+    out, out16 = {}, {}
     names = {0: "constant_operands", 1: "random_operands", 2: "random_operands_with_dequant_valu",
              3: "gemm_like_operands_with_dequant_valu"}
     iters = 12000
-    for mode, name in names.items():
-        if probe.qoq_probe_mfma(mode, iters // 10, cus, sink.data_ptr(), stream) != 0:
-            raise RuntimeError("qoq_probe_mfma refused its arguments")
-        torch.cuda.synchronize()
-        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        e0.record()
-        probe.qoq_probe_mfma(mode, iters, cus, sink.data_ptr(), stream)
-        e1.record()
-        torch.cuda.synchronize()
-        tops = 2.0 * 32 ** 3 * 16 * iters * 4 * cus / (e0.elapsed_time(e1) * 1e-3) / 1e12
-        out[name] = round(tops / INT8_PEAK_TOPS, 4)
+    for run, ops, rounds, res in ((probe.qoq_probe_mfma, 2.0 * 32 ** 3, iters, out),
+                                  (probe.qoq_probe_mfma16, 2.0 * 16 * 16 * 64, 2 * iters, out16)):
+        for mode, name in names.items():
+            if run(mode, rounds // 10, cus, sink.data_ptr(), stream) != 0:
+                raise RuntimeError("the matrix-core probe refused its arguments")
+            torch.cuda.synchronize()
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            run(mode, rounds, cus, sink.data_ptr(), stream)
+            e1.record()
+            torch.cuda.synchronize()
+            tops = ops * 16 * rounds * 4 * cus / (e0.elapsed_time(e1) * 1e-3) / 1e12
+            res[name] = round(tops / INT8_PEAK_TOPS, 4)
     out["kernel"] = ("v_mfma_i32_32x32x32_i8 back to back, one wave per SIMD on %d compute units, 16 accumulator tiles, "
                      "no memory or LDS traffic; fractions of the published peak" % cus)
+    out["mfma_16x16x64"] = out16
     return out
 
 

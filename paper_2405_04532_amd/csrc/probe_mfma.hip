@@ -1,7 +1,8 @@
 // Measurement probe, not part of the W4A8 boundary: what the INT8 matrix cores sustain on this machine.
 //
-// One wave per SIMD on every compute unit issues v_mfma_i32_32x32x32_i8 back to back into 16 accumulator tiles, the
-// shape of the compute-bound GEMM's main loop, with no memory or LDS traffic at all.  The modes differ in the operand
+// One wave per SIMD on every compute unit issues v_mfma_i32_32x32x32_i8 or v_mfma_i32_16x16x64_i8 (the instructions of the
+// compute-bound GEMM with one and with two workgroups per compute unit) back to back into 16 accumulator tiles, with no
+// memory or LDS traffic at all.  The modes differ in the operand
 // data and in the vector work issued beside the matrix instructions: the matrix cores are power limited, so the clock
 // they sustain, and with it the attainable rate, depends on how many operand bits toggle between consecutive
 // instructions and on what else the compute unit is doing.  The benchmark reports these rates next to the GEMM's so
@@ -15,15 +16,18 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-template <int MODE>
+template <int MODE, bool WIDE>                          // WIDE: 32x32x32, else 16x16x64
 __global__ __launch_bounds__(256) void mfma_kernel(int iters, int* sink)
 {
+    typedef std::conditional_t<WIDE, v16i, v4i> Acc;
+    constexpr int kRegs = WIDE ? 16 : 4;
     v4i a[8], b[8];
     uint32_t h = (threadIdx.x + blockIdx.x * 256u) * 2654435761u + 12345u;
     auto next = [&]() { h ^= h << 13; h ^= h >> 17; h ^= h << 5; return h; };
@@ -44,9 +48,9 @@ __global__ __launch_bounds__(256) void mfma_kernel(int iters, int* sink)
             b[i] = MODE == 3 ? (v4i){small4(), small4(), small4(), small4()} : (v4i){(int)next(), (int)next(), (int)next(), (int)next()};
         }
     }
-    v16i c[16];
+    Acc c[16];
     for (int i = 0; i < 16; ++i)
-        for (int j = 0; j < 16; ++j) c[i][j] = 0;
+        for (int j = 0; j < kRegs; ++j) c[i][j] = 0;
     uint32_t x[4] = {next(), next(), next(), next()}, y[4] = {0, 0, 0, 0};
     uint32_t S = 0x00030003u, B = 0x01010101u;
     const uint32_t M = 0x0f0f0f0fu, X = 0x80808080u;
@@ -55,7 +59,8 @@ __global__ __launch_bounds__(256) void mfma_kernel(int iters, int* sink)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int ia = MODE == 0 ? 0 : (i & 7), ib = MODE == 0 ? 0 : ((i * 3) & 7);
-            asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+a"(c[i]) : "v"(a[ia]), "v"(b[ib]));
+            if constexpr (WIDE) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+a"(c[i]) : "v"(a[ia]), "v"(b[ib]));
+            else asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(c[i]) : "v"(a[ia]), "v"(b[ib]));
             if (MODE >= 2)   // unpack + multiply-add + sign flip of one operand dword
                 asm volatile("v_lshrrev_b32 %0, 4, %1\n\tv_and_b32 %0, %2, %0\n\tv_pk_mad_u16 %0, %3, %0, %4\n\ts_nop 0\n\tv_xor_b32 %0, %5, %0"
                              : "=&v"(y[i & 3]) : "v"(x[i & 3]), "v"(M), "v"(S), "v"(B), "v"(X));
@@ -63,8 +68,23 @@ __global__ __launch_bounds__(256) void mfma_kernel(int iters, int* sink)
     }
     int s = 0;
     for (int i = 0; i < 16; ++i)
-        for (int j = 0; j < 16; ++j) s += c[i][j];
+        for (int j = 0; j < kRegs; ++j) s += c[i][j];
     if (s == 0x7fffffff) sink[0] = s + (int)(y[0] + y[1] + y[2] + y[3]);   // data dependent: keeps the work alive
+}
+
+template <bool WIDE>
+int run(int mode, int iters, int workgroups, void* sink, void* stream)
+{
+    if (mode < 0 || mode > 3 || iters < 1 || workgroups < 1 || workgroups > 65536 || !sink) return 1;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    int* out = static_cast<int*>(sink);
+    switch (mode) {
+        case 0: hipLaunchKernelGGL((mfma_kernel<0, WIDE>), dim3((unsigned)workgroups), dim3(256), 0, s, iters, out); break;
+        case 1: hipLaunchKernelGGL((mfma_kernel<1, WIDE>), dim3((unsigned)workgroups), dim3(256), 0, s, iters, out); break;
+        case 2: hipLaunchKernelGGL((mfma_kernel<2, WIDE>), dim3((unsigned)workgroups), dim3(256), 0, s, iters, out); break;
+        default: hipLaunchKernelGGL((mfma_kernel<3, WIDE>), dim3((unsigned)workgroups), dim3(256), 0, s, iters, out); break;
+    }
+    return hipGetLastError() == hipSuccess ? 0 : 2;
 }
 
 }  // namespace
@@ -74,14 +94,11 @@ __global__ __launch_bounds__(256) void mfma_kernel(int iters, int* sink)
 // Returns 0, 1 on a bad argument, 2 if the launch failed.
 extern "C" int qoq_probe_mfma(int mode, int iters, int workgroups, void* sink, void* stream)
 {
-    if (mode < 0 || mode > 3 || iters < 1 || workgroups < 1 || workgroups > 65536 || !sink) return 1;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    int* out = static_cast<int*>(sink);
-    switch (mode) {
-        case 0: hipLaunchKernelGGL(mfma_kernel<0>, dim3((unsigned)workgroups), dim3(256), 0, s, iters, out); break;
-        case 1: hipLaunchKernelGGL(mfma_kernel<1>, dim3((unsigned)workgroups), dim3(256), 0, s, iters, out); break;
-        case 2: hipLaunchKernelGGL(mfma_kernel<2>, dim3((unsigned)workgroups), dim3(256), 0, s, iters, out); break;
-        default: hipLaunchKernelGGL(mfma_kernel<3>, dim3((unsigned)workgroups), dim3(256), 0, s, iters, out); break;
-    }
-    return hipGetLastError() == hipSuccess ? 0 : 2;
+    return run<true>(mode, iters, workgroups, sink, stream);
+}
+
+// The same with the 16x16x64 instruction: half the operations, 2 * 16 * 16 * 64 * 16 * iters * 4 * workgroups.
+extern "C" int qoq_probe_mfma16(int mode, int iters, int workgroups, void* sink, void* stream)
+{
+    return run<false>(mode, iters, workgroups, sink, stream);
 }

@@ -357,15 +357,6 @@ __device__ inline void unpack8(const uint4& v, double (&f)[8])
     for (int j = 0; j < 8; ++j) f[j] = (double)__half2float(h[j]);
 }
 
-__device__ inline uint4 pack8(const double (&f)[8])
-{
-    uint32_t w[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        w[j] = (uint32_t)double_to_half_rne(f[2 * j]) | ((uint32_t)double_to_half_rne(f[2 * j + 1]) << 16);
-    return make_uint4(w[0], w[1], w[2], w[3]);
-}
-
 // The machine operations behind the FP32 decision routines of qoq_half_decide.h.  keep(): an empty asm on the value,
 // which keeps the compiler from merging an FP32 product with a conversion next to it (of an FP16 factor, or of the
 // product to FP16) into one mixed-precision multiply-add with a zero addend: that turns a product of -0 into +0.
