@@ -74,9 +74,8 @@ def load_read_probe():
 
 
 def mfma_ceiling(dev):
-    """What the INT8 matrix cores sustain on this machine, with no memory traffic at all (csrc/probe_mfma.hip): one
-    wave per SIMD issuing nothing but the compute-bound kernels' matrix instruction, 32x32x32 with one workgroup per
-    compute unit and 16x16x64 with two, about 3 ms per mode so that the clock settles.  Fractions of the published peak."""
+    """What the INT8 matrix cores sustain on this machine, with no memory traffic at all (csrc/probe_mfma.hip): nothing
+    but the compute-bound kernels' matrix instruction, 32x32x32 from one wave per SIMD and 16x16x64 from two, about 3 ms per mode so that the clock settles.  Fractions of the published peak."""
     import torch
     probe = load_read_probe()
     sink = torch.zeros(16, dtype=torch.int32, device=dev)
@@ -86,22 +85,22 @@ def mfma_ceiling(dev):
     names = {0: "constant_operands", 1: "random_operands", 2: "random_operands_with_dequant_valu",
              3: "gemm_like_operands_with_dequant_valu"}
     iters = 12000
-    for run, ops, rounds, res in ((probe.qoq_probe_mfma, 2.0 * 32 ** 3, iters, out),
-                                  (probe.qoq_probe_mfma16, 2.0 * 16 * 16 * 64, 2 * iters, out16)):
+    for run, ops, rounds, wgs, res in ((probe.qoq_probe_mfma, 2.0 * 32 ** 3, iters, cus, out),
+                                       (probe.qoq_probe_mfma16, 2.0 * 16 * 16 * 64, iters, 2 * cus, out16)):
         for mode, name in names.items():
-            if run(mode, rounds // 10, cus, sink.data_ptr(), stream) != 0:
+            if run(mode, rounds // 10, wgs, sink.data_ptr(), stream) != 0:
                 raise RuntimeError("the matrix-core probe refused its arguments")
             torch.cuda.synchronize()
             e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             e0.record()
-            run(mode, rounds, cus, sink.data_ptr(), stream)
+            run(mode, rounds, wgs, sink.data_ptr(), stream)
             e1.record()
             torch.cuda.synchronize()
-            tops = ops * 16 * rounds * 4 * cus / (e0.elapsed_time(e1) * 1e-3) / 1e12
+            tops = ops * 16 * rounds * 4 * wgs / (e0.elapsed_time(e1) * 1e-3) / 1e12
             res[name] = round(tops / INT8_PEAK_TOPS, 4)
     out["kernel"] = ("v_mfma_i32_32x32x32_i8 back to back, one wave per SIMD on %d compute units, 16 accumulator tiles, "
                      "no memory or LDS traffic; fractions of the published peak" % cus)
-    out["mfma_16x16x64"] = out16
+    out["mfma_16x16x64"] = dict(out16, kernel="v_mfma_i32_16x16x64_i8, two waves per SIMD")
     return out
 
 

@@ -1,7 +1,7 @@
 // Measurement probe, not part of the W4A8 boundary: what the INT8 matrix cores sustain on this machine.
 //
-// One wave per SIMD on every compute unit issues v_mfma_i32_32x32x32_i8 or v_mfma_i32_16x16x64_i8 (the instructions of the
-// compute-bound GEMM with one and with two workgroups per compute unit) back to back into 16 accumulator tiles, with no
+// Each wave issues v_mfma_i32_32x32x32_i8 or v_mfma_i32_16x16x64_i8 (the instructions of the compute-bound GEMM with one and
+// with two workgroups per compute unit) back to back into 16 accumulator tiles, with no
 // memory or LDS traffic at all.  The modes differ in the operand
 // data and in the vector work issued beside the matrix instructions: the matrix cores are power limited, so the clock
 // they sustain, and with it the attainable rate, depends on how many operand bits toggle between consecutive
@@ -9,7 +9,7 @@
 // that its fraction of the published peak can be read against what the hardware sustains with this kind of work.
 //   mode 0  small constant operands (nothing toggles)
 //   mode 1  random INT8 operands, eight register sets rotated between instructions
-//   mode 2  mode 1 plus, per matrix instruction, the vector work of the in-register UINT4 -> INT8 dequantizer
+//   mode 2  mode 1 plus, per 32x32x32 or two 16x16x64 instructions, the vector work of the in-register UINT4 -> INT8 dequantizer
 //           (unpack, packed multiply-add, sign flip: Sections 5.2.2-5.2.3 of arXiv 2405.04532)
 //   mode 3  mode 2 with operand statistics of the GEMM: one operand random bytes (dequantized weights), the other small
 //           integers (quantized activations: most codes within +-8)
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256) void mfma_kernel(int iters, int* sink)
             const int ia = MODE == 0 ? 0 : (i & 7), ib = MODE == 0 ? 0 : ((i * 3) & 7);
             if constexpr (WIDE) asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %0" : "+a"(c[i]) : "v"(a[ia]), "v"(b[ib]));
             else asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(c[i]) : "v"(a[ia]), "v"(b[ib]));
-            if (MODE >= 2)   // unpack + multiply-add + sign flip of one operand dword
+            if (MODE >= 2 && (WIDE || !(i & 1)))   // unpack + multiply-add + sign flip of one operand dword, per 64 K operations
                 asm volatile("v_lshrrev_b32 %0, 4, %1\n\tv_and_b32 %0, %2, %0\n\tv_pk_mad_u16 %0, %3, %0, %4\n\ts_nop 0\n\tv_xor_b32 %0, %5, %0"
                              : "=&v"(y[i & 3]) : "v"(x[i & 3]), "v"(M), "v"(S), "v"(B), "v"(X));
         }
