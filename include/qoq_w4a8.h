@@ -123,7 +123,8 @@ int qoq_w4a8_gemm(const int8_t* qx, const void* sx_fp16, const int32_t* rowsum,
  * caller's workspace: 16 MiB of partial tiles and 256 KiB of counters per GPU, held by every GPU the library runs on
  * until the process ends.  The call allocates and frees nothing (the first call on a device looks up the array's
  * address on that device, which allocates nothing either; make that first call before a capture begins).
- *   - A problem whose launch configuration needs more scratch than that returns QOQ_ERR_WORKSPACE and enqueues
+ *   - Where the fastest launch configuration needs more scratch than that, one of 65 to 512 tokens that needs none is
+ *     taken if K is short enough for it (K <= 8192); else the call returns QOQ_ERR_WORKSPACE and enqueues
  *     nothing (use qoq_w4a8_gemm with a workspace; qoq_gemm_workspace_bytes tells the size: up to 16 MiB + the
  *     counters fit).
  *   - Every call on a GPU shares that GPU's array: calls that overlap in time on one GPU (two streams, two threads)

@@ -76,15 +76,21 @@ int gemm_common(const int8_t* qx, const void* sx, const int32_t* rowsum, const v
     if (!aligned16(qx) || !aligned16(packed) || !aligned16(out16) || !aligned16(out32) || !aligned16(ws))
         return QOQ_ERR_ALIGN;
     int tile_m, split_k;
-    qoq::pick_gemm_config(M, N, K, mode, forced(), tile_m, split_k);
+    const qoq::GemmTuning tuning = forced();
+    qoq::pick_gemm_config(M, N, K, mode, tuning, tile_m, split_k);
+    const auto scratch_holds = [&] {
+        const size_t counters = qoq::gemm_counter_bytes(M, N, K, tile_m, split_k);
+        return counters <= kScratchCounterBytes && qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k) - counters <= kScratchPartBytes;
+    };
+    // where the fastest plan exchanges more than the static scratch holds, one that exchanges nothing, if there is one
+    if (static_scratch && tuning.tile_m == 0 && !scratch_holds()) qoq::pick_gemm_config_without_workspace(M, N, K, mode, tile_m, split_k);
     if ((uint64_t)M * (uint64_t)K >= ((uint64_t)1 << 32)) return QOQ_ERR_SHAPE;  // 32-bit activation offsets
     if (tile_m <= 71 && (uint64_t)N * (uint64_t)K >= ((uint64_t)1 << 33)) return QOQ_ERR_SHAPE;  // 32-bit weight offsets (4 GiB packed)
     const size_t need = qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k);
     size_t parts_offset = 0;
     if (static_scratch) {
         // the library's own per-device array instead of a caller's workspace: fixed counter region, then partial tiles
-        const size_t counters = qoq::gemm_counter_bytes(M, N, K, tile_m, split_k);
-        if (counters > kScratchCounterBytes || need - counters > kScratchPartBytes) return QOQ_ERR_WORKSPACE;
+        if (!scratch_holds()) return QOQ_ERR_WORKSPACE;
         if (!arch_ok()) return QOQ_ERR_ARCH;
         if (need) {
             const int rc = scratch_of_current_device(&ws);

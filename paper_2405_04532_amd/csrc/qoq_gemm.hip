@@ -1730,6 +1730,30 @@ static double astat_cost(int64_t M, int64_t N, int64_t G, int tile_m, int mode)
     return t.start + (t.fragment + t.fragment_group * (double)G) * f + (t.per_mb + t.per_mb_again * again) * mb;
 }
 
+// The cheaper of the activation-stationary tiles that hold all of K, if it takes less than `limit`; else 0.
+static int best_side_by_side(int64_t M, int64_t N, int64_t G, int mode, double limit)
+{
+    int tile_m = 0;
+    for (const int cand : {71, 70}) {
+        if (G > astat_max_groups(astat_tile(cand))) continue;
+        const double c = astat_cost(M, N, G, cand, mode);
+        if (c < limit) { tile_m = cand; limit = c; }
+    }
+    return tile_m;
+}
+
+// A plan of 65 to 512 tokens that exchanges nothing between workgroups, for calls without room for partial tiles; false if K
+// is too long for one.
+bool pick_gemm_config_without_workspace(int64_t M, int64_t N, int64_t K, int mode, int& tile_m, int& split_k)
+{
+    const int64_t G = K / kGroup;
+    const int tile = M > 64 && M <= 512 ? best_side_by_side(M, N, G, mode, 1e29) : 0;
+    if (!tile) return false;
+    tile_m = tile;
+    split_k = (int)astat_nwg(M, N, G, tile, 0);
+    return true;
+}
+
 // The other plans' times from their estimates, which rank these plans among each other but were fitted elsewhere (whole
 // layers in group mode): off by up to 40% for small tiles per channel, 3 to 6% after this (9% for 32-token tiles).
 static double measured_cost(int64_t N, int64_t G, int tile_m, int mode, double estimate)
@@ -1845,13 +1869,7 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
         // fastest plan on average; against the best without these tiles it gains 5% on average and is more than 2% slower for
         // 45, the worst by 7% (6528 x 20480 at 72 tokens, 34.5 us, 32.0 without).
         if (M <= 512) {
-            chosen = 1.01 * measured_cost(N, G, tile_m, mode, chosen);
-            int astat = 0;
-            for (const int cand : {71, 70}) {
-                if (G > astat_max_groups(astat_tile(cand))) continue;
-                const double c = astat_cost(M, N, G, cand, mode);
-                if (c < chosen) { astat = cand; chosen = c; }
-            }
+            const int astat = best_side_by_side(M, N, G, mode, 1.01 * measured_cost(N, G, tile_m, mode, chosen));
             if (astat) {
                 tile_m = astat;
                 split_k = (int)astat_nwg(M, N, G, tile_m, 0);

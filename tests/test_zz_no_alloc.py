@@ -69,6 +69,13 @@ def test_every_kernel_family(api, M, N, K, mode, cfg):
     assert _same_bits(got, want)
 
 
+def test_a_plan_without_partial_tiles_where_the_fastest_has_too_many(api):
+    M, N, K, mode = 97, 23936, 6528, 1
+    assert api.gemm_workspace_bytes(M, N, K, mode) > (16 << 20) + (256 << 10)
+    got, want = _both(api, M, N, K, mode, seed=91)
+    assert _same_bits(got, want)
+
+
 def test_scratch_limit_is_an_error_not_an_allocation(api):
     """A configuration whose partial tiles exceed the 16 MiB of the library's array is refused; the output is untouched."""
     M, N, K = 2048, 4096, 8192
