@@ -99,7 +99,7 @@ __device__ __forceinline__ int row_swizzle(int r) { return (r >> 1) & 7; }   // 
 // follows must not write them (a documented wait-state requirement the compiler honours for its own stores but
 // cannot for inline assembly, which it does not know to be a store: partial sums whose registers were reused at
 // once came out corrupted in a few lanes).  Hence the idle cycles inside the store statements.  The streaming
-// kernel goes further and keeps its stores out of the loop altogether (below): they go out after the last copy,
+// kernel goes further and keeps its stores out of the loop altogether: they go out after the last copy,
 // together with the wait for their completion, from registers the same statement keeps alive.
 __device__ __forceinline__ void store_sc1(int4* ptr, v4i v)
 {

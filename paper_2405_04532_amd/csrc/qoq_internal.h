@@ -37,8 +37,9 @@ struct GemmArgs {
     void* out_fp16;          // [M, N] FP16, or null
     int32_t* out_i32;        // [M, N] INT32, or null
     void* workspace;         // split-k counters and partial tiles when split_k > 1
-    int tile_m;              // 16, 32, 64 (streaming kernels) or 128 ... 131 (compute-bound kernel, four tile shapes)
-    int split_k;             // compute-bound kernel: k-slices per tile; streaming kernel: workgroups sharing the unit stream
+    int tile_m;              // 16, 32, 64 (streaming kernels), 65 ... 68 (lockstep), 69 ... 71 (activation-stationary: 16, 32,
+                             // 64 tokens) or 128 ... 132 (compute-bound kernels, five tile shapes)
+    int split_k;             // compute-bound kernels: k-slices per tile; the others: workgroups per token tile (and k-slice)
     size_t parts_offset = 0; // byte offset of the partial tiles inside the workspace; 0 = directly behind the counters
 };
 // Bytes of arrival counters at the start of the workspace of a (tile_m, split_k) launch (0 if it exchanges nothing).

@@ -41,7 +41,7 @@
 // instead of 16.6, Llama-3-70B heads 64 x 1024 18.2 instead of 19.9.  The vector pipe is active half of the time: 150 of the
 // 250 vector instructions per chunk unpack codes.  Taking the longest sequences first, or two waves per workgroup, was slower.
 // Relative error of the output against FP64 on the same cache (1 to 64 sequences, 64 to 8192 tokens, 1 to 16 heads per KV head):
-// 2.0e-4 to 2.4e-4, the FP16 softmax weights' own; 3% less than with one tile per instruction on average, nowhere more.
+// 2.0e-4 to 2.5e-4, the FP16 softmax weights' own; 3% less than with one tile per instruction on average, nowhere more.
 // The scale/zero words of a chunk are loaded together with its codes, one chunk ahead of the arithmetic (the
 // prefetch of the dequantization parameters of Section 5.3).  Partial (max, sum, acc) of the waves meet in LDS.
 #include <hip/hip_fp16.h>
