@@ -15,7 +15,8 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqoq_w4a8.so")
 PROBE_LIB = os.path.join(HERE, "libqoq_probe.so")     # measurement probes of the benchmark (plain streaming read, matrix-core ceiling)
 PY_LIB = os.path.join(HERE, "_qoq_py.so")             # native argument marshalling of api.py's hot calls (host code only)
-SOURCES = ["qoq_api.hip", "qoq_pack.hip", "qoq_act.hip", "qoq_gemm.hip", "qoq_gemm_astat.hip", "qoq_gemm_mma16.hip", "qoq_kv4.hip", "qoq_transforms.hip"]
+SOURCES = ["qoq_api.hip", "qoq_pack.hip", "qoq_act.hip", "qoq_gemm.hip", "qoq_gemm_astat.hip", "qoq_gemm_mma16.hip", "qoq_gemm_mma8_group_256.hip", "qoq_gemm_mma8_group_128.hip",
+           "qoq_gemm_mma8_channel_256.hip", "qoq_gemm_mma8_channel_128.hip", "qoq_kv4.hip", "qoq_transforms.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed FP32 instructions off (they have produced wrong results on these machines)
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

@@ -82,7 +82,11 @@ int gemm_common(const int8_t* qx, const void* sx, const int32_t* rowsum, const v
         const size_t counters = qoq::gemm_counter_bytes(M, N, K, tile_m, split_k);
         return counters <= kScratchCounterBytes && qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k) - counters <= kScratchPartBytes;
     };
-    // where the fastest plan exchanges more than the static scratch holds, one that exchanges nothing, if there is one
+    // Where the fastest plan exchanges more than there is room for, the fastest without the eight-wave kernels; in the static
+    // scratch then one that exchanges nothing, if there is one.
+    const auto room = [&] { return static_scratch ? scratch_holds() : (ws && ws_bytes >= qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k)); };
+    if (tuning.tile_m == 0 && tile_m == 130 && qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k) && !room())
+        qoq::pick_gemm_config(M, N, K, mode, tuning, tile_m, split_k, false);
     if (static_scratch && tuning.tile_m == 0 && !scratch_holds()) qoq::pick_gemm_config_without_workspace(M, N, K, mode, tile_m, split_k);
     if ((uint64_t)M * (uint64_t)K >= ((uint64_t)1 << 32)) return QOQ_ERR_SHAPE;  // 32-bit activation offsets
     if (tile_m <= 71 && (uint64_t)N * (uint64_t)K >= ((uint64_t)1 << 33)) return QOQ_ERR_SHAPE;  // 32-bit weight offsets (4 GiB packed)
@@ -144,7 +148,11 @@ size_t qoq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int mode)
     if (!qoq::shape_ok(N, K, mode) || M <= 0) return 0;
     int tile_m, split_k;
     qoq::pick_gemm_config(M, N, K, mode, forced(), tile_m, split_k);
-    return qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k);
+    const size_t need = qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k);
+    // never less than a shape needs without the eight-wave kernels: a size that a program has stored stays what it was, or grows
+    qoq::pick_gemm_config(M, N, K, mode, forced(), tile_m, split_k, false);
+    const size_t without = qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k);
+    return need > without ? need : without;
 }
 
 int qoq_w4a8_linear(const void* x_fp16, const void* packed, int64_t M, int64_t N, int64_t K, int mode, void* out_fp16,

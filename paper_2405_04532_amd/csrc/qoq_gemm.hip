@@ -934,11 +934,10 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
 // ------------------------------------------------------------------------------------------
 // "mma" kernel (compute bound, M > 64).  Four waves per workgroup, exactly one per SIMD; a wave owns
 // 128 tokens x (32 * CF) channels in 4 x CF accumulator tiles of v_mfma_i32_32x32x32_i8 (CF = 4: 256
-// accumulator registers per lane).  Four workgroup shapes share the code:
+// accumulator registers per lane).  Three workgroup shapes share the code:
 //     CF = 4, waves 2 x 2 : 256 tokens x 256 channels  (large problems: fewest bytes per MFMA)
 //     CF = 2, waves 1 x 4 : 128 tokens x 256 channels  (few tokens; with more of these tiles than compute units the
 //                           16x16x64 kernel of qoq_gemm_mma16.hip takes over, two workgroups per compute unit)
-//     CF = 2, waves 2 x 2 : 256 tokens x 128 channels  (few channels)
 //     CF = 3, waves 2 x 2 : 256 tokens x 192 channels  (tile counts that fill the CUs where 256 x 256 leaves a
 //                           quarter idle, e.g. N = 12288).  A wave's three 32-row fragments are then every second
 //                           one of the tile's six, so that both waves see the same half of every 64-channel block.
@@ -1492,9 +1491,24 @@ void launch_mma(const GemmDev& p, bool fp16, hipStream_t s)
     else mma_kernel<GROUP, OUT_I32, CF, WM><<<grid, kMmaThreads, 0, s>>>(p);
 }
 
+// 16-token fragments of a token tile of the eight-wave kernels: equal tiles of three to nine.
+static int eight_wave_fragments(int64_t M)
+{
+    const int64_t frags = (M + 15) / 16, tiles = (frags + 8) / 9;
+    return (int)std::max<int64_t>(3, (frags + tiles - 1) / tiles);
+}
+
+// Channels of a tile of the eight-wave kernels: 128, or 256 where tiles of 128 (times the k-slices) need more than a round of
+// 256 workgroups.
+static int64_t eight_wave_width(int64_t M, int64_t N, int64_t S)
+{
+    const int64_t tm = 16 * eight_wave_fragments(M);
+    return ((M + tm - 1) / tm) * ((N + 127) / 128) * S <= 256 ? 128 : 256;
+}
+
 // tile_m selects the kernel and its shape: 16 / 32 / 64 = streaming kernel with that many tokens per tile;
-// 128 = compute-bound kernel, 256 tokens x 256 channels; 129 = 128 tokens x 256 channels; 130 = 256 x 128;
-// 131 = 256 x 192; 132 = 128 x 256, two workgroups per compute unit.  The error of a launch is read, and thereby cleared,
+// 128 = compute-bound kernel, 256 tokens x 256 channels; 129 = 128 tokens x 256 channels; 131 = 256 x 192; 132 = 128 x 256,
+// two workgroups per compute unit; 130 = eight waves on up to 144 tokens x 128 or 256 channels.  The error of a launch is read, and thereby cleared,
 // once: by the launcher of another file that made it, or here.
 template <bool GROUP>
 hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStream_t s)
@@ -1525,7 +1539,9 @@ hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStrea
     } else if (tile_m == 129) {
         launch_mma<GROUP, 2, 1>(p, fp16, s);
     } else if (tile_m == 130) {
-        launch_mma<GROUP, 2, 2>(p, fp16, s);
+        const int mf = eight_wave_fragments(p.M);
+        if (eight_wave_width(p.M, p.N, p.S) == 128) return GROUP ? launch_mma8_group_128(p, mf, s) : launch_mma8_channel_128(p, mf, s);
+        return GROUP ? launch_mma8_group_256(p, mf, s) : launch_mma8_channel_256(p, mf, s);
     } else if (tile_m == 131) {
         launch_mma<GROUP, 3, 2>(p, fp16, s);
     } else if (tile_m == 132) {
@@ -1539,25 +1555,32 @@ hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStrea
 }  // namespace
 
 // ---- launch configuration --------------------------------------------------------------------------
-// tile_m: 16 / 32 / 64 = streaming kernel with that many tokens per tile; 128 / 129 / 130 / 131 = compute-bound
-// kernel with 256 x 256, 128 x 256, 256 x 128, 256 x 192 (tokens x channels) tiles.  split_k: streaming kernel = number of
-// workgroups the unit stream is dealt to (per token tile); compute-bound kernel = k-slices per tile.
-static void mma_tile_shape(int tile_m, int64_t& tm, int64_t& tn)
+// tile_m: 16 / 32 / 64 = streaming kernel with that many tokens per tile; 128 / 129 / 131 / 132 = compute-bound kernel with
+// 256 x 256, 128 x 256, 256 x 192, 128 x 256 (tokens x channels) tiles; 130 = eight-wave kernel, equal token tiles.
+// split_k: streaming kernel = number of workgroups the unit stream is dealt to (per token tile); the others = k-slices per tile.
+static void mma_tile_shape(int64_t M, int64_t N, int tile_m, int64_t S, int64_t& tm, int64_t& tn)
 {
-    tm = (tile_m == 129 || tile_m == 132) ? 128 : 256;
-    tn = tile_m == 130 ? 128 : tile_m == 131 ? 192 : 256;
+    tm = tile_m == 130 ? 16 * eight_wave_fragments(M) : (tile_m == 129 || tile_m == 132) ? 128 : 256;
+    tn = tile_m == 130 ? eight_wave_width(M, N, S) : tile_m == 131 ? 192 : 256;
 }
-static int64_t mma_tiles(int64_t M, int64_t N, int tile_m)
+static int64_t mma_tiles(int64_t M, int64_t N, int tile_m, int64_t S)
 {
     int64_t tm, tn;
-    mma_tile_shape(tile_m, tm, tn);
+    mma_tile_shape(M, N, tile_m, S, tm, tn);
     return ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
+}
+// Arrival counters of the tiles (eight-wave kernel: room for its 128-channel tiles of every 256 tokens, whatever the width).
+static size_t mma_counter_bytes(int64_t M, int64_t N, int tile_m, int64_t S)
+{
+    int64_t n = mma_tiles(M, N, tile_m, S);
+    if (tile_m == 130) n = std::max(n, ((M + 255) / 256) * ((N + 127) / 128));
+    return align256((size_t)n * sizeof(int));
 }
 // k-slices of the compute-bound kernel: only when its tiles leave most CUs idle and every slice still has a
 // long run of groups (a partial tile costs 128-256 KiB of traffic each way plus a device-wide hand-over).
 static int mma_split(int64_t M, int64_t N, int64_t G, int tile_m, int forced_split)
 {
-    const int64_t tiles = mma_tiles(M, N, tile_m);
+    const int64_t tiles = mma_tiles(M, N, tile_m, 1);
     int64_t S = 1;
     if (forced_split > 0) S = forced_split;
     else if (tiles < 160) S = std::min<int64_t>(256 / tiles, G / 24);
@@ -1566,14 +1589,14 @@ static int mma_split(int64_t M, int64_t N, int64_t G, int tile_m, int forced_spl
     const int64_t gps = (G + S - 1) / S;
     return (int)((G + gps - 1) / gps);
 }
-// Cost model fitted to measurements on MI355X (all four shapes on the Llama-2-7B and Llama-3-70B layers at
+// Cost model of the four-wave kernels fitted to measurements on MI355X (all shapes on the Llama-2-7B and Llama-3-70B layers at
 // M = 512 ... 4096, within 5%), in microseconds: workgroups run in rounds of one per CU; a workgroup needs about
 // 8 us of prologue and epilogue plus, per group, a time that grows with the share of the CUs that are busy (the
 // clock drops as more matrix cores run): light-load time x (1 + 0.45 load^2); a split adds the hand-over.
 static double mma_cost(int64_t M, int64_t N, int64_t G, int tile_m, int& S)
 {
     S = mma_split(M, N, G, tile_m, 0);
-    const int64_t wgs = mma_tiles(M, N, tile_m) * S;
+    const int64_t wgs = mma_tiles(M, N, tile_m, S) * S;
     if (tile_m == 132) {
         // two workgroups per compute unit (128 x 256 tiles, shallower rings): worth it only when some compute units
         // really get two; a pair then takes about 1.85 times one workgroup's time per group at full load
@@ -1597,7 +1620,7 @@ static double mma_cost(int64_t M, int64_t N, int64_t G, int tile_m, int& S)
     }
     const int64_t rounds = (wgs + 255) / 256;
     const double load = (double)wgs / (double)(rounds * 256);
-    const double light = tile_m == 128 ? 1.18 : tile_m == 131 ? 0.92 : tile_m == 130 ? 0.64 : 0.62;
+    const double light = tile_m == 128 ? 1.18 : tile_m == 131 ? 0.92 : 0.62;
     const double per_group = light * (1.0 + 0.45 * load * load);
     return (double)rounds * (8.0 + per_group * (double)((G + S - 1) / S)) +
            (S > 1 ? (tile_m == 128 ? 30.0 : tile_m == 131 ? 22.0 : 9.0) : 0.0);
@@ -1781,14 +1804,42 @@ static double measured_cost(int64_t N, int64_t G, int tile_m, int mode, double e
         case 129: row = 5; break;
         case 131: row = 6; break;
         case 132: row = 7; break;
-        default: return estimate;                            // 128, 130: hardly ever the best at these sizes
+        default: return estimate;                            // 128: hardly ever the best at these sizes
     }
     const Fit& t = fits[row][mode != 0];
     return t.start + t.scale * estimate + t.per_mb * (double)N * (double)G * (double)kGroup / 2.0e6;
 }
 
-void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTuning& forced, int& tile_m, int& split_k)
+// Eight-wave kernels (tile_m 130): the cheapest number of k-slices, and with it the width, by a fit to 6600 times of 1300 shapes (65 ... 2048
+// tokens, K = 256 ... 28672, both modes; weights half from memory, half from the last-level cache; root mean square error 5 to
+// 6%), in microseconds: a start, more for every further round of 256 workgroups, per group of a slice a time that grows with the
+// token fragments and with the share of the compute units that are busy, the hand-over of slices, and the weights' way from memory.
+static double eight_wave_cost(int64_t M, int64_t N, int64_t G, int mode, int& S)
 {
+    struct Fit { double start, round, group, group_fragment, group_fragment_load, slices, slice_fragment, per_mb; };
+    static const Fit fits[2][2] = {                          // [channels][mode]
+        {{7.62, 6.39, 0.193, 0.0588, 0.0308, 0.56, 0.195, 0.0327}, {8.51, 7.44, 0.0, 0.0725, 0.0294, 0.82, 0.189, 0.0247}},     // 256 channels
+        {{7.48, 6.43, 0.0422, 0.0443, 0.0123, 0.86, 0.1155, 0.0378}, {8.07, 6.84, 0.0, 0.0413, 0.0123, 0.94, 0.1143, 0.0357}}};  // 128 channels
+    double best = 1e30;
+    const double mf = (double)eight_wave_fragments(M), mb = (double)N * (double)G * (double)kGroup / 2.0e6;
+    for (int64_t s = 1; s <= 8 && (s == 1 || (mma_tiles(M, N, 130, s) * s <= 272 && G >= 6 * s)); ++s) {
+        const int64_t gps = (G + s - 1) / s;
+        if ((G + gps - 1) / gps != s) continue;              // an empty slice
+        const Fit& t = fits[eight_wave_width(M, N, s) == 128][mode != 0];
+        const int64_t tiles = mma_tiles(M, N, 130, s), rounds = (tiles * s + 255) / 256;
+        const double rest = (double)(tiles * s - (rounds - 1) * 256) / 256.0, load = (double)(rounds - 1) + rest * rest;
+        const double c = t.start + t.round * (double)(rounds - 1) +
+                         (double)gps * ((double)rounds * (t.group + t.group_fragment * mf) + t.group_fragment_load * load * mf) +
+                         (s > 1 ? t.slices + t.slice_fragment * (double)s * mf : 0.0) + t.per_mb * mb;
+        if (c < best) { best = c; S = (int)s; }
+    }
+    return best;
+}
+
+// The plan without the eight-wave kernels; cost = its estimate in microseconds (up to 64 tokens: 0).
+static void pick_other_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTuning& forced, int& tile_m, int& split_k, double& cost)
+{
+    cost = 0.0;
     const int64_t G = K / kGroup;
     const bool pairs_ok = N % 128 == 0;                // the pair-streaming kernel takes whole block pairs
     const int natural = M <= 16 ? 16 : M <= 32 ? 32 : 64;   // smallest streaming tile that holds min(M, 64) tokens
@@ -1855,11 +1906,11 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
         return;
     }
     if (!forced.tile_m && M > 64) {
-        // Cheapest of the four tile shapes of the compute-bound kernel or, for a few hundred tokens, the streaming
+        // Cheapest of the tile shapes of the compute-bound kernels or, for a few hundred tokens, the streaming
         // kernels (they re-read the weights once per token tile but spread K over the whole chip).
         int S;
         double best = mma_cost(M, N, G, 128, S);
-        for (int cand = 129; cand <= 132; ++cand) {
+        for (const int cand : {129, 131, 132}) {
             const double c = mma_cost(M, N, G, cand, S);
             if (c < 0.98 * best) { best = c; tile_m = cand; }
         }
@@ -1871,10 +1922,12 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
         // they gain, more or less, where the weights are still in a cache.  Of the 3300 shapes the choice is within 0.4% of the
         // fastest plan on average; against the best without these tiles it gains 5% on average and is more than 2% slower for
         // 45, the worst by 7% (6528 x 20480 at 72 tokens, 34.5 us, 32.0 without).
+        cost = measured_cost(N, G, tile_m, mode, chosen);
         if (M <= 512) {
-            const int astat = best_side_by_side(M, N, G, mode, 1.01 * measured_cost(N, G, tile_m, mode, chosen));
+            const int astat = best_side_by_side(M, N, G, mode, 1.01 * cost);
             if (astat) {
                 tile_m = astat;
+                cost = astat_cost(M, N, G, tile_m, mode);
                 split_k = (int)astat_nwg(M, N, G, tile_m, 0);
                 return;
             }
@@ -1892,6 +1945,29 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
         return;
     }
     split_k = mma_split(M, N, G, tile_m, forced.split_k);
+}
+
+void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTuning& forced, int& tile_m, int& split_k, bool eight_waves)
+{
+    double cost;
+    pick_other_config(M, N, K, mode, forced, tile_m, split_k, cost);
+    if (forced.tile_m || !eight_waves || M <= 64 || N * K >= ((int64_t)1 << 33)) return;
+    // Taken where the estimate is ahead by a share of the other plan's that depends on how far off that one's estimate is: by
+    // nothing for the 64-token streaming, lockstep and 128 x 256 tiles (where the two are within 5% of each other the eight-wave
+    // kernels are 6 to 8% faster, the worst of 71 shapes 4% slower), 7% for the former two where K has to be cut, 5% for 64-token
+    // activation-stationary and 256 x 192 tiles, 10% for 32-token activation-stationary tiles, 12% for two-per-CU tiles (ahead
+    // by less, 8% slower at worst), 15% for the smaller streaming tiles; 5% more for less than eight groups, where starts and
+    // stores are all there is.  Of 500 shapes whose plan changes: 17% faster on average, 8 more than 2% slower, by 7% at most.
+    int S = 1;
+    const double eight = eight_wave_cost(M, N, K / kGroup, mode, S);
+    double ahead = 0.85;
+    if (tile_m == 129) ahead = 1.0;
+    else if (tile_m >= 64 && tile_m <= 66) ahead = S > 1 ? 0.93 : 1.0;
+    else if (tile_m == 71 || tile_m == 131) ahead = 0.95;
+    else if (tile_m == 70) ahead = 0.90;
+    else if (tile_m == 132) ahead = 0.88;
+    if (K < 8 * kGroup) ahead -= 0.05;
+    if (eight < ahead * cost - 0.3) { tile_m = 130; split_k = S; }
 }
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int split_k)
@@ -1914,9 +1990,17 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int spl
     }
     if (split_k <= 1) return 0;
     int64_t tm, tn;
-    mma_tile_shape(tile_m, tm, tn);
-    const size_t tiles = (size_t)mma_tiles(M, N, tile_m);
-    return align256(tiles * sizeof(int)) + tiles * (size_t)split_k * (size_t)(tm * tn) * sizeof(int32_t);
+    mma_tile_shape(M, N, tile_m, split_k, tm, tn);
+    const size_t tiles = (size_t)mma_tiles(M, N, tile_m, split_k);
+    size_t sums = tiles * (size_t)(tm * tn);
+    if (tile_m == 130) {
+        // each of the waves that share an output hands over its own fragments, rounded up; room for whole steps of 256 tokens,
+        // so that a program whose batches vary a little sizes its workspace once
+        const int64_t waves = tn == 256 ? 2 : 4;
+        sums = std::max<size_t>(tiles * (size_t)(16 * waves * ((eight_wave_fragments(M) + waves - 1) / waves) * tn),
+                                (size_t)((M + 255) / 256 * 256) * (size_t)((N + 127) / 128 * 128));
+    }
+    return mma_counter_bytes(M, N, tile_m, split_k) + sums * (size_t)split_k * sizeof(int32_t);
 }
 
 size_t gemm_counter_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int split_k)
@@ -1927,7 +2011,7 @@ size_t gemm_counter_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int split
         return align256((size_t)(((M + tile - 1) / tile) * (N / 16)) * sizeof(int));
     }
     if (tile_m <= 64) return align256((size_t)(((M + tile_m - 1) / tile_m) * (N / 64)) * sizeof(int));
-    return align256((size_t)mma_tiles(M, N, tile_m) * sizeof(int));
+    return mma_counter_bytes(M, N, tile_m, split_k);
 }
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
@@ -1974,7 +2058,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         p.upw = 0;
         p.S = a.split_k;
         p.gps = (int)((L.G + a.split_k - 1) / a.split_k);
-        counters = align256((size_t)mma_tiles(a.M, a.N, a.tile_m) * sizeof(int));
+        counters = mma_counter_bytes(a.M, a.N, a.tile_m, a.split_k);
     }
     p.parts = reinterpret_cast<int4*>(reinterpret_cast<uint8_t*>(a.workspace) + (a.parts_offset ? a.parts_offset : counters));
     return a.mode == 0 ? launch_any<true>(p, a.tile_m, nwg, a.out_fp16 != nullptr, s)

@@ -190,4 +190,11 @@ int astat_max_groups(int tile);
 // qoq_gemm_mma16.hip: the compute-bound kernel with 16x16x64 matrix instructions (tile_m code 132).
 hipError_t launch_mma16(const GemmDev& p, bool group, bool fp16, hipStream_t s);
 
+// qoq_gemm_mma8.h: eight waves on one output tile of 256 or 128 channels and 16 mf tokens (tile_m code 130); one
+// translation unit per mode and width, since each compiles seven kernels.
+hipError_t launch_mma8_group_256(const GemmDev& p, int mf, hipStream_t s);
+hipError_t launch_mma8_group_128(const GemmDev& p, int mf, hipStream_t s);
+hipError_t launch_mma8_channel_256(const GemmDev& p, int mf, hipStream_t s);
+hipError_t launch_mma8_channel_128(const GemmDev& p, int mf, hipStream_t s);
+
 }  // namespace qoq

@@ -38,7 +38,7 @@ struct GemmArgs {
     int32_t* out_i32;        // [M, N] INT32, or null
     void* workspace;         // split-k counters and partial tiles when split_k > 1
     int tile_m;              // 16, 32, 64 (streaming kernels), 65 ... 68 (lockstep), 69 ... 71 (activation-stationary: 16, 32,
-                             // 64 tokens) or 128 ... 132 (compute-bound kernels, five tile shapes)
+                             // 64 tokens) or 128 ... 132 (compute-bound kernels, 130 with eight waves)
     int split_k;             // compute-bound kernels: k-slices per tile; the others: workgroups per token tile (and k-slice)
     size_t parts_offset = 0; // byte offset of the partial tiles inside the workspace; 0 = directly behind the counters
 };
@@ -73,7 +73,9 @@ size_t kv4_decode_workspace_bytes(int64_t B, int64_t H, int64_t Hkv, int64_t S_m
 
 // Launch configuration the library picks for a problem (also sizes the workspace).
 struct GemmTuning { int tile_m, split_k; };  // 0 = let the heuristic decide
-void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTuning& forced, int& tile_m, int& split_k);
+// eight_waves = false: a plan without those kernels, whose k-slices take more workspace.
+void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTuning& forced, int& tile_m, int& split_k,
+                      bool eight_waves = true);
 bool pick_gemm_config_without_workspace(int64_t M, int64_t N, int64_t K, int mode, int& tile_m, int& split_k);
 
 }  // namespace qoq

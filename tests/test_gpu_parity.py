@@ -733,3 +733,60 @@ def test_rows_of_one_wave(api, M, K):
         assert (_np(qx).astype(np.int64) == rqx).all() and (_np(sx).view(np.uint16) == rsx.view(np.uint16)).all()
         assert (_np(rowsum).astype(np.int64) == rrow).all()
         assert np.allclose(_np(tx), rtx, rtol=1e-4, atol=1e-2)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M,N,K,split_k", [
+    # tiles of 128 channels
+    (1, 64, 128, 1),          # one token, one block, one group: a ring of one bundle, half a stage of two groups
+    (49, 192, 256, 1),        # four token fragments, the last of one token; a tile and a half of channels
+    (65, 320, 384, 1),        # five; a stage of two groups whose second lies past the end
+    (96, 128, 640, 2),        # six; slices of three and two groups
+    (112, 320, 1152, 1),      # seven; more bundles than the ring is deep
+    (128, 256, 1152, 3),      # eight; three slices
+    (129, 576, 896, 1),       # nine, the last of one token; four channel tiles and a part of one
+    (144, 64, 3328, 4),       # nine; slices of seven and five groups
+    (145, 320, 256, 1),       # two token tiles of five
+    (290, 448, 768, 2),       # three of seven; k-slices
+    # tiles of 256 channels: more than 256 tiles of 128
+    (48, 16448, 256, 2), (49, 32960, 128, 1), (145, 16576, 384, 1), (96, 16576, 640, 2), (290, 11072, 256, 1),
+    (256, 16576, 640, 1), (130, 16576, 1152, 2)])
+def test_eight_wave_kernels(api, mode, M, N, K, split_k):
+    """Three to nine token fragments per tile and their edges, both widths, rings that are not filled, odd groups, k-slices;
+    exact accumulators, and the same on a second launch in the same workspace (counters left at zero)."""
+    w, x = rand_inputs(M, N, K, seed=71 + M + N)
+    ref = (ogemm.forward_per_channel if mode else ogemm.forward_group)(_np(w), _np(x))
+    blob = api.pack_weights(w, mode)
+    qx, sx, rowsum, tx = api.quant_act_per_token(x, want_tx=True)
+    rs = rowsum if mode else None
+    api.set_gemm_config(130, split_k)
+    try:
+        assert api.query_gemm_config(M, N, K, mode) == (130, split_k)
+        ws = api.new_workspace(api.gemm_workspace_bytes(M, N, K, mode), DEV)
+        for _ in range(2):
+            acc = api.w4a8_gemm_i32(qx, blob, N, mode, rowsum=rs, workspace=ws)
+            assert (_np(acc).astype(np.int64) == ref["acc"]).all()
+        out = api.w4a8_gemm(qx, sx, blob, N, mode, rowsum=rs, workspace=ws)
+        folded = api.w4a8_gemm_token_sum(qx, sx, tx, blob, N, workspace=ws) if mode else None
+        api.set_gemm_config(16, 1)
+        plain = api.w4a8_gemm_token_sum(qx, sx, tx, blob, N) if mode else None
+    finally:
+        api.set_gemm_config()
+    check_fp16(out, ref["out64"])
+    assert folded is None or torch.equal(folded, plain)      # the same sums through the same FP32 expression
+
+
+def test_eight_wave_plan_without_room_for_its_slices(api):
+    """A shape whose plan cuts K, called with no workspace: as before, a plan that needs none, with the same result."""
+    M, N, K = 110, 12288, 5120
+    tile, slices = api.query_gemm_config(M, N, K)
+    assert tile == 130 and slices > 1
+    w, x = rand_inputs(M, N, K, seed=5)
+    blob = api.pack_weights(w)
+    qx, sx, _, _ = api.quant_act_per_token(x)
+    want = api.w4a8_gemm(qx, sx, blob, N)
+    got = torch.empty_like(want)
+    p = lambda t: t.data_ptr()
+    st = torch.cuda.current_stream().cuda_stream
+    assert api.lib().qoq_w4a8_gemm(p(qx), p(sx), None, p(blob), M, N, K, 0, p(got), None, 0, st) == 0
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
