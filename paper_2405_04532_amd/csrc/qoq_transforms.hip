@@ -2,7 +2,7 @@
 // channel gather for the activation-aware reordering, scaled-Hadamard rotation of block-input tensors.
 // These run when a model is prepared, not in the serving loop (at run time the reordering is the gather fused
 // into the activation quantizer, qoq_act.hip, and the rotation is folded into the preceding layer's weights),
-// so they are written for exactness first: the rotation sums in FP64, where sums of FP16 numbers are exact for
+// so they are written for exactness first: the rotation sums in FP64 or in whole numbers, where sums of FP16 numbers are exact for
 // these sizes, and rounds once to FP16.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <cmath>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 #include "qoq_fp16.h"
@@ -169,8 +170,9 @@ __global__ __launch_bounds__(256) void gather_direct_kernel(const __half* __rest
 
 // dst[r, b*n .. b*n+n) = src[r, b*n .. b*n+n) H_n * scale, H_n the Sylvester Hadamard matrix (entry (i, j) =
 // (-1)^popcount(i & j)), by the in-place butterfly: log2(n) stages of n/2 additions and subtractions.
-// FP64 throughout: every partial sum of at most 8192 FP16 numbers is a multiple of 2^-24 below 2^29 and therefore
-// exact, so the result is the exact product times `scale`, rounded once, whatever the order of the stages.
+// Exact sums: every partial sum of at most 8192 FP16 numbers is a multiple of 2^-24 below 2^29, which FP64 holds (and 32-bit
+// integers where the sums are small), so the result is the exact product times `scale`, rounded once, whatever the order of the
+// stages.
 constexpr int kMaxHadamard = 8192;
 
 // FP64 -> FP16, round to nearest even, for results that are zero or of at least 2^-126: the fraction bits below
@@ -187,37 +189,34 @@ __device__ __forceinline__ unsigned short half_rne_by_odd(double d)
     return __half_as_ushort(__float2half_rn(f));
 }
 
+// Sum of non-negative numbers over a wave.
+__device__ __forceinline__ float wave_sum_of(float v)
+{
+    auto moved = [](float x, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, false));
+    };
+    v += moved(v, std::integral_constant<int, 0xB1>());      // lanes ^1, ^2, then the mirrored half row and row of 16
+    v += moved(v, std::integral_constant<int, 0x4E>());
+    v += moved(v, std::integral_constant<int, 0x141>());
+    v += moved(v, std::integral_constant<int, 0x140>());
+    auto lane = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+    return (lane(0) + lane(16)) + (lane(32) + lane(48));
+}
+
 // Blocks of rows * K contiguous elements are cut into segments of 2048 * CH elements, one workgroup of 256 threads each
 // (a segment holds whole blocks; CH = 4 only for n = 8192).  A thread keeps 8 * CH elements in registers and takes the
 // stages in three layouts, with two exchanges through LDS instead of one per stage:
 //     A  16-byte chunks as they are loaded: element bits 0..2, and 11.. (chunks 256 apart)
 //     B  element bits 3..6 in registers
 //     C  element bits 7..10 in registers
-// and the FP16 results go back to chunk order through LDS for 16-byte stores.  A single workgroup with one LDS round
-// trip and one barrier per stage (twelve of them at n = 4096) was bound by LDS and barriers: 22016 x 4096 in 863 us,
-// 0.42 TB/s; this one takes 111 us, 3.2 TB/s (a copy of the tensor 67 us), bound by vector issue (FP64 additions,
-// conversions) together with its LDS traffic of 36 bytes per element.  LDS position of element i: 8 bytes of padding per 8 elements and 64 more per 128, which spreads all
-// three access patterns evenly over the 64 banks.
-template <int CH>
-__global__ __launch_bounds__(256) void hadamard_kernel(const uint4* __restrict__ src, int64_t chunks, int n, double scale,
-                                                       uint4* __restrict__ dst)
+// and the FP16 results go back to chunk order through LDS for 16-byte stores.  LDS position of element i: one element of padding
+// per 8 and eight more per 128, which spreads all three access patterns evenly over the 64 banks (two lanes to a bank at most).
+template <class T, int CH>
+__device__ __forceinline__ void hadamard_segment(T (&v)[CH][8], T* buf, int64_t c0, int64_t chunks, int n, double scale, uint4* __restrict__ dst)
 {
-    constexpr int kElems = 2048 * CH;
     auto pos = [](int i) { return i + (i >> 3) + ((i >> 7) << 3); };
-    __shared__ double buf[kElems + kElems / 8 + kElems / 16];
     const int t = threadIdx.x;
-    const int64_t c0 = (int64_t)blockIdx.x * (256 * CH);
-    double v[CH][8];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const int64_t at = c0 + c * 256 + t;
-        const uint4 raw = at < chunks ? src[at] : make_uint4(0u, 0u, 0u, 0u);
-        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-            v[c][e] = (double)__half2float(__ushort_as_half((unsigned short)(w[e >> 1] >> (16 * (e & 1)))));
-    }
-    auto butterfly = [](double& a, double& b) { const double s = a + b; b = a - b; a = s; };
+    auto butterfly = [](T& a, T& b) { const T s = a + b; b = a - b; a = s; };
     // ---- A
 #pragma unroll
     for (int h = 1; h < 8; h <<= 1)
@@ -242,7 +241,7 @@ __global__ __launch_bounds__(256) void hadamard_kernel(const uint4* __restrict__
     __syncthreads();
     // ---- B and C: sixteen elements at a time, `step` elements apart, from element `first` on
     auto stages16 = [&](int first, int step) __attribute__((always_inline)) {
-        double x[16];
+        T x[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) x[j] = buf[pos(first + j * step)];
 #pragma unroll
@@ -262,24 +261,97 @@ __global__ __launch_bounds__(256) void hadamard_kernel(const uint4* __restrict__
         for (int j = 0; j < 16; ++j) buf[pos(first + j * 8)] = v[j >> 3][j & 7];
     }
     __syncthreads();
-    unsigned short r[CH / 2][16];
+    uint32_t r[CH / 2][8];                               // pairs of FP16 results
+    const float below = (float)(scale * (1.0 - 4 * 0x1p-24)), above = (float)(scale * (1.0 + 4 * 0x1p-24));
 #pragma unroll
     for (int s = 0; s < CH / 2; ++s) {
         stages16((t & 127) + (t >> 7) * 2048 + s * 4096, 128);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) r[s][j] = half_rne_by_odd(v[j >> 3][j & 7] * scale);
+        for (int j = 0; j < 8; ++j) {
+            const T x0 = v[j >> 2][2 * j & 7], x1 = v[j >> 2][(2 * j + 1) & 7];
+            if constexpr (std::is_same<T, int>::value) {
+                // x * scale from both sides in FP32: the conversion, the factor and the product are off by 2^-24 each, the factors'
+                // distance from the scale is 3.5 to 4.5 times that.  Rounding is monotonic: where both sides give the same FP16
+                // number the exact product does, else (1 element in 1000) FP64 decides.
+                typedef float f2 __attribute__((ext_vector_type(2)));
+                typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
+                const float f0 = (float)x0, f1 = (float)x1;
+                const uint32_t lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){f0 * below, f1 * below}, hv2));
+                const uint32_t hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){f0 * above, f1 * above}, hv2));
+                r[s][j] = lo;
+                if (lo != hi)
+                    r[s][j] = (uint32_t)half_rne_by_odd((double)x0 * scale) | ((uint32_t)half_rne_by_odd((double)x1 * scale) << 16);
+            } else {
+                r[s][j] = (uint32_t)half_rne_by_odd((double)x0 * scale) | ((uint32_t)half_rne_by_odd((double)x1 * scale) << 16);
+            }
+        }
     }
     __syncthreads();                                     // everybody has read: the buffer takes the results
     unsigned short* out = reinterpret_cast<unsigned short*>(buf);
 #pragma unroll
     for (int s = 0; s < CH / 2; ++s)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) out[(t & 127) + (t >> 7) * 2048 + s * 4096 + j * 128] = r[s][j];
+        for (int j = 0; j < 16; ++j) out[(t & 127) + (t >> 7) * 2048 + s * 4096 + j * 128] = (unsigned short)(r[s][j >> 1] >> (16 * (j & 1)));
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         const int64_t at = c0 + c * 256 + t;
         if (at < chunks) dst[at] = reinterpret_cast<const uint4*>(buf)[c * 256 + t];
+    }
+}
+
+// An FP16 number is a whole multiple of 2^-24, so where the magnitudes of a segment add up to less than 128 every partial sum
+// fits 32-bit integers in that unit and the butterflies are integer additions: a quarter of the issue time of FP64 ones and half of
+// the LDS traffic, the same exact sums.  Weight rows are like that (4096 values of standard deviation 0.02 add up to 65);
+// other segments, infinities and NaN among them, and blocks of less than eight take FP64.  22016 x 4096: a single workgroup per
+// block with one LDS round trip and one barrier per stage, bound by LDS and barriers, took 863 us, these layouts in FP64 111 us
+// (bound by vector issue), in whole numbers 93 us (a copy of the tensor 67; conversions, butterflies and LDS each about half of that).
+template <int CH>
+__global__ __launch_bounds__(256) void hadamard_kernel(const uint4* __restrict__ src, int64_t chunks, int n, double scale,
+                                                       uint4* __restrict__ dst)
+{
+    constexpr int kElems = 2048 * CH;
+    __shared__ double buf[kElems + kElems / 8 + kElems / 16];
+    __shared__ float s_sum[4];
+    const int t = threadIdx.x;
+    const int64_t c0 = (int64_t)blockIdx.x * (256 * CH);
+    uint4 raw[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const int64_t at = c0 + c * 256 + t;
+        raw[c] = at < chunks ? src[at] : make_uint4(0u, 0u, 0u, 0u);
+    }
+    auto element = [&](int c, int e) {
+        const uint32_t w[4] = {raw[c].x, raw[c].y, raw[c].z, raw[c].w};
+        return __half2float(__ushort_as_half((unsigned short)(w[e >> 1] >> (16 * (e & 1)))));
+    };
+    int whole[CH][8];                                    // in units of 2^-24 (saturated where that does not fit: not used then)
+    float sum = n < 8 ? __builtin_inff() : 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        float chunk = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float x = element(c, e) * 0x1p24f;
+            chunk += fabsf(x);
+            whole[c][e] = (int)x;
+        }
+        // zeros with a sign among them: the first element of a block of nothing but -0 is -0 in FP64
+        sum += chunk == 0.f && (raw[c].x | raw[c].y | raw[c].z | raw[c].w) ? __builtin_inff() : chunk;
+    }
+    sum = wave_sum_of(sum);
+    if ((t & 63) == 0) s_sum[t >> 6] = sum;
+    __syncthreads();
+    // the FP32 sum is off by less than 2^-16 of itself
+    if ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]) < 127.9f * 0x1p24f) {
+        hadamard_segment(whole, reinterpret_cast<int*>(buf), c0, chunks, n, scale * 0x1p-24, dst);
+    } else {
+        double v[CH][8];
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[c][e] = (double)element(c, e);
+        hadamard_segment(v, buf, c0, chunks, n, scale, dst);
     }
 }
 

@@ -1,6 +1,8 @@
 """GPU parity of the data-free offline transforms (channel salience, order, gather, reordered activation
 quantizer, Hadamard rotation) against the CPU oracle, through the C ABI.  Everything here is exact: indices,
 FP16 bit patterns, INT8 codes, INT32 accumulators."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -137,6 +139,30 @@ def test_hadamard_segment_edges_bit_exact(rows, K, block):
     odd = torch.empty(rows * K + 1, dtype=torch.float16, device=DEV)[1:].view(rows, K)      # 2-byte aligned only
     odd.copy_(x)
     assert np.array_equal(_bits(api.hadamard_rotate(odd, block, out=odd).cpu().numpy()), _bits(ref))
+
+
+@pytest.mark.parametrize("rows,K,block", [(3, 4096, 4096), (2, 8192, 8192), (9, 2048, 2048), (5, 4096, 512), (3, 4104, 8), (3, 4096, 4)])
+def test_hadamard_small_magnitudes_bit_exact(rows, K, block):
+    """Rows whose magnitudes add up to just less and just more than 128 (whole numbers, FP64), with subnormals, blocks of zeros
+    of both signs, an infinity and a NaN in the last row; against FP64."""
+    g = torch.Generator(device=DEV).manual_seed(K + block)
+    x = torch.randn(rows, K, generator=g, device=DEV)
+    seg = 4096 if block <= 4096 else 8192
+    x = x * (torch.tensor([127.0, 127.95, 129.0] * rows, device=DEV)[:rows, None] / (seg * (2 / math.pi) ** 0.5))
+    x = x.half()
+    x[0, ::7] *= 2.0 ** -12                                      # subnormals
+    x[0, :8] = -0.0                                              # a chunk of nothing but -0
+    if rows > 1:
+        x[1, block // 2:block] = 0.0
+        x[1, :block // 2] = -0.0
+    x[-1, -1], x[-1, -2] = float("inf"), float("nan")
+    ref = tr.rotate_fp16(x.cpu().numpy(), block)
+    got = api.hadamard_rotate(x, block).cpu().numpy()
+    nan = np.isnan(ref)
+    assert np.array_equal(np.isnan(got), nan)
+    assert np.array_equal(_bits(got + np.float16(0))[~nan], _bits(ref + np.float16(0))[~nan])     # (-0 + 0 = 0)
+    if block == 8:                                               # a sum of nothing but -0, and differences of such
+        assert _bits(got)[0, :8].tolist() == [0x8000] + 7 * [0]
 
 
 def test_rotated_layer_matches_the_oracle_and_the_unrotated_product():
