@@ -58,17 +58,60 @@ __global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* __rest
     }
 }
 
-// Sorting by rank: new place of channel k = how many channels come before it (larger salience, or equal and a smaller
-// index).  A workgroup settles 64 channels, one per lane; its sixteen waves count over sixteen parts of the channels (two
-// vector instructions per pair) and meet in LDS.  K^2 work, for K <= kRankMaxK: 14336 channels in 27 us, where the copy to the
-// host, the sort there and the copy back took 0.7 ms.  bad[0] = 1 if some salience is not finite (the order is then
-// meaningless), else 0.
-constexpr int kRankMaxK = 32768, kRankTile = 8192;
-__global__ __launch_bounds__(1024) void channel_order_kernel(const float* __restrict__ salience, int K, int32_t* __restrict__ perm,
-                                                             int32_t* __restrict__ bad)
+// The same for up to 1024 rows in one pass, without a zero fill before it or atomics: a workgroup takes 64 channels (whole lines of
+// 128 bytes) x all rows, thread (8-channel chunk c, row group q of 128) has its up to eight loads in flight together.
+// 1024 x 14336 with its launches: 4.6 us, 7.8 in slabs; 129 x 4096 4.0 and 5.7.
+constexpr int kColumnRows = 1024;
+__global__ __launch_bounds__(1024) void channel_absmax_columns_kernel(const uint4* __restrict__ x, int M, int chunks, int* __restrict__ out_bits)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t s_key[kRankTile];
-    __shared__ uint32_t s_rank[64];
+    __shared__ uint4 s_max[16][8];
+    typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
+    auto pair_max = [](uint32_t a, uint32_t b) {         // of FP16 pairs of magnitudes; a NaN is not taken
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(hv2, a), __builtin_bit_cast(hv2, b)));
+    };
+    const int cl = threadIdx.x & 7, q = threadIdx.x >> 3;
+    const int c = (int)blockIdx.x * 8 + cl;
+    const uint4* col = x + min(c, chunks - 1);
+    uint4 v[kColumnRows / 128];
+#pragma unroll
+    for (int j = 0; j < kColumnRows / 128; ++j)
+        if (128 * j < M) v[j] = col[(int64_t)min(q + 128 * j, M - 1) * chunks];   // past the end: the last row once more
+        else v[j] = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t mx[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int j = 0; j < kColumnRows / 128; ++j) {
+        const uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mx[i] = pair_max(mx[i], w[i] & 0x7FFF7FFFu);
+    }
+    // the eight rows of a wave: lanes 8, 16 and 32 apart
+#pragma unroll
+    for (int h = 8; h < 64; h <<= 1)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mx[i] = pair_max(mx[i], (uint32_t)__shfl_xor((int)mx[i], h));
+    if ((threadIdx.x & 63) < 8) s_max[threadIdx.x >> 6][cl] = make_uint4(mx[0], mx[1], mx[2], mx[3]);
+    __syncthreads();
+    if (threadIdx.x >= 64) return;                       // one wave: thread = channel
+    const int ch = threadIdx.x, chunk = (int)blockIdx.x * 8 + (ch >> 3);
+    if (chunk >= chunks) return;
+    uint32_t m = 0;
+#pragma unroll
+    for (int wv = 0; wv < 16; ++wv) m = max(m, (uint32_t) reinterpret_cast<const unsigned short*>(s_max[wv])[ch]);   // magnitudes order like their bits
+    out_bits[(int64_t)blockIdx.x * 64 + ch] = __float_as_int(__half2float(__ushort_as_half((unsigned short)m)));
+}
+
+// Sorting by rank: new place of channel k = how many channels come before it (larger salience, or equal and a smaller
+// index).  A workgroup settles 64 channels: it sorts them, finds for every channel of the layer by binary search how many of the 64
+// it comes before, and counts those numbers; the sums over the counts are the 64 ranks.  Seven steps per channel and workgroup
+// where comparing every pair took 64 (14336 channels: 25.5 us; a host sort with its copies 0.7 ms): 10.8 us, 19 if all are equal, which all
+// meet in one counter, for K <= kRankMaxK.
+// bad[0] = 1 if some salience is not finite (the order is then meaningless), else 0.
+constexpr int kRankMaxK = 32768, kRankThreads = 1024, kRankAhead = 8;
+__global__ __launch_bounds__(kRankThreads) void channel_order_kernel(const float* __restrict__ salience, int K, int32_t* __restrict__ perm,
+                                                                     int32_t* __restrict__ bad)
+{
+    __shared__ uint32_t s_sorted[64];                    // keys of the workgroup's channels, ascending
+    __shared__ uint32_t s_count[64 + 1];                 // channels elsewhere that come before exactly so many of them
     __shared__ int s_bad;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     auto key_of = [](float f) {                          // unsigned integers in the order of the floats, -0 = +0
@@ -76,44 +119,52 @@ __global__ __launch_bounds__(1024) void channel_order_kernel(const float* __rest
         return b & 0x80000000u ? ~b : b | 0x80000000u;
     };
     const int k0 = (int)blockIdx.x * 64, k = k0 + lane;
-    const uint32_t mine = k < K ? key_of(salience[k]) : 0u;
-    if (threadIdx.x < 64) s_rank[threadIdx.x] = 0;
-    if (threadIdx.x == 64) s_bad = 0;
-    uint32_t rank = 0;
-    bool nonfinite = false;
-    for (int j0 = 0; j0 < K; j0 += kRankTile) {
-        __syncthreads();
-        for (int j = threadIdx.x; j < kRankTile; j += 1024) {
-            const float f = j0 + j < K ? salience[j0 + j] : 0.f;
-            nonfinite |= !(fabsf(f) < __builtin_inff());
-            s_key[j] = j0 + j < K ? key_of(f) : 0u;      // past the end: before nobody (a finite float's key is not 0)
+    uint32_t before = 0;                                 // of the workgroup's own channels, those before this lane's (wave 0)
+    if (wave == 0) {
+        const uint32_t mine = k < K ? key_of(salience[k]) : 0u;              // past the end: behind every finite one
+        for (int e = 0; e < 64; ++e) {
+            const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, e);
+            before += other > mine || (other == mine && e < lane);
         }
-        __syncthreads();
-        for (int blk = wave; blk < kRankTile / 64; blk += 16) {              // 64 keys that every lane compares its own with
-            const int j = j0 + blk * 64;
-            if (j >= K) break;
-            const uint4* keys = reinterpret_cast<const uint4*>(s_key + blk * 64);
-            // ties count in blocks before this workgroup's own channels, not behind; a key above mine - 1 is one of at least mine
-            const uint32_t floor_key = j < k0 ? mine - 1 : mine;
-            uint32_t n[4] = {0, 0, 0, 0};
+        s_sorted[63 - before] = mine;                    // (a permutation of 0 ... 63)
+        s_count[lane] = 0;
+        if (lane == 0) { s_count[64] = 0; s_bad = 0; }
+    }
+    __syncthreads();
+    bool nonfinite = false;
+    for (int j0 = 0; j0 < K; j0 += kRankThreads * kRankAhead) {
+        float f[kRankAhead];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const uint4 t = keys[e];
-                n[0] += t.x > floor_key;
-                n[1] += t.y > floor_key;
-                n[2] += t.z > floor_key;
-                n[3] += t.w > floor_key;
-            }
-            rank += (n[0] + n[1]) + (n[2] + n[3]);
-            if (j == k0)                                                     // its own 64: equal keys in front of its own
-                for (int e = 0; e < 63; ++e) rank += e < lane && s_key[blk * 64 + e] == mine;
+        for (int a = 0; a < kRankAhead; ++a) f[a] = salience[min(j0 + a * kRankThreads + (int)threadIdx.x, K - 1)];
+        uint32_t v[kRankAhead], at[kRankAhead];
+#pragma unroll
+        for (int a = 0; a < kRankAhead; ++a) {
+            const int j = j0 + a * kRankThreads + (int)threadIdx.x;
+            nonfinite |= !(fabsf(f[a]) < __builtin_inff());
+            v[a] = key_of(f[a]) - (j < k0 ? 0u : 1u);    // ties: a channel in front comes before an equal one, one behind does not
+            at[a] = 0;
+        }
+        // how many of the 64 are at most v
+#pragma unroll
+        for (int h = 32; h >= 1; h >>= 1)
+#pragma unroll
+            for (int a = 0; a < kRankAhead; ++a) at[a] += s_sorted[at[a] + h - 1] <= v[a] ? h : 0;
+#pragma unroll
+        for (int a = 0; a < kRankAhead; ++a) {
+            const int j = j0 + a * kRankThreads + (int)threadIdx.x;
+            at[a] += s_sorted[at[a]] <= v[a];
+            if (j < K && (uint32_t)(j - k0) >= 64u) atomicAdd(&s_count[at[a]], 1u);
         }
     }
-    atomicAdd(&s_rank[lane], rank);
     if (nonfinite) s_bad = 1;
     __syncthreads();
-    if (threadIdx.x < 64 && k < K) perm[min((int)s_rank[lane], K - 1)] = k;   // (the bound only matters for NaNs)
-    if (blockIdx.x == 0 && threadIdx.x == 0) bad[0] = s_bad;
+    if (wave != 0) return;
+    // channel at ascending place p: everybody that comes before more than p of the 64
+    const int p = 63 - (int)before;
+    uint32_t rank = before;
+    for (int c = 1; c <= 64; ++c) rank += c > p ? s_count[c] : 0u;
+    if (k < K) perm[min((int)rank, K - 1)] = k;          // (the bound only matters for NaNs)
+    if (blockIdx.x == 0 && lane == 0) bad[0] = s_bad;
 }
 
 // dst[r, j] = src[r, perm[j]].  A workgroup brings ROWS rows into LDS as whole lines and gathers there: thread t makes
@@ -303,7 +354,7 @@ __device__ __forceinline__ void hadamard_segment(T (&v)[CH][8], T* buf, int64_t 
 // An FP16 number is a whole multiple of 2^-24, so where the magnitudes of a segment add up to less than 128 every partial sum
 // fits 32-bit integers in that unit and the butterflies are integer additions: a quarter of the issue time of FP64 ones and half of
 // the LDS traffic, the same exact sums.  Weight rows are like that (4096 values of standard deviation 0.02 add up to 65);
-// other segments, infinities and NaN among them, and blocks of less than eight take FP64.  22016 x 4096: a single workgroup per
+// other segments, infinities and NaN among them, and blocks of less than eight or of 8192 take FP64.  22016 x 4096: a single workgroup per
 // block with one LDS round trip and one barrier per stage, bound by LDS and barriers, took 863 us, these layouts in FP64 111 us
 // (bound by vector issue), in whole numbers 93 us (a copy of the tensor 67; conversions, butterflies and LDS each about half of that).
 template <int CH>
@@ -321,38 +372,43 @@ __global__ __launch_bounds__(256) void hadamard_kernel(const uint4* __restrict__
         const int64_t at = c0 + c * 256 + t;
         raw[c] = at < chunks ? src[at] : make_uint4(0u, 0u, 0u, 0u);
     }
-    auto element = [&](int c, int e) {
-        const uint32_t w[4] = {raw[c].x, raw[c].y, raw[c].z, raw[c].w};
-        return __half2float(__ushort_as_half((unsigned short)(w[e >> 1] >> (16 * (e & 1)))));
-    };
-    int whole[CH][8];                                    // in units of 2^-24 (saturated where that does not fit: not used then)
-    float sum = n < 8 ? __builtin_inff() : 0.f;
+    float x[CH][8];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        float chunk = 0.f;
+        const uint32_t w[4] = {raw[c].x, raw[c].y, raw[c].z, raw[c].w};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float x = element(c, e) * 0x1p24f;
-            chunk += fabsf(x);
-            whole[c][e] = (int)x;
+        for (int e = 0; e < 8; ++e) x[c][e] = __half2float(__ushort_as_half((unsigned short)(w[e >> 1] >> (16 * (e & 1)))));
+    }
+    if constexpr (CH == 2) {                             // (8192 weights of the usual size add up to more than 128)
+        float sum = n < 8 ? __builtin_inff() : 0.f;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            float chunk = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) chunk += fabsf(x[c][e]);
+            // zeros with a sign among them: the first element of a block of nothing but -0 is -0 in FP64
+            sum += chunk == 0.f && (raw[c].x | raw[c].y | raw[c].z | raw[c].w) ? __builtin_inff() : chunk;
         }
-        // zeros with a sign among them: the first element of a block of nothing but -0 is -0 in FP64
-        sum += chunk == 0.f && (raw[c].x | raw[c].y | raw[c].z | raw[c].w) ? __builtin_inff() : chunk;
-    }
-    sum = wave_sum_of(sum);
-    if ((t & 63) == 0) s_sum[t >> 6] = sum;
-    __syncthreads();
-    // the FP32 sum is off by less than 2^-16 of itself
-    if ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]) < 127.9f * 0x1p24f) {
-        hadamard_segment(whole, reinterpret_cast<int*>(buf), c0, chunks, n, scale * 0x1p-24, dst);
-    } else {
-        double v[CH][8];
+        sum = wave_sum_of(sum);
+        if ((t & 63) == 0) s_sum[t >> 6] = sum;
+        __syncthreads();
+        // the FP32 sum is off by less than 2^-16 of itself
+        if ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]) < 127.9f) {
+            int whole[CH][8];                            // in units of 2^-24
 #pragma unroll
-        for (int c = 0; c < CH; ++c)
+            for (int c = 0; c < CH; ++c)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[c][e] = (double)element(c, e);
-        hadamard_segment(v, buf, c0, chunks, n, scale, dst);
+                for (int e = 0; e < 8; ++e) whole[c][e] = (int)(x[c][e] * 0x1p24f);
+            hadamard_segment(whole, reinterpret_cast<int*>(buf), c0, chunks, n, scale * 0x1p-24, dst);
+            return;
+        }
     }
+    double v[CH][8];
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[c][e] = (double)x[c][e];
+    hadamard_segment(v, buf, c0, chunks, n, scale, dst);
 }
 
 // The same for tensors that are no whole number of 16-byte chunks or not aligned to them, and for a few short blocks: one
@@ -380,6 +436,13 @@ __global__ __launch_bounds__(256) void hadamard_block_kernel(const __half* __res
 
 hipError_t launch_channel_absmax(const void* x, int64_t M, int64_t K, float* absmax, hipStream_t s)
 {
+    // One slab of rows is stored as it is; up to 1024 rows go in one pass, whose workgroups take longer the more rows there are; beyond, the
+    // slabs of rows meet by atomics.
+    if (M > kAbsmaxRows && M <= kColumnRows) {
+        channel_absmax_columns_kernel<<<(unsigned)((K / 8 + 7) / 8), 1024, 0, s>>>(static_cast<const uint4*>(x), (int)M, (int)(K / 8),
+                                                                                  reinterpret_cast<int*>(absmax));
+        return hipGetLastError();
+    }
     if (M == 0 || M > kAbsmaxRows) {
         const hipError_t e = launch_zero(absmax, (size_t)K * sizeof(float), s);
         if (e != hipSuccess || M == 0) return e;
@@ -397,7 +460,7 @@ int channel_order_max_k() { return kRankMaxK; }
 
 hipError_t launch_channel_order(const float* salience, int64_t K, int32_t* perm, int32_t* bad, hipStream_t s)
 {
-    channel_order_kernel<<<(unsigned)((K + 63) / 64), 1024, 0, s>>>(salience, (int)K, perm, bad);
+    channel_order_kernel<<<(unsigned)((K + 63) / 64), kRankThreads, 0, s>>>(salience, (int)K, perm, bad);
     return hipGetLastError();
 }
 

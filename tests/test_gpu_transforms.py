@@ -80,6 +80,19 @@ def test_gather_on_either_side_of_its_rules(rows, K):
     assert torch.equal(api.gather_channels(x, perm), x[:, perm.long()])
 
 
+@pytest.mark.parametrize("M,K", [(129, 8), (130, 72), (255, 4104), (1000, 64), (1024, 520), (1025, 520)])
+def test_salience_in_one_pass_over_the_rows(M, K):
+    """Up to 1024 rows by columns: a part of a 64-channel workgroup, rows past the last multiple of 128, the maximum in the last
+    row, infinities taken and NaN not; 1025 rows by slabs."""
+    x = torch.randn(M, K, generator=torch.Generator(device=DEV).manual_seed(M), device=DEV).half()
+    x[M - 1, K - 1], x[M // 2, 0] = -60000.0, float("-inf")
+    x[:, 1] = float("nan")
+    x[M - 1, 1] = 0.25
+    out = torch.full((K,), -1.0, device=DEV)
+    assert api.lib().qoq_channel_absmax(x.data_ptr(), M, K, out.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(out, torch.nan_to_num(x.float(), nan=0.0, posinf=math.inf, neginf=-math.inf).abs().amax(0))
+
+
 def test_gather_and_reordered_quantizer_bit_exact():
     M, K, N = 70, 2048, 192
     x = wl.make_activations(M, K, 61, DEV)
