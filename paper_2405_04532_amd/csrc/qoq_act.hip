@@ -12,6 +12,7 @@
 #include "qoq_internal.h"
 #include "qoq_fp16.h"
 #include "qoq_half_decide.h"
+#include "qoq_act_codes.h"
 
 namespace qoq {
 namespace {
@@ -79,19 +80,6 @@ __device__ __forceinline__ double wave_sum_f64(double v)
     return (lane(v, 0) + lane(v, 16)) + (lane(v, 32) + lane(v, 48));
 }
 
-// round_half_away(x / s), clamped to [-127, 127], for FP16 values x and s > 0 (held in FP32), without a division.
-// x and s have 11-bit significands, so the exact quotient is either exactly on a rounding midpoint k + 1/2 or at
-// least 2^-12 away from every midpoint (|x / s| < 256); x * fl(1 / s) is within 3e-5 of the quotient, and pushing
-// it 1e-4 away from zero sends exact midpoints up and nothing else across: the result is the one the correctly
-// rounded division followed by round-half-away gives, bit for bit (checked against exact rational arithmetic on
-// the FP16 neighbours of all midpoints of several thousand scales, and on the GPU against the CPU reference).
-__device__ __forceinline__ int quantize_code(float x, float inv_s)
-{
-    const float t = x * inv_s;
-    const int a = (int)(t + copysignf(0.5f + 1e-4f, t));   // conversion truncates toward zero
-    return max(-127, min(127, a));
-}
-
 __device__ inline float block_reduce_max(float v, float* smem)
 {
     v = wave_max_nonneg(v);
@@ -125,10 +113,7 @@ __global__ __launch_bounds__(kThreads) void act_quant_kernel(const __half* __res
     }
     amax = block_reduce_max(amax, s_f);
 
-    // sx = fp16(absmax / 127): the FP32 quotient of an FP16 value by 127 never lies close
-    // enough to an FP16 rounding midpoint for the intermediate rounding to matter.
-    __half sxh = __float2half_rn(amax / 127.0f);
-    if (__half2float(sxh) == 0.f) sxh = __float2half_rn(1.0f);
+    const __half sxh = scale_of_row(amax);
     const float s = __half2float(sxh);
     const float inv_s = 1.0f / s;
 
@@ -181,19 +166,9 @@ struct RowReader {
     }
 };
 
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ h2 half2_of(uint32_t w) { return __builtin_bit_cast(h2, w); }
-
 // Quantize a token row that the workgroup holds in registers (chunk c = threadIdx.x + i * blockDim.x in v[i],
 // zeros past the end): absmax, scale, INT8 codes, sums.  Used by the plain quantizer and by the producers the
-// quantization is fused into.  These kernels are bound by vector instructions as much as by memory, so the codes take
-// two instructions per element: x * (1/s) pushed away from zero by a relative 2^-20 and added to 1.5 * 2^23 in one
-// fused multiply-add leaves round(x / s) in the low byte of the sum.  As in quantize_code the exact quotient is on a
-// rounding midpoint or at least 2^-12 away from every one; the push (at most 1.4e-4 at 127, and at least 2^-20 - 2^-23
-// of the quotient, where the reciprocal and the factor are off by 2^-23 together) sends exact midpoints away from zero
-// and nothing else across.  No clamp is needed: with a normal FP16 scale |x / s| <= 127 (1 + 2^-11).  A subnormal scale
-// is too coarse for that and takes quantize_code.  Infinities (scale infinite, x * 0) and NaN leave a quiet NaN, whose
-// low byte is the code 0 that the conversion of quantize_code gives.
+// quantization is fused into.  These kernels are bound by vector instructions as much as by memory.
 template <int CACHE>
 __device__ inline void quantize_cached_row(const uint4 (&v)[CACHE], int chunks, int64_t m, int64_t K,
                                            int8_t* __restrict__ qx, __half* __restrict__ sx,
@@ -202,41 +177,24 @@ __device__ inline void quantize_cached_row(const uint4 (&v)[CACHE], int chunks, 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = (int)blockDim.x >> 6;
     h2 mx = half2_of(0u);
 #pragma unroll
-    for (int i = 0; i < CACHE; ++i) {
-        const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) mx = __builtin_elementwise_max(mx, half2_of(w[j] & 0x7FFF7FFFu));
-    }
+    for (int i = 0; i < CACHE; ++i) mx = max_of_chunk(v[i], mx);
     float amax = wave_max_nonneg(fmaxf((float)mx.x, (float)mx.y));
     if (lane == 0) s_f[wave] = amax;
     __syncthreads();
     amax = wave_max_nonneg(lane < waves ? s_f[lane] : 0.f);
 
-    __half sxh = __float2half_rn(amax / 127.0f);   // see act_quant_kernel for why FP32 suffices here
-    if (__half2float(sxh) == 0.f) sxh = __float2half_rn(1.0f);
+    const __half sxh = scale_of_row(amax);
     const float s = __half2float(sxh);
     const float inv_s = 1.0f / s;
 
     int isum = 0;
     uint2* qrow = reinterpret_cast<uint2*>(qx + m * K);
     if (__builtin_amdgcn_readfirstlane(__float_as_int(s)) >= __float_as_int(0x1p-14f)) {
-        const float push = inv_s * (1.0f + 0x1p-20f), magic = 12582912.0f;
+        const float push = inv_s * (1.0f + 0x1p-20f);
 #pragma unroll
         for (int i = 0; i < CACHE; ++i) {
             const int c = (int)threadIdx.x + i * (int)blockDim.x;
-            if (c < chunks) {
-                const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-                uint32_t r[8], packed[2];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) r[j] = __float_as_uint(fmaf((float)half2_of(w[j >> 1])[j & 1], push, magic));
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {          // the four low bytes of r[4j .. 4j + 3]
-                    packed[j] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(r[4 * j + 3], r[4 * j + 2], 0x0C0C0400u),
-                                                      __builtin_amdgcn_perm(r[4 * j + 1], r[4 * j], 0x0C0C0400u), 0x05040100u);
-                    isum = __builtin_amdgcn_sdot4((int)packed[j], 0x01010101, isum, false);
-                }
-                qrow[c] = make_uint2(packed[0], packed[1]);
-            }
+            if (c < chunks) qrow[c] = codes_of_chunk(v[i], push, isum);
         }
     } else {
 #pragma unroll 1
@@ -246,17 +204,7 @@ __device__ inline void quantize_cached_row(const uint4 (&v)[CACHE], int chunks, 
 #pragma unroll
             for (int x = 1; x < CACHE; ++x)            // (selects: an indexed register array would go to scratch memory)
                 if (i == x) vi = v[x];
-            if (c < chunks) {
-                const uint32_t w[4] = {vi.x, vi.y, vi.z, vi.w};
-                uint32_t packed[2] = {0u, 0u};
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int a = quantize_code((float)half2_of(w[j >> 1])[j & 1], inv_s);
-                    isum += a;
-                    packed[j >> 2] |= (uint32_t)(a & 0xFF) << (8 * (j & 3));
-                }
-                qrow[c] = make_uint2(packed[0], packed[1]);
-            }
+            if (c < chunks) qrow[c] = codes_of_chunk_clamped(vi, inv_s, isum);
         }
     }
     if (!rowsum && !tx) {                          // group mode needs neither sum: no second reduction

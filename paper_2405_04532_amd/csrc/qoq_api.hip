@@ -106,15 +106,23 @@ int gemm_common(const int8_t* qx, const void* sx, const int32_t* rowsum, const v
     }
     if (x_fp16 && !aligned16(x_fp16)) return QOQ_ERR_ALIGN;
     if (!arch_ok()) return QOQ_ERR_ARCH;
-    if (x_fp16 &&
-        qoq::launch_act_quant(x_fp16, M, K, const_cast<int8_t*>(qx), const_cast<void*>(sx), const_cast<int32_t*>(rowsum),
-                              nullptr, static_cast<hipStream_t>(stream)) != hipSuccess)
-        return QOQ_ERR_HIP;
     qoq::GemmArgs a;
     a.qx = qx; a.sx = sx; a.rowsum = rowsum; a.tx = tx; a.blob = static_cast<const uint8_t*>(packed);
     a.M = M; a.N = N; a.K = K; a.mode = mode;
     a.out_fp16 = out16; a.out_i32 = out32; a.workspace = ws;
     a.tile_m = tile_m; a.split_k = split_k; a.parts_offset = parts_offset;
+    // One launch for few and short tokens; not where a result takes the place of tokens that other workgroups still read.
+    const auto over_tokens = [&](const void* p, size_t bytes) {
+        const uintptr_t x0 = reinterpret_cast<uintptr_t>(x_fp16), p0 = reinterpret_cast<uintptr_t>(p);
+        return p && p0 < x0 + (size_t)(M * K) * 2 && x0 < p0 + bytes;
+    };
+    if (x_fp16 && tuning.tile_m == 0 && qoq::linear_in_one_launch(M, K) && !over_tokens(out16, (size_t)(M * N) * 2) &&
+        !over_tokens(qx, (size_t)(M * K)) && !over_tokens(sx, (size_t)M * 2) && !over_tokens(rowsum, (size_t)M * 4))
+        return qoq::launch_linear(a, x_fp16, static_cast<hipStream_t>(stream)) == hipSuccess ? QOQ_OK : QOQ_ERR_HIP;
+    if (x_fp16 &&
+        qoq::launch_act_quant(x_fp16, M, K, const_cast<int8_t*>(qx), const_cast<void*>(sx), const_cast<int32_t*>(rowsum),
+                              nullptr, static_cast<hipStream_t>(stream)) != hipSuccess)
+        return QOQ_ERR_HIP;
     return qoq::launch_gemm(a, static_cast<hipStream_t>(stream)) == hipSuccess ? QOQ_OK : QOQ_ERR_HIP;
 }
 

@@ -2014,9 +2014,8 @@ size_t gemm_counter_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int split
     return mma_counter_bytes(M, N, tile_m, split_k);
 }
 
-hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
+static GemmDev device_args(const GemmArgs& a)
 {
-    if (a.M == 0) return hipSuccess;
     const BlobLayout L = make_layout(a.N, a.K, a.mode);
     GemmDev p;
     p.qx = a.qx;
@@ -2031,6 +2030,26 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     p.out32 = a.out_i32;
     p.M = (int)a.M; p.N = (int)a.N; p.K = (int)a.K; p.G = (int)L.G;
     p.counters = reinterpret_cast<int*>(a.workspace);
+    return p;
+}
+
+bool linear_in_one_launch(int64_t M, int64_t K) { return astat_linear_takes(M, K); }
+
+hipError_t launch_linear(const GemmArgs& a, const void* x_fp16, hipStream_t s)
+{
+    GemmDev p = device_args(a);
+    p.upw = 0;
+    p.S = 1;
+    p.gps = p.G;
+    p.parts = nullptr;
+    return launch_astat_linear(p, x_fp16, const_cast<int8_t*>(a.qx), const_cast<void*>(a.sx), const_cast<int32_t*>(a.rowsum), a.mode == 0, s);
+}
+
+hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
+{
+    if (a.M == 0) return hipSuccess;
+    const BlobLayout L = make_layout(a.N, a.K, a.mode);
+    GemmDev p = device_args(a);
     int nwg = 0;
     size_t counters;
     if (a.tile_m >= 69 && a.tile_m <= 71) {

@@ -36,6 +36,9 @@
 //     cache-bypassing loads.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
+#include "qoq_act_codes.h"
 #include "qoq_gemm_common.h"
 #include "qoq_layout.h"
 
@@ -46,9 +49,70 @@ constexpr int kAsThreads = 512;
 constexpr int kAsWaves = 8;
 constexpr int kAsMaxFrags = 128;     // fragments per workgroup when k-slices meet in the workspace (host-checked)
 
-template <int MF, int J, int R, bool GROUP, int OUT>
-__global__ __launch_bounds__(kAsThreads) void astat_kernel(GemmDev p)
+// FP16 tokens that the kernel quantizes itself, and where their codes, scales and sums go (rowsum may be null).
+struct TokensIn {
+    const __half* x;
+    int8_t* qx;
+    __half* sx;
+    int32_t* rowsum;
+};
+constexpr int kTokenLds = 32 * 1024;         // codes of a workgroup's tokens
+constexpr int kTokenChunks = 8;              // 16-byte chunks of FP16 that a thread holds
+static_assert(kTokenChunks * 8 * kAsThreads == kTokenLds, "one byte of codes per element held");
+
+// For few and short tokens a launch of the quantizer costs more than its work, on the device (2.3 us) and on the host (2.5 us),
+// so every workgroup quantizes all of them itself, while its first weights are on their way: 16 x 256 x 256 with one launch 4.9 us,
+// with two 7.9 (issued one after the other); 1 x 4096 x 6144 per channel 5.6 and 8.3, 4 x 8192 x 22016 18.3 and 20.4.  512 / rows threads per
+// row (rows: p.M rounded up to a power of two); scales and codes as the quantizer decides them (qoq_act_codes.h).
+// Workgroup 0 writes them out for the caller.  Leaves the codes in `codes` (token-major, 16-byte chunks XORed with the row
+// number inside each 128 bytes), maxima and sums in s_amax, s_sum.
+__device__ __forceinline__ void quantize_tokens(const GemmDev& p, const TokensIn& in, const uint4 (&v)[kTokenChunks], int row, int tr,
+                                                int per_row, bool want_sums, char* codes, uint32_t* s_amax, int* s_sum)
 {
+    auto row16 = [](auto x, auto join) {               // joined over each 16 lanes, which are of one row
+        auto moved = [&](auto ctrl) {
+            return __builtin_amdgcn_update_dpp(x, x, decltype(ctrl)::value, 0xF, 0xF, false);
+        };
+        x = join(x, moved(std::integral_constant<int, 0xB1>()));
+        x = join(x, moved(std::integral_constant<int, 0x4E>()));
+        x = join(x, moved(std::integral_constant<int, 0x141>()));
+        return join(x, moved(std::integral_constant<int, 0x140>()));
+    };
+    const bool on = row < p.M, lead = on && (threadIdx.x & 15) == 0;
+    h2 mx = half2_of(0u);
+#pragma unroll
+    for (int i = 0; i < kTokenChunks; ++i) mx = max_of_chunk(v[i], mx);
+    const int bits = row16(__float_as_int(fmaxf((float)mx.x, (float)mx.y)), [](int a, int b) { return max(a, b); });
+    if (lead) atomicMax(&s_amax[row], (uint32_t)bits);   // non-negative: the bits order like the values
+    __syncthreads();
+    if (on) {
+        const float s = __half2float(scale_of_row(__uint_as_float(s_amax[row]))), inv_s = 1.0f / s;
+        int isum = 0;
+#pragma unroll
+        for (int i = 0; i < kTokenChunks; ++i) {
+            const int c = tr + i * per_row;
+            if (c < p.K / 8) {
+                const uint2 q = s >= 0x1p-14f ? codes_of_chunk(v[i], inv_s * (1.0f + 0x1p-20f), isum) : codes_of_chunk_clamped(v[i], inv_s, isum);
+                *reinterpret_cast<uint2*>(codes + row * p.K + (((c >> 1) ^ (row & 7)) * 16) + (c & 1) * 8) = q;
+                if (blockIdx.x == 0) reinterpret_cast<uint2*>(in.qx + (size_t)row * p.K)[c] = q;
+            }
+        }
+        if (want_sums) {
+            isum = row16(isum, [](int a, int b) { return a + b; });
+            if (lead) atomicAdd(&s_sum[row], isum);
+        }
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && (int)threadIdx.x < p.M) {
+        in.sx[threadIdx.x] = scale_of_row(__uint_as_float(s_amax[threadIdx.x]));
+        if (in.rowsum) in.rowsum[threadIdx.x] = s_sum[threadIdx.x];
+    }
+}
+
+template <int MF, int J, int R, bool GROUP, int OUT, bool FUSED>
+__device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
+{
+    static_assert(!FUSED || MF == 1, "the kernel quantizes up to sixteen tokens");
     // R = fragments whose units are in flight ahead of the one being multiplied: a ring of R * J units per wave
     static_assert(J * MF <= 16, "128 registers of activations per lane");
     constexpr int D = R * J;
@@ -56,10 +120,13 @@ __global__ __launch_bounds__(kAsThreads) void astat_kernel(GemmDev p)
     // LDS: first every wave's private staging area of the activation preload, afterwards, in the same bytes, the
     // double-buffered exchange of the waves' fragment sums.
     constexpr int kWaveStage = 16 * 1024;
-    __shared__ __attribute__((aligned(16))) char lds_raw[kAsWaves * kWaveStage];
-    static_assert(2 * kAsWaves * kEl * 16 <= kAsWaves * kWaveStage, "the exchange buffers fit in the staging areas");
+    constexpr int kLds = FUSED ? 2 * kTokenLds : kAsWaves * kWaveStage;
+    __shared__ __attribute__((aligned(16))) char lds_raw[kLds];
+    static_assert(2 * kAsWaves * kEl * 16 <= (FUSED ? kTokenLds : kLds), "the exchange buffers fit in the staging areas");
     int4 (*red)[kAsWaves][kEl] = reinterpret_cast<int4 (*)[kAsWaves][kEl]>(lds_raw);
     __shared__ int s_last[kAsMaxFrags];
+    __shared__ uint32_t s_amax[16];                    // FUSED: the tokens' largest magnitudes and sums of codes
+    __shared__ int s_sum[16];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -106,7 +173,37 @@ __global__ __launch_bounds__(kAsThreads) void astat_kernel(GemmDev p)
     for (int j = 0; j < J; ++j)
 #pragma unroll
         for (int mf = 0; mf < MF; ++mf) a[j][mf][0] = a[j][mf][1] = (v4i){0, 0, 0, 0};   // slots past the slice stay zero
-    {
+    if constexpr (FUSED) {
+        const int rows_log = p.M <= 1 ? 0 : 32 - __builtin_clz(p.M - 1), per_row = kAsThreads >> rows_log;
+        const int row = (int)threadIdx.x >> (9 - rows_log), tr = (int)threadIdx.x & (per_row - 1);
+        const bool want_sums = !GROUP || in.rowsum;
+        if (threadIdx.x < 16) { s_amax[threadIdx.x] = 0; s_sum[threadIdx.x] = 0; }
+        // the tokens first, then the weights, whose way is the longer one; chunks past the end of a row read as zeros
+        const __amdgpu_buffer_rsrc_t tokens = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half*>(in.x), 0, p.M * p.K * 2, 0x00020000);
+        uint4 v[kTokenChunks];
+#pragma unroll
+        for (int i = 0; i < kTokenChunks; ++i) {
+            const int c = tr + i * per_row;
+            v[i] = make_uint4(0u, 0u, 0u, 0u);
+            if (i * per_row < p.K / 8)                 // workgroup-uniform
+                v[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(tokens, row < p.M && c < p.K / 8 ? (row * (p.K / 8) + c) * 16 : p.M * p.K * 2, 0, 0));
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < J; ++j) load_unit(r * J + j, j, f0 + min(r, nfr - 1));
+        __syncthreads();
+        char* codes = lds_raw + kTokenLds;
+        quantize_tokens(p, in, v, row, tr, per_row, want_sums, codes, s_amax, s_sum);
+        const int mr = min(ml, p.M - 1);               // rows past M repeat the last one
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            if (slot_valid(j)) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+                    a[j][0][ks] = *reinterpret_cast<const v4i*>(codes + mr * p.K + (((group_of(j) * 8 + ks * 4 + q) ^ (mr & 7)) * 16));
+            }
+    } else {
         constexpr int JP = J >= 8 ? 8 : 4;                                   // groups per pass
         constexpr int RP = (128 / JP) < MF * 16 ? (128 / JP) : MF * 16;      // token rows per pass
         constexpr int kRowPasses = MF * 16 / RP, kJPasses = (J + JP - 1) / JP, kDma = RP * JP / 8;
@@ -167,7 +264,7 @@ __global__ __launch_bounds__(kAsThreads) void astat_kernel(GemmDev p)
             read_pass(pp / kJPasses, pp % kJPasses);
         }
     }
-    __syncthreads();    // the staging areas become the exchange buffers of the fragment sums
+    if constexpr (!FUSED) __syncthreads();    // the staging areas become the exchange buffers of the fragment sums
 
     // ---- epilogue role: thread t owns element t of every fragment tile (one token, four consecutive channels) ----
     const int el = threadIdx.x;
@@ -178,8 +275,13 @@ __global__ __launch_bounds__(kAsThreads) void astat_kernel(GemmDev p)
     int c_rs = 0;
     if (e_on) {
         const int mc = min(e_m, p.M - 1);
-        c_sx = OUT == OUT_FP16 ? __half2float(p.sx[mc]) : 0.f;
-        c_rs = GROUP ? 0 : p.rowsum[mc];
+        if constexpr (FUSED) {
+            c_sx = __half2float(scale_of_row(__uint_as_float(s_amax[mc])));
+            c_rs = GROUP ? 0 : s_sum[mc];
+        } else {
+            c_sx = OUT == OUT_FP16 ? __half2float(p.sx[mc]) : 0.f;
+            c_rs = GROUP ? 0 : p.rowsum[mc];
+        }
     }
     auto channel_of = [&](int nf) __attribute__((always_inline)) { return (nf >> 2) * 64 + 16 * (e_ln >> 4) + 4 * (nf & 3); };
     auto epilogue = [&](int nf, v4i sum, uint2 sw, uint32_t zw) __attribute__((always_inline)) {
@@ -291,6 +393,19 @@ __global__ __launch_bounds__(kAsThreads) void astat_kernel(GemmDev p)
     }
 }
 
+template <int MF, int J, int R, bool GROUP, int OUT>
+__global__ __launch_bounds__(kAsThreads) void astat_kernel(GemmDev p)
+{
+    astat_run<MF, J, R, GROUP, OUT, false>(p, TokensIn{});
+}
+
+// Up to sixteen FP16 tokens through the quantizer and the GEMM in one launch.
+template <int J, int R, bool GROUP>
+__global__ __launch_bounds__(kAsThreads) void astat_linear_kernel(GemmDev p, TokensIn in)
+{
+    astat_run<1, J, R, GROUP, OUT_FP16, true>(p, in);
+}
+
 template <int MF, int J, int R, bool GROUP>
 void launch_j(const GemmDev& p, dim3 grid, bool fp16, hipStream_t s)
 {
@@ -319,7 +434,32 @@ hipError_t launch_mode(const GemmDev& p, int tile, dim3 grid, bool fp16, hipStre
     return hipGetLastError();
 }
 
+template <bool GROUP>
+void launch_linear(const GemmDev& p, const TokensIn& in, dim3 grid, hipStream_t s)
+{
+    if ((p.G + kAsWaves - 1) / kAsWaves <= 4) astat_linear_kernel<4, 2, GROUP><<<grid, kAsThreads, 0, s>>>(p, in);
+    else astat_linear_kernel<8, 1, GROUP><<<grid, kAsThreads, 0, s>>>(p, in);
+}
+
 }  // namespace
+
+bool astat_linear_takes(int64_t M, int64_t K)
+{
+    if (M < 1 || M > 16 || K / kGroup > astat_max_groups(16)) return false;
+    int64_t rows = 1;
+    while (rows < M) rows *= 2;
+    return rows * K <= kTokenLds;
+}
+
+hipError_t launch_astat_linear(const GemmDev& p, const void* x, int8_t* qx, void* sx, int32_t* rowsum, bool group, hipStream_t s)
+{
+    if (!astat_linear_takes(p.M, p.K)) return hipErrorInvalidValue;
+    const TokensIn in{static_cast<const __half*>(x), qx, static_cast<__half*>(sx), rowsum};
+    const dim3 grid((unsigned)(p.N / 16 < 256 ? p.N / 16 : 256));
+    if (group) launch_linear<true>(p, in, grid, s);
+    else launch_linear<false>(p, in, grid, s);
+    return hipGetLastError();
+}
 
 int astat_max_groups(int tile) { return kAsWaves * (tile == 64 ? 4 : 8); }
 

@@ -186,6 +186,9 @@ __device__ __forceinline__ void finish4(const GemmDev& p, int m, int n0, v4i v, 
 hipError_t launch_astat(const GemmDev& p, int tile_m, int nwg, bool group, bool fp16, hipStream_t s);
 // Largest number of quantization groups one workgroup of that kernel can keep resident for `tile` tokens.
 int astat_max_groups(int tile);
+// The 16-token kernel that quantizes its tokens itself (quantizer and GEMM in one launch), for what astat_linear_takes.
+bool astat_linear_takes(int64_t M, int64_t K);
+hipError_t launch_astat_linear(const GemmDev& p, const void* x, int8_t* qx, void* sx, int32_t* rowsum, bool group, hipStream_t s);
 
 // qoq_gemm_mma16.hip: the compute-bound kernel with 16x16x64 matrix instructions (tile_m code 132).
 hipError_t launch_mma16(const GemmDev& p, bool group, bool fp16, hipStream_t s);

@@ -45,6 +45,9 @@ struct GemmArgs {
 // Bytes of arrival counters at the start of the workspace of a (tile_m, split_k) launch (0 if it exchanges nothing).
 size_t gemm_counter_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int split_k);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
+// Quantizer and GEMM in one launch, for few and short tokens; a.qx, a.sx and a.rowsum are written.
+bool linear_in_one_launch(int64_t M, int64_t K);
+hipError_t launch_linear(const GemmArgs& a, const void* x_fp16, hipStream_t s);
 
 // Workspace a (tile_m, split_k) launch needs: per-tile counters, then the partial tiles.
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int split_k);

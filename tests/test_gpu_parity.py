@@ -790,3 +790,35 @@ def test_eight_wave_plan_without_room_for_its_slices(api):
     st = torch.cuda.current_stream().cuda_stream
     assert api.lib().qoq_w4a8_gemm(p(qx), p(sx), None, p(blob), M, N, K, 0, p(got), None, 0, st) == 0
     assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M,N,K", [
+    (1, 64, 128), (1, 4160, 8192),        # one group, the longest row; more fragments than workgroups
+    (2, 192, 8192), (3, 320, 4096),       # rows of 256 and 128 threads; sixteen groups a wave short of its last slot
+    (4, 64, 8192), (5, 448, 3968),        # the most elements; 31 groups
+    (9, 576, 1152), (16, 256, 2048),      # rows of 32 threads, nine groups, the most elements
+    (16, 64, 2176), (5, 64, 8192)])       # just past what is quantized in the kernel: two launches
+def test_linear_in_one_launch(api, mode, M, N, K):
+    """Few and short tokens are quantized inside the GEMM kernel: codes, scales, sums and output as the quantizer and the GEMM give
+    them, with a row of zeros, subnormal scales, infinities and NaN; and where the output lies over the tokens."""
+    w, _ = rand_inputs(M, N, K, seed=9 + M + K)
+    blob = api.pack_weights(w, mode)
+    for rep in range(3):
+        x = wl.make_activations(M, K, 40 * rep + M + K, DEV, outlier_count=max(1, K // 100))
+        if rep == 1:
+            x[M // 2] = 0
+            x[M - 1] *= 2.0 ** -16                       # subnormal scale
+        if rep == 2:
+            x[0, K - 1], x[M - 1, 0] = float("inf"), float("nan")
+        qx2, sx2, rowsum2, _ = api.quant_act_per_token(x)
+        want = api.w4a8_gemm(qx2, sx2, blob, N, mode, rowsum=rowsum2 if mode else None)
+        out, qx, sx, rowsum = api.w4a8_linear(x, blob, N, mode)
+        assert torch.equal(qx, qx2) and torch.equal(rowsum, rowsum2)
+        assert torch.equal(sx.view(torch.int16), sx2.view(torch.int16))
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+    both = torch.empty(M * max(N, K), dtype=torch.float16, device=DEV)
+    over, tokens = both[:M * N].view(M, N), both[:M * K].view(M, K)
+    tokens.copy_(x)
+    api.w4a8_linear(tokens, blob, N, mode, out=over)
+    assert torch.equal(over.view(torch.int16), want.view(torch.int16))
