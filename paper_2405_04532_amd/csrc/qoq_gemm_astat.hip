@@ -57,7 +57,8 @@ struct TokensIn {
     int32_t* rowsum;
 };
 constexpr int kTokenLds = 32 * 1024;         // codes of a workgroup's tokens
-constexpr int kTokenChunks = 8;              // 16-byte chunks of FP16 that a thread holds
+constexpr int kTokenChunks = 8;              // 16-byte chunks of FP16 that a thread holds at most
+constexpr int kFewTokenChunks = 2;           // compiled for as many too: loads and codes of chunks that are not there take time as well
 static_assert(kTokenChunks * 8 * kAsThreads == kTokenLds, "one byte of codes per element held");
 
 // For few and short tokens a launch of the quantizer costs more than its work, on the device (2.3 us) and on the host (2.5 us),
@@ -66,7 +67,8 @@ static_assert(kTokenChunks * 8 * kAsThreads == kTokenLds, "one byte of codes per
 // row (rows: p.M rounded up to a power of two); scales and codes as the quantizer decides them (qoq_act_codes.h).
 // Workgroup 0 writes them out for the caller.  Leaves the codes in `codes` (token-major, 16-byte chunks XORed with the row
 // number inside each 128 bytes), maxima and sums in s_amax, s_sum.
-__device__ __forceinline__ void quantize_tokens(const GemmDev& p, const TokensIn& in, const uint4 (&v)[kTokenChunks], int row, int tr,
+template <int CHUNKS>
+__device__ __forceinline__ void quantize_tokens(const GemmDev& p, const TokensIn& in, const uint4 (&v)[CHUNKS], int row, int tr,
                                                 int per_row, bool want_sums, char* codes, uint32_t* s_amax, int* s_sum)
 {
     auto row16 = [](auto x, auto join) {               // joined over each 16 lanes, which are of one row
@@ -81,7 +83,7 @@ __device__ __forceinline__ void quantize_tokens(const GemmDev& p, const TokensIn
     const bool on = row < p.M, lead = on && (threadIdx.x & 15) == 0;
     h2 mx = half2_of(0u);
 #pragma unroll
-    for (int i = 0; i < kTokenChunks; ++i) mx = max_of_chunk(v[i], mx);
+    for (int i = 0; i < CHUNKS; ++i) mx = max_of_chunk(v[i], mx);
     const int bits = row16(__float_as_int(fmaxf((float)mx.x, (float)mx.y)), [](int a, int b) { return max(a, b); });
     if (lead) atomicMax(&s_amax[row], (uint32_t)bits);   // non-negative: the bits order like the values
     __syncthreads();
@@ -89,7 +91,7 @@ __device__ __forceinline__ void quantize_tokens(const GemmDev& p, const TokensIn
         const float s = __half2float(scale_of_row(__uint_as_float(s_amax[row]))), inv_s = 1.0f / s;
         int isum = 0;
 #pragma unroll
-        for (int i = 0; i < kTokenChunks; ++i) {
+        for (int i = 0; i < CHUNKS; ++i) {
             const int c = tr + i * per_row;
             if (c < p.K / 8) {
                 const uint2 q = s >= 0x1p-14f ? codes_of_chunk(v[i], inv_s * (1.0f + 0x1p-20f), isum) : codes_of_chunk_clamped(v[i], inv_s, isum);
@@ -109,9 +111,11 @@ __device__ __forceinline__ void quantize_tokens(const GemmDev& p, const TokensIn
     }
 }
 
-template <int MF, int J, int R, bool GROUP, int OUT, bool FUSED>
+// CHUNKS > 0: the tokens come as FP16, so many chunks of them per thread
+template <int MF, int J, int R, bool GROUP, int OUT, int CHUNKS>
 __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
 {
+    constexpr bool FUSED = CHUNKS > 0;
     static_assert(!FUSED || MF == 1, "the kernel quantizes up to sixteen tokens");
     // R = fragments whose units are in flight ahead of the one being multiplied: a ring of R * J units per wave
     static_assert(J * MF <= 16, "128 registers of activations per lane");
@@ -180,9 +184,9 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
         if (threadIdx.x < 16) { s_amax[threadIdx.x] = 0; s_sum[threadIdx.x] = 0; }
         // the tokens first, then the weights, whose way is the longer one; chunks past the end of a row read as zeros
         const __amdgpu_buffer_rsrc_t tokens = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half*>(in.x), 0, p.M * p.K * 2, 0x00020000);
-        uint4 v[kTokenChunks];
+        uint4 v[CHUNKS];
 #pragma unroll
-        for (int i = 0; i < kTokenChunks; ++i) {
+        for (int i = 0; i < CHUNKS; ++i) {
             const int c = tr + i * per_row;
             v[i] = make_uint4(0u, 0u, 0u, 0u);
             if (i * per_row < p.K / 8)                 // workgroup-uniform
@@ -396,14 +400,14 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
 template <int MF, int J, int R, bool GROUP, int OUT>
 __global__ __launch_bounds__(kAsThreads) void astat_kernel(GemmDev p)
 {
-    astat_run<MF, J, R, GROUP, OUT, false>(p, TokensIn{});
+    astat_run<MF, J, R, GROUP, OUT, 0>(p, TokensIn{});
 }
 
 // Up to sixteen FP16 tokens through the quantizer and the GEMM in one launch.
-template <int J, int R, bool GROUP>
+template <int J, int R, bool GROUP, int CHUNKS>
 __global__ __launch_bounds__(kAsThreads) void astat_linear_kernel(GemmDev p, TokensIn in)
 {
-    astat_run<1, J, R, GROUP, OUT_FP16, true>(p, in);
+    astat_run<1, J, R, GROUP, OUT_FP16, CHUNKS>(p, in);
 }
 
 template <int MF, int J, int R, bool GROUP>
@@ -434,11 +438,19 @@ hipError_t launch_mode(const GemmDev& p, int tile, dim3 grid, bool fp16, hipStre
     return hipGetLastError();
 }
 
-template <bool GROUP>
+template <bool GROUP, int CHUNKS>
 void launch_linear(const GemmDev& p, const TokensIn& in, dim3 grid, hipStream_t s)
 {
-    if ((p.G + kAsWaves - 1) / kAsWaves <= 4) astat_linear_kernel<4, 2, GROUP><<<grid, kAsThreads, 0, s>>>(p, in);
-    else astat_linear_kernel<8, 1, GROUP><<<grid, kAsThreads, 0, s>>>(p, in);
+    if ((p.G + kAsWaves - 1) / kAsWaves <= 4) astat_linear_kernel<4, 2, GROUP, CHUNKS><<<grid, kAsThreads, 0, s>>>(p, in);
+    else astat_linear_kernel<8, 1, GROUP, CHUNKS><<<grid, kAsThreads, 0, s>>>(p, in);
+}
+
+// Elements of M tokens of K, M rounded up to a power of two: what the threads of a workgroup share.
+int64_t token_elements(int64_t M, int64_t K)
+{
+    int64_t rows = 1;
+    while (rows < M) rows *= 2;
+    return rows * K;
 }
 
 }  // namespace
@@ -446,9 +458,7 @@ void launch_linear(const GemmDev& p, const TokensIn& in, dim3 grid, hipStream_t 
 bool astat_linear_takes(int64_t M, int64_t K)
 {
     if (M < 1 || M > 16 || K / kGroup > astat_max_groups(16)) return false;
-    int64_t rows = 1;
-    while (rows < M) rows *= 2;
-    return rows * K <= kTokenLds;
+    return token_elements(M, K) <= kTokenLds;            // (16 x 4096 x 6144 per channel: 8.3 us in one launch, 7.7 in two)
 }
 
 hipError_t launch_astat_linear(const GemmDev& p, const void* x, int8_t* qx, void* sx, int32_t* rowsum, bool group, hipStream_t s)
@@ -456,8 +466,9 @@ hipError_t launch_astat_linear(const GemmDev& p, const void* x, int8_t* qx, void
     if (!astat_linear_takes(p.M, p.K)) return hipErrorInvalidValue;
     const TokensIn in{static_cast<const __half*>(x), qx, static_cast<__half*>(sx), rowsum};
     const dim3 grid((unsigned)(p.N / 16 < 256 ? p.N / 16 : 256));
-    if (group) launch_linear<true>(p, in, grid, s);
-    else launch_linear<false>(p, in, grid, s);
+    const bool few = token_elements(p.M, p.K) <= (int64_t)kFewTokenChunks * 8 * kAsThreads;
+    if (group) few ? launch_linear<true, kFewTokenChunks>(p, in, grid, s) : launch_linear<true, kTokenChunks>(p, in, grid, s);
+    else few ? launch_linear<false, kFewTokenChunks>(p, in, grid, s) : launch_linear<false, kTokenChunks>(p, in, grid, s);
     return hipGetLastError();
 }
 
