@@ -174,9 +174,10 @@ int qoq_w4a8_gemm_token_sum(const int8_t* qx, const void* sx_fp16, const float* 
 /* Activation quantization and GEMM in one call: exactly
  *   qoq_quant_act_per_token(x -> qx, sx, rowsum);  qoq_w4a8_gemm(qx, sx, rowsum, packed -> out)
  * enqueued back to back on `stream` (Section 5.1 places the activation quantization directly in front of
- * the GEMM).  A single-launch variant, in which a few workgroups quantize the rows while the others
- * prefetch weights and a counter releases them, was measured slower than the two launches on MI355X (the
- * device-wide hand-over costs more than a launch) and is not part of the library.
+ * the GEMM), or, for up to sixteen tokens of together at most 32768 elements (K <= 8192), as one launch in which every
+ * workgroup quantizes the tokens itself.  A single-launch variant for more, in which a few workgroups quantize the rows
+ * while the others prefetch weights and a counter releases them, was measured slower than the two launches on
+ * MI355X (the device-wide hand-over costs more than a launch) and is not part of the library.
  *   x_fp16     [M, K] FP16 row-major (read only)
  *   qx         [M, K] INT8 (written), sx_fp16 [M] FP16 (written)
  *   rowsum     [M] INT32 (written); required in per-channel mode, may be NULL in group mode

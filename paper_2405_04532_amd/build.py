@@ -58,8 +58,11 @@ def _check_astat_prologue(path):
     for line in open(path):
         t = line.strip()
         m = re.match(r"(_ZN3qoq\S*astat_kernelILi(\d+)ELi(\d+)ELi(\d+)ELb([01])ELi(\d+)E\S*):", t)
+        deep = re.match(r"(_ZN3qoq\S*astat_deep_kernelILi(\d+)ELb([01])ELi(\d+)E\S*):", t)     # sixteen waves, R = 1
         if m:
             kernel = (m.group(1), int(m.group(3)) * int(m.group(4)) * (2 if m.group(5) == "1" else 1))
+        elif deep:
+            kernel = (deep.group(1), int(deep.group(2)) * (2 if deep.group(3) == "1" else 1))
         elif "astat weight prologue begin" in t:
             counting, count = True, 0
         elif "astat weight prologue end" in t:

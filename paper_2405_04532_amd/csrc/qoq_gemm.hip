@@ -1710,11 +1710,15 @@ static void astat_slices(int64_t G, int tile_m, int64_t& S, int64_t& gps)
     gps = (G + S - 1) / S;
     S = (G + gps - 1) / gps;
 }
+// Sixteen tokens and K up to 14336: sixteen waves hold all of K.  (The workspace keeps its size for two slices: a plan's need does
+// not tell how it is met.)
+static bool astat_deep(int64_t G, int tile_m) { return tile_m == 69 && G > astat_max_groups(16) && G <= astat_deep_groups(); }
 static int64_t astat_nwg(int64_t M, int64_t N, int64_t G, int tile_m, int64_t forced_nwg)
 {
     const int64_t tile = astat_tile(tile_m), m_tiles = (M + tile - 1) / tile, frags = N / 16;
     int64_t S, gps;
     astat_slices(G, tile_m, S, gps);
+    if (astat_deep(G, tile_m)) S = 1;
     int64_t nwg = forced_nwg > 0 ? forced_nwg : std::max<int64_t>(1, 256 / (m_tiles * S));
     // Consecutive workgroups go to consecutive XCDs: with a multiple of eight per token tile the workgroups of one fragment
     // run sit on the same XCD in every tile and share its weights through that L2.  Taken where it costs at most 8% of the
@@ -2055,6 +2059,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     if (a.tile_m >= 69 && a.tile_m <= 71) {
         int64_t S, gps;
         astat_slices(L.G, a.tile_m, S, gps);
+        if (astat_deep(L.G, a.tile_m)) { S = 1; gps = L.G; }
         p.upw = 0;
         nwg = a.split_k;
         p.S = (int)S; p.gps = (int)gps;

@@ -111,23 +111,25 @@ __device__ __forceinline__ void quantize_tokens(const GemmDev& p, const TokensIn
     }
 }
 
-// CHUNKS > 0: the tokens come as FP16, so many chunks of them per thread
-template <int MF, int J, int R, bool GROUP, int OUT, int CHUNKS>
+// W waves.  ROWS: tokens that the preload of a 16-token tile moves (8: half the staging, for up to eight tokens).  CHUNKS > 0: the
+// tokens come as FP16, so many chunks of them per thread.
+template <int W, int MF, int J, int R, bool GROUP, int OUT, int ROWS, int CHUNKS>
 __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
 {
     constexpr bool FUSED = CHUNKS > 0;
-    static_assert(!FUSED || MF == 1, "the kernel quantizes up to sixteen tokens");
+    static_assert(W == 8 || (W == 16 && MF == 1), "wave counts");
+    static_assert(!FUSED || (MF == 1 && W == 8), "the kernel quantizes up to sixteen tokens");
     // R = fragments whose units are in flight ahead of the one being multiplied: a ring of R * J units per wave
     static_assert(J * MF <= 16, "128 registers of activations per lane");
     constexpr int D = R * J;
     constexpr int kEl = MF * 64;                       // int4 elements of a fragment tile: mf * 64 + lane
     // LDS: first every wave's private staging area of the activation preload, afterwards, in the same bytes, the
     // double-buffered exchange of the waves' fragment sums.
-    constexpr int kWaveStage = 16 * 1024;
-    constexpr int kLds = FUSED ? 2 * kTokenLds : kAsWaves * kWaveStage;
+    constexpr int kWaveStage = 128 * 1024 / W;
+    constexpr int kLds = FUSED ? 2 * kTokenLds : W * kWaveStage;
     __shared__ __attribute__((aligned(16))) char lds_raw[kLds];
-    static_assert(2 * kAsWaves * kEl * 16 <= (FUSED ? kTokenLds : kLds), "the exchange buffers fit in the staging areas");
-    int4 (*red)[kAsWaves][kEl] = reinterpret_cast<int4 (*)[kAsWaves][kEl]>(lds_raw);
+    static_assert(2 * W * kEl * 16 <= (FUSED ? kTokenLds : kLds), "the exchange buffers fit in the staging areas");
+    int4 (*red)[W][kEl] = reinterpret_cast<int4 (*)[W][kEl]>(lds_raw);
     __shared__ int s_last[kAsMaxFrags];
     __shared__ uint32_t s_amax[16];                    // FUSED: the tokens' largest magnitudes and sums of codes
     __shared__ int s_sum[16];
@@ -149,7 +151,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
     // waves of a workgroup (and, the workgroups running in step, all of them) read eight different 128-byte
     // columns of the activation rows spread over the whole row -- with interleaved ownership every wave would be in
     // the same kilobyte of the row at the same time, which a few L2 channels then have to serve to the whole chip.
-    const int jeff = (p.gps + kAsWaves - 1) / kAsWaves;             // <= J (host-checked)
+    const int jeff = (p.gps + W - 1) / W;             // <= J (host-checked)
     auto slot_valid = [&](int j) __attribute__((always_inline)) { return j < jeff && g_lo + wave * jeff + j < g_hi; };
     auto group_of = [&](int j) __attribute__((always_inline)) { return min(g_lo + wave * jeff + min(j, jeff - 1), g_hi - 1); };
 
@@ -178,7 +180,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
 #pragma unroll
         for (int mf = 0; mf < MF; ++mf) a[j][mf][0] = a[j][mf][1] = (v4i){0, 0, 0, 0};   // slots past the slice stay zero
     if constexpr (FUSED) {
-        const int rows_log = p.M <= 1 ? 0 : 32 - __builtin_clz(p.M - 1), per_row = kAsThreads >> rows_log;
+        const int rows_log = p.M <= 1 ? 0 : 32 - __builtin_clz(p.M - 1), per_row = (64 * W) >> rows_log;
         const int row = (int)threadIdx.x >> (9 - rows_log), tr = (int)threadIdx.x & (per_row - 1);
         const bool want_sums = !GROUP || in.rowsum;
         if (threadIdx.x < 16) { s_amax[threadIdx.x] = 0; s_sum[threadIdx.x] = 0; }
@@ -208,10 +210,11 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
                     a[j][0][ks] = *reinterpret_cast<const v4i*>(codes + mr * p.K + (((group_of(j) * 8 + ks * 4 + q) ^ (mr & 7)) * 16));
             }
     } else {
-        constexpr int JP = J >= 8 ? 8 : 4;                                   // groups per pass
-        constexpr int RP = (128 / JP) < MF * 16 ? (128 / JP) : MF * 16;      // token rows per pass
-        constexpr int kRowPasses = MF * 16 / RP, kJPasses = (J + JP - 1) / JP, kDma = RP * JP / 8;
-        static_assert(kDma * 1024 <= kWaveStage && RP % 16 == 0, "a pass fits the wave's staging area");
+        static_assert(ROWS == 16 || (ROWS == 8 && MF == 1), "rows of a pass");
+        constexpr int JP = (J >= 8 && W == 8) || (J > 4 && ROWS == 8) ? 8 : 4;                                   // groups per pass
+        constexpr int RP = ROWS == 8 ? 8 : (128 / JP) < MF * 16 ? (128 / JP) : MF * 16;      // token rows per pass
+        constexpr int kRowPasses = ROWS == 8 ? 1 : MF * 16 / RP, kJPasses = (J + JP - 1) / JP, kDma = RP * JP / 8;
+        static_assert(kDma * 1024 <= kWaveStage && RP % ROWS == 0, "a pass fits the wave's staging area");
         const char* abase = reinterpret_cast<const char*>(p.qx);
         const uint32_t region = (uint32_t)(uintptr_t)&lds_raw[0] + (uint32_t)wave * kWaveStage;
         const char* region_ptr = lds_raw + wave * kWaveStage;
@@ -229,13 +232,13 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
         };
         auto read_pass = [&](int rp, int jp) __attribute__((always_inline)) {
 #pragma unroll
-            for (int mm = 0; mm < RP / 16; ++mm)
+            for (int mm = 0; mm < RP / ROWS; ++mm)
 #pragma unroll
                 for (int jj = 0; jj < JP; ++jj) {
-                    const int mf = rp * (RP / 16) + mm, j = jp * JP + jj;
+                    const int mf = rp * (RP / ROWS) + mm, j = jp * JP + jj;
                     if (j < J) {
                         if (slot_valid(j)) {                                 // wave-uniform
-                            const int row_local = mm * 16 + ml;
+                            const int row_local = mm * 16 + (ml & (ROWS - 1));
 #pragma unroll
                             for (int ks = 0; ks < 2; ++ks)
                                 a[j][mf][ks] = *reinterpret_cast<const v4i*>(region_ptr + row_local * (JP * 128) +
@@ -349,7 +352,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
             if (e_on) {
                 v4i sum = (v4i){0, 0, 0, 0};
 #pragma unroll
-                for (int ww = 0; ww < kAsWaves; ++ww) {
+                for (int ww = 0; ww < W; ++ww) {
                     const int4 o = red[buf][ww][el];
                     sum += (v4i){o.x, o.y, o.z, o.w};
                 }
@@ -368,7 +371,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
     // fragments at which this workgroup arrived last ----------------------------------------------------------
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    for (int i = threadIdx.x; i < nfr; i += kAsThreads) {
+    for (int i = threadIdx.x; i < nfr; i += (64 * W)) {
         int* ctr = p.counters + mt_idx * nf_total + f0 + i;
         const int old = __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const bool last = old == p.S - 1;
@@ -397,24 +400,50 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
     }
 }
 
-template <int MF, int J, int R, bool GROUP, int OUT>
+template <int MF, int J, int R, bool GROUP, int OUT, int ROWS = 16>
 __global__ __launch_bounds__(kAsThreads) void astat_kernel(GemmDev p)
 {
-    astat_run<MF, J, R, GROUP, OUT, 0>(p, TokensIn{});
+    astat_run<8, MF, J, R, GROUP, OUT, ROWS, 0>(p, TokensIn{});
+}
+
+// Sixteen waves of 128 registers, for sixteen tokens and K between what eight waves hold and 14336 (seven groups per wave): one
+// workgroup then holds all of K, where two k-slices of eight waves met in memory (stores drained, a counter, loads past the
+// caches: about 2 us).  11008 x 4096 at one token 11.6 us -> 8.9, at sixteen 11.1 -> 10.3; 14336 x 4096 per channel 10.5 -> 8.2; 9216 x
+// 28672 per channel 35.5 -> 23.5.  Up to eight tokens need half the staging: all groups of a wave in one pass, not two one
+// after the other (8.9 and 9.9 us; eight waves, K = 8192 x 10240: 11.2 and 11.6).
+template <int J, bool GROUP, int OUT, int ROWS>
+__global__ __launch_bounds__(1024) void astat_deep_kernel(GemmDev p)
+{
+    astat_run<16, 1, J, 1, GROUP, OUT, ROWS, 0>(p, TokensIn{});
 }
 
 // Up to sixteen FP16 tokens through the quantizer and the GEMM in one launch.
 template <int J, int R, bool GROUP, int CHUNKS>
 __global__ __launch_bounds__(kAsThreads) void astat_linear_kernel(GemmDev p, TokensIn in)
 {
-    astat_run<1, J, R, GROUP, OUT_FP16, CHUNKS>(p, in);
+    astat_run<8, 1, J, R, GROUP, OUT_FP16, 16, CHUNKS>(p, in);
 }
 
 template <int MF, int J, int R, bool GROUP>
 void launch_j(const GemmDev& p, dim3 grid, bool fp16, hipStream_t s)
 {
+    if constexpr (MF == 1) {
+        if (p.M <= 8) {
+            if (fp16) astat_kernel<MF, J, R, GROUP, OUT_FP16, 8><<<grid, kAsThreads, 0, s>>>(p);
+            else astat_kernel<MF, J, R, GROUP, OUT_I32, 8><<<grid, kAsThreads, 0, s>>>(p);
+            return;
+        }
+    }
     if (fp16) astat_kernel<MF, J, R, GROUP, OUT_FP16><<<grid, kAsThreads, 0, s>>>(p);
     else astat_kernel<MF, J, R, GROUP, OUT_I32><<<grid, kAsThreads, 0, s>>>(p);
+}
+
+constexpr int kDeepGroups = 7 * 16;
+template <bool GROUP, int OUT>
+void launch_deep(const GemmDev& p, dim3 grid, hipStream_t s)
+{
+    if (p.gps <= 6 * 16) p.M <= 8 ? astat_deep_kernel<6, GROUP, OUT, 8><<<grid, 1024, 0, s>>>(p) : astat_deep_kernel<6, GROUP, OUT, 16><<<grid, 1024, 0, s>>>(p);
+    else p.M <= 8 ? astat_deep_kernel<7, GROUP, OUT, 8><<<grid, 1024, 0, s>>>(p) : astat_deep_kernel<7, GROUP, OUT, 16><<<grid, 1024, 0, s>>>(p);
 }
 
 template <bool GROUP>
@@ -430,6 +459,10 @@ hipError_t launch_mode(const GemmDev& p, int tile, dim3 grid, bool fp16, hipStre
         if (need <= 4) launch_j<2, 4, 2, GROUP>(p, grid, fp16, s);
         else if (need <= 8) launch_j<2, 8, 1, GROUP>(p, grid, fp16, s);
         else return hipErrorInvalidValue;
+    } else if (p.gps > astat_max_groups(16)) {
+        if (p.gps > kDeepGroups) return hipErrorInvalidValue;
+        if (fp16) launch_deep<GROUP, OUT_FP16>(p, grid, s);
+        else launch_deep<GROUP, OUT_I32>(p, grid, s);
     } else {
         if (need <= 4) launch_j<1, 4, 2, GROUP>(p, grid, fp16, s);
         else if (need <= 8) launch_j<1, 8, 1, GROUP>(p, grid, fp16, s);
@@ -472,13 +505,15 @@ hipError_t launch_astat_linear(const GemmDev& p, const void* x, int8_t* qx, void
     return hipGetLastError();
 }
 
+int astat_deep_groups() { return kDeepGroups; }
+
 int astat_max_groups(int tile) { return kAsWaves * (tile == 64 ? 4 : 8); }
 
 hipError_t launch_astat(const GemmDev& p, int tile_m, int nwg, bool group, bool fp16, hipStream_t s)
 {
     const int tile = tile_m == 71 ? 64 : tile_m == 70 ? 32 : 16;
     const int nf_total = p.N / 16;
-    if (nwg < 1 || p.S < 1 || p.gps < 1 || p.gps > astat_max_groups(tile)) return hipErrorInvalidValue;
+    if (nwg < 1 || p.S < 1 || p.gps < 1 || p.gps > (tile == 16 ? kDeepGroups : astat_max_groups(tile))) return hipErrorInvalidValue;
     if (p.S > 1 && (nf_total + nwg - 1) / nwg > kAsMaxFrags) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nwg, (unsigned)((p.M + tile - 1) / tile), (unsigned)p.S);
     return group ? launch_mode<true>(p, tile, grid, fp16, s) : launch_mode<false>(p, tile, grid, fp16, s);

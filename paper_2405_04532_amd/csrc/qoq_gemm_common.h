@@ -186,6 +186,8 @@ __device__ __forceinline__ void finish4(const GemmDev& p, int m, int n0, v4i v, 
 hipError_t launch_astat(const GemmDev& p, int tile_m, int nwg, bool group, bool fp16, hipStream_t s);
 // Largest number of quantization groups one workgroup of that kernel can keep resident for `tile` tokens.
 int astat_max_groups(int tile);
+// The same for sixteen waves and sixteen tokens.
+int astat_deep_groups();
 // The 16-token kernel that quantizes its tokens itself (quantizer and GEMM in one launch), for what astat_linear_takes.
 bool astat_linear_takes(int64_t M, int64_t K);
 hipError_t launch_astat_linear(const GemmDev& p, const void* x, int8_t* qx, void* sx, int32_t* rowsum, bool group, hipStream_t s);

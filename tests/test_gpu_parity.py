@@ -822,3 +822,25 @@ def test_linear_in_one_launch(api, mode, M, N, K):
     tokens.copy_(x)
     api.w4a8_linear(tokens, blob, N, mode, out=over)
     assert torch.equal(over.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M", [1, 8, 9, 16])
+@pytest.mark.parametrize("N,K", [(64, 8320), (128, 11008), (64, 12288), (192, 12416), (64, 14336), (64, 14464), (64, 2176), (64, 8192)])
+def test_activation_stationary_long_rows(api, mode, M, N, K):
+    """Sixteen tokens or fewer at the edges of what eight and sixteen waves hold (64, 96, 112 groups; beyond, two slices), the
+    staging of eight and of sixteen rows; exact accumulators."""
+    w, x = rand_inputs(M, N, K, seed=83 + M + N)
+    ref = (ogemm.forward_per_channel if mode else ogemm.forward_group)(_np(w), _np(x))
+    blob = api.pack_weights(w, mode)
+    qx, sx, rowsum, _ = api.quant_act_per_token(x)
+    rs = rowsum if mode else None
+    api.set_gemm_config(69, 0)
+    try:
+        ws = api.new_workspace(api.gemm_workspace_bytes(M, N, K, mode), DEV)
+        acc = api.w4a8_gemm_i32(qx, blob, N, mode, rowsum=rs, workspace=ws)
+        out = api.w4a8_gemm(qx, sx, blob, N, mode, rowsum=rs, workspace=ws)
+    finally:
+        api.set_gemm_config()
+    assert (_np(acc).astype(np.int64) == ref["acc"]).all()
+    check_fp16(out, ref["out64"])
