@@ -61,7 +61,7 @@ namespace {
 template <int CNT>
 __device__ __forceinline__ void store_sc1_and_wait(int4* ptr, int stride, const v4i (&v)[CNT])
 {
-    static_assert(CNT == 1 || CNT == 2 || CNT == 4 || CNT == 8, "fragments per lane (of one or two tiles)");
+    static_assert(CNT == 3 || CNT == 4 || CNT == 6 || CNT == 8, "fragments per lane (of one or two tiles)");
     if constexpr (CNT == 8) {
         asm volatile("global_store_dwordx4 %0, %8, off sc1\n\tglobal_store_dwordx4 %1, %9, off sc1\n\t"
                      "global_store_dwordx4 %2, %10, off sc1\n\tglobal_store_dwordx4 %3, %11, off sc1\n\t"
@@ -72,11 +72,16 @@ __device__ __forceinline__ void store_sc1_and_wait(int4* ptr, int stride, const 
                      "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]) : "memory");
         return;
     }
-    if constexpr (CNT == 1)
-        asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" :: "v"(ptr), "v"(v[0]) : "memory");
-    else if constexpr (CNT == 2)
-        asm volatile("global_store_dwordx4 %0, %2, off sc1\n\tglobal_store_dwordx4 %1, %3, off sc1\n\ts_waitcnt vmcnt(0)"
-                     :: "v"(ptr), "v"(ptr + stride), "v"(v[0]), "v"(v[1]) : "memory");
+    if constexpr (CNT == 6)
+        asm volatile("global_store_dwordx4 %0, %6, off sc1\n\tglobal_store_dwordx4 %1, %7, off sc1\n\t"
+                     "global_store_dwordx4 %2, %8, off sc1\n\tglobal_store_dwordx4 %3, %9, off sc1\n\t"
+                     "global_store_dwordx4 %4, %10, off sc1\n\tglobal_store_dwordx4 %5, %11, off sc1\n\ts_waitcnt vmcnt(0)"
+                     :: "v"(ptr), "v"(ptr + stride), "v"(ptr + 2 * stride), "v"(ptr + 3 * stride), "v"(ptr + 4 * stride),
+                     "v"(ptr + 5 * stride), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]) : "memory");
+    else if constexpr (CNT == 3)
+        asm volatile("global_store_dwordx4 %0, %3, off sc1\n\tglobal_store_dwordx4 %1, %4, off sc1\n\t"
+                     "global_store_dwordx4 %2, %5, off sc1\n\ts_waitcnt vmcnt(0)"
+                     :: "v"(ptr), "v"(ptr + stride), "v"(ptr + 2 * stride), "v"(v[0]), "v"(v[1]), "v"(v[2]) : "memory");
     else
         asm volatile("global_store_dwordx4 %0, %4, off sc1\n\tglobal_store_dwordx4 %1, %5, off sc1\n\t"
                      "global_store_dwordx4 %2, %6, off sc1\n\tglobal_store_dwordx4 %3, %7, off sc1\n\ts_waitcnt vmcnt(0)"
@@ -109,7 +114,7 @@ __device__ __forceinline__ void finish_shared_blocks(const GemmDev& p, int npart
     // last to arrive at a block: add every contributor's partial tile, element by element, and finish it
     constexpr int kEl = MF * kThreads;                                     // int4 elements of a partial tile
     constexpr int kRounds = (kEl + THREADS - 1) / THREADS;   // elements per thread
-    constexpr int kBatch = MF == 4 ? 5 : 6;                                // contributors loaded at once
+    constexpr int kBatch = MF >= 3 ? 5 : 6;                                // contributors loaded at once
     v4i t[2 * kRounds * kBatch];
     uint2 c_s[2 * kRounds];
     uint32_t c_z[2 * kRounds];
@@ -263,6 +268,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     // ---- copy roles -----------------------------------------------------------------------
     // producer: lane 4r+c copies 16-byte chunk c ^ h(r) of row r of a 16-row activation block: a quad
     // reads one 64-byte row segment; h spreads the rows over the LDS banks for the fragment reads
+    // (copies of eight rows x whole 128-byte lines were measured 0 - 2% slower here and in the lockstep kernel)
     uint32_t a_voff[kAHalf];                               // blocks ph * kAHalf .. of the group
     {
         const int r = lane >> 2, c = lane & 3;
@@ -708,7 +714,7 @@ template <int NB, int MF, bool GROUP, int OUT>
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void lockstep_kernel(GemmDev p)
 {
     static_assert(NB == 2 || NB == 4, "pairs or quads");
-    static_assert(MF == 1 || MF == 2 || MF == 4, "token tiles of 16, 32 or 64");
+    static_assert(MF >= 1 && MF <= 4, "token tiles of 16, 32, 48 or 64");
     constexpr bool kParity = NB == 2;                  // consumer waves split the two groups of an iteration between them
     constexpr int kRing = 3;
     constexpr int kABlocks = 2 * MF;                   // 1 KiB blocks (m-fragment, k-step) per group
@@ -1473,7 +1479,7 @@ void launch_stream(const GemmDev& p, bool fp16, dim3 grid, hipStream_t s)
 {
     // 64-token tiles: the LDS-staged kernel; smaller tiles: the register-streaming kernel (measured faster there:
     // its activation traffic shrinks with the tile while the staged kernel's per-iteration barriers do not)
-    if constexpr (MF == 4) {
+    if constexpr (MF >= 3) {
         if (fp16) stream_kernel<MF, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
         else stream_kernel<MF, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
     } else {
@@ -1513,15 +1519,23 @@ static int64_t eight_wave_width(int64_t M, int64_t N, int64_t S)
 template <bool GROUP>
 hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStream_t s)
 {
+    // As many tiles of 48 tokens as of 64 hold all tokens (33 ... 48, 65 ... 96, 129 ... 144): no copies and products for rows that are not
+    // there (us with 64 and with 48: 37 tokens x 8192 x 57344 51.3 -> 49.7, x 28672 x 8192 32.6 -> 29.8, x 4096 x 12288 12.4 -> 11.6;
+    // 130 x 11008 x 4096 22.3 -> 20.4).
+    const bool three = p.M <= 48 * ((p.M + 63) / 64);
     if (tile_m >= 69 && tile_m <= 71) {
         return launch_astat(p, tile_m, nwg, GROUP, fp16, s);
     } else if (tile_m == 66) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 63) / 64));
-        if (fp16) lockstep_kernel<4, 4, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
+        if (three && fp16) lockstep_kernel<4, 3, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
+        else if (three) lockstep_kernel<4, 3, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
+        else if (fp16) lockstep_kernel<4, 4, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
         else lockstep_kernel<4, 4, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
     } else if (tile_m == 65) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 63) / 64));
-        if (fp16) lockstep_kernel<2, 4, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
+        if (three && fp16) lockstep_kernel<2, 3, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
+        else if (three) lockstep_kernel<2, 3, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
+        else if (fp16) lockstep_kernel<2, 4, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
         else lockstep_kernel<2, 4, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
     } else if (tile_m == 67) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 31) / 32));
@@ -1535,6 +1549,7 @@ hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStrea
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + tile_m - 1) / tile_m));
         if (tile_m == 16) launch_stream<1, GROUP>(p, fp16, grid, s);
         else if (tile_m == 32) launch_stream<2, GROUP>(p, fp16, grid, s);
+        else if (three) launch_stream<3, GROUP>(p, fp16, grid, s);
         else launch_stream<4, GROUP>(p, fp16, grid, s);
     } else if (tile_m == 129) {
         launch_mma<GROUP, 2, 1>(p, fp16, s);
@@ -1857,7 +1872,7 @@ static void pick_other_config(int64_t M, int64_t N, int64_t K, int mode, const G
     // The activation-stationary kernels are the fastest wherever a workgroup's registers hold the activations of
     // all of K, or of half of it (two k-slices meeting in the workspace), and there is at least a fragment per
     // compute unit.  Measured on the Llama-2-7B layers: up to 32 tokens 5 - 30% ahead of the register-streaming and
-    // lockstep kernels for K = 4096 and 5 - 13% for K = 11008 (two slices).  At 33 - 64 tokens loading the [64, K]
+    // lockstep kernels for K = 4096 and 5 - 13% for K = 11008 (two slices; one at up to 16 tokens, 7 - 23% more).  At 33 - 64 tokens loading the [64, K]
     // slab into every compute unit costs about 3 us more than at 16 tokens (the compute unit's vector cache takes in
     // about 100 bytes per ns; reading the slab pre-tiled straight into registers was measured no faster), which only
     // the widest layers win back (gate/up: 17.1 us against 18.3 us; QKV: 13.0 against 12.3); layers of 192 - 704

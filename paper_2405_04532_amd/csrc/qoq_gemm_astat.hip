@@ -12,8 +12,8 @@
 //   * Workgroup = eight waves, two per SIMD, 256 registers per lane each.  Wave w keeps the activations of the
 //     quantization groups g_lo + w * J' + j (j = 0 .. J'-1, J' <= J) of the workgroup's k-slice: J * MF * 2 operands
 //     of 16 bytes per lane (MF = tokens / 16), at most 128 registers -- together the 256 KiB a [64, 4096] INT8 slab
-//     takes; J <= 4 at 64 tokens, <= 8 at 32 and 16 tokens (sixteen groups per wave at 16 tokens, i.e. all of
-//     K = 11008 in one workgroup, lost to two k-slices of eight: every compute unit then loads half the slab).
+//     takes; J <= 4 at 64 tokens, <= 8 at 32 and 16 tokens.  For 16 tokens and K of 8320 ... 14336 sixteen waves of 128
+//     registers hold all of K, seven groups each (astat_deep_kernel); sixteen groups in each of eight waves lost to two k-slices.
 //     (Four waves with twice the registers each were tried first: the compiler then parks part of the activations
 //     in accumulation registers and copies them back in front of every matrix instruction.)  Slots past the end
 //     of the slice hold zeros, so the loop needs no bounds logic: whatever weights are loaded for such a slot are
@@ -213,7 +213,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
         static_assert(ROWS == 16 || (ROWS == 8 && MF == 1), "rows of a pass");
         constexpr int JP = (J >= 8 && W == 8) || (J > 4 && ROWS == 8) ? 8 : 4;                                   // groups per pass
         constexpr int RP = ROWS == 8 ? 8 : (128 / JP) < MF * 16 ? (128 / JP) : MF * 16;      // token rows per pass
-        constexpr int kRowPasses = ROWS == 8 ? 1 : MF * 16 / RP, kJPasses = (J + JP - 1) / JP, kDma = RP * JP / 8;
+        constexpr int kRowPasses = ROWS == 8 ? 1 : (MF * 16 + RP - 1) / RP, kJPasses = (J + JP - 1) / JP, kDma = RP * JP / 8;
         static_assert(kDma * 1024 <= kWaveStage && RP % ROWS == 0, "a pass fits the wave's staging area");
         const char* abase = reinterpret_cast<const char*>(p.qx);
         const uint32_t region = (uint32_t)(uintptr_t)&lds_raw[0] + (uint32_t)wave * kWaveStage;
@@ -221,6 +221,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
         auto issue_pass = [&](int rp, int jp) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < kDma; ++i) {
+                if (ROWS == 16 && rp * RP + i * 8 / JP >= MF * 16) continue;      // 48 tokens: half of the second pass
                 const int flat = i * 64 + lane;                              // 16-byte position inside the pass
                 const int row_local = flat / (JP * 8), pos = flat % (JP * 8);
                 const uint32_t row = (uint32_t)min(m0 + rp * RP + row_local, p.M - 1);   // rows past M repeat the last one
@@ -236,7 +237,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
 #pragma unroll
                 for (int jj = 0; jj < JP; ++jj) {
                     const int mf = rp * (RP / ROWS) + mm, j = jp * JP + jj;
-                    if (j < J) {
+                    if (j < J && mf < MF) {
                         if (slot_valid(j)) {                                 // wave-uniform
                             const int row_local = mm * 16 + (ml & (ROWS - 1));
 #pragma unroll
@@ -450,7 +451,12 @@ template <bool GROUP>
 hipError_t launch_mode(const GemmDev& p, int tile, dim3 grid, bool fp16, hipStream_t s)
 {
     const int need = (p.gps + kAsWaves - 1) / kAsWaves;   // groups per wave
-    if (tile == 64) {
+    if (tile == 48) {
+        if (need <= 2) launch_j<3, 2, 2, GROUP>(p, grid, fp16, s);
+        else if (need <= 3) launch_j<3, 3, 2, GROUP>(p, grid, fp16, s);
+        else if (need <= 4) launch_j<3, 4, 2, GROUP>(p, grid, fp16, s);
+        else return hipErrorInvalidValue;
+    } else if (tile == 64) {
         if (need <= 2) launch_j<4, 2, 2, GROUP>(p, grid, fp16, s);
         else if (need <= 3) launch_j<4, 3, 2, GROUP>(p, grid, fp16, s);
         else if (need <= 4) launch_j<4, 4, 2, GROUP>(p, grid, fp16, s);
@@ -516,7 +522,10 @@ hipError_t launch_astat(const GemmDev& p, int tile_m, int nwg, bool group, bool 
     if (nwg < 1 || p.S < 1 || p.gps < 1 || p.gps > (tile == 16 ? kDeepGroups : astat_max_groups(tile))) return hipErrorInvalidValue;
     if (p.S > 1 && (nf_total + nwg - 1) / nwg > kAsMaxFrags) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nwg, (unsigned)((p.M + tile - 1) / tile), (unsigned)p.S);
-    return group ? launch_mode<true>(p, tile, grid, fp16, s) : launch_mode<false>(p, tile, grid, fp16, s);
+    // As many tiles of 48 tokens as of 64 hold them all (33 ... 48, 65 ... 96, 129 ... 144): a quarter less to load
+    // in front of the loop and to multiply in it (4096 x 12288 at 80 tokens 16.5 -> 14.3 us, at 130 20.9 -> 18.9; 22016 at 37 16.5 -> 15.1).
+    const int rows = tile == 64 && p.M <= 48 * (int)grid.y ? 48 : tile;
+    return group ? launch_mode<true>(p, rows, grid, fp16, s) : launch_mode<false>(p, rows, grid, fp16, s);
 }
 
 }  // namespace qoq

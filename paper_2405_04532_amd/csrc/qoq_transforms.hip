@@ -23,8 +23,8 @@ namespace {
 // salience).  A workgroup takes 256 channels x 128 rows: thread (8-channel chunk c, row group q of 8) has the 16 loads of
 // its rows in flight together, maxima of FP16 pairs, the eight row groups meet in LDS and one of them goes on;
 // non-negative floats order like their bit patterns, so the slabs of rows meet with an integer atomic maximum on a
-// zero-filled array; a slab alone stores its maxima, and nothing is filled (1 x 14336: 3.2 us instead of 4.9).  Bound by HBM latency and bandwidth: 1024 x 14336 (29 MB) in 8 us; with one thread per 8 channels
-// and 64 rows one after the other, 112 workgroups in all, it was 33 us.
+// zero-filled array; a slab alone stores its maxima, and nothing is filled (1 x 14336: 3.2 us instead of 4.9).  Bound by HBM latency and bandwidth: 1024 x 14336 (29 MB) in 7.8 us (by columns, below, 4.6);
+// with one thread per 8 channels // and 64 rows one after the other, 112 workgroups in all, it was 33 us.
 constexpr int kAbsmaxRows = 128;
 __global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* __restrict__ x, int64_t M, int chunks, int* __restrict__ out_bits)
 {

@@ -825,6 +825,30 @@ def test_linear_in_one_launch(api, mode, M, N, K):
 
 
 @pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M", [33, 48, 49, 96, 97, 144, 145])
+@pytest.mark.parametrize("tile,nwg,N,K", [(64, 3, 128, 640), (64, 2, 64, 4224), (65, 1, 256, 384), (66, 1, 256, 640), (71, 2, 64, 2048), (71, 3, 128, 3072),
+                                          (71, 4, 64, 4096), (71, 2, 64, 5120)])
+def test_tiles_of_48_tokens(api, mode, M, tile, nwg, N, K):
+    """The 64-token kernels on either side of the token counts that as many 48-token tiles hold: whole blocks and shared ones, two
+    and one k-slices; exact accumulators."""
+    w, x = rand_inputs(M, N, K, seed=89 + M + K)
+    ref = (ogemm.forward_per_channel if mode else ogemm.forward_group)(_np(w), _np(x))
+    blob = api.pack_weights(w, mode)
+    qx, sx, rowsum, _ = api.quant_act_per_token(x)
+    rs = rowsum if mode else None
+    api.set_gemm_config(tile, nwg)
+    try:
+        assert api.query_gemm_config(M, N, K, mode)[0] == tile
+        ws = api.new_workspace(api.gemm_workspace_bytes(M, N, K, mode), DEV)
+        acc = api.w4a8_gemm_i32(qx, blob, N, mode, rowsum=rs, workspace=ws)
+        out = api.w4a8_gemm(qx, sx, blob, N, mode, rowsum=rs, workspace=ws)
+    finally:
+        api.set_gemm_config()
+    assert (_np(acc).astype(np.int64) == ref["acc"]).all()
+    check_fp16(out, ref["out64"])
+
+
+@pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("M", [1, 8, 9, 16])
 @pytest.mark.parametrize("N,K", [(64, 8320), (128, 11008), (64, 12288), (192, 12416), (64, 14336), (64, 14464), (64, 2176), (64, 8192)])
 def test_activation_stationary_long_rows(api, mode, M, N, K):
