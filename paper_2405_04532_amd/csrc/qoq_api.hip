@@ -82,10 +82,11 @@ int gemm_common(const int8_t* qx, const void* sx, const int32_t* rowsum, const v
         const size_t counters = qoq::gemm_counter_bytes(M, N, K, tile_m, split_k);
         return counters <= kScratchCounterBytes && qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k) - counters <= kScratchPartBytes;
     };
-    // Where the fastest plan exchanges more than there is room for, the fastest without the eight-wave kernels; in the static
+    // Where the fastest plan exchanges more than there is room for, the fastest without the eight-wave kernels and without 48-token
+    // tiles in place of 32-token ones; in the static
     // scratch then one that exchanges nothing, if there is one.
     const auto room = [&] { return static_scratch ? scratch_holds() : (ws && ws_bytes >= qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k)); };
-    if (tuning.tile_m == 0 && tile_m == 130 && qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k) && !room())
+    if (tuning.tile_m == 0 && qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k) && !room())
         qoq::pick_gemm_config(M, N, K, mode, tuning, tile_m, split_k, false);
     if (static_scratch && tuning.tile_m == 0 && !scratch_holds()) qoq::pick_gemm_config_without_workspace(M, N, K, mode, tile_m, split_k);
     if ((uint64_t)M * (uint64_t)K >= ((uint64_t)1 << 32)) return QOQ_ERR_SHAPE;  // 32-bit activation offsets

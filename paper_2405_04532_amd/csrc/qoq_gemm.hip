@@ -1987,6 +1987,16 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
     else if (tile_m == 132) ahead = 0.88;
     if (K < 8 * kGroup) ahead -= 0.05;
     if (eight < ahead * cost - 0.3) { tile_m = 130; split_k = S; }
+    // 65 ... 96 tokens and long rows: two 48-token tiles read the weights twice where three of 32 read them three times, on half as many
+    // k's per workgroup.  11008 x 4096 at 73 ... 92 tokens 19.0 -> 16.7 us, 14336 x 4096 per channel 20.5 -> 17.5, 13824 x 2432 18.2 -> 17.1 (25
+    // shapes of 2304 ... 4544 channels, none slower); with fewer channels or shorter rows the hand-over takes more than that (13696 x
+    // 1920 the same, x 1344 0.93 of the speed, x 384 0.76; 9728 x 4544 0.95).
+    const int64_t G = K / kGroup;
+    if (tile_m == 32 && M <= 96 && N >= 2304 && G >= 80) {
+        const int64_t units = (N / 64) * G, nwg = stream_plan(M, N, G, 64, 0).nwg, upw = (units + nwg - 1) / nwg;
+        tile_m = 64;
+        split_k = (int)((units + upw - 1) / upw);
+    }
 }
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int split_k)

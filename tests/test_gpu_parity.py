@@ -849,6 +849,27 @@ def test_tiles_of_48_tokens(api, mode, M, tile, nwg, N, K):
 
 
 @pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M,N,K,tile", [(65, 4096, 10240, 64), (96, 2368, 10880, 64), (80, 2240, 10240, 32), (72, 3712, 9216, 32)])
+def test_long_rows_on_tiles_of_48_tokens(api, mode, M, N, K, tile):
+    """Plans on either side of the width from which 65 to 96 tokens of long rows take 48-token tiles, and with a workspace that is too small
+    for those; exact accumulators."""
+    assert api.query_gemm_config(M, N, K, mode)[0] == tile
+    w, x = rand_inputs(M, N, K, seed=97 + M)
+    ref = (ogemm.forward_per_channel if mode else ogemm.forward_group)(_np(w), _np(x))
+    blob = api.pack_weights(w, mode)
+    qx, sx, rowsum, _ = api.quant_act_per_token(x)
+    rs = rowsum if mode else None
+    ws = api.new_workspace(api.gemm_workspace_bytes(M, N, K, mode), DEV)
+    acc = api.w4a8_gemm_i32(qx, blob, N, mode, rowsum=rs, workspace=ws)
+    assert (_np(acc).astype(np.int64) == ref["acc"]).all()
+    check_fp16(api.w4a8_gemm(qx, sx, blob, N, mode, rowsum=rs, workspace=ws), ref["out64"])
+    if tile == 64:
+        small = api.new_workspace(api.gemm_workspace_bytes(M, N, K, mode) * 6 // 10, DEV)
+        acc = api.w4a8_gemm_i32(qx, blob, N, mode, rowsum=rs, workspace=small)
+        assert (_np(acc).astype(np.int64) == ref["acc"]).all()
+
+
+@pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("M", [1, 8, 9, 16])
 @pytest.mark.parametrize("N,K", [(64, 8320), (128, 11008), (64, 12288), (192, 12416), (64, 14336), (64, 14464), (64, 2176), (64, 8192)])
 def test_activation_stationary_long_rows(api, mode, M, N, K):
