@@ -55,13 +55,14 @@ const char* qoq_status_string(int status);
 size_t qoq_packed_bytes(int64_t N, int64_t K, int mode);
 
 /* Bytes of workspace qoq_w4a8_gemm / qoq_w4a8_gemm_i32 need for this problem (may be 0;
- * always a multiple of 16).  Used for split-k: per-tile arrival counters and partial tiles. */
+ * always a multiple of 16).  Used for split-k: a fixed area of arrival counters (256 KiB), then partial tiles. */
 size_t qoq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int mode);
 
 /* Zero-fill a workspace (dev pointer, 16-byte aligned, size a multiple of 16) on `stream`.
  * A workspace must be zero-filled ONCE after allocation, before its first GEMM call: the
  * GEMM relies on its arrival counters being zero on entry and leaves them zero on exit, so
- * later calls need no further preparation (and no memset appears on the hot path). */
+ * later calls need no further preparation (and no memset appears on the hot path).  The counters of every call lie in
+ * the same area whatever its shape, and no call's partial tiles do, so calls of any shapes may take turns. */
 int qoq_gemm_workspace_prepare(void* workspace, size_t workspace_bytes, void* stream);
 
 /* Offline weight path (Section 4.1 Eq. 3-4, Section 5.2.1): quantize FP16 weights and store
@@ -265,10 +266,11 @@ int qoq_kv4_unpack(const void* cache, int64_t B, int64_t Hkv, int64_t S_max, int
  * two adjacent blocks per workgroup in lockstep (N % 128 == 0; else as 64); 66 = four blocks in lockstep
  * (N % 256 == 0; else as 65); 67, 68 = two blocks in lockstep with 32 / 16 tokens per tile (else as 32 / 16);
  * 69, 70, 71 = activation-stationary kernel with 16 / 32 / 64 tokens per tile (activations resident in registers,
- * only weights streamed; K beyond what a workgroup holds is cut into slices that meet in the workspace);
+ * only weights streamed; K beyond what a workgroup holds is cut into slices that meet in the workspace; as 16 / 32 / 64 where
+ * that would take more than 65536 arrival counters);
  * 128, 129, 131 = compute-bound kernel with tiles of 256 x 256, 128 x 256, 256 x 192 (tokens x channels); 132 = 128 x 256
  * tiles with two workgroups per compute unit; 130 = eight waves per tile of 128 or 256 channels and equal shares of at most 144 tokens.
- * split_k >= 0 (0 = auto): for the compute-bound kernel the number of k-slices per output tile, for the
+ * split_k >= 0 (0 = auto): for the compute-bound kernel the number of k-slices per output tile (one with more than 65536 tiles), for the
  * streaming kernels the number of workgroups the stream of work units is dealt to (activation-stationary kernels:
  * workgroups per token tile and k-slice that share the layer's 16-channel fragments).
  * Not part of the hot-call contract: the setting is process-wide (two atomics, no lock), so a thread that changes

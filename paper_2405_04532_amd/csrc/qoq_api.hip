@@ -7,6 +7,7 @@
 
 #include "../../include/qoq_w4a8.h"
 #include "qoq_internal.h"
+#include "qoq_workspace.h"
 
 namespace {
 
@@ -36,12 +37,10 @@ int arch_ok()
 
 // ---- scratch of the entry point that allocates nothing ---------------------------------------------------
 // One array per GPU (every device that loads the library holds its own copy at its own address until the
-// process ends): a fixed region of arrival counters, then the partial tiles.  The counter region is the same for
-// every shape, so partial tiles of one call never land where a later call expects counters; the kernels leave
-// every counter they used at zero, and the array starts out zero-filled, so nothing is cleared per call.
-constexpr size_t kScratchCounterBytes = (size_t)256 << 10;
-constexpr size_t kScratchPartBytes = (size_t)16 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchCounterBytes + kScratchPartBytes];
+// process ends), laid out as every workspace (qoq_workspace.h); the kernels leave every counter they used at zero, and the
+// array starts out zero-filled, so nothing is cleared per call.
+constexpr size_t kScratchBytes = qoq::kCounterBytes + ((size_t)16 << 20);
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 // The array's name is a host-side stand-in, not a device address: its address on the CURRENT device is looked up
 // once per device and kept; host code uses only that pointer.
@@ -78,10 +77,7 @@ int gemm_common(const int8_t* qx, const void* sx, const int32_t* rowsum, const v
     int tile_m, split_k;
     const qoq::GemmTuning tuning = forced();
     qoq::pick_gemm_config(M, N, K, mode, tuning, tile_m, split_k);
-    const auto scratch_holds = [&] {
-        const size_t counters = qoq::gemm_counter_bytes(M, N, K, tile_m, split_k);
-        return counters <= kScratchCounterBytes && qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k) - counters <= kScratchPartBytes;
-    };
+    const auto scratch_holds = [&] { return qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k) <= kScratchBytes; };
     // Where the fastest plan exchanges more than there is room for, the fastest without the eight-wave kernels and without 48-token
     // tiles in place of 32-token ones; in the static
     // scratch then one that exchanges nothing, if there is one.
@@ -92,15 +88,13 @@ int gemm_common(const int8_t* qx, const void* sx, const int32_t* rowsum, const v
     if ((uint64_t)M * (uint64_t)K >= ((uint64_t)1 << 32)) return QOQ_ERR_SHAPE;  // 32-bit activation offsets
     if (tile_m <= 71 && (uint64_t)N * (uint64_t)K >= ((uint64_t)1 << 33)) return QOQ_ERR_SHAPE;  // 32-bit weight offsets (4 GiB packed)
     const size_t need = qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k);
-    size_t parts_offset = 0;
     if (static_scratch) {
-        // the library's own per-device array instead of a caller's workspace: fixed counter region, then partial tiles
+        // the library's own per-device array instead of a caller's workspace
         if (!scratch_holds()) return QOQ_ERR_WORKSPACE;
         if (!arch_ok()) return QOQ_ERR_ARCH;
         if (need) {
             const int rc = scratch_of_current_device(&ws);
             if (rc != QOQ_OK) return rc;
-            parts_offset = kScratchCounterBytes;
         }
     } else if (need && (!ws || ws_bytes < need)) {
         return QOQ_ERR_WORKSPACE;
@@ -111,7 +105,7 @@ int gemm_common(const int8_t* qx, const void* sx, const int32_t* rowsum, const v
     a.qx = qx; a.sx = sx; a.rowsum = rowsum; a.tx = tx; a.blob = static_cast<const uint8_t*>(packed);
     a.M = M; a.N = N; a.K = K; a.mode = mode;
     a.out_fp16 = out16; a.out_i32 = out32; a.workspace = ws;
-    a.tile_m = tile_m; a.split_k = split_k; a.parts_offset = parts_offset;
+    a.tile_m = tile_m; a.split_k = split_k;
     // One launch for few and short tokens; not where a result takes the place of tokens that other workgroups still read.
     const auto over_tokens = [&](const void* p, size_t bytes) {
         const uintptr_t x0 = reinterpret_cast<uintptr_t>(x_fp16), p0 = reinterpret_cast<uintptr_t>(p);

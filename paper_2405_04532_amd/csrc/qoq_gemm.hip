@@ -41,6 +41,7 @@
 #include "qoq_internal.h"
 #include "qoq_gemm_common.h"
 #include "qoq_walk.h"
+#include "qoq_workspace.h"
 
 namespace qoq {
 namespace {
@@ -1584,13 +1585,6 @@ static int64_t mma_tiles(int64_t M, int64_t N, int tile_m, int64_t S)
     mma_tile_shape(M, N, tile_m, S, tm, tn);
     return ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
 }
-// Arrival counters of the tiles (eight-wave kernel: room for its 128-channel tiles of every 256 tokens, whatever the width).
-static size_t mma_counter_bytes(int64_t M, int64_t N, int tile_m, int64_t S)
-{
-    int64_t n = mma_tiles(M, N, tile_m, S);
-    if (tile_m == 130) n = std::max(n, ((M + 255) / 256) * ((N + 127) / 128));
-    return align256((size_t)n * sizeof(int));
-}
 // k-slices of the compute-bound kernel: only when its tiles leave most CUs idle and every slice still has a
 // long run of groups (a partial tile costs 128-256 KiB of traffic each way plus a device-wide hand-over).
 static int mma_split(int64_t M, int64_t N, int64_t G, int tile_m, int forced_split)
@@ -1728,6 +1722,14 @@ static void astat_slices(int64_t G, int tile_m, int64_t& S, int64_t& gps)
 // Sixteen tokens and K up to 14336: sixteen waves hold all of K.  (The workspace keeps its size for two slices: a plan's need does
 // not tell how it is met.)
 static bool astat_deep(int64_t G, int tile_m) { return tile_m == 69 && G > astat_max_groups(16) && G <= astat_deep_groups(); }
+// Fragments whose k-slices meet in the workspace.
+static int64_t astat_counters(int64_t M, int64_t N, int64_t G, int tile_m)
+{
+    int64_t S, gps;
+    astat_slices(G, tile_m, S, gps);
+    const int64_t tile = astat_tile(tile_m);
+    return S <= 1 ? 0 : (M + tile - 1) / tile * (N / 16);
+}
 static int64_t astat_nwg(int64_t M, int64_t N, int64_t G, int tile_m, int64_t forced_nwg)
 {
     const int64_t tile = astat_tile(tile_m), m_tiles = (M + tile - 1) / tile, frags = N / 16;
@@ -1888,6 +1890,8 @@ static void pick_other_config(int64_t M, int64_t N, int64_t K, int mode, const G
         const bool fits = M <= 32 ? S <= 2 : (S == 1 && G <= (cand == 71 ? 32 : 64));
         if (take && fits) tile_m = cand;
     }
+    // slices that would need more counters than there are, which only a forced configuration does: as the streaming kernel
+    if (tile_m >= 69 && tile_m <= 71 && astat_counters(M, N, G, tile_m) > kMaxCounters) tile_m = astat_tile(tile_m);
     if (tile_m >= 69 && tile_m <= 71) {
         split_k = (int)astat_nwg(M, N, G, tile_m, forced.split_k);
         return;
@@ -1959,11 +1963,12 @@ static void pick_other_config(int64_t M, int64_t N, int64_t K, int mode, const G
     if (tile_m <= 64) {
         const int64_t units = (N / 64) * G;
         const int64_t nwg = (tile_m == stream_tile && forced.split_k <= 0) ? plan.nwg : stream_plan(M, N, G, tile_m, forced.split_k).nwg;
-        const int64_t upw = (units + nwg - 1) / nwg;
+        const int64_t upw = stream_units_per_workgroup(M, N, G, tile_m, nwg);
         split_k = (int)((units + upw - 1) / upw);
         return;
     }
     split_k = mma_split(M, N, G, tile_m, forced.split_k);
+    if (split_k > 1 && mma_tiles(M, N, tile_m, split_k) > kMaxCounters) split_k = 1;   // only where a split is forced
 }
 
 void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTuning& forced, int& tile_m, int& split_k, bool eight_waves)
@@ -1993,7 +1998,7 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
     // 1920 the same, x 1344 0.93 of the speed, x 384 0.76; 9728 x 4544 0.95).
     const int64_t G = K / kGroup;
     if (tile_m == 32 && M <= 96 && N >= 2304 && G >= 80) {
-        const int64_t units = (N / 64) * G, nwg = stream_plan(M, N, G, 64, 0).nwg, upw = (units + nwg - 1) / nwg;
+        const int64_t units = (N / 64) * G, upw = stream_units_per_workgroup(M, N, G, 64, stream_plan(M, N, G, 64, 0).nwg);
         tile_m = 64;
         split_k = (int)((units + upw - 1) / upw);
     }
@@ -2006,7 +2011,7 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int spl
         astat_slices(K / kGroup, tile_m, S, gps);
         if (S <= 1) return 0;
         const int64_t tile = astat_tile(tile_m), m_tiles = (M + tile - 1) / tile, frags = N / 16;
-        return align256((size_t)(m_tiles * frags) * sizeof(int)) + (size_t)(m_tiles * frags * S) * (size_t)(tile * 64);
+        return kCounterBytes + (size_t)(m_tiles * frags * S) * (size_t)(tile * 64);
     }
     if (tile_m >= 65 && tile_m <= 68) return 0;        // whole block pairs / quads per workgroup: nothing is exchanged
     if (tile_m <= 64) {
@@ -2014,8 +2019,7 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int spl
         const int64_t units = (N / 64) * (K / kGroup);
         const int64_t upw = (units + split_k - 1) / split_k;
         if (upw * 1 >= units && split_k <= 1) return 0;
-        const size_t counters = align256((size_t)(m_tiles * (N / 64)) * sizeof(int));
-        return counters + (size_t)m_tiles * (size_t)split_k * 2 * (size_t)(tile_m * 64) * sizeof(int32_t);
+        return kCounterBytes + (size_t)m_tiles * (size_t)split_k * 2 * (size_t)(tile_m * 64) * sizeof(int32_t);
     }
     if (split_k <= 1) return 0;
     int64_t tm, tn;
@@ -2029,18 +2033,7 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int spl
         sums = std::max<size_t>(tiles * (size_t)(16 * waves * ((eight_wave_fragments(M) + waves - 1) / waves) * tn),
                                 (size_t)((M + 255) / 256 * 256) * (size_t)((N + 127) / 128 * 128));
     }
-    return mma_counter_bytes(M, N, tile_m, split_k) + sums * (size_t)split_k * sizeof(int32_t);
-}
-
-size_t gemm_counter_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int split_k)
-{
-    if (gemm_workspace_bytes(M, N, K, tile_m, split_k) == 0) return 0;
-    if (tile_m >= 69 && tile_m <= 71) {
-        const int64_t tile = astat_tile(tile_m);
-        return align256((size_t)(((M + tile - 1) / tile) * (N / 16)) * sizeof(int));
-    }
-    if (tile_m <= 64) return align256((size_t)(((M + tile_m - 1) / tile_m) * (N / 64)) * sizeof(int));
-    return mma_counter_bytes(M, N, tile_m, split_k);
+    return kCounterBytes + sums * (size_t)split_k * sizeof(int32_t);
 }
 
 static GemmDev device_args(const GemmArgs& a)
@@ -2080,7 +2073,6 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     const BlobLayout L = make_layout(a.N, a.K, a.mode);
     GemmDev p = device_args(a);
     int nwg = 0;
-    size_t counters;
     if (a.tile_m >= 69 && a.tile_m <= 71) {
         int64_t S, gps;
         astat_slices(L.G, a.tile_m, S, gps);
@@ -2088,7 +2080,6 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         p.upw = 0;
         nwg = a.split_k;
         p.S = (int)S; p.gps = (int)gps;
-        counters = gemm_counter_bytes(a.M, a.N, a.K, a.tile_m, a.split_k);
     } else if (a.tile_m >= 65 && a.tile_m <= 68) {
         const int64_t width = a.tile_m == 66 ? 256 : 128;
         if (a.N % width != 0) return hipErrorInvalidValue;
@@ -2096,20 +2087,16 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
         p.upw = (int)((pairs + a.split_k - 1) / a.split_k);   // whole block pairs per workgroup
         nwg = a.split_k;
         p.S = 1; p.gps = (int)L.G;
-        counters = 0;
     } else if (a.tile_m <= 64) {
-        const int64_t units = (a.N / 64) * L.G;
-        p.upw = (int)((units + a.split_k - 1) / a.split_k);
+        p.upw = (int)stream_units_per_workgroup(a.M, a.N, L.G, a.tile_m, a.split_k);
         nwg = a.split_k;
         p.S = 1; p.gps = (int)L.G;
-        counters = align256((size_t)(((a.M + a.tile_m - 1) / a.tile_m) * (a.N / 64)) * sizeof(int));
     } else {
         p.upw = 0;
         p.S = a.split_k;
         p.gps = (int)((L.G + a.split_k - 1) / a.split_k);
-        counters = mma_counter_bytes(a.M, a.N, a.tile_m, a.split_k);
     }
-    p.parts = reinterpret_cast<int4*>(reinterpret_cast<uint8_t*>(a.workspace) + (a.parts_offset ? a.parts_offset : counters));
+    p.parts = reinterpret_cast<int4*>(reinterpret_cast<uint8_t*>(a.workspace) + kCounterBytes);
     return a.mode == 0 ? launch_any<true>(p, a.tile_m, nwg, a.out_fp16 != nullptr, s)
                        : launch_any<false>(p, a.tile_m, nwg, a.out_fp16 != nullptr, s);
 }

@@ -36,20 +36,17 @@ struct GemmArgs {
     int mode;
     void* out_fp16;          // [M, N] FP16, or null
     int32_t* out_i32;        // [M, N] INT32, or null
-    void* workspace;         // split-k counters and partial tiles when split_k > 1
+    void* workspace;         // arrival counters and partial tiles (qoq_workspace.h) of a launch that exchanges sums
     int tile_m;              // 16, 32, 64 (streaming kernels), 65 ... 68 (lockstep), 69 ... 71 (activation-stationary: 16, 32,
                              // 64 tokens) or 128 ... 132 (compute-bound kernels, 130 with eight waves)
     int split_k;             // compute-bound kernels: k-slices per tile; the others: workgroups per token tile (and k-slice)
-    size_t parts_offset = 0; // byte offset of the partial tiles inside the workspace; 0 = directly behind the counters
 };
-// Bytes of arrival counters at the start of the workspace of a (tile_m, split_k) launch (0 if it exchanges nothing).
-size_t gemm_counter_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int split_k);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 // Quantizer and GEMM in one launch, for few and short tokens; a.qx, a.sx and a.rowsum are written.
 bool linear_in_one_launch(int64_t M, int64_t K);
 hipError_t launch_linear(const GemmArgs& a, const void* x_fp16, hipStream_t s);
 
-// Workspace a (tile_m, split_k) launch needs: per-tile counters, then the partial tiles.
+// Workspace a (tile_m, split_k) launch needs: the counter area, then its partial tiles; 0 if it exchanges nothing.
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int split_k);
 hipError_t launch_zero(void* dst, size_t bytes, hipStream_t s);
 

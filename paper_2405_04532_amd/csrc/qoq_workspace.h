@@ -1,0 +1,24 @@
+// The GEMM workspace, where workgroups that share an output meet (internal to the library).
+//
+// [arrival counters: kCounterBytes][partial tiles].  The counters of every call lie in the first kCounterBytes, its partial
+// tiles behind them, whatever the shape and the kernel: calls of different shapes take turns in one workspace, each
+// relies on its counters being zero and leaves them zero, and none may find an earlier call's sums there.
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+namespace qoq {
+
+constexpr size_t kCounterBytes = (size_t)256 << 10;
+constexpr int64_t kMaxCounters = (int64_t)(kCounterBytes / sizeof(int));
+
+// Units (64-channel block, group) per workgroup of the streaming kernels when `nwg` workgroups share a token tile of `tile`.
+// With more blocks than counters (600000 channels at 400 tokens) a workgroup takes whole blocks, and nothing is exchanged.
+inline int64_t stream_units_per_workgroup(int64_t M, int64_t N, int64_t G, int tile, int64_t nwg)
+{
+    const int64_t blocks = N / 64, upw = (blocks * G + nwg - 1) / nwg;
+    if ((M + tile - 1) / tile * blocks <= kMaxCounters) return upw;
+    return (upw + G - 1) / G * G;
+}
+
+}  // namespace qoq

@@ -889,3 +889,22 @@ def test_activation_stationary_long_rows(api, mode, M, N, K):
         api.set_gemm_config()
     assert (_np(acc).astype(np.int64) == ref["acc"]).all()
     check_fp16(out, ref["out64"])
+
+
+@pytest.mark.parametrize("mode,N,K,tokens", [
+    (0, 4096, 11008, (160, 389, 160, 512, 64, 24, 300)),      # few counters and many, in the eight-wave and in the smaller tiles
+    (0, 4096, 11008, (260, 400, 260, 40, 17, 40)),
+    (1, 2048, 14336, (33, 100, 17, 130, 33)),
+    (0, 256, 4096, (16, 70, 1, 200, 16))])
+def test_token_counts_take_turns_in_one_workspace(api, mode, N, K, tokens):
+    """One workspace, of the size that the largest of these calls needs, serves them all in any order: no call finds sums of another
+    where it expects counters.  Accumulators into outputs that hold something else before, exact."""
+    w, x = rand_inputs(max(tokens), N, K, seed=101 + N)
+    blob = api.pack_weights(w, mode)
+    qx, _, rowsum, _ = api.quant_act_per_token(x)
+    ref = (ogemm.forward_per_channel if mode else ogemm.forward_group)(_np(w), _np(x))["acc"]
+    ws = api.new_workspace(max(api.gemm_workspace_bytes(M, N, K, mode) for M in tokens), DEV)
+    for M in tokens:
+        acc = torch.full((M, N), 0x5A5A5A5A, dtype=torch.int32, device=DEV)
+        api.w4a8_gemm_i32(qx[:M], blob, N, mode, rowsum=rowsum[:M] if mode else None, out=acc, workspace=ws)
+        assert (_np(acc).astype(np.int64) == ref[:M]).all(), M

@@ -6,7 +6,8 @@ the library's own qoq_query_gemm_config and qoq_gemm_workspace_bytes), the same 
 the header the kernels themselves include), the same clamps for rows past M, groups past the end of a run or slice,
 fragments past N, and the copies issued past the end of a run.  Each global address the model forms -- packed codes,
 level-2 metadata, channel scales and zeros, INT8 activations, token scales and sums, partial tiles and counters in the
-workspace -- is checked against the size of its buffer.  A copy that read group G of the last token row (128 bytes
+workspace -- is checked against the size of its buffer.  The counters of every plan lie in one area of the workspace and
+every plan's partial tiles behind it, so no call finds the sums of a call of another shape where it expects counters.  A copy that read group G of the last token row (128 bytes
 past the activations) once went unnoticed until it faulted on the GPU; this test makes that class of mistake fail
 on the CPU."""
 import os
@@ -19,12 +20,13 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CHECKER = r'''
 #include "qoq_layout.h"
 #include "qoq_walk.h"
+#include "qoq_workspace.h"
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 using namespace qoq;
 typedef long long ll;
-static ll M, N, K, G, ws_bytes, counters_bytes; static int mode, tile, split;
+static ll M, N, K, G, ws_bytes; static const ll counters_bytes = kCounterBytes; static int mode, tile, split;
 static ll n_codes, n_meta, n_scales, n_zeros, n_qx, n_sx, n_rs;
 static const char* fail = nullptr; static ll fail_off, fail_len, fail_size;
 static inline void chk(const char* what, ll off, ll len, ll size) {
@@ -34,7 +36,7 @@ static ll cdiv(ll a, ll b) { return (a + b - 1) / b; }
 
 // ---- LDS-staged and register-streaming kernels: units = (64-channel block, group) dealt in runs ----------------
 static void check_stream(int MF, bool staged) {
-    const ll blocks = N / 64, total = blocks * G, nwg = split, upw = cdiv(total, nwg), nf_total = N / 16, m_tiles = cdiv(M, 16 * MF);
+    const ll blocks = N / 64, total = blocks * G, nwg = split, upw = stream_units_per_workgroup(M, N, G, 16 * MF, nwg), nf_total = N / 16, m_tiles = cdiv(M, 16 * MF);
     const ll kEl = MF * 256;                                   // int4 elements of a partial tile
     for (ll mt = 0; mt < m_tiles; ++mt) for (ll wg = 0; wg < nwg; ++wg) {
         const ll m0 = mt * 16 * MF;
@@ -189,7 +191,7 @@ static void check_mma() {
 int main(int argc, char** argv) {
     FILE* f = fopen(argv[1], "r");
     long checked = 0;
-    while (fscanf(f, "%lld %lld %lld %d %d %d %lld %lld", &M, &N, &K, &mode, &tile, &split, &ws_bytes, &counters_bytes) == 8) {
+    while (fscanf(f, "%lld %lld %lld %d %d %d %lld", &M, &N, &K, &mode, &tile, &split, &ws_bytes) == 7) {
         G = K / kGroup;
         n_codes = N * K / 2; n_meta = mode == 0 ? N * G * 2 : 0; n_scales = 2 * N; n_zeros = mode == 1 ? N : 0;
         n_qx = M * K; n_sx = (2 * M + 3) / 4 * 4; n_rs = 4 * M;       // (token scales are read in whole 4-byte words)
@@ -235,6 +237,10 @@ def _plans(api):
                         tile, split = api.query_gemm_config(M, N, K, mode)
                         ws = api.gemm_workspace_bytes(M, N, K, mode)
                         lines.append((M, N, K, mode, tile, split, ws))
+            # more blocks, fragments or tiles than there are counters
+            for M, N, K in {(0, 0): [(408, 623680, 128), (139, 3066752, 256)], (64, 5): [(4096, 65664, 256)], (16, 7): [(640, 131072, 256)],
+                            (69, 5): [(6000, 4096, 16384)], (71, 3): [(9000, 8192, 5120)], (129, 2): [(33000, 65536, 256)]}.get(cfg, ()):
+                lines.append((M, N, K, 1, *api.query_gemm_config(M, N, K, 1), api.gemm_workspace_bytes(M, N, K, 1)))
         finally:
             api.set_gemm_config(0, 0)
     return lines
@@ -247,7 +253,6 @@ def test_every_launch_plan_stays_inside_its_buffers(tmp_path):
     L = api.lib()
     plans = _plans(api)
     assert len(plans) > 1500
-    # the counters sit at the start of the workspace: their size is what separates them from the partial tiles
     src = tmp_path / "bounds.cpp"
     src.write_text(CHECKER)
     exe = tmp_path / "bounds"
@@ -255,25 +260,10 @@ def test_every_launch_plan_stays_inside_its_buffers(tmp_path):
     listing = tmp_path / "plans.txt"
     with open(listing, "w") as f:
         for M, N, K, mode, tile, split, ws in plans:
-            f.write("%d %d %d %d %d %d %d %d\n" % (M, N, K, mode, tile, split, ws, _counter_bytes(M, N, K, tile, split, ws)))
+            f.write("%d %d %d %d %d %d %d\n" % (M, N, K, mode, tile, split, ws))
     out = subprocess.run([str(exe), str(listing)], capture_output=True, text=True)
     assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout[-2000:]
     assert int(out.stdout.split()[1]) == len(plans)
-
-
-def _counter_bytes(M, N, K, tile, split, ws):
-    """Size of the counter area at the start of the workspace (256-byte aligned), as the header states the layout."""
-    if ws == 0:
-        return 0
-    al = lambda v: (v + 255) // 256 * 256
-    if tile <= 64:
-        return al(-(-M // tile) * (N // 64) * 4)
-    if 69 <= tile <= 71:
-        t = {69: 16, 70: 32, 71: 64}[tile]
-        return al(-(-M // t) * (N // 16) * 4)
-    tm = 128 if tile in (129, 132) else 256
-    tn = 128 if tile == 130 else 192 if tile == 131 else 256
-    return al(-(-M // tm) * -(-N // tn) * 4)
 
 
 def test_the_checker_catches_a_planted_overrun(tmp_path):
@@ -285,7 +275,7 @@ def test_the_checker_catches_a_planted_overrun(tmp_path):
     exe = tmp_path / "bounds"
     subprocess.check_call(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2405_04532_amd", "csrc"), str(src), "-o", str(exe)])
     listing = tmp_path / "plans.txt"
-    listing.write_text("64 256 1152 0 64 8 0 0\n")          # nine groups: the last iteration of a block has one unit
+    listing.write_text("64 256 1152 0 64 8 0\n")          # nine groups: the last iteration of a block has one unit
     out = subprocess.run([str(exe), str(listing)], capture_output=True, text=True)
     assert out.returncode == 1 and "outside" in out.stdout
 
