@@ -354,7 +354,8 @@ __device__ __forceinline__ void hadamard_segment(T (&v)[CH][8], T* buf, int64_t 
 // An FP16 number is a whole multiple of 2^-24, so where the magnitudes of a segment add up to less than 128 every partial sum
 // fits 32-bit integers in that unit and the butterflies are integer additions: a quarter of the issue time of FP64 ones and half of
 // the LDS traffic, the same exact sums.  Weight rows are like that (4096 values of standard deviation 0.02 add up to 65);
-// other segments, infinities and NaN among them, and blocks of less than eight or of 8192 take FP64.  22016 x 4096: a single workgroup per
+// other segments, infinities and NaN among them, and blocks of less than eight or of 8192 take FP64, and so do segments with a -0
+// in them: whole numbers have one zero, while FP64 sums of FP16 numbers are -0 only where a -0 went in (-0 - (x - x) = -0).  22016 x 4096: a single workgroup per
 // block with one LDS round trip and one barrier per stage, bound by LDS and barriers, took 863 us, these layouts in FP64 111 us
 // (bound by vector issue), in whole numbers 93 us (a copy of the tensor 67; conversions, butterflies and LDS each about half of that).
 template <int CH>
@@ -380,15 +381,18 @@ __global__ __launch_bounds__(256) void hadamard_kernel(const uint4* __restrict__
         for (int e = 0; e < 8; ++e) x[c][e] = __half2float(__ushort_as_half((unsigned short)(w[e >> 1] >> (16 * (e & 1)))));
     }
     if constexpr (CH == 2) {                             // (8192 weights of the usual size add up to more than 128)
+        typedef short s2 __attribute__((ext_vector_type(2)));
         float sum = n < 8 ? __builtin_inff() : 0.f;
+        s2 lowest = {0, 0};                              // of the bits as 16-bit integers, among which those of -0 are the lowest
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            float chunk = 0.f;
+            const uint32_t w[4] = {raw[c].x, raw[c].y, raw[c].z, raw[c].w};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) chunk += fabsf(x[c][e]);
-            // zeros with a sign among them: the first element of a block of nothing but -0 is -0 in FP64
-            sum += chunk == 0.f && (raw[c].x | raw[c].y | raw[c].z | raw[c].w) ? __builtin_inff() : chunk;
+            for (int i = 0; i < 4; ++i) lowest = __builtin_elementwise_min(lowest, __builtin_bit_cast(s2, w[i]));
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sum += fabsf(x[c][e]);
         }
+        if (min(lowest.x, lowest.y) == -32768) sum = __builtin_inff();
         sum = wave_sum_of(sum);
         if ((t & 63) == 0) s_sum[t >> 6] = sum;
         __syncthreads();

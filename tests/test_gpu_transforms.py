@@ -154,28 +154,59 @@ def test_hadamard_segment_edges_bit_exact(rows, K, block):
     assert np.array_equal(_bits(api.hadamard_rotate(odd, block, out=odd).cpu().numpy()), _bits(ref))
 
 
+def _butterflies(x, block):
+    """The rotation in FP64 with the stages in the order in which the segment kernel takes them, which sign of a zero can depend on."""
+    v = x.cpu().numpy().astype(np.float64).reshape(-1, block)
+    with np.errstate(invalid="ignore"):                          # infinities
+        for h in (1, 2, 4, 2048, 4096) + tuple(8 << i for i in range(8)):
+            if h < block:
+                p = v.reshape(-1, block // (2 * h), 2, h)
+                v = np.stack([p[:, :, 0] + p[:, :, 1], p[:, :, 0] - p[:, :, 1]], axis=2).reshape(-1, block)
+        return (v * (1.0 / math.sqrt(block))).reshape(x.shape).astype(np.float16)
+
+
+@pytest.mark.parametrize("signed_zeros", [False, True])
 @pytest.mark.parametrize("rows,K,block", [(3, 4096, 4096), (2, 8192, 8192), (9, 2048, 2048), (5, 4096, 512), (3, 4104, 8), (3, 4096, 4)])
-def test_hadamard_small_magnitudes_bit_exact(rows, K, block):
+def test_hadamard_small_magnitudes_bit_exact(rows, K, block, signed_zeros):
     """Rows whose magnitudes add up to just less and just more than 128 (whole numbers, FP64), with subnormals, blocks of zeros
-    of both signs, an infinity and a NaN in the last row; against FP64."""
+    (of both signs: FP64), an infinity and a NaN in the last row; against FP64, zeros with their signs."""
     g = torch.Generator(device=DEV).manual_seed(K + block)
     x = torch.randn(rows, K, generator=g, device=DEV)
     seg = 4096 if block <= 4096 else 8192
     x = x * (torch.tensor([127.0, 127.95, 129.0] * rows, device=DEV)[:rows, None] / (seg * (2 / math.pi) ** 0.5))
     x = x.half()
     x[0, ::7] *= 2.0 ** -12                                      # subnormals
-    x[0, :8] = -0.0                                              # a chunk of nothing but -0
+    x = torch.where(x == 0, torch.zeros_like(x), x)              # (subnormals rounded to -0)
+    x[0, :8] = -0.0 if signed_zeros else 0.0                     # a chunk of nothing but -0
     if rows > 1:
         x[1, block // 2:block] = 0.0
-        x[1, :block // 2] = -0.0
+        x[1, :block // 2] = -0.0 if signed_zeros else 0.0
     x[-1, -1], x[-1, -2] = float("inf"), float("nan")
-    ref = tr.rotate_fp16(x.cpu().numpy(), block)
+    ref = _butterflies(x, block)
     got = api.hadamard_rotate(x, block).cpu().numpy()
     nan = np.isnan(ref)
     assert np.array_equal(np.isnan(got), nan)
-    assert np.array_equal(_bits(got + np.float16(0))[~nan], _bits(ref + np.float16(0))[~nan])     # (-0 + 0 = 0)
-    if block == 8:                                               # a sum of nothing but -0, and differences of such
+    assert np.array_equal(_bits(got)[~nan], _bits(ref)[~nan])
+    if block == 8 and signed_zeros:                              # a sum of nothing but -0, and differences of such
         assert _bits(got)[0, :8].tolist() == [0x8000] + 7 * [0]
+
+
+@pytest.mark.parametrize("block,others", [(8, 0.01), (8, 1000.0), (512, 0.01), (4096, 0.01)])
+def test_hadamard_signs_of_zero(block, others):
+    """Blocks of zeros of both signs and pairs that cancel give the zeros of FP64 sums, whatever the sum of the other magnitudes in
+    their segment."""
+    x = torch.full((4, 8192), others, dtype=torch.float16, device=DEV)
+    pos, neg, v = torch.tensor([0.0, -0.0, 0.01], dtype=torch.float16, device=DEV)
+    for at, eight in ((0, (neg, neg, v, -v, pos, pos, pos, pos)), (8, (neg, pos, v, v, pos, pos, pos, pos)),
+                      (4096, (neg,) * 8), (4104, (neg, pos) * 4), (4112, (pos,) * 8)):     # two segments
+        x[:2, at:at + 8] = torch.stack(eight)
+    if block > 8:                                                # the whole block cancels
+        x[2, :block] = 0.0
+        x[2, :4] = torch.stack((neg, neg, v, -v))
+        x[3, 4096:4096 + block] = -0.0
+    got = _bits(api.hadamard_rotate(x, block).cpu().numpy())
+    ref = _bits(_butterflies(x, block))
+    assert (ref == 0x8000).any() and np.array_equal(got, ref)
 
 
 def test_rotated_layer_matches_the_oracle_and_the_unrotated_product():
