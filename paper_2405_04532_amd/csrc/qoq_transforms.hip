@@ -24,9 +24,9 @@ namespace {
 // its rows in flight together, maxima of FP16 pairs, the eight row groups meet in LDS and one of them goes on;
 // non-negative floats order like their bit patterns, so the slabs of rows meet with an integer atomic maximum on a
 // zero-filled array; a slab alone stores its maxima, and nothing is filled (1 x 14336: 3.2 us instead of 4.9).  Bound by HBM latency and bandwidth: 1024 x 14336 (29 MB) in 7.8 us (by columns, below, 4.6);
-// with one thread per 8 channels // and 64 rows one after the other, 112 workgroups in all, it was 33 us.
+// with one thread per 8 channels and 64 rows one after the other, 112 workgroups in all, it was 33 us.
 constexpr int kAbsmaxRows = 128;
-__global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* __restrict__ x, int64_t M, int chunks, int* __restrict__ out_bits)
+__global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* __restrict__ x, int64_t M, int chunks, int* __restrict__ out_bits, bool alone)
 {
     __shared__ uint4 s_max[8][32];
     const int cl = threadIdx.x & 31, q = threadIdx.x >> 5;
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* __rest
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int bits = __float_as_int(__half2float(__ushort_as_half((unsigned short)(w[j >> 1] >> (16 * (j & 1))))));
-        if (gridDim.y == 1) out_bits[(int64_t)c * 8 + j] = bits;
+        if (alone) out_bits[(int64_t)c * 8 + j] = bits;
         else atomicMax(out_bits + (int64_t)c * 8 + j, bits);
     }
 }
@@ -455,7 +455,7 @@ hipError_t launch_channel_absmax(const void* x, int64_t M, int64_t K, float* abs
     for (int64_t m0 = 0; m0 < M; m0 += (int64_t)65535 * kAbsmaxRows) {       // at most 65535 slabs in a launch
         const int64_t rows = std::min<int64_t>(M - m0, (int64_t)65535 * kAbsmaxRows);
         const dim3 grid((unsigned)((chunks + 31) / 32), (unsigned)((rows + kAbsmaxRows - 1) / kAbsmaxRows));
-        channel_absmax_kernel<<<grid, 256, 0, s>>>(static_cast<const uint4*>(x) + m0 * chunks, rows, (int)chunks, reinterpret_cast<int*>(absmax));
+        channel_absmax_kernel<<<grid, 256, 0, s>>>(static_cast<const uint4*>(x) + m0 * chunks, rows, (int)chunks, reinterpret_cast<int*>(absmax), M <= kAbsmaxRows);
     }
     return hipGetLastError();
 }

@@ -93,6 +93,16 @@ def test_salience_in_one_pass_over_the_rows(M, K):
     assert torch.equal(out, torch.nan_to_num(x.float(), nan=0.0, posinf=math.inf, neginf=-math.inf).abs().amax(0))
 
 
+@pytest.mark.parametrize("M", [65535 * 128, 65535 * 128 + 1, 65535 * 128 + 128, 65535 * 128 + 129])
+def test_salience_of_more_rows_than_a_launch_takes(M):
+    """The last launch has no rows, one row, one slab and two slabs of its own: it adds to the maxima of the one before."""
+    x = torch.zeros(M, 8, dtype=torch.float16, device=DEV)
+    x[0, 0], x[M // 2, 1], x[M - 1, 2] = 3.0, -5.0, 7.0
+    out = torch.full((8,), -1.0, device=DEV)
+    assert api.lib().qoq_channel_absmax(x.data_ptr(), M, 8, out.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    assert out.tolist() == [3.0, 5.0, 7.0] + [0.0] * 5
+
+
 def test_gather_and_reordered_quantizer_bit_exact():
     M, K, N = 70, 2048, 192
     x = wl.make_activations(M, K, 61, DEV)
