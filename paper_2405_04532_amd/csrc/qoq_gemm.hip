@@ -1498,21 +1498,6 @@ void launch_mma(const GemmDev& p, bool fp16, hipStream_t s)
     else mma_kernel<GROUP, OUT_I32, CF, WM><<<grid, kMmaThreads, 0, s>>>(p);
 }
 
-// 16-token fragments of a token tile of the eight-wave kernels: equal tiles of three to nine.
-static int eight_wave_fragments(int64_t M)
-{
-    const int64_t frags = (M + 15) / 16, tiles = (frags + 8) / 9;
-    return (int)std::max<int64_t>(3, (frags + tiles - 1) / tiles);
-}
-
-// Channels of a tile of the eight-wave kernels: 128, or 256 where tiles of 128 (times the k-slices) need more than a round of
-// 256 workgroups.
-static int64_t eight_wave_width(int64_t M, int64_t N, int64_t S)
-{
-    const int64_t tm = 16 * eight_wave_fragments(M);
-    return ((M + tm - 1) / tm) * ((N + 127) / 128) * S <= 256 ? 128 : 256;
-}
-
 // tile_m selects the kernel and its shape: 16 / 32 / 64 = streaming kernel with that many tokens per tile;
 // 128 = compute-bound kernel, 256 tokens x 256 channels; 129 = 128 tokens x 256 channels; 131 = 256 x 192; 132 = 128 x 256,
 // two workgroups per compute unit; 130 = eight waves on up to 144 tokens x 128 or 256 channels.  The error of a launch is read, and thereby cleared,

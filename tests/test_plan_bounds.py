@@ -2,8 +2,8 @@
 the caller handed over -- checked on the host, for every kernel family, over a grid of shapes.
 
 A host model walks each launch the way its kernel does: the same partition of the work over workgroups (taken from
-the library's own qoq_query_gemm_config and qoq_gemm_workspace_bytes), the same iteration structure (csrc/qoq_walk.h,
-the header the kernels themselves include), the same clamps for rows past M, groups past the end of a run or slice,
+the library's own qoq_query_gemm_config and qoq_gemm_workspace_bytes), the same iteration structure and tiles (csrc/qoq_walk.h,
+qoq_workspace.h, the headers the library itself includes), the same clamps for rows past M, groups past the end of a run or slice,
 fragments past N, and the copies issued past the end of a run.  Each global address the model forms -- packed codes,
 level-2 metadata, channel scales and zeros, INT8 activations, token scales and sums, partial tiles and counters in the
 workspace -- is checked against the size of its buffer.  The counters of every plan lie in one area of the workspace and
@@ -24,6 +24,7 @@ CHECKER = r'''
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 using namespace qoq;
 typedef long long ll;
 static ll M, N, K, G, ws_bytes; static const ll counters_bytes = kCounterBytes; static int mode, tile, split;
@@ -110,37 +111,15 @@ static void check_lockstep(int NB, int MF) {
 }
 
 // ---- activation-stationary kernels ---------------------------------------------------------------------------------
-static void check_astat(int tl) {
-    const int MF = tl / 16, waves = 8, cap = waves * (tl == 64 ? 4 : 8);
-    ll S = cdiv(G, cap), gps = cdiv(G, S); S = cdiv(G, gps);
-    const ll nf_total = N / 16, nwg = split, base = nf_total / nwg, rem = nf_total - base * nwg, m_tiles = cdiv(M, tl), kEl = MF * 64;
-    const ll jeff = cdiv(gps, waves);
-    if (jeff * MF > 16) { fail = "astat capacity"; return; }
+// Weights, constants and partial tiles of a workgroup's fragments: `waves` waves of jeff groups each, kEl int4 per tile.
+static void check_fragments(ll nwg, ll waves, ll S, ll gps, ll m_tiles, ll kEl) {
+    const ll nf_total = N / 16, base = nf_total / nwg, rem = nf_total - base * nwg, jeff = cdiv(gps, waves);
     for (ll mt = 0; mt < m_tiles; ++mt) for (ll sl = 0; sl < S; ++sl) for (ll wg = 0; wg < nwg; ++wg) {
-        const ll m0 = mt * tl, f0 = wg * base + std::min(wg, rem), f1 = f0 + base + (wg < rem ? 1 : 0);
-        if (f0 >= f1) continue;
-        const ll g_lo = sl * gps, g_hi = std::min(G, g_lo + gps);
+        const ll f0 = wg * base + std::min(wg, rem), f1 = f0 + base + (wg < rem ? 1 : 0), g_lo = sl * gps, g_hi = std::min(G, g_lo + gps);
         if (g_lo >= g_hi) { fail = "astat empty slice"; return; }
-        if (wg == 0) {   // the activation preload does not depend on the workgroup's fragments
-            // compiled group capacity per wave: the smallest instantiation that holds jeff groups
-            const ll J = tl == 64 ? std::max<ll>(jeff, 2) : (jeff <= 4 ? 4 : 8);
-            const ll JP = J >= 8 ? 8 : 4, RP = std::min<ll>(128 / JP, MF * 16), row_passes = MF * 16 / RP, j_passes = cdiv(J, JP), dma = RP * JP / 8;
-            if (dma * 1024 > 16384) { fail = "astat staging"; return; }
-            for (int w = 0; w < waves; ++w) for (ll rp = 0; rp < row_passes; ++rp) for (ll jp = 0; jp < j_passes; ++jp) {
-                for (ll flat = 0; flat < dma * 64; ++flat) {
-                    const ll row_local = flat / (JP * 8), pos = flat % (JP * 8);
-                    const ll row = std::min(m0 + rp * RP + row_local, M - 1);
-                    const ll col = std::min((g_lo + w * jeff + jp * JP) * kGroup + ((pos ^ (row_local & 15)) * 16), K - 16);
-                    chk("qx", row * K + col, 16, n_qx);
-                }
-                for (ll mm = 0; mm < RP / 16; ++mm) for (ll jj = 0; jj < JP; ++jj) for (int lane = 0; lane < 64; ++lane) for (int ks = 0; ks < 2; ++ks) {
-                    const ll row_local = mm * 16 + (lane & 15), L = jj * 8 + ks * 4 + (lane >> 4);
-                    chk("staging", row_local * JP * 128 + ((L ^ (row_local & 15)) * 16), 16, dma * 1024);
-                }
-            }
-        }
+        if (S > 1 && f1 - f0 > 128) { fail = "astat fragments"; return; }
         for (ll nf = f0; nf < f1; ++nf) {
-            for (int w = 0; w < waves; ++w) for (ll j = 0; j < std::max<ll>(jeff, 1) + 3; ++j) {   // slots past jeff re-read the last group
+            for (int w = 0; w < waves; ++w) for (ll j = 0; j < jeff + 3; ++j) {   // slots past jeff re-read the last group
                 const ll g = std::min(g_lo + w * jeff + std::min(j, jeff - 1), g_hi - 1);
                 chk("codes", (nf * G + g) * 1024, 1024, n_codes);
                 if (mode == 0) chk("meta", (g * nf_total + nf) * 32, 32, n_meta);
@@ -154,10 +133,144 @@ static void check_astat(int tl) {
         }
     }
 }
+static void check_astat(int tl) {
+    const ll m_tiles = cdiv(M, tl);
+    if (tl == 64 && M <= 48 * m_tiles) tl = 48;               // as many tiles of 48 tokens
+    const bool deep = tl == 16 && G > 64 && G <= 112;          // sixteen waves of seven groups hold all of K
+    const ll MF = tl / 16, waves = deep ? 16 : 8, cap = deep ? 112 : tl >= 48 ? 32 : 64, stage = 128 * 1024 / waves;
+    ll S = cdiv(G, cap), gps = cdiv(G, S); S = cdiv(G, gps);
+    const ll jeff = cdiv(gps, waves), rows = tl == 16 && M <= 8 ? 8 : 16;
+    const ll J = deep ? (gps <= 96 ? 6 : 7) : tl >= 48 ? std::max<ll>(jeff, 2) : jeff <= 4 ? 4 : 8;   // groups per wave, as compiled
+    if (jeff > J || J * MF > 16) { fail = "astat capacity"; return; }
+    // the activation preload, the same for every workgroup of a token tile and slice
+    const ll JP = (J >= 8 && waves == 8) || (J > 4 && rows == 8) ? 8 : 4, RP = rows == 8 ? 8 : std::min<ll>(128 / JP, MF * 16);
+    const ll row_passes = rows == 8 ? 1 : cdiv(MF * 16, RP), j_passes = cdiv(J, JP), dma = RP * JP / 8;
+    if (dma * 1024 > stage || 2 * waves * MF * 1024 > 128 * 1024) { fail = "astat staging"; return; }
+    for (ll mt = 0; mt < m_tiles; ++mt) for (ll sl = 0; sl < S; ++sl) {
+        const ll m0 = mt * tl, g_lo = sl * gps, g_hi = std::min(G, g_lo + gps);
+        if (m0 >= M) { fail = "astat token tile"; return; }
+        for (int w = 0; w < waves; ++w) for (ll rp = 0; rp < row_passes; ++rp) for (ll jp = 0; jp < j_passes; ++jp) {
+            std::vector<char> copied(dma * 64);
+            for (ll i = 0; i < dma; ++i) {
+                if (rows == 16 && rp * RP + i * 8 / JP >= MF * 16) continue;   // 48 tokens: half of the second pass
+                for (ll flat = i * 64; flat < i * 64 + 64; ++flat) {
+                    const ll row_local = flat / (JP * 8), pos = flat % (JP * 8);
+                    const ll row = std::min(m0 + rp * RP + row_local, M - 1);
+                    const ll col = std::min((g_lo + w * jeff + jp * JP) * kGroup + ((pos ^ (row_local & 15)) * 16), K - 16);
+                    chk("qx", row * K + col, 16, n_qx);
+                    copied[flat] = 1;
+                }
+            }
+            for (ll mm = 0; mm < RP / rows; ++mm) for (ll jj = 0; jj < JP; ++jj) for (int lane = 0; lane < 64; ++lane) for (int ks = 0; ks < 2; ++ks) {
+                const ll j = jp * JP + jj;
+                if (j >= J || rp * (RP / rows) + mm >= MF || j >= jeff || g_lo + w * jeff + j >= g_hi) continue;
+                const ll row_local = mm * 16 + (lane & 15 & (rows - 1)), at = row_local * JP * 8 + ((jj * 8 + ks * 4 + (lane >> 4)) ^ (row_local & 15));
+                chk("staging", at * 16, 16, dma * 1024);
+                if (!fail && !copied[at]) { fail = "staging, not copied"; return; }
+            }
+        }
+    }
+    check_fragments(split, waves, S, gps, m_tiles, MF * 64);
+}
+// Few short tokens, quantized by every workgroup in front of its first fragment (512 threads).
+static void check_linear() {
+    ll rows = 1, log = 0;
+    while (rows < M) { rows *= 2; ++log; }
+    const ll per_row = 512 / rows, chunks = rows * K <= 2 * 8 * 512 ? 2 : 8;   // as compiled
+    if (M > 16 || rows * K > 32768 || G > 64) { fail = "linear capacity"; return; }
+    std::vector<char> made(M * K / 8);
+    for (ll t = 0; t < 512; ++t) for (ll i = 0; i < chunks; ++i) {
+        const ll row = t >> (9 - log), c = (t & (per_row - 1)) + i * per_row;
+        if (row >= M || c >= K / 8) continue;
+        chk("x", (row * (K / 8) + c) * 16, 16, M * K * 2);
+        chk("LDS codes", row * K + (((c >> 1) ^ (row & 7)) * 16) + (c & 1) * 8, 8, 32768);
+        chk("qx", (row * (K / 8) + c) * 8, 8, n_qx);
+        made[row * (K / 8) + c] = 1;
+    }
+    for (char m : made) if (!m) { fail = "linear, a chunk left out"; return; }
+    const ll jeff = cdiv(G, 8);
+    for (int w = 0; w < 8; ++w) for (ll j = 0; j < jeff && w * jeff + j < G; ++j) for (int lane = 0; lane < 64; ++lane) for (int ks = 0; ks < 2; ++ks) {
+        const ll row = std::min<ll>(lane & 15, M - 1);
+        chk("LDS codes", row * K + ((((w * jeff + j) * 8 + ks * 4 + (lane >> 4)) ^ (row & 7)) * 16), 16, M * K);
+    }
+    check_fragments(std::min<ll>(N / 16, 256), 8, 1, G, 1, 64);
+}
+
+// ---- eight waves on equal token tiles ------------------------------------------------------------------------------
+static int swizzle(int row) { return (row >> 1) & 7; }
+static void check_mma8() {
+    const ll MF = eight_wave_fragments(M), TM = 16 * MF, TN = eight_wave_width(M, N, split), WC = TN / 64, WK = 8 / WC, SG = WK / 2;
+    const ll kUnits = TN / 16, ABytes = SG * TM * 128, WBytes = SG * TN * 64, Slab = ABytes + WBytes + 512, EBytes = 2304;
+    const ll R = 4 * Slab + EBytes <= 160 * 1024 ? 4 : 3, ring = std::max(R * Slab, 16 * MF * 1024);
+    const ll n_tiles = cdiv(N, TN), m_tiles = cdiv(M, TM), tiles = n_tiles * m_tiles, S = split, gps = cdiv(G, S), nf_total = N / 16;
+    if (MF < 3 || MF > 9 || ring + EBytes > 160 * 1024 || cdiv(G, gps) != S) { fail = "mma8 shape"; return; }
+    // LDS, the same for all tiles: copies into a slab, reads of one, the exchange of the waves' sums
+    const ll kACopies = SG * TM / 8, kAMost = cdiv(kACopies, 8);
+    for (int wave = 0; wave < 8; ++wave) {
+        const ll kw = wave % WK, wc = wave / WK, sg = kw >> 1, half = kw & 1;
+        for (ll k = 0; k < kAMost; ++k) {
+            const ll i = std::min(k * 8 + wave, kACopies - 1);
+            chk("LDS activations", i / (TM / 8) * TM * 128 + i % (TM / 8) * 1024, 1024, ABytes);
+        }
+        for (int u = 0; u < 2; ++u) chk("LDS weights", ABytes + (wave * 2 + u) * 1024, 1024, ABytes + WBytes);
+        for (int lane = 0; lane < 64; ++lane) {
+            const int r16 = lane & 15, kb = lane >> 4;
+            for (ll tf = 0; tf < MF; ++tf)
+                chk("LDS activation operands", sg * TM * 128 + r16 * 128 + ((4 * half + kb) ^ swizzle(r16)) * 16 + tf * 2048, 16, (sg + 1) * TM * 128);
+            for (ll f = 0; f < 4; ++f) {
+                chk("LDS weight operands", ABytes + (sg * kUnits + wc * 4 + f) * 1024 + lane * 16 + half * 8, 8, ABytes + WBytes);
+                chk("LDS metadata", ABytes + WBytes + sg * 256 + wc * 128 + f * 32 + (r16 >> 1) * 4, 4, Slab);
+            }
+        }
+        ll lo = 0, hi = MF;
+        for (ll bit = WK / 2; bit >= 1; bit >>= 1) {
+            const ll mid = (lo + hi + 1) / 2, upper = 4 * (hi - mid) * 64, pair = (((wave >> 1) & ~(bit - 1)) | (wave & (bit - 1))) * 4 * MF * 64;
+            const ll give = wave & bit ? mid - lo : hi - mid, take = wave & bit ? hi - mid : mid - lo;
+            chk("LDS exchange", pair * 16, ((wave & bit ? upper : 0) + 4 * give * 64) * 16, ring);
+            chk("LDS exchange", pair * 16, ((wave & bit ? 0 : upper) + 4 * take * 64) * 16, ring);
+            if (4 * (give + take) > 4 * MF) { fail = "exchange area"; return; }
+            if (wave & bit) lo = mid; else hi = mid;
+        }
+    }
+    std::vector<char> seen(tiles);
+    for (ll b = 0; b < tiles; ++b) {
+        const ll xcd = b & 7, slot = b >> 3, q = tiles >> 3, r = tiles & 7, L = xcd * q + std::min(xcd, r) + slot;
+        const ll panel = L / (4 * n_tiles), rows = std::min<ll>(4, m_tiles - panel * 4), rem = L - panel * 4 * n_tiles;
+        const ll tni = rem / rows, tmi = panel * 4 + rem % rows, m_base = tmi * TM, n_base = tni * TN, nf_base = tni * kUnits;
+        if (tni >= n_tiles || tmi >= m_tiles || seen[tmi * n_tiles + tni]++) { fail = "tile order"; return; }
+        for (int d = 0; d < 256; ++d) {                        // epilogue constants: 256 of each, clamped
+            if (d < 128) chk("sx", m_base * 2 + std::min<ll>(d, (M - m_base - 1) >> 1) * 4, 4, n_sx);
+            if (d < 128) chk("scales", n_base * 2 + std::min<ll>(d, ((N - n_base) >> 1) - 1) * 4, 4, n_scales);
+            if (mode == 1) chk("rowsum", (m_base + std::min<ll>(d, M - m_base - 1)) * 4, 4, n_rs);
+            if (mode == 1 && d < 64) chk("zeros", n_base + std::min<ll>(d, ((N - n_base) >> 2) - 1) * 4, 4, n_zeros);
+        }
+        for (ll sl = 0; sl < S; ++sl) {
+            const ll g_first = sl * gps, Gs = std::min(G - g_first, gps), g_last = g_first + Gs - 1, T = cdiv(Gs, SG);
+            if (Gs < 1) { fail = "mma8 empty slice"; return; }
+            for (ll st = 0; st <= T; ++st) {                   // activations of stages 0 .. T-1, weights of 0 .. T (bundle T-1 holds those of T)
+                for (ll sg = 0; sg < SG; ++sg) {
+                    const ll g = std::min(g_first + st * SG + sg, g_last);
+                    if (st < T) for (ll rb = 0; rb < TM / 8; ++rb) for (int r8 = 0; r8 < 8; ++r8)
+                        chk("qx", std::min(m_base + rb * 8 + r8, M - 1) * K + g * kGroup, 128, n_qx);
+                    for (ll u = 0; u < kUnits; ++u) {
+                        const ll nf = std::min(nf_base + u, nf_total - 1);
+                        chk("codes", nf * G * 1024 + g * 1024, 1024, n_codes);
+                        if (mode == 0) chk("meta", g * nf_total * 32 + nf * 32, 32, n_meta);
+                    }
+                }
+            }
+            if (S > 1) {
+                const ll NJ = 4 * cdiv(MF, WK);
+                chk("counter", (tmi * n_tiles + tni) * 4, 4, counters_bytes);
+                chk("parts", counters_bytes + ((tmi * n_tiles + tni) * S + sl) * NJ * 512 * 16, NJ * 512 * 16, ws_bytes);
+            }
+        }
+    }
+}
 
 // ---- compute-bound kernel -------------------------------------------------------------------------------------------
 static void check_mma() {
-    const ll tm = (tile == 129 || tile == 132) ? 128 : 256, tn = tile == 130 ? 128 : tile == 131 ? 192 : 256;
+    const ll tm = (tile == 129 || tile == 132) ? 128 : 256, tn = tile == 131 ? 192 : 256;
     const ll n_tiles = cdiv(N, tn), m_tiles = cdiv(M, tm), S = split, gps = cdiv(G, S), nf_total = N / 16;
     const ll kACopies = tm / 64, kUnits = tn / 16, kWCopies = kUnits / 4, tiles = n_tiles * m_tiles;
     if (cdiv(G, gps) != S) { fail = "mma slices"; return; }
@@ -196,13 +309,16 @@ int main(int argc, char** argv) {
         n_codes = N * K / 2; n_meta = mode == 0 ? N * G * 2 : 0; n_scales = 2 * N; n_zeros = mode == 1 ? N : 0;
         n_qx = M * K; n_sx = (2 * M + 3) / 4 * 4; n_rs = 4 * M;       // (token scales are read in whole 4-byte words)
         fail = nullptr;
-        if (tile == 64) check_stream(4, true);
+        const int wide = M <= 48 * cdiv(M, 64) ? 3 : 4;        // as many tiles of 48 tokens hold them all
+        if (tile == 0) check_linear();
+        else if (tile == 64) check_stream(wide, true);
         else if (tile == 32 || tile == 16) check_stream(tile / 16, false);
-        else if (tile == 65) check_lockstep(2, 4);
-        else if (tile == 66) check_lockstep(4, 4);
+        else if (tile == 65) check_lockstep(2, wide);
+        else if (tile == 66) check_lockstep(4, wide);
         else if (tile == 67) check_lockstep(2, 2);
         else if (tile == 68) check_lockstep(2, 1);
         else if (tile >= 69 && tile <= 71) check_astat(tile == 71 ? 64 : tile == 70 ? 32 : 16);
+        else if (tile == 130) check_mma8();
         else check_mma();
         if (fail) {
             printf("M=%lld N=%lld K=%lld mode=%d tile=%d split=%d: %s access [%lld, +%lld) outside %lld bytes\n", M, N, K, mode, tile,
@@ -219,9 +335,9 @@ int main(int argc, char** argv) {
 
 def _plans(api):
     shapes = [(N, K) for N in (64, 192, 256, 4096, 12288, 22016, 57344) for K in (128, 1152, 4096, 11008, 28672)]
-    Ms = (1, 7, 16, 17, 32, 33, 63, 64, 65, 100, 128, 130, 200, 256, 300, 512, 1000, 1024, 4096)
-    forced = [(0, 0), (16, 0), (16, 7), (32, 0), (32, 9), (64, 0), (64, 5), (65, 0), (65, 3), (66, 0), (67, 0), (68, 2),
-              (69, 0), (69, 5), (70, 0), (71, 0), (71, 3), (128, 0), (128, 3), (129, 0), (129, 2), (130, 0), (131, 0), (131, 2),
+    Ms = (1, 7, 9, 16, 17, 32, 33, 48, 63, 64, 65, 96, 100, 128, 130, 200, 256, 300, 512, 1000, 1024, 4096)
+    forced = [(0, 0), (16, 0), (16, 7), (32, 0), (32, 9), (64, 0), (64, 5), (65, 0), (65, 3), (66, 0), (66, 2), (67, 0), (68, 2),
+              (69, 0), (69, 5), (70, 0), (71, 0), (71, 3), (128, 0), (128, 3), (129, 0), (129, 2), (130, 0), (130, 2), (130, 5), (131, 0), (131, 2),
               (132, 0)]
     lines = []
     for cfg in forced:
@@ -231,7 +347,7 @@ def _plans(api):
                 if cfg != (0, 0) and (N, K) not in ((192, 1152), (256, 128), (4096, 4096), (4096, 11008), (22016, 4096), (12288, 1152)):
                     continue                                   # forced configurations: a smaller set of shapes
                 for M in Ms:
-                    if cfg != (0, 0) and M not in (1, 17, 64, 100, 300, 1024):
+                    if cfg != (0, 0) and M not in (1, 9, 17, 48, 64, 96, 100, 300, 1024):
                         continue
                     for mode in (0, 1):
                         tile, split = api.query_gemm_config(M, N, K, mode)
@@ -243,6 +359,10 @@ def _plans(api):
                 lines.append((M, N, K, 1, *api.query_gemm_config(M, N, K, 1), api.gemm_workspace_bytes(M, N, K, 1)))
         finally:
             api.set_gemm_config(0, 0)
+    for M in range(1, 17):                                     # one launch: tile code 0 of the checker
+        rows = 1 << (M - 1).bit_length()
+        for K in (128, 256, 1152, 8192 // rows, 16384 // rows, 32768 // rows):
+            lines += [(M, N, K, mode, 0, 0, 0) for N in (64, 320, 5120) for mode in (0, 1) if rows * K <= 32768 and K <= 8192 and K % 128 == 0]
     return lines
 
 
@@ -259,25 +379,37 @@ def test_every_launch_plan_stays_inside_its_buffers(tmp_path):
     subprocess.check_call(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2405_04532_amd", "csrc"), str(src), "-o", str(exe)])
     listing = tmp_path / "plans.txt"
     with open(listing, "w") as f:
-        for M, N, K, mode, tile, split, ws in plans:
-            f.write("%d %d %d %d %d %d %d\n" % (M, N, K, mode, tile, split, ws))
+        for plan in plans:
+            f.write("%d %d %d %d %d %d %d\n" % plan)
     out = subprocess.run([str(exe), str(listing)], capture_output=True, text=True)
     assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout[-2000:]
     assert int(out.stdout.split()[1]) == len(plans)
 
 
-def test_the_checker_catches_a_planted_overrun(tmp_path):
-    """The mistake that once faulted on the GPU, planted in the host model's input: a run that is allowed to reach
-    group G (one past the last) of the last token row must be reported."""
-    src = tmp_path / "bounds.cpp"
-    src.write_text(CHECKER.replace("const ll gsel = std::min<ll>(o.g + (e < o.n ? e : 0), G - 1);",
-                                   "const ll gsel = o.g + e;"))
-    exe = tmp_path / "bounds"
-    subprocess.check_call(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2405_04532_amd", "csrc"), str(src), "-o", str(exe)])
+@pytest.mark.parametrize("right,wrong,plan", [
+    # a run that is allowed to reach group G (one past the last) of the last token row: nine groups, the last iteration has one unit
+    ("const ll gsel = std::min<ll>(o.g + (e < o.n ? e : 0), G - 1);", "const ll gsel = o.g + e;", "64 256 1152 0 64 4 0"),
+    # eight waves: a stage of two groups whose second lies past the slice; a token row past M
+    ("const ll g = std::min(g_first + st * SG + sg, g_last);", "const ll g = g_first + st * SG + sg;", "100 320 1152 0 130 1 0"),
+    ("chk(\"qx\", std::min(m_base + rb * 8 + r8, M - 1)", "chk(\"qx\", (m_base + rb * 8 + r8)", "100 320 1152 0 130 1 0"),
+    # sixteen waves: the last waves' groups past the end of the row
+    ("const ll col = std::min((g_lo + w * jeff + jp * JP) * kGroup + ((pos ^ (row_local & 15)) * 16), K - 16);",
+     "const ll col = (g_lo + w * jeff + jp * JP) * kGroup + ((pos ^ (row_local & 15)) * 16);", "16 64 12416 0 69 4 0"),
+    # 48 tokens: the second pass read in full
+    ("if (rows == 16 && rp * RP + i * 8 / JP >= MF * 16) continue;", "if (rp * RP + i * 8 / JP >= 32) continue;", "48 64 2048 0 71 4 0"),
+    # tokens of one launch: a row that takes more chunks than its threads hold
+    ("rows * K <= 2 * 8 * 512 ? 2 : 8", "2", "16 64 2048 0 0 0 0")])
+def test_the_checker_catches_a_planted_overrun(tmp_path, right, wrong, plan):
+    """Mistakes planted in the host model, the first of which once faulted on the GPU, must be reported."""
+    assert CHECKER.count(right) == 1
     listing = tmp_path / "plans.txt"
-    listing.write_text("64 256 1152 0 64 8 0\n")          # nine groups: the last iteration of a block has one unit
-    out = subprocess.run([str(exe), str(listing)], capture_output=True, text=True)
-    assert out.returncode == 1 and "outside" in out.stdout
+    listing.write_text(plan + "\n")
+    for source, status in ((CHECKER, 0), (CHECKER.replace(right, wrong), 1)):
+        src, exe = tmp_path / "bounds.cpp", tmp_path / "bounds"
+        src.write_text(source)
+        subprocess.check_call(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2405_04532_amd", "csrc"), str(src), "-o", str(exe)])
+        out = subprocess.run([str(exe), str(listing)], capture_output=True, text=True)
+        assert out.returncode == status and ("outside" in out.stdout or "left out" in out.stdout) == bool(status), out.stdout
 
 
 @pytest.mark.parametrize("M,N,K,mode,tile,nwg", [(130, 12288, 4096, 0, 71, 80), (65, 10240, 8192, 0, 70, 80), (100, 10240, 8192, 1, 70, 64),
