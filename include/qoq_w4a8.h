@@ -54,7 +54,7 @@ const char* qoq_status_string(int status);
 /* Size in bytes of the packed-weight blob for an [N, K] layer; 0 if the shape is unsupported. */
 size_t qoq_packed_bytes(int64_t N, int64_t K, int mode);
 
-/* Bytes of workspace qoq_w4a8_gemm / qoq_w4a8_gemm_i32 need for this problem (may be 0;
+/* Bytes of workspace for qoq_w4a8_gemm / qoq_w4a8_gemm_i32 with this problem: what the call needs or more (may be 0;
  * always a multiple of 16).  Used for split-k: a fixed area of arrival counters (256 KiB), then partial tiles. */
 size_t qoq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int mode);
 
@@ -124,10 +124,9 @@ int qoq_w4a8_gemm(const int8_t* qx, const void* sx_fp16, const int32_t* rowsum,
  * caller's workspace: 16 MiB of partial tiles and 256 KiB of counters per GPU, held by every GPU the library runs on
  * until the process ends.  The call allocates and frees nothing (the first call on a device looks up the array's
  * address on that device, which allocates nothing either; make that first call before a capture begins).
- *   - Where the fastest launch configuration needs more scratch than that, one of 65 to 512 tokens that needs none is
- *     taken if K is short enough for it (K <= 8192); else the call returns QOQ_ERR_WORKSPACE and enqueues
- *     nothing (use qoq_w4a8_gemm with a workspace; qoq_gemm_workspace_bytes tells the size: up to 16 MiB + the
- *     counters fit).
+ *   - Where the fastest launch configuration needs more scratch than that, the fastest without eight-wave kernels is
+ *     taken; where that does too, one of 65 to 512 tokens that needs none if K is short enough for it (K <= 8192); else the
+ *     call returns QOQ_ERR_WORKSPACE and enqueues nothing (use qoq_w4a8_gemm with a workspace of qoq_gemm_workspace_bytes).
  *   - Every call on a GPU shares that GPU's array: calls that overlap in time on one GPU (two streams, two threads)
  *     race on it; order them on one stream.  The array keeps the last call's partial tiles; its counters are left
  *     at zero by every call, which is all the next call relies on.

@@ -79,8 +79,7 @@ int gemm_common(const int8_t* qx, const void* sx, const int32_t* rowsum, const v
     qoq::pick_gemm_config(M, N, K, mode, tuning, tile_m, split_k);
     const auto scratch_holds = [&] { return qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k) <= kScratchBytes; };
     // Where the fastest plan exchanges more than there is room for, the fastest without the eight-wave kernels and without 48-token
-    // tiles in place of 32-token ones; in the static
-    // scratch then one that exchanges nothing, if there is one.
+    // tiles in place of 32-token ones; in the static scratch then one that exchanges nothing, if there is one.
     const auto room = [&] { return static_scratch ? scratch_holds() : (ws && ws_bytes >= qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k)); };
     if (tuning.tile_m == 0 && qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k) && !room())
         qoq::pick_gemm_config(M, N, K, mode, tuning, tile_m, split_k, false);
@@ -152,7 +151,9 @@ size_t qoq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int mode)
     int tile_m, split_k;
     qoq::pick_gemm_config(M, N, K, mode, forced(), tile_m, split_k);
     const size_t need = qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k);
-    // never less than a shape needs without the eight-wave kernels: a size that a program has stored stays what it was, or grows
+    // Never less than the shape needs without the eight-wave kernels, even where those exchange nothing: a program that sizes its
+    // workspace for its largest batch then has what smaller batches cut into slices take (182 tokens x 11008 x 15232 per channel exchange
+    // nothing, 137 take 23 MB; with the plan's own need one call in 300 of such a program would be refused).
     qoq::pick_gemm_config(M, N, K, mode, forced(), tile_m, split_k, false);
     const size_t without = qoq::gemm_workspace_bytes(M, N, K, tile_m, split_k);
     return need > without ? need : without;

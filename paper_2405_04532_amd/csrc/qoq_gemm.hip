@@ -1699,14 +1699,12 @@ static StreamPlan pair_plan(int64_t M, int64_t N, int64_t G, int64_t forced_nwg,
 static int astat_tile(int tile_m) { return tile_m == 71 ? 64 : tile_m == 70 ? 32 : 16; }
 static void astat_slices(int64_t G, int tile_m, int64_t& S, int64_t& gps)
 {
-    const int64_t cap = astat_max_groups(astat_tile(tile_m));
+    // sixteen tokens and K up to 14336: sixteen waves hold all of K
+    const int64_t cap = tile_m == 69 && G <= astat_deep_groups() ? astat_deep_groups() : astat_max_groups(astat_tile(tile_m));
     S = (G + cap - 1) / cap;
     gps = (G + S - 1) / S;
     S = (G + gps - 1) / gps;
 }
-// Sixteen tokens and K up to 14336: sixteen waves hold all of K.  (The workspace keeps its size for two slices: a plan's need does
-// not tell how it is met.)
-static bool astat_deep(int64_t G, int tile_m) { return tile_m == 69 && G > astat_max_groups(16) && G <= astat_deep_groups(); }
 // Fragments whose k-slices meet in the workspace.
 static int64_t astat_counters(int64_t M, int64_t N, int64_t G, int tile_m)
 {
@@ -1720,7 +1718,6 @@ static int64_t astat_nwg(int64_t M, int64_t N, int64_t G, int tile_m, int64_t fo
     const int64_t tile = astat_tile(tile_m), m_tiles = (M + tile - 1) / tile, frags = N / 16;
     int64_t S, gps;
     astat_slices(G, tile_m, S, gps);
-    if (astat_deep(G, tile_m)) S = 1;
     int64_t nwg = forced_nwg > 0 ? forced_nwg : std::max<int64_t>(1, 256 / (m_tiles * S));
     // Consecutive workgroups go to consecutive XCDs: with a multiple of eight per token tile the workgroups of one fragment
     // run sit on the same XCD in every tile and share its weights through that L2.  Taken where it costs at most 8% of the
@@ -2009,16 +2006,9 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int tile_m, int spl
     if (split_k <= 1) return 0;
     int64_t tm, tn;
     mma_tile_shape(M, N, tile_m, split_k, tm, tn);
-    const size_t tiles = (size_t)mma_tiles(M, N, tile_m, split_k);
-    size_t sums = tiles * (size_t)(tm * tn);
-    if (tile_m == 130) {
-        // each of the waves that share an output hands over its own fragments, rounded up; room for whole steps of 256 tokens,
-        // so that a program whose batches vary a little sizes its workspace once
-        const int64_t waves = tn == 256 ? 2 : 4;
-        sums = std::max<size_t>(tiles * (size_t)(16 * waves * ((eight_wave_fragments(M) + waves - 1) / waves) * tn),
-                                (size_t)((M + 255) / 256 * 256) * (size_t)((N + 127) / 128 * 128));
-    }
-    return kCounterBytes + sums * (size_t)split_k * sizeof(int32_t);
+    const int64_t waves = tn == 256 ? 2 : 4;          // of an eight-wave workgroup share an output; each hands over its own fragments, rounded up
+    if (tile_m == 130) tm = 16 * waves * ((tm / 16 + waves - 1) / waves);
+    return kCounterBytes + (size_t)mma_tiles(M, N, tile_m, split_k) * (size_t)(tm * tn) * (size_t)split_k * sizeof(int32_t);
 }
 
 static GemmDev device_args(const GemmArgs& a)
@@ -2061,7 +2051,6 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s)
     if (a.tile_m >= 69 && a.tile_m <= 71) {
         int64_t S, gps;
         astat_slices(L.G, a.tile_m, S, gps);
-        if (astat_deep(L.G, a.tile_m)) { S = 1; gps = L.G; }
         p.upw = 0;
         nwg = a.split_k;
         p.S = (int)S; p.gps = (int)gps;

@@ -30,7 +30,9 @@ typedef long long ll;
 static ll M, N, K, G, ws_bytes; static const ll counters_bytes = kCounterBytes; static int mode, tile, split;
 static ll n_codes, n_meta, n_scales, n_zeros, n_qx, n_sx, n_rs;
 static const char* fail = nullptr; static ll fail_off, fail_len, fail_size;
+static ll parts_end;                                                   // of the partial tiles that the plan touches
 static inline void chk(const char* what, ll off, ll len, ll size) {
+    if (what[0] == 'p') parts_end = std::max(parts_end, off + len);
     if (!fail && (off < 0 || off + len > size)) { fail = what; fail_off = off; fail_len = len; fail_size = size; }
 }
 static ll cdiv(ll a, ll b) { return (a + b - 1) / b; }
@@ -304,11 +306,13 @@ static void check_mma() {
 int main(int argc, char** argv) {
     FILE* f = fopen(argv[1], "r");
     long checked = 0;
-    while (fscanf(f, "%lld %lld %lld %d %d %d %lld", &M, &N, &K, &mode, &tile, &split, &ws_bytes) == 7) {
+    int forced;
+    while (fscanf(f, "%lld %lld %lld %d %d %d %lld %d", &M, &N, &K, &mode, &tile, &split, &ws_bytes, &forced) == 8) {
         G = K / kGroup;
         n_codes = N * K / 2; n_meta = mode == 0 ? N * G * 2 : 0; n_scales = 2 * N; n_zeros = mode == 1 ? N : 0;
         n_qx = M * K; n_sx = (2 * M + 3) / 4 * 4; n_rs = 4 * M;       // (token scales are read in whole 4-byte words)
         fail = nullptr;
+        parts_end = 0;
         const int wide = M <= 48 * cdiv(M, 64) ? 3 : 4;        // as many tiles of 48 tokens hold them all
         if (tile == 0) check_linear();
         else if (tile == 64) check_stream(wide, true);
@@ -320,6 +324,8 @@ int main(int argc, char** argv) {
         else if (tile >= 69 && tile <= 71) check_astat(tile == 71 ? 64 : tile == 70 ? 32 : 16);
         else if (tile == 130) check_mma8();
         else check_mma();
+        // the size of one plan, and not the larger of two: what it touches and no more
+        if (!fail && forced && tile >= 128 && parts_end != ws_bytes) { fail = "workspace"; fail_off = 0; fail_len = parts_end; fail_size = ws_bytes; }
         if (fail) {
             printf("M=%lld N=%lld K=%lld mode=%d tile=%d split=%d: %s access [%lld, +%lld) outside %lld bytes\n", M, N, K, mode, tile,
                    split, fail, fail_off, fail_len, fail_size);
@@ -352,17 +358,17 @@ def _plans(api):
                     for mode in (0, 1):
                         tile, split = api.query_gemm_config(M, N, K, mode)
                         ws = api.gemm_workspace_bytes(M, N, K, mode)
-                        lines.append((M, N, K, mode, tile, split, ws))
+                        lines.append((M, N, K, mode, tile, split, ws, int(cfg != (0, 0))))
             # more blocks, fragments or tiles than there are counters
             for M, N, K in {(0, 0): [(408, 623680, 128), (139, 3066752, 256)], (64, 5): [(4096, 65664, 256)], (16, 7): [(640, 131072, 256)],
                             (69, 5): [(6000, 4096, 16384)], (71, 3): [(9000, 8192, 5120)], (129, 2): [(33000, 65536, 256)]}.get(cfg, ()):
-                lines.append((M, N, K, 1, *api.query_gemm_config(M, N, K, 1), api.gemm_workspace_bytes(M, N, K, 1)))
+                lines.append((M, N, K, 1, *api.query_gemm_config(M, N, K, 1), api.gemm_workspace_bytes(M, N, K, 1), int(cfg != (0, 0))))
         finally:
             api.set_gemm_config(0, 0)
     for M in range(1, 17):                                     # one launch: tile code 0 of the checker
         rows = 1 << (M - 1).bit_length()
         for K in (128, 256, 1152, 8192 // rows, 16384 // rows, 32768 // rows):
-            lines += [(M, N, K, mode, 0, 0, 0) for N in (64, 320, 5120) for mode in (0, 1) if rows * K <= 32768 and K <= 8192 and K % 128 == 0]
+            lines += [(M, N, K, mode, 0, 0, 0, 0) for N in (64, 320, 5120) for mode in (0, 1) if rows * K <= 32768 and K <= 8192 and K % 128 == 0]
     return lines
 
 
@@ -380,7 +386,7 @@ def test_every_launch_plan_stays_inside_its_buffers(tmp_path):
     listing = tmp_path / "plans.txt"
     with open(listing, "w") as f:
         for plan in plans:
-            f.write("%d %d %d %d %d %d %d\n" % plan)
+            f.write("%d %d %d %d %d %d %d %d\n" % plan)
     out = subprocess.run([str(exe), str(listing)], capture_output=True, text=True)
     assert out.returncode == 0 and out.stdout.startswith("ok"), out.stdout[-2000:]
     assert int(out.stdout.split()[1]) == len(plans)
@@ -388,17 +394,19 @@ def test_every_launch_plan_stays_inside_its_buffers(tmp_path):
 
 @pytest.mark.parametrize("right,wrong,plan", [
     # a run that is allowed to reach group G (one past the last) of the last token row: nine groups, the last iteration has one unit
-    ("const ll gsel = std::min<ll>(o.g + (e < o.n ? e : 0), G - 1);", "const ll gsel = o.g + e;", "64 256 1152 0 64 4 0"),
+    ("const ll gsel = std::min<ll>(o.g + (e < o.n ? e : 0), G - 1);", "const ll gsel = o.g + e;", "64 256 1152 0 64 4 0 0"),
     # eight waves: a stage of two groups whose second lies past the slice; a token row past M
-    ("const ll g = std::min(g_first + st * SG + sg, g_last);", "const ll g = g_first + st * SG + sg;", "100 320 1152 0 130 1 0"),
-    ("chk(\"qx\", std::min(m_base + rb * 8 + r8, M - 1)", "chk(\"qx\", (m_base + rb * 8 + r8)", "100 320 1152 0 130 1 0"),
+    ("const ll g = std::min(g_first + st * SG + sg, g_last);", "const ll g = g_first + st * SG + sg;", "100 320 1152 0 130 1 0 1"),
+    ("chk(\"qx\", std::min(m_base + rb * 8 + r8, M - 1)", "chk(\"qx\", (m_base + rb * 8 + r8)", "100 320 1152 0 130 1 0 1"),
+    # their counters and sums in a workspace of another size
+    ("parts_end != ws_bytes", "parts_end != ws_bytes + 256", "96 128 640 0 130 2 393216 1"),
     # sixteen waves: the last waves' groups past the end of the row
     ("const ll col = std::min((g_lo + w * jeff + jp * JP) * kGroup + ((pos ^ (row_local & 15)) * 16), K - 16);",
-     "const ll col = (g_lo + w * jeff + jp * JP) * kGroup + ((pos ^ (row_local & 15)) * 16);", "16 64 12416 0 69 4 0"),
+     "const ll col = (g_lo + w * jeff + jp * JP) * kGroup + ((pos ^ (row_local & 15)) * 16);", "16 64 12416 0 69 4 0 1"),
     # 48 tokens: the second pass read in full
-    ("if (rows == 16 && rp * RP + i * 8 / JP >= MF * 16) continue;", "if (rp * RP + i * 8 / JP >= 32) continue;", "48 64 2048 0 71 4 0"),
+    ("if (rows == 16 && rp * RP + i * 8 / JP >= MF * 16) continue;", "if (rp * RP + i * 8 / JP >= 32) continue;", "48 64 2048 0 71 4 0 1"),
     # tokens of one launch: a row that takes more chunks than its threads hold
-    ("rows * K <= 2 * 8 * 512 ? 2 : 8", "2", "16 64 2048 0 0 0 0")])
+    ("rows * K <= 2 * 8 * 512 ? 2 : 8", "2", "16 64 2048 0 0 0 0 0")])
 def test_the_checker_catches_a_planted_overrun(tmp_path, right, wrong, plan):
     """Mistakes planted in the host model, the first of which once faulted on the GPU, must be reported."""
     assert CHECKER.count(right) == 1
@@ -420,3 +428,13 @@ def test_side_by_side_tiles_share_an_xcd(M, N, K, mode, tile, nwg):
     every token tile) and hold all of K, whatever K is; a small remainder behind a full round stays with the two-per-CU tile."""
     from paper_2405_04532_amd import api
     assert api.query_gemm_config(M, N, K, mode) == (tile, nwg)
+
+
+def test_workspaces_hold_what_their_kernels_exchange():
+    """110 tokens x 5120 x 12288: two k-slices of 96 tiles of 112 tokens x 128 channels, of which each of four waves hands over two
+    fragments of every 64 channels; one token of 11008: one workgroup holds all of K, and nothing is exchanged."""
+    from paper_2405_04532_amd import api
+    assert api.query_gemm_config(110, 12288, 5120) == (130, 2)
+    assert api.gemm_workspace_bytes(110, 12288, 5120) == (256 << 10) + 2 * 96 * (4 * 2 * 512 * 16)
+    for mode in (0, 1):
+        assert api.query_gemm_config(1, 4096, 11008, mode)[0] == 69 and api.gemm_workspace_bytes(1, 4096, 11008, mode) == 0

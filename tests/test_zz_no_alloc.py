@@ -69,8 +69,12 @@ def test_every_kernel_family(api, M, N, K, mode, cfg):
     assert _same_bits(got, want)
 
 
-def test_a_plan_without_partial_tiles_where_the_fastest_has_too_many(api):
-    M, N, K, mode = 97, 23936, 6528, 1
+@pytest.mark.parametrize("M,N,K,mode", [
+    (97, 23936, 6528, 1),          # the fastest plan exchanges nothing, the one a workspace has room for as well does
+    (67, 15872, 11136, 0),         # its sums just fit the array
+    (261, 4032, 4224, 0),          # they do not: the plan without the eight-wave kernels
+    (73, 20608, 6144, 0)])         # nor do that one's: tiles that exchange nothing
+def test_a_plan_without_partial_tiles_where_the_fastest_has_too_many(api, M, N, K, mode):
     assert api.gemm_workspace_bytes(M, N, K, mode) > (16 << 20) + (256 << 10)
     got, want = _both(api, M, N, K, mode, seed=91)
     assert _same_bits(got, want)
