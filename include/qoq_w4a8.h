@@ -62,7 +62,9 @@ size_t qoq_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int mode);
  * A workspace must be zero-filled ONCE after allocation, before its first GEMM call: the
  * GEMM relies on its arrival counters being zero on entry and leaves them zero on exit, so
  * later calls need no further preparation (and no memset appears on the hot path).  The counters of every call lie in
- * the same area whatever its shape, and no call's partial tiles do, so calls of any shapes may take turns. */
+ * the first QOQ_GEMM_COUNTER_BYTES whatever its shape, and no call's partial tiles do, so calls of any shapes may take
+ * turns, and only those bytes (or the whole of a smaller workspace) have to be zero. */
+#define QOQ_GEMM_COUNTER_BYTES 262144
 int qoq_gemm_workspace_prepare(void* workspace, size_t workspace_bytes, void* stream);
 
 /* Offline weight path (Section 4.1 Eq. 3-4, Section 5.2.1): quantize FP16 weights and store

@@ -21,6 +21,7 @@ QOQ_PER_CHANNEL = 1
 # qoq_status
 QOQ_OK, QOQ_ERR_NULL, QOQ_ERR_SHAPE, QOQ_ERR_ALIGN, QOQ_ERR_BLOB, QOQ_ERR_WORKSPACE, QOQ_ERR_ARCH, QOQ_ERR_HIP = range(8)
 GROUP = 128
+GEMM_COUNTER_BYTES = 256 << 10    # QOQ_GEMM_COUNTER_BYTES: the part of a workspace that has to be zero
 DEVICE_ORDER_MAX = 32768          # channels that qoq_channel_order sorts
 
 _lib = None
@@ -232,7 +233,8 @@ def new_workspace(nbytes, device):
 def _workspace(M, N, K, mode, device, workspace):
     need = gemm_workspace_bytes(M, N, K, mode)
     if workspace is None and need:
-        workspace = new_workspace(need, device)
+        workspace = torch.empty(need, dtype=torch.uint8, device=device)
+        _check(lib().qoq_gemm_workspace_prepare(_ptr(workspace), min(need, GEMM_COUNTER_BYTES), _stream(device)))
     return workspace, (workspace.numel() * workspace.element_size() if workspace is not None else 0)
 
 

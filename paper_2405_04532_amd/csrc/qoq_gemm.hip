@@ -1953,7 +1953,8 @@ static void pick_other_config(int64_t M, int64_t N, int64_t K, int mode, const G
     if (split_k > 1 && mma_tiles(M, N, tile_m, split_k) > kMaxCounters) split_k = 1;   // only where a split is forced
 }
 
-void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTuning& forced, int& tile_m, int& split_k, bool eight_waves)
+void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTuning& forced, int& tile_m, int& split_k, bool eight_waves,
+                      double before_slices)
 {
     double cost;
     pick_other_config(M, N, K, mode, forced, tile_m, split_k, cost);
@@ -1965,7 +1966,8 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
     // by less, 8% slower at worst), 15% for the smaller streaming tiles; 5% more for less than eight groups, where starts and
     // stores are all there is.  Of 500 shapes whose plan changes: 17% faster on average, 8 more than 2% slower, by 7% at most.
     int S = 1;
-    const double eight = eight_wave_cost(M, N, K / kGroup, mode, S);
+    double eight = eight_wave_cost(M, N, K / kGroup, mode, S);
+    if (S > 1) eight += before_slices;
     double ahead = 0.85;
     if (tile_m == 129) ahead = 1.0;
     else if (tile_m >= 64 && tile_m <= 66) ahead = S > 1 ? 0.93 : 1.0;

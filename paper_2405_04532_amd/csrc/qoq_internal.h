@@ -74,9 +74,9 @@ size_t kv4_decode_workspace_bytes(int64_t B, int64_t H, int64_t Hkv, int64_t S_m
 // Launch configuration the library picks for a problem (also sizes the workspace).
 struct GemmTuning { int tile_m, split_k; };  // 0 = let the heuristic decide
 // eight_waves = false: a plan without those kernels, whose k-slices take more workspace, and without 48-token tiles in place of
-// 32-token ones.
+// 32-token ones.  before_slices: microseconds that their k-slices cost the caller beside the launch.
 void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTuning& forced, int& tile_m, int& split_k,
-                      bool eight_waves = true);
+                      bool eight_waves = true, double before_slices = 0.0);
 bool pick_gemm_config_without_workspace(int64_t M, int64_t N, int64_t K, int mode, int& tile_m, int& split_k);
 
 }  // namespace qoq

@@ -5,12 +5,16 @@
 // Nothing is kept between calls.  The interpreter lock is released around the library call, as ctypes does.
 #include <Python.h>
 
+#include <algorithm>
+
+
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/qoq_w4a8.h"
+#include "qoq_workspace.h"
 
 namespace {
 
@@ -225,7 +229,8 @@ struct Ref {                                    // an owned reference that is dr
     explicit operator bool() const { return o != nullptr; }
 };
 
-// Workspace of a GEMM call: the caller's, or one of the size the problem needs, prepared on the stream.
+// Workspace of a GEMM call: the caller's, or one of what the call exchanges, its counters zeroed on the stream (zeroing all of it, as
+// a workspace that is kept is prepared, took 4 to 11 us more for 12 to 39 MB).
 struct Workspace {
     at::Tensor own;
     void* ptr = nullptr;
@@ -239,11 +244,11 @@ struct Workspace {
             bytes = (size_t)t->numel() * t->element_size();
             return true;
         }
-        bytes = qoq_gemm_workspace_bytes(M, N, K, (int)mode);
+        bytes = qoq::gemm_fresh_workspace_bytes(M, N, K, (int)mode);
         if (!bytes) return true;
         own = new_like(on, {(int64_t)bytes}, at::kByte);
         ptr = own.data_ptr();
-        return call([&] { return qoq_gemm_workspace_prepare(ptr, bytes, stream); });
+        return call([&] { return qoq_gemm_workspace_prepare(ptr, std::min(bytes, (size_t)QOQ_GEMM_COUNTER_BYTES), stream); });
     }
 };
 

@@ -21,6 +21,10 @@ inline int64_t stream_units_per_workgroup(int64_t M, int64_t N, int64_t G, int t
     return (upw + G - 1) / G * G;
 }
 
+// Workspace for a call that makes one of its own: what its plan exchanges.  0 as well where the plan without eight-wave
+// kernels exchanges nothing and is not further behind than zeroing the counters takes; without a workspace a call takes that one.
+size_t gemm_fresh_workspace_bytes(int64_t M, int64_t N, int64_t K, int mode);
+
 // 16-token fragments of a token tile of the eight-wave kernels (qoq_gemm_mma8.h): equal tiles of three to nine.
 inline int eight_wave_fragments(int64_t M)
 {

@@ -174,3 +174,45 @@ def test_calls_run_on_the_current_stream(name):
     side.synchronize()
     assert len(got) == len(want) and all(torch.equal(a, b) for a, b in zip(got, want))
     assert any(bool(t.view(torch.uint8).any()) for t in want)
+
+
+def _calls_without_a_workspace(m, n, k, mode):
+    """The GEMM entry points on zeros with every result given: whatever else is allocated is their own workspace."""
+    new = lambda dtype, *s: torch.zeros(s, dtype=dtype, device=DEV)
+    packed = new(torch.uint8, api.packed_bytes(n, k, mode))
+    x, qx, sx, rowsum, out = new(torch.float16, m, k), new(torch.int8, m, k), new(torch.float16, m), new(torch.int32, m), new(torch.float16, m, n)
+    calls = [lambda: api.w4a8_gemm(qx, sx, packed, n, mode, rowsum=rowsum, out=out),
+             lambda: api.w4a8_linear(x, packed, n, mode, out=out, qx=qx, sx=sx, rowsum=rowsum)]
+    return calls + ([lambda: api.w4a8_gemm_token_sum(qx, sx, new(torch.float32, m), packed, n, out=out)] if mode else [])
+
+
+@gpu
+@pytest.mark.parametrize("mode", [0, 1])
+def test_a_call_without_a_workspace_zeroes_the_counters_only(mode):
+    """Half of the places for partial tiles of this plan are not used: in a block that the allocator has had before they keep what they
+    held, while the counters are zeroed."""
+    m, n, k = 64, 4096, 11008
+    need = api.gemm_workspace_bytes(m, n, k, mode)
+    assert need > api.GEMM_COUNTER_BYTES == 256 << 10
+    for call in _calls_without_a_workspace(m, n, k, mode):
+        block = torch.full((need,), 0x5A, dtype=torch.uint8, device=DEV)
+        where = block.data_ptr()
+        del block
+        call()
+        block = torch.empty(need, dtype=torch.uint8, device=DEV)
+        assert block.data_ptr() == where
+        kept = (block[api.GEMM_COUNTER_BYTES:] == 0x5A).float().mean().item()
+        assert not block[:api.GEMM_COUNTER_BYTES].any() and 0.4 < kept < 0.6
+        del block
+
+
+@gpu
+@pytest.mark.parametrize("m,n,k,made", [(1024, 4096, 11008, False),       # uncut: nothing is exchanged, whatever a kept workspace is sized for
+                                        (65, 15616, 3840, False),         # cut it gains less than zeroing counters takes
+                                        (138, 15808, 8192, True), (389, 4096, 11008, True), (64, 4096, 4096, False)])
+def test_a_call_without_a_workspace_makes_one_where_that_pays(m, n, k, made):
+    for call in _calls_without_a_workspace(m, n, k, 0):
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        call()
+        assert (torch.cuda.max_memory_allocated() > before) == made
