@@ -1977,11 +1977,14 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
     if (K < 8 * kGroup) ahead -= 0.05;
     if (eight < ahead * cost - 0.3) { tile_m = 130; split_k = S; }
     // 65 ... 96 tokens and long rows: two 48-token tiles read the weights twice where three of 32 read them three times, on half as many
-    // k's per workgroup.  11008 x 4096 at 73 ... 92 tokens 19.0 -> 16.7 us, 14336 x 4096 per channel 20.5 -> 17.5, 13824 x 2432 18.2 -> 17.1 (25
-    // shapes of 2304 ... 4544 channels, none slower); with fewer channels or shorter rows the hand-over takes more than that (13696 x
-    // 1920 the same, x 1344 0.93 of the speed, x 384 0.76; 9728 x 4544 0.95).
+    // k's per workgroup.  11008 x 4096 at 73 ... 92 tokens 19.0 -> 16.7 us, 14336 x 4096 per channel 20.5 -> 17.5, 13824 x 2432 18.2 -> 17.1.
+    // With fewer channels or shorter rows the hand-over takes more than that (13696 x 1920 the same, x 1344 0.93 of the speed, x 384 0.76;
+    // 9728 x 4544 0.95).  Upwards a 32-token workgroup has one block whatever their number, up to 85, and a 48-token one more units
+    // with every block: 11008 x 5120 per channel 16.6 us on 32 tokens, 18.6 on 48, x 4608 0.92 of the speed, x 4352 0.98, x 4096 1.10; in
+    // groups x 5120 0.96, x 4608 0.96, x 4480 1.05.  Of 359 measured shapes that take it 1.07 of the speed on average, 11 below 0.98
+    // (10240 x 3840 per channel 0.95).
     const int64_t G = K / kGroup;
-    if (tile_m == 32 && M <= 96 && N >= 2304 && G >= 80) {
+    if (tile_m == 32 && M <= 96 && N >= 2304 && G >= 80 && N <= (mode ? 4096 + 6 * (G - 80) : 4480 + 8 * (G - 80))) {
         const int64_t units = (N / 64) * G, upw = stream_units_per_workgroup(M, N, G, 64, stream_plan(M, N, G, 64, 0).nwg);
         tile_m = 64;
         split_k = (int)((units + upw - 1) / upw);

@@ -430,6 +430,14 @@ def test_side_by_side_tiles_share_an_xcd(M, N, K, mode, tile, nwg):
     assert api.query_gemm_config(M, N, K, mode) == (tile, nwg)
 
 
+@pytest.mark.parametrize("M,N,K,mode,tile", [(80, 4096, 11008, 0, 64), (88, 4480, 11008, 0, 64), (96, 5120, 11008, 0, 32), (80, 4096, 11008, 1, 64),
+                                             (80, 4608, 11008, 1, 32), (65, 5120, 11008, 1, 32)])
+def test_tiles_of_48_tokens_in_place_of_32(M, N, K, mode, tile):
+    """Long rows: up to a width where the 32-token tiles, a block per workgroup, are as fast."""
+    from paper_2405_04532_amd import api
+    assert api.query_gemm_config(M, N, K, mode)[0] == tile
+
+
 def test_workspaces_hold_what_their_kernels_exchange():
     """110 tokens x 5120 x 12288: two k-slices of 96 tiles of 112 tokens x 128 channels, of which each of four waves hands over two
     fragments of every 64 channels; one token of 11008: one workgroup holds all of K, and nothing is exchanged."""
