@@ -1960,11 +1960,9 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
     pick_other_config(M, N, K, mode, forced, tile_m, split_k, cost);
     if (forced.tile_m || !eight_waves || M <= 64 || N * K >= ((int64_t)1 << 33)) return;
     // Taken where the estimate is ahead by a share of the other plan's that depends on how far off that one's estimate is: by
-    // nothing for the 64-token streaming, lockstep and 128 x 256 tiles (where the two are within 5% of each other the eight-wave
-    // kernels are 6 to 8% faster, the worst of 71 shapes 4% slower), 7% for the former two where K has to be cut, 5% for 64-token
-    // activation-stationary and 256 x 192 tiles, 10% for 32-token activation-stationary tiles, 12% for two-per-CU tiles (ahead
-    // by less, 8% slower at worst), 15% for the smaller streaming tiles; 5% more for less than eight groups, where starts and
-    // stores are all there is.  Of 500 shapes whose plan changes: 17% faster on average, 8 more than 2% slower, by 7% at most.
+    // nothing for the 64-token streaming, lockstep and 128 x 256 tiles, 7% for the former two where K has to be cut, 5% for 64-token
+    // activation-stationary and 256 x 192 tiles, 10% for 32-token activation-stationary tiles, 12% for two-per-CU tiles, 15% for
+    // the smaller streaming tiles; 5% more for less than eight groups, where starts and stores are all there is.
     int S = 1;
     double eight = eight_wave_cost(M, N, K / kGroup, mode, S);
     if (S > 1) eight += before_slices;
@@ -1975,6 +1973,10 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
     else if (tile_m == 70) ahead = 0.90;
     else if (tile_m == 132) ahead = 0.88;
     if (K < 8 * kGroup) ahead -= 0.05;
+    // One token tile and short rows in slices, against tiles that exchange nothing: below 26 groups 0.93 to 0.98 of their speed on
+    // average (2560 x 16384 at 130 tokens 18.3 us, 21.6 in slices); per channel against the activation-stationary tiles at any K that
+    // those hold (44 shapes of 3072 ... 4096: 0.92 on average, the best the same; 4096 x 16384 at 130 tokens 20.6 and 24.0).
+    if (S > 1 && M <= 144 && ((tile_m == 71 && mode) || ((tile_m == 65 || tile_m == 66 || tile_m == 71) && K < 26 * kGroup))) ahead = 0.0;
     if (eight < ahead * cost - 0.3) { tile_m = 130; split_k = S; }
     // 65 ... 96 tokens and long rows: two 48-token tiles read the weights twice where three of 32 read them three times, on half as many
     // k's per workgroup.  11008 x 4096 at 73 ... 92 tokens 19.0 -> 16.7 us, 14336 x 4096 per channel 20.5 -> 17.5, 13824 x 2432 18.2 -> 17.1.

@@ -438,6 +438,14 @@ def test_tiles_of_48_tokens_in_place_of_32(M, N, K, mode, tile):
     assert api.query_gemm_config(M, N, K, mode)[0] == tile
 
 
+@pytest.mark.parametrize("M,N,K,mode,tile", [(130, 16384, 4096, 1, 71), (144, 15872, 3584, 1, 71), (130, 16384, 2560, 0, 66), (65, 14336, 3072, 0, 71),
+                                             (130, 15872, 4096, 0, 130), (112, 13376, 7808, 0, 130)])
+def test_short_rows_are_not_cut(M, N, K, mode, tile):
+    """One token tile: the eight-wave kernel takes k-slices of short rows only where they are ahead of tiles that exchange nothing."""
+    from paper_2405_04532_amd import api
+    assert api.query_gemm_config(M, N, K, mode)[0] == tile
+
+
 def test_workspaces_hold_what_their_kernels_exchange():
     """110 tokens x 5120 x 12288: two k-slices of 96 tiles of 112 tokens x 128 channels, of which each of four waves hands over two
     fragments of every 64 channels; one token of 11008: one workgroup holds all of K, and nothing is exchanged."""
