@@ -23,8 +23,9 @@ namespace {
 // salience).  A workgroup takes 256 channels x 128 rows: thread (8-channel chunk c, row group q of 8) has the 16 loads of
 // its rows in flight together, maxima of FP16 pairs, the eight row groups meet in LDS and one of them goes on;
 // non-negative floats order like their bit patterns, so the slabs of rows meet with an integer atomic maximum on a
-// zero-filled array; a slab alone stores its maxima, and nothing is filled (1 x 14336: 3.2 us instead of 4.9).  Bound by HBM latency and bandwidth: 1024 x 14336 (29 MB) in 7.8 us (by columns, below, 4.6);
-// with one thread per 8 channels and 64 rows one after the other, 112 workgroups in all, it was 33 us.
+// zero-filled array; a slab alone stores its maxima, and nothing is filled (1 x 14336: 3.2 us instead of 4.9).  Bound by HBM
+// latency and bandwidth: 1025 x 14336 (29 MB) from memory 9.9 us with its fill (one row less by columns, below, 6.9); with one thread per
+// 8 channels and 64 rows one after the other, 112 workgroups in all, it was 33 us.
 constexpr int kAbsmaxRows = 128;
 __global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* __restrict__ x, int64_t M, int chunks, int* __restrict__ out_bits, bool alone)
 {
@@ -60,7 +61,7 @@ __global__ __launch_bounds__(256) void channel_absmax_kernel(const uint4* __rest
 
 // The same for up to 1024 rows in one pass, without a zero fill before it or atomics: a workgroup takes 64 channels (whole lines of
 // 128 bytes) x all rows, thread (8-channel chunk c, row group q of 128) has its up to eight loads in flight together.
-// 1024 x 14336 with its launches: 4.6 us, 7.8 in slabs; 129 x 4096 4.0 and 5.7.
+// From memory, with the fill where there is one: 1024 x 14336 6.9 us, 9.6 in slabs; 1024 x 28672 13.7 and 16.4; 129 x 4096 3.2 and 5.0.
 constexpr int kColumnRows = 1024;
 __global__ __launch_bounds__(1024) void channel_absmax_columns_kernel(const uint4* __restrict__ x, int M, int chunks, int* __restrict__ out_bits)
 {
