@@ -908,3 +908,29 @@ def test_token_counts_take_turns_in_one_workspace(api, mode, N, K, tokens):
         acc = torch.full((M, N), 0x5A5A5A5A, dtype=torch.int32, device=DEV)
         api.w4a8_gemm_i32(qx[:M], blob, N, mode, rowsum=rowsum[:M] if mode else None, out=acc, workspace=ws)
         assert (_np(acc).astype(np.int64) == ref[:M]).all(), M
+
+
+def test_captured_calls_in_one_workspace_and_without(api):
+    """Calls of three token counts that exchange sums, in one workspace and with workspaces of their own, captured and replayed with
+    eager calls in that workspace between: every replay as the eager result."""
+    N, K, tokens = 4096, 11008, (160, 389, 64)
+    w, x = rand_inputs(max(tokens), N, K, seed=113)
+    blob = api.pack_weights(w)
+    qx, sx, _, _ = api.quant_act_per_token(x)
+    ws = api.new_workspace(max(api.gemm_workspace_bytes(M, N, K) for M in tokens), DEV)
+    want = {M: api.w4a8_gemm(qx[:M], sx[:M], blob, N, workspace=ws) for M in tokens}
+    outs = [(M, given, torch.empty(M, N, dtype=torch.float16, device=DEV)) for given in (ws, None) for M in tokens]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for M, given, out in outs:
+            api.w4a8_gemm(qx[:M], sx[:M], blob, N, out=out, workspace=given)
+    for rep in range(4):
+        for _, _, out in outs:
+            out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for M, _, out in outs:
+            assert torch.equal(out.view(torch.int16), want[M].view(torch.int16)), (rep, M)
+        M = tokens[rep % 3]
+        assert torch.equal(api.w4a8_gemm(qx[:M], sx[:M], blob, N, workspace=ws).view(torch.int16), want[M].view(torch.int16))
