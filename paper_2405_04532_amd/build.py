@@ -19,7 +19,9 @@ SOURCES = ["qoq_api.hip", "qoq_pack.hip", "qoq_act.hip", "qoq_gemm.hip", "qoq_ge
            "qoq_gemm_mma8_channel_256.hip", "qoq_gemm_mma8_channel_128.hip", "qoq_kv4.hip", "qoq_transforms.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed FP32 instructions off (they have produced wrong results on these machines)
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # the first fourteen dwords of plain kernel arguments come in scalar registers (qoq_gemm_common.h)
+         "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 
 
 def _compile(src, extra):

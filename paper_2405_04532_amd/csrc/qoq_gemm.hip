@@ -171,7 +171,7 @@ __device__ __forceinline__ void finish_shared_blocks(const GemmDev& p, int npart
                 if (ww > wl[k]) break;                                      // these loads go to memory: none is issued twice
                 const int which = first_partial(ww, k) ? 0 : 1;
                 t[(k * kRounds + r) * kBatch + x] =
-                    load_through(p.parts + ((size_t)(blockIdx.y * gridDim.x + ww) * 2 + which) * kEl + el);
+                    load_through(p.parts + ((size_t)(blockIdx.y * p.nwg + ww) * 2 + which) * kEl + el);
             }
         }
     }
@@ -194,7 +194,7 @@ __device__ __forceinline__ void finish_shared_blocks(const GemmDev& p, int npart
                     u[x] = (v4i){0, 0, 0, 0};
                     if (ww > wl[k]) continue;
                     const int which = first_partial(ww, k) ? 0 : 1;
-                    u[x] = load_through(p.parts + ((size_t)(blockIdx.y * gridDim.x + ww) * 2 + which) * kEl + el);
+                    u[x] = load_through(p.parts + ((size_t)(blockIdx.y * p.nwg + ww) * 2 + which) * kEl + el);
                 }
 #pragma unroll
                 for (int x = 0; x < 4; ++x)
@@ -214,8 +214,9 @@ __device__ __forceinline__ void finish_shared_blocks(const GemmDev& p, int npart
 }
 
 template <int MF, bool GROUP, int OUT>
-__global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void stream_kernel(GemmDev p)
+__global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void stream_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
+    const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
     // Weights: every consumer wave owns a deep private ring of 1 KiB units.  Activations, metadata and
     // scales: shallow rings, one slot per iteration (= two consecutive groups of a block), filled by
     // four producer waves (producer (pk, ph) copies half ph of the activation blocks of the pk-th group of
@@ -376,7 +377,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
     // copies and proves that the slots refilled next are no longer being read.
     const int tid = f * 64 + lane;                          // owner lanes: index inside a partial tile
     const bool owner = !producer && e == 0;
-    int4* my_parts = p.parts + (size_t)(blockIdx.y * gridDim.x + wg) * 2 * (MF * kThreads);
+    int4* my_parts = p.parts + (size_t)(blockIdx.y * p.nwg + wg) * 2 * (MF * kThreads);
     int npart = 0, part_block0 = 0, part_block1 = 0;   // (scalars: an indexed array would be moved to LDS)
     // Partial tiles of the run (at most two: a first segment that starts inside a block, a last one that ends
     // inside a block) stay in registers and are written out after the loop, so that no store sits among the copies.
@@ -514,8 +515,9 @@ constexpr int kRsThreads = 512;
 constexpr int kRsWaves = 8;
 
 template <int MF, bool GROUP, int OUT>
-__global__ __launch_bounds__(kRsThreads) void rstream_kernel(GemmDev p)
+__global__ __launch_bounds__(kRsThreads) void rstream_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
+    const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
     constexpr int kEl = MF * kThreads;                              // int4 elements of a 64-channel tile: (mf * 4 + f) * 64 + lane
     constexpr int kRounds = (kEl + kRsThreads - 1) / kRsThreads;    // elements per thread after the reduction
     __shared__ int4 red[kRsWaves][kEl];
@@ -599,7 +601,7 @@ __global__ __launch_bounds__(kRsThreads) void rstream_kernel(GemmDev p)
     for (int r = 0; r < kRounds; ++r) part0[r] = part1[r] = (v4i){0, 0, 0, 0};
     bool has_part0 = false, has_part1 = false;
     int npart = 0, part_block0 = 0, part_block1 = 0, seg_index = 0;   // (scalars: an indexed array would be moved to LDS)
-    int4* my_parts = p.parts + (size_t)(blockIdx.y * gridDim.x + wg) * 2 * kEl;
+    int4* my_parts = p.parts + (size_t)(blockIdx.y * p.nwg + wg) * 2 * kEl;
 
     // One item ahead: the loads of the next iteration go out, then the current one is computed.  (Deeper
     // register prefetch with a fixed number of loads per iteration was measured and is no faster: the loop is not
@@ -712,8 +714,9 @@ __global__ __launch_bounds__(kRsThreads) void rstream_kernel(GemmDev p)
 // The host picks this kernel where that many whole pairs / quads, times the token tiles, still fill the chip.
 // ------------------------------------------------------------------------------------------
 template <int NB, int MF, bool GROUP, int OUT>
-__global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void lockstep_kernel(GemmDev p)
+__global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void lockstep_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
+    const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
     static_assert(NB == 2 || NB == 4, "pairs or quads");
     static_assert(MF >= 1 && MF <= 4, "token tiles of 16, 32, 48 or 64");
     constexpr bool kParity = NB == 2;                  // consumer waves split the two groups of an iteration between them
@@ -972,8 +975,9 @@ constexpr int kMmaDepth = 3;
 constexpr int kMSlotBytes = 1024;                   // metadata: 256 B per copying wave
 
 template <bool GROUP, int OUT, int CF, int WM>
-__global__ __launch_bounds__(kMmaThreads, 1) void mma_kernel(GemmDev p)
+__global__ __launch_bounds__(kMmaThreads, 1) void mma_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
+    const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
     constexpr int DEPTH = kMmaDepth;
     constexpr int kASlots = DEPTH, kWSlots = DEPTH;
     constexpr int WN = 4 / WM;                      // waves along the channels
@@ -1481,11 +1485,11 @@ void launch_stream(const GemmDev& p, bool fp16, dim3 grid, hipStream_t s)
     // 64-token tiles: the LDS-staged kernel; smaller tiles: the register-streaming kernel (measured faster there:
     // its activation traffic shrinks with the tile while the staged kernel's per-iteration barriers do not)
     if constexpr (MF >= 3) {
-        if (fp16) stream_kernel<MF, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
-        else stream_kernel<MF, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
+        if (fp16) launch_gemm_kernel(stream_kernel<MF, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
+        else launch_gemm_kernel(stream_kernel<MF, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
     } else {
-        if (fp16) rstream_kernel<MF, GROUP, OUT_FP16><<<grid, kRsThreads, 0, s>>>(p);
-        else rstream_kernel<MF, GROUP, OUT_I32><<<grid, kRsThreads, 0, s>>>(p);
+        if (fp16) launch_gemm_kernel(rstream_kernel<MF, GROUP, OUT_FP16>, grid, kRsThreads, s, p);
+        else launch_gemm_kernel(rstream_kernel<MF, GROUP, OUT_I32>, grid, kRsThreads, s, p);
     }
 }
 
@@ -1494,8 +1498,8 @@ void launch_mma(const GemmDev& p, bool fp16, hipStream_t s)
 {
     constexpr int TMt = 128 * WM, TNt = 32 * CF * (4 / WM);
     const dim3 grid((unsigned)(((p.N + TNt - 1) / TNt) * ((p.M + TMt - 1) / TMt)), (unsigned)p.S);
-    if (fp16) mma_kernel<GROUP, OUT_FP16, CF, WM><<<grid, kMmaThreads, 0, s>>>(p);
-    else mma_kernel<GROUP, OUT_I32, CF, WM><<<grid, kMmaThreads, 0, s>>>(p);
+    if (fp16) launch_gemm_kernel(mma_kernel<GROUP, OUT_FP16, CF, WM>, grid, kMmaThreads, s, p);
+    else launch_gemm_kernel(mma_kernel<GROUP, OUT_I32, CF, WM>, grid, kMmaThreads, s, p);
 }
 
 // tile_m selects the kernel and its shape: 16 / 32 / 64 = streaming kernel with that many tokens per tile;
@@ -1513,24 +1517,24 @@ hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStrea
         return launch_astat(p, tile_m, nwg, GROUP, fp16, s);
     } else if (tile_m == 66) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 63) / 64));
-        if (three && fp16) lockstep_kernel<4, 3, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
-        else if (three) lockstep_kernel<4, 3, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
-        else if (fp16) lockstep_kernel<4, 4, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
-        else lockstep_kernel<4, 4, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
+        if (three && fp16) launch_gemm_kernel(lockstep_kernel<4, 3, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
+        else if (three) launch_gemm_kernel(lockstep_kernel<4, 3, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
+        else if (fp16) launch_gemm_kernel(lockstep_kernel<4, 4, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
+        else launch_gemm_kernel(lockstep_kernel<4, 4, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
     } else if (tile_m == 65) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 63) / 64));
-        if (three && fp16) lockstep_kernel<2, 3, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
-        else if (three) lockstep_kernel<2, 3, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
-        else if (fp16) lockstep_kernel<2, 4, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
-        else lockstep_kernel<2, 4, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
+        if (three && fp16) launch_gemm_kernel(lockstep_kernel<2, 3, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
+        else if (three) launch_gemm_kernel(lockstep_kernel<2, 3, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
+        else if (fp16) launch_gemm_kernel(lockstep_kernel<2, 4, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
+        else launch_gemm_kernel(lockstep_kernel<2, 4, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
     } else if (tile_m == 67) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 31) / 32));
-        if (fp16) lockstep_kernel<2, 2, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
-        else lockstep_kernel<2, 2, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
+        if (fp16) launch_gemm_kernel(lockstep_kernel<2, 2, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
+        else launch_gemm_kernel(lockstep_kernel<2, 2, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
     } else if (tile_m == 68) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 15) / 16));
-        if (fp16) lockstep_kernel<2, 1, GROUP, OUT_FP16><<<grid, kStreamThreads, 0, s>>>(p);
-        else lockstep_kernel<2, 1, GROUP, OUT_I32><<<grid, kStreamThreads, 0, s>>>(p);
+        if (fp16) launch_gemm_kernel(lockstep_kernel<2, 1, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
+        else launch_gemm_kernel(lockstep_kernel<2, 1, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
     } else if (tile_m <= 64) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + tile_m - 1) / tile_m));
         if (tile_m == 16) launch_stream<1, GROUP>(p, fp16, grid, s);

@@ -49,9 +49,9 @@ constexpr int kAsThreads = 512;
 constexpr int kAsWaves = 8;
 constexpr int kAsMaxFrags = 128;     // fragments per workgroup when k-slices meet in the workspace (host-checked)
 
-// FP16 tokens that the kernel quantizes itself, and where their codes, scales and sums go (rowsum may be null).
+// Where the codes, scales and sums of FP16 tokens go that the kernel quantizes itself (rowsum may be null); GemmDev::qx then
+// is the address of the tokens.
 struct TokensIn {
-    const __half* x;
     int8_t* qx;
     __half* sx;
     int32_t* rowsum;
@@ -141,7 +141,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
     const int m0 = mt_idx * (16 * MF);
     const int G = p.G, nf_total = p.N / 16;
     // fragments of this workgroup: contiguous runs whose lengths differ by at most one
-    const int nwg = gridDim.x, base = nf_total / nwg, rem = nf_total - base * nwg;
+    const int nwg = p.nwg, base = nf_total / nwg, rem = nf_total - base * nwg;
     const int wg = blockIdx.x;
     const int f0 = wg * base + min(wg, rem), f1 = f0 + base + (wg < rem ? 1 : 0);
     if (f0 >= f1) return;                              // whole workgroup: nothing to do
@@ -185,7 +185,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
         const bool want_sums = !GROUP || in.rowsum;
         if (threadIdx.x < 16) { s_amax[threadIdx.x] = 0; s_sum[threadIdx.x] = 0; }
         // the tokens first, then the weights, whose way is the longer one; chunks past the end of a row read as zeros
-        const __amdgpu_buffer_rsrc_t tokens = __builtin_amdgcn_make_buffer_rsrc(const_cast<__half*>(in.x), 0, p.M * p.K * 2, 0x00020000);
+        const __amdgpu_buffer_rsrc_t tokens = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(p.qx), 0, p.M * p.K * 2, 0x00020000);
         uint4 v[CHUNKS];
 #pragma unroll
         for (int i = 0; i < CHUNKS; ++i) {
@@ -402,8 +402,9 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
 }
 
 template <int MF, int J, int R, bool GROUP, int OUT, int ROWS = 16>
-__global__ __launch_bounds__(kAsThreads) void astat_kernel(GemmDev p)
+__global__ __launch_bounds__(kAsThreads) void astat_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
+    const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
     astat_run<8, MF, J, R, GROUP, OUT, ROWS, 0>(p, TokensIn{});
 }
 
@@ -413,15 +414,17 @@ __global__ __launch_bounds__(kAsThreads) void astat_kernel(GemmDev p)
 // 28672 per channel 35.5 -> 23.5.  Up to eight tokens need half the staging: all groups of a wave in one pass, not two one
 // after the other (8.9 and 9.9 us; eight waves, K = 8192 x 10240: 11.2 and 11.6).
 template <int J, bool GROUP, int OUT, int ROWS>
-__global__ __launch_bounds__(1024) void astat_deep_kernel(GemmDev p)
+__global__ __launch_bounds__(1024) void astat_deep_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
+    const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
     astat_run<16, 1, J, 1, GROUP, OUT, ROWS, 0>(p, TokensIn{});
 }
 
 // Up to sixteen FP16 tokens through the quantizer and the GEMM in one launch.
 template <int J, int R, bool GROUP, int CHUNKS>
-__global__ __launch_bounds__(kAsThreads) void astat_linear_kernel(GemmDev p, TokensIn in)
+__global__ __launch_bounds__(kAsThreads) void astat_linear_kernel(QOQ_GEMM_PARAMS, GemmTail tail, TokensIn in)
 {
+    const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
     astat_run<8, 1, J, R, GROUP, OUT_FP16, 16, CHUNKS>(p, in);
 }
 
@@ -430,21 +433,21 @@ void launch_j(const GemmDev& p, dim3 grid, bool fp16, hipStream_t s)
 {
     if constexpr (MF == 1) {
         if (p.M <= 8) {
-            if (fp16) astat_kernel<MF, J, R, GROUP, OUT_FP16, 8><<<grid, kAsThreads, 0, s>>>(p);
-            else astat_kernel<MF, J, R, GROUP, OUT_I32, 8><<<grid, kAsThreads, 0, s>>>(p);
+            if (fp16) launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT_FP16, 8>, grid, kAsThreads, s, p);
+            else launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT_I32, 8>, grid, kAsThreads, s, p);
             return;
         }
     }
-    if (fp16) astat_kernel<MF, J, R, GROUP, OUT_FP16><<<grid, kAsThreads, 0, s>>>(p);
-    else astat_kernel<MF, J, R, GROUP, OUT_I32><<<grid, kAsThreads, 0, s>>>(p);
+    if (fp16) launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT_FP16>, grid, kAsThreads, s, p);
+    else launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT_I32>, grid, kAsThreads, s, p);
 }
 
 constexpr int kDeepGroups = 7 * 16;
 template <bool GROUP, int OUT>
 void launch_deep(const GemmDev& p, dim3 grid, hipStream_t s)
 {
-    if (p.gps <= 6 * 16) p.M <= 8 ? astat_deep_kernel<6, GROUP, OUT, 8><<<grid, 1024, 0, s>>>(p) : astat_deep_kernel<6, GROUP, OUT, 16><<<grid, 1024, 0, s>>>(p);
-    else p.M <= 8 ? astat_deep_kernel<7, GROUP, OUT, 8><<<grid, 1024, 0, s>>>(p) : astat_deep_kernel<7, GROUP, OUT, 16><<<grid, 1024, 0, s>>>(p);
+    if (p.gps <= 6 * 16) p.M <= 8 ? launch_gemm_kernel(astat_deep_kernel<6, GROUP, OUT, 8>, grid, 1024, s, p) : launch_gemm_kernel(astat_deep_kernel<6, GROUP, OUT, 16>, grid, 1024, s, p);
+    else p.M <= 8 ? launch_gemm_kernel(astat_deep_kernel<7, GROUP, OUT, 8>, grid, 1024, s, p) : launch_gemm_kernel(astat_deep_kernel<7, GROUP, OUT, 16>, grid, 1024, s, p);
 }
 
 template <bool GROUP>
@@ -480,8 +483,8 @@ hipError_t launch_mode(const GemmDev& p, int tile, dim3 grid, bool fp16, hipStre
 template <bool GROUP, int CHUNKS>
 void launch_linear(const GemmDev& p, const TokensIn& in, dim3 grid, hipStream_t s)
 {
-    if ((p.G + kAsWaves - 1) / kAsWaves <= 4) astat_linear_kernel<4, 2, GROUP, CHUNKS><<<grid, kAsThreads, 0, s>>>(p, in);
-    else astat_linear_kernel<8, 1, GROUP, CHUNKS><<<grid, kAsThreads, 0, s>>>(p, in);
+    if ((p.G + kAsWaves - 1) / kAsWaves <= 4) launch_gemm_kernel(astat_linear_kernel<4, 2, GROUP, CHUNKS>, grid, kAsThreads, s, p, in);
+    else launch_gemm_kernel(astat_linear_kernel<8, 1, GROUP, CHUNKS>, grid, kAsThreads, s, p, in);
 }
 
 // Elements of M tokens of K, M rounded up to a power of two: what the threads of a workgroup share.
@@ -500,10 +503,12 @@ bool astat_linear_takes(int64_t M, int64_t K)
     return token_elements(M, K) <= kTokenLds;            // (16 x 4096 x 6144 per channel: 8.3 us in one launch, 7.7 in two)
 }
 
-hipError_t launch_astat_linear(const GemmDev& p, const void* x, int8_t* qx, void* sx, int32_t* rowsum, bool group, hipStream_t s)
+hipError_t launch_astat_linear(const GemmDev& layer, const void* x, int8_t* qx, void* sx, int32_t* rowsum, bool group, hipStream_t s)
 {
-    if (!astat_linear_takes(p.M, p.K)) return hipErrorInvalidValue;
-    const TokensIn in{static_cast<const __half*>(x), qx, static_cast<__half*>(sx), rowsum};
+    if (!astat_linear_takes(layer.M, layer.K)) return hipErrorInvalidValue;
+    const TokensIn in{qx, static_cast<__half*>(sx), rowsum};
+    GemmDev p = layer;
+    p.qx = static_cast<const int8_t*>(x);
     const dim3 grid((unsigned)(p.N / 16 < 256 ? p.N / 16 : 256));
     const bool few = token_elements(p.M, p.K) <= (int64_t)kFewTokenChunks * 8 * kAsThreads;
     if (group) few ? launch_linear<true, kFewTokenChunks>(p, in, grid, s) : launch_linear<true, kTokenChunks>(p, in, grid, s);

@@ -30,7 +30,42 @@ struct GemmDev {
     int M, N, K, G, gps, S;  // gps = groups per k-split, S = number of k-splits (tiled kernel)
     int upw;                 // stream kernel: work units per workgroup
     int token_sum;           // per-channel FP16 epilogue in the token-sum form: `rowsum` then holds the FP32 sums t_X
+    int nwg;                 // gridDim.x
 };
+
+// How a GemmDev reaches a kernel.  The first fourteen dwords of a kernel's arguments, where they are plain values, arrive in
+// scalar registers with the wave (build.py asks for it): what the first loads need is there when the kernel starts.  A structure
+// does not, and fetching it took every kernel about 0.3 us before its first load went out (the one-token Llama-2-7B decoder
+// layer, ten kernels, 59.5 -> 55.5 us; 16 x 256 x 256 in one launch 4.46 -> 4.09); what only the epilogue needs still comes that way, behind the loads.
+struct GemmTail {
+    const __half* scales;
+    const uint8_t* zeros;
+    const int32_t* rowsum;
+    __half* out16;
+    int32_t* out32;
+    int* counters;
+    int4* parts;
+    int token_sum;
+};
+#define QOQ_GEMM_PARAMS const int8_t *a_qx, const uint4 *a_codes, const uint16_t *a_meta, const __half *a_sx, int a_M, int a_N, int a_K, int a_share, \
+                        int a_S, int a_nwg
+#define QOQ_GEMM_ARGS a_qx, a_codes, a_meta, a_sx, a_M, a_N, a_K, a_share, a_S, a_nwg
+__device__ __forceinline__ GemmDev gemm_dev(QOQ_GEMM_PARAMS, const GemmTail& t)
+{
+    GemmDev p;
+    p.qx = a_qx; p.codes = a_codes; p.meta = a_meta; p.sx = a_sx;
+    p.M = a_M; p.N = a_N; p.K = a_K; p.G = a_K / 128; p.gps = p.upw = a_share; p.S = a_S; p.nwg = a_nwg;
+    p.scales = t.scales; p.zeros = t.zeros; p.rowsum = t.rowsum; p.out16 = t.out16; p.out32 = t.out32;
+    p.counters = t.counters; p.parts = t.parts; p.token_sum = t.token_sum;
+    return p;
+}
+// `more`: further arguments of the kernel, behind the structure.
+template <class Kernel, class... More>
+void launch_gemm_kernel(Kernel* kernel, dim3 grid, int threads, hipStream_t s, const GemmDev& p, const More&... more)
+{
+    const GemmTail tail{p.scales, p.zeros, p.rowsum, p.out16, p.out32, p.counters, p.parts, p.token_sum};
+    kernel<<<grid, threads, 0, s>>>(p.qx, p.codes, p.meta, p.sx, p.M, p.N, p.K, p.upw ? p.upw : p.gps, p.S, (int)grid.x, tail, more...);
+}
 
 enum { OUT_FP16 = 0, OUT_I32 = 1 };
 

@@ -50,8 +50,9 @@ template <int N, class F>
 __device__ __forceinline__ void unrolled(F&& f) { unrolled_over(f, std::make_integer_sequence<int, N>()); }
 
 template <bool GROUP, int OUT>
-__global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(GemmDev p)
+__global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
+    const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
     constexpr int kASlots = kDepth, kWSlots = kDepth;
     constexpr int TMt = kTileM, TNt = kTileN;       // tile: tokens x channels
     constexpr int kABlocks = TMt / 16;              // 1 KiB blocks (16 tokens x 64 k) per activation slab
@@ -392,7 +393,7 @@ hipError_t launch_mma16(const GemmDev& p, bool group, bool fp16, hipStream_t s)
     const dim3 grid((unsigned)(((p.N + kTileN - 1) / kTileN) * ((p.M + kTileM - 1) / kTileM)), (unsigned)p.S);
     auto* kern = group ? (fp16 ? mma16_kernel<true, OUT_FP16> : mma16_kernel<true, OUT_I32>)
                        : (fp16 ? mma16_kernel<false, OUT_FP16> : mma16_kernel<false, OUT_I32>);
-    kern<<<grid, kMmaThreads, 0, s>>>(p);
+    launch_gemm_kernel(kern, grid, kMmaThreads, s, p);
     return hipGetLastError();
 }
 

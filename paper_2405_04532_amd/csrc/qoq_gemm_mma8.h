@@ -61,8 +61,9 @@ struct M8Shape {
 };
 
 template <bool GROUP, int MF, int WC>
-__global__ __launch_bounds__(kM8Threads) __attribute__((amdgpu_waves_per_eu(2, 2))) void mma8_kernel(GemmDev p)
+__global__ __launch_bounds__(kM8Threads) __attribute__((amdgpu_waves_per_eu(2, 2))) void mma8_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
+    const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
     using Sh = M8Shape<MF, WC>;
     constexpr int WK = Sh::WK, SG = Sh::SG, TM = Sh::TM, TN = Sh::TN, R = Sh::R;
     constexpr int kUnits = TN / 16;                 // weight units of a group
@@ -438,13 +439,13 @@ hipError_t launch_mma8_tile(const GemmDev& p, int mf, hipStream_t s)
     const int tm = 16 * mf, tn = 64 * WC;
     const dim3 grid((unsigned)(((p.N + tn - 1) / tn) * ((p.M + tm - 1) / tm)), (unsigned)p.S);
     switch (mf) {
-        case 3: mma8_kernel<GROUP, 3, WC><<<grid, kM8Threads, 0, s>>>(p); break;
-        case 4: mma8_kernel<GROUP, 4, WC><<<grid, kM8Threads, 0, s>>>(p); break;
-        case 5: mma8_kernel<GROUP, 5, WC><<<grid, kM8Threads, 0, s>>>(p); break;
-        case 6: mma8_kernel<GROUP, 6, WC><<<grid, kM8Threads, 0, s>>>(p); break;
-        case 7: mma8_kernel<GROUP, 7, WC><<<grid, kM8Threads, 0, s>>>(p); break;
-        case 8: mma8_kernel<GROUP, 8, WC><<<grid, kM8Threads, 0, s>>>(p); break;
-        case 9: mma8_kernel<GROUP, 9, WC><<<grid, kM8Threads, 0, s>>>(p); break;
+        case 3: launch_gemm_kernel(mma8_kernel<GROUP, 3, WC>, grid, kM8Threads, s, p); break;
+        case 4: launch_gemm_kernel(mma8_kernel<GROUP, 4, WC>, grid, kM8Threads, s, p); break;
+        case 5: launch_gemm_kernel(mma8_kernel<GROUP, 5, WC>, grid, kM8Threads, s, p); break;
+        case 6: launch_gemm_kernel(mma8_kernel<GROUP, 6, WC>, grid, kM8Threads, s, p); break;
+        case 7: launch_gemm_kernel(mma8_kernel<GROUP, 7, WC>, grid, kM8Threads, s, p); break;
+        case 8: launch_gemm_kernel(mma8_kernel<GROUP, 8, WC>, grid, kM8Threads, s, p); break;
+        case 9: launch_gemm_kernel(mma8_kernel<GROUP, 9, WC>, grid, kM8Threads, s, p); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
