@@ -148,7 +148,8 @@ __global__ __launch_bounds__(kThreads) void act_quant_kernel(const __half* __res
 }
 
 // Single-read variant: up to 1024 threads, up to kCache 16-byte chunks (8 halves each) per thread in registers.
-// The kernels index by blockDim.x; row_threads() below says how many threads a row gets.
+// row_threads() below says how many threads a row gets; the kernels take that number as an argument, which is there when they start
+// (blockDim.x would have to be fetched).
 constexpr int kWide = 1024;
 constexpr int kCache = 4;
 constexpr int64_t kMaxCachedK = 32768;
@@ -166,15 +167,15 @@ struct RowReader {
     }
 };
 
-// Quantize a token row that the workgroup holds in registers (chunk c = threadIdx.x + i * blockDim.x in v[i],
+// Quantize a token row that the workgroup holds in registers (chunk c = threadIdx.x + i * threads in v[i],
 // zeros past the end): absmax, scale, INT8 codes, sums.  Used by the plain quantizer and by the producers the
 // quantization is fused into.  These kernels are bound by vector instructions as much as by memory.
 template <int CACHE>
-__device__ inline void quantize_cached_row(const uint4 (&v)[CACHE], int chunks, int64_t m, int64_t K,
+__device__ inline void quantize_cached_row(const uint4 (&v)[CACHE], int chunks, int threads, int64_t m, int64_t K,
                                            int8_t* __restrict__ qx, __half* __restrict__ sx,
                                            int32_t* __restrict__ rowsum, float* __restrict__ tx, float* s_f, int* s_i)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = (int)blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = threads >> 6;
     h2 mx = half2_of(0u);
 #pragma unroll
     for (int i = 0; i < CACHE; ++i) mx = max_of_chunk(v[i], mx);
@@ -193,13 +194,13 @@ __device__ inline void quantize_cached_row(const uint4 (&v)[CACHE], int chunks, 
         const float push = inv_s * (1.0f + 0x1p-20f);
 #pragma unroll
         for (int i = 0; i < CACHE; ++i) {
-            const int c = (int)threadIdx.x + i * (int)blockDim.x;
+            const int c = (int)threadIdx.x + i * threads;
             if (c < chunks) qrow[c] = codes_of_chunk(v[i], push, isum);
         }
     } else {
 #pragma unroll 1
         for (int i = 0; i < CACHE; ++i) {
-            const int c = (int)threadIdx.x + i * (int)blockDim.x;
+            const int c = (int)threadIdx.x + i * threads;
             uint4 vi = v[0];
 #pragma unroll
             for (int x = 1; x < CACHE; ++x)            // (selects: an indexed register array would go to scratch memory)
@@ -235,18 +236,18 @@ __device__ inline void quantize_cached_row(const uint4 (&v)[CACHE], int chunks, 
 }
 
 template <int CACHE>
-__global__ __launch_bounds__(kWide) void act_quant_cached_kernel(const __half* __restrict__ x, int64_t K,
+__global__ __launch_bounds__(kWide) void act_quant_cached_kernel(const __half* __restrict__ x, int K, int threads,
                                                                  int8_t* __restrict__ qx, __half* __restrict__ sx,
                                                                  int32_t* __restrict__ rowsum, float* __restrict__ tx)
 {
     __shared__ float s_f[kWide / 64];
     __shared__ int s_i[kWide / 64];
     const int64_t m = blockIdx.x;
-    const RowReader row(x + m * K, (int)K * 2);
+    const RowReader row(x + m * K, K * 2);
     uint4 v[CACHE];
 #pragma unroll
-    for (int i = 0; i < CACHE; ++i) v[i] = row((int)threadIdx.x + i * (int)blockDim.x);
-    quantize_cached_row(v, (int)(K / 8), m, K, qx, sx, rowsum, tx, s_f, s_i);
+    for (int i = 0; i < CACHE; ++i) v[i] = row((int)threadIdx.x + i * threads);
+    quantize_cached_row(v, K / 8, threads, m, K, qx, sx, rowsum, tx, s_f, s_i);
 }
 
 // The same with the input channels taken in a new order (activation-aware channel reordering, Section 4.3):
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(kWide) void act_quant_cached_kernel(const __half* _
 // Indices are clamped to the row.  LDS: the row, then the two arrays of the reduction.
 template <int CACHE>
 __global__ __launch_bounds__(kWide) void act_quant_reordered_kernel(const __half* __restrict__ x, const int32_t* __restrict__ perm,
-                                                                    int64_t K, int8_t* __restrict__ qx, __half* __restrict__ sx,
+                                                                    int K, int threads, int8_t* __restrict__ qx, __half* __restrict__ sx,
                                                                     int32_t* __restrict__ rowsum, float* __restrict__ tx)
 {
     extern __shared__ __attribute__((aligned(16))) char s_mem[];
@@ -263,23 +264,23 @@ __global__ __launch_bounds__(kWide) void act_quant_reordered_kernel(const __half
     float* s_f = reinterpret_cast<float*>(s_mem + K * 2);
     int* s_i = reinterpret_cast<int*>(s_f + kWide / 64);
     const int64_t m = blockIdx.x;
-    const RowReader row(x + m * K, (int)K * 2), order(perm, (int)K * 4);
-    const int chunks = (int)(K / 8), last = (int)K - 1;
+    const RowReader row(x + m * K, K * 2), order(perm, K * 4);
+    const int chunks = K / 8, last = K - 1;
     uint4 v[CACHE], p[2 * CACHE];
 #pragma unroll
-    for (int i = 0; i < CACHE; ++i) v[i] = row((int)threadIdx.x + i * (int)blockDim.x);
+    for (int i = 0; i < CACHE; ++i) v[i] = row((int)threadIdx.x + i * threads);
 #pragma unroll
-    for (int i = 0; i < 2 * CACHE; ++i) p[i] = order(2 * ((int)threadIdx.x + (i >> 1) * (int)blockDim.x) + (i & 1));
+    for (int i = 0; i < 2 * CACHE; ++i) p[i] = order(2 * ((int)threadIdx.x + (i >> 1) * threads) + (i & 1));
 #pragma unroll
     for (int i = 0; i < CACHE; ++i) {
-        const int c = (int)threadIdx.x + i * (int)blockDim.x;
+        const int c = (int)threadIdx.x + i * threads;
         if (c < chunks) s_row[c] = v[i];
     }
     __syncthreads();
     const unsigned short* s_half = reinterpret_cast<const unsigned short*>(s_mem);
 #pragma unroll
     for (int i = 0; i < CACHE; ++i) {
-        const int c = (int)threadIdx.x + i * (int)blockDim.x;
+        const int c = (int)threadIdx.x + i * threads;
         if (c < chunks) {
             const uint32_t idx[8] = {p[2 * i].x, p[2 * i].y, p[2 * i].z, p[2 * i].w,
                                      p[2 * i + 1].x, p[2 * i + 1].y, p[2 * i + 1].z, p[2 * i + 1].w};
@@ -290,7 +291,7 @@ __global__ __launch_bounds__(kWide) void act_quant_reordered_kernel(const __half
             v[i] = make_uint4(w[0], w[1], w[2], w[3]);
         }
     }
-    quantize_cached_row(v, chunks, m, K, qx, sx, rowsum, tx, s_f, s_i);
+    quantize_cached_row(v, chunks, threads, m, K, qx, sx, rowsum, tx, s_f, s_i);
 }
 
 // ---- producers with the quantization fused in (Section 5.1: the activations are quantized inside the
@@ -386,23 +387,23 @@ __device__ __forceinline__ double silu_f64(double g)
 // y = x * (1 / sqrt(mean(x^2) + eps)) * gamma
 template <int CACHE>
 __global__ __launch_bounds__(kWide) void rmsnorm_quant_kernel(const __half* __restrict__ x, const __half* __restrict__ gamma,
-                                                              double eps, int64_t K, double inv_K, __half* __restrict__ y,
-                                                              int8_t* __restrict__ qx, __half* __restrict__ sx,
+                                                              int K, int threads, double eps, double inv_K, int8_t* __restrict__ qx,
+                                                              __half* __restrict__ sx, __half* __restrict__ y,
                                                               int32_t* __restrict__ rowsum, float* __restrict__ tx)
 {
     __shared__ float s_f[kWide / 64];
     __shared__ int s_i[kWide / 64];
     __shared__ double s_d[kWide / 64];
     const int64_t m = blockIdx.x;
-    const RowReader row(x + m * K, (int)K * 2), grow(gamma, (int)K * 2);
-    const int chunks = (int)(K / 8);
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = (int)blockDim.x >> 6;
+    const RowReader row(x + m * K, K * 2), grow(gamma, K * 2);
+    const int chunks = K / 8;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = threads >> 6;
     uint4 v[CACHE], gv[CACHE];                         // the weights are fetched with the row, not after the reduction
     double ss = 0.0, ss1 = 0.0;
 #pragma unroll
-    for (int i = 0; i < CACHE; ++i) v[i] = row((int)threadIdx.x + i * (int)blockDim.x);
+    for (int i = 0; i < CACHE; ++i) v[i] = row((int)threadIdx.x + i * threads);
 #pragma unroll
-    for (int i = 0; i < CACHE; ++i) gv[i] = grow((int)threadIdx.x + i * (int)blockDim.x);
+    for (int i = 0; i < CACHE; ++i) gv[i] = grow((int)threadIdx.x + i * threads);
 #pragma unroll
     for (int i = 0; i < CACHE; ++i) {
         double f[8];
@@ -428,7 +429,7 @@ __global__ __launch_bounds__(kWide) void rmsnorm_quant_kernel(const __half* __re
     uint64_t risky = 0;                                // elements to redo in FP64, bit = chunk * 8 + half
 #pragma unroll
     for (int i = 0; i < CACHE; ++i) {
-        const int c = (int)threadIdx.x + i * (int)blockDim.x;
+        const int c = (int)threadIdx.x + i * threads;
         if (c < chunks) {
             const __half* hx = reinterpret_cast<const __half*>(&v[i]);
             const __half* hg = reinterpret_cast<const __half*>(&gv[i]);
@@ -461,18 +462,18 @@ __global__ __launch_bounds__(kWide) void rmsnorm_quant_kernel(const __half* __re
     while (risky) {
         const int idx = __ffsll((unsigned long long)risky) - 1;
         risky &= risky - 1;
-        const int64_t k = ((int64_t)threadIdx.x + (int64_t)(idx >> 3) * (int64_t)blockDim.x) * 8 + (idx & 7);
+        const int64_t k = ((int64_t)threadIdx.x + (int64_t)(idx >> 3) * (int64_t)threads) * 8 + (idx & 7);
         const double fx = (double)__half2float(x[m * K + k]), fg = (double)__half2float(gamma[k]);
         patch_half(v, idx, (uint32_t)double_to_half_rne(fx * (1.0 / sqrt(ss / (double)K + eps)) * fg));
     }
     if (y) {
 #pragma unroll
         for (int i = 0; i < CACHE; ++i) {
-            const int c = (int)threadIdx.x + i * (int)blockDim.x;
+            const int c = (int)threadIdx.x + i * threads;
             if (c < chunks) reinterpret_cast<uint4*>(y + m * K)[c] = v[i];
         }
     }
-    quantize_cached_row(v, chunks, m, K, qx, sx, rowsum, tx, s_f, s_i);
+    quantize_cached_row(v, chunks, threads, m, K, qx, sx, rowsum, tx, s_f, s_i);
 }
 
 // 1 / (1 + exp(-g)) in FP32 from the hardware exponential (base 2) and reciprocal, one unit in the last place each:
@@ -490,7 +491,7 @@ __device__ __forceinline__ float sigmoid_f32(float g)
 
 // gate_up [M, 2K]: y = gate / (1 + exp(-gate)) * up with gate = first K columns, up = last K
 template <int CACHE>
-__global__ __launch_bounds__(kWide) void silu_mul_quant_kernel(const __half* __restrict__ gate_up, int64_t K,
+__global__ __launch_bounds__(kWide) void silu_mul_quant_kernel(const __half* __restrict__ gate_up, int K, int threads,
                                                                __half* __restrict__ y, int8_t* __restrict__ qx,
                                                                __half* __restrict__ sx, int32_t* __restrict__ rowsum,
                                                                float* __restrict__ tx)
@@ -498,8 +499,8 @@ __global__ __launch_bounds__(kWide) void silu_mul_quant_kernel(const __half* __r
     __shared__ float s_f[kWide / 64];
     __shared__ int s_i[kWide / 64];
     const int64_t m = blockIdx.x;
-    const RowReader grow(gate_up + m * 2 * K, (int)K * 2), urow(gate_up + m * 2 * K + K, (int)K * 2);
-    const int chunks = (int)(K / 8), wave_first = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+    const RowReader grow(gate_up + m * 2 * K, K * 2), urow(gate_up + m * 2 * K + K, K * 2);
+    const int chunks = K / 8, wave_first = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
     constexpr int kAhead = CACHE < 2 ? CACHE : 2;      // chunks in flight
     uint4 v[CACHE], gb[kAhead], ub[kAhead];
     const float minus_zero = opaque(-0.0f);
@@ -507,18 +508,18 @@ __global__ __launch_bounds__(kWide) void silu_mul_quant_kernel(const __half* __r
     uint32_t first = 0;                                // gate and up of the first of them
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) {
-        gb[i] = grow((int)threadIdx.x + i * (int)blockDim.x);
-        ub[i] = urow((int)threadIdx.x + i * (int)blockDim.x);
+        gb[i] = grow((int)threadIdx.x + i * threads);
+        ub[i] = urow((int)threadIdx.x + i * threads);
     }
 #pragma unroll
     for (int i = 0; i < CACHE; ++i) {
         const uint4 gv = gb[i % kAhead], uv = ub[i % kAhead];
         if (i + kAhead < CACHE) {
-            gb[i % kAhead] = grow((int)threadIdx.x + (i + kAhead) * (int)blockDim.x);
-            ub[i % kAhead] = urow((int)threadIdx.x + (i + kAhead) * (int)blockDim.x);
+            gb[i % kAhead] = grow((int)threadIdx.x + (i + kAhead) * threads);
+            ub[i % kAhead] = urow((int)threadIdx.x + (i + kAhead) * threads);
         }
         v[i] = make_uint4(0u, 0u, 0u, 0u);
-        if (wave_first + i * (int)blockDim.x < chunks) {   // (whole waves past the end of the row have nothing to do)
+        if (wave_first + i * threads < chunks) {   // (whole waves past the end of the row have nothing to do)
             const uint32_t g4[4] = {gv.x, gv.y, gv.z, gv.w}, u4[4] = {uv.x, uv.y, uv.z, uv.w};
             uint32_t w[4], diff[4];
 #pragma unroll
@@ -546,7 +547,7 @@ __global__ __launch_bounds__(kWide) void silu_mul_quant_kernel(const __half* __r
         const int idx = __ffsll((unsigned long long)risky) - 1;
         risky &= risky - 1;
         if (again) {
-            const int64_t k = ((int64_t)threadIdx.x + (int64_t)(idx >> 3) * (int64_t)blockDim.x) * 8 + (idx & 7);
+            const int64_t k = ((int64_t)threadIdx.x + (int64_t)(idx >> 3) * (int64_t)threads) * 8 + (idx & 7);
             const unsigned short* row = reinterpret_cast<const unsigned short*>(gate_up + m * 2 * K);
             first = (uint32_t)row[k] | ((uint32_t)row[K + k] << 16);
         }
@@ -556,11 +557,11 @@ __global__ __launch_bounds__(kWide) void silu_mul_quant_kernel(const __half* __r
     if (y) {
 #pragma unroll
         for (int i = 0; i < CACHE; ++i) {
-            const int c = (int)threadIdx.x + i * (int)blockDim.x;
+            const int c = (int)threadIdx.x + i * threads;
             if (c < chunks) reinterpret_cast<uint4*>(y + m * K)[c] = v[i];
         }
     }
-    quantize_cached_row(v, chunks, m, K, qx, sx, rowsum, tx, s_f, s_i);
+    quantize_cached_row(v, chunks, threads, m, K, qx, sx, rowsum, tx, s_f, s_i);
 }
 
 }  // namespace
@@ -591,7 +592,7 @@ hipError_t launch_act_quant(const void* x_fp16, int64_t M, int64_t K, int8_t* qx
     if (K <= kMaxCachedK) {
         const int64_t wide = row_threads(M, K);
         auto* kern = QOQ_BY_CHUNKS(act_quant_cached_kernel, wide, K);
-        kern<<<dim3((unsigned)M), (unsigned)wide, 0, s>>>(static_cast<const __half*>(x_fp16), K, qx, static_cast<__half*>(sx), rowsum, tx);
+        kern<<<dim3((unsigned)M), (unsigned)wide, 0, s>>>(static_cast<const __half*>(x_fp16), (int)K, (int)wide, qx, static_cast<__half*>(sx), rowsum, tx);
         return hipGetLastError();
     }
     act_quant_kernel<<<dim3((unsigned)M), kThreads, 0, s>>>(static_cast<const __half*>(x_fp16), K, qx,
@@ -607,7 +608,7 @@ hipError_t launch_act_quant_reordered(const void* x_fp16, const int32_t* perm, i
     const int64_t wide = row_threads(M, K);
     auto* kern = QOQ_BY_CHUNKS(act_quant_reordered_kernel, wide, K);
     const unsigned lds = (unsigned)(K * 2 + (kWide / 64) * (sizeof(float) + sizeof(int)));
-    kern<<<dim3((unsigned)M), (unsigned)wide, lds, s>>>(static_cast<const __half*>(x_fp16), perm, K, qx, static_cast<__half*>(sx),
+    kern<<<dim3((unsigned)M), (unsigned)wide, lds, s>>>(static_cast<const __half*>(x_fp16), perm, (int)K, (int)wide, qx, static_cast<__half*>(sx),
                                                         rowsum, tx);
     return hipGetLastError();
 }
@@ -620,8 +621,8 @@ hipError_t launch_rmsnorm_quant(const void* x_fp16, const void* gamma_fp16, doub
     if (M == 0) return hipSuccess;
     const int64_t wide = row_threads(M, K);
     auto* kern = QOQ_BY_CHUNKS(rmsnorm_quant_kernel, wide, K);
-    kern<<<dim3((unsigned)M), (unsigned)wide, 0, s>>>(static_cast<const __half*>(x_fp16), static_cast<const __half*>(gamma_fp16), eps, K,
-                                            1.0 / (double)K, static_cast<__half*>(y_fp16), qx, static_cast<__half*>(sx), rowsum, tx);
+    kern<<<dim3((unsigned)M), (unsigned)wide, 0, s>>>(static_cast<const __half*>(x_fp16), static_cast<const __half*>(gamma_fp16), (int)K, (int)wide,
+                                            eps, 1.0 / (double)K, qx, static_cast<__half*>(sx), static_cast<__half*>(y_fp16), rowsum, tx);
     return hipGetLastError();
 }
 
@@ -631,7 +632,7 @@ hipError_t launch_silu_mul_quant(const void* gate_up_fp16, int64_t M, int64_t K,
     if (M == 0) return hipSuccess;
     const int64_t wide = row_threads(M, K, true);
     auto* kern = QOQ_BY_CHUNKS(silu_mul_quant_kernel, wide, K);
-    kern<<<dim3((unsigned)M), (unsigned)wide, 0, s>>>(static_cast<const __half*>(gate_up_fp16), K, static_cast<__half*>(y_fp16), qx,
+    kern<<<dim3((unsigned)M), (unsigned)wide, 0, s>>>(static_cast<const __half*>(gate_up_fp16), (int)K, (int)wide, static_cast<__half*>(y_fp16), qx,
                                             static_cast<__half*>(sx), rowsum, tx);
     return hipGetLastError();
 }
