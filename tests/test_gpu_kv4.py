@@ -157,6 +157,33 @@ def test_attention_split_over_workgroups(H, Hkv):
                                             ws.data_ptr(), 16, None) == api.QOQ_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("B,H,Hkv,S,ways", [(2, 2, 1, 8192, 32), (2, 8, 4, 4100, 16), (4, 32, 8, 640, 4), (4, 32, 8, 768, 8),
+                                            (6, 8, 8, 2560, 8), (13, 8, 8, 1600, 4)])
+def test_attention_shared_by_workgroups(B, H, Hkv, S, ways):
+    """Every number of workgroups to a sequence, lengths at the edges of chunks and of the shares; a workspace with room for
+    fewer of them is used as far as it goes, down to the smallest that is accepted."""
+    per_way = B * H * 130 * 4
+    assert api.kv4_attention_workspace_bytes(B, H, Hkv, S) == ways * per_way
+    lens = [S, 1, 32 * ways, 32 * ways + 1, 31, S - 31] + [S // 2 + 7 * i for i in range(B)]
+    _attention_case(B, H, Hkv, S, lens[:B], 30 + ways, split=True)
+    k, v = wl.make_kv(B, Hkv, S, 128, 31, DEV)
+    q = wl.make_queries(B, H, 128, 31, DEV)
+    cache = api.kv4_new_cache(B, Hkv, S, DEV)
+    api.kv4_append(cache, k.permute(0, 2, 1, 3).contiguous(), v.permute(0, 2, 1, 3).contiguous(),
+                   torch.zeros(B, dtype=torch.int32, device=DEV), S)
+    seq = torch.tensor(lens[:B], dtype=torch.int32, device=DEV)
+    whole = api.kv4_attention_decode(q, cache, seq, Hkv, S)
+    least = min(256 // (B * Hkv), 8, S // 512)
+    for room in {ways, ways // 2 + 1, least}:
+        if room < max(least, 1):
+            continue
+        ws = torch.full((room * per_way + 256,), 0xFF, dtype=torch.uint8, device=DEV)
+        got = api.kv4_attention_decode(q, cache, seq, Hkv, S, workspace=ws[:room * per_way])
+        assert (ws[room * per_way:] == 0xFF).all()
+        # two orders of the same FP32 sums, FP16 softmax weights relative to another maximum: 2^-11 of the values
+        assert torch.allclose(whole.float(), got.float(), rtol=2e-3, atol=2e-3)
+
+
 def test_attention_long_sequence_many_pages():
     _attention_case(2, 2, 2, 2500, [2500, 1999], 50)
 
