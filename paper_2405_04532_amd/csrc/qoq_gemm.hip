@@ -213,7 +213,7 @@ __device__ __forceinline__ void finish_shared_blocks(const GemmDev& p, int npart
     }
 }
 
-template <int MF, bool GROUP, int OUT>
+template <int MF, bool GROUP, int OUT, bool NT>
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void stream_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
     const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
         islot = islot + 1 == kARing ? 0 : islot + 1;
     };
     auto issue_consumer = [&](int j) __attribute__((always_inline)) {
-        dma16(codes_base, w_voff + lookup(tb.off0, j), wring_addr + islot * 1024);
+        dma16<NT>(codes_base, w_voff + lookup(tb.off0, j), wring_addr + islot * 1024);
         islot = islot + 1 == kWRing ? 0 : islot + 1;
     };
 
@@ -514,7 +514,7 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
 constexpr int kRsThreads = 512;
 constexpr int kRsWaves = 8;
 
-template <int MF, bool GROUP, int OUT>
+template <int MF, bool GROUP, int OUT, bool NT>
 __global__ __launch_bounds__(kRsThreads) void rstream_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
     const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
@@ -562,7 +562,8 @@ __global__ __launch_bounds__(kRsThreads) void rstream_kernel(QOQ_GEMM_PARAMS, Ge
 #pragma unroll
         for (int f = 0; f < kNFrag; ++f) {
             const int nf = blk * kNFrag + f;
-            item.w[f] = p.codes[(size_t)((nf * G + g) << 6) + lane];
+            const u32x4* at = reinterpret_cast<const u32x4*>(p.codes) + (size_t)((nf * G + g) << 6) + lane;
+            item.w[f] = __builtin_bit_cast(uint4, NT ? __builtin_nontemporal_load(at) : *at);
             if (GROUP) item.mt[f] = p.meta[((size_t)g * nf_total + nf) * 16 + ml];
         }
 #pragma unroll
@@ -713,7 +714,7 @@ __global__ __launch_bounds__(kRsThreads) void rstream_kernel(QOQ_GEMM_PARAMS, Ge
 // Workgroups own whole pairs / quads (p.upw of them, all K): no partial tiles, no workspace.  N % (64 * NB) == 0.
 // The host picks this kernel where that many whole pairs / quads, times the token tiles, still fill the chip.
 // ------------------------------------------------------------------------------------------
-template <int NB, int MF, bool GROUP, int OUT>
+template <int NB, int MF, bool GROUP, int OUT, bool NT>
 __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void lockstep_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
     const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
@@ -810,15 +811,15 @@ __global__ __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(
             const uint32_t nf = (uint32_t)G << 10;      // the next fragment's units lie G KiB further
             if constexpr (kParity) {
                 const uint32_t unit = ((uint32_t)(csb * (4 * NB) + frag0) * (uint32_t)G + (uint32_t)(cg + (e & two))) << 10;
-                dma16(codes_base, lane16 + unit, wring_addr + slot * kWSlot);
-                dma16(codes_base, lane16 + unit + nf, wring_addr + slot * kWSlot + 1024);
+                dma16<NT>(codes_base, lane16 + unit, wring_addr + slot * kWSlot);
+                dma16<NT>(codes_base, lane16 + unit + nf, wring_addr + slot * kWSlot + 1024);
             } else {
                 const uint32_t unit = ((uint32_t)(csb * (4 * NB) + frag0) * (uint32_t)G + (uint32_t)cg) << 10;
                 const uint32_t ng = (uint32_t)two << 10;   // the next group's unit follows (the same one again on an odd tail)
-                dma16(codes_base, lane16 + unit, wring_addr + slot * kWSlot);
-                dma16(codes_base, lane16 + unit + nf, wring_addr + slot * kWSlot + 1024);
-                dma16(codes_base, lane16 + unit + ng, wring_addr + slot * kWSlot + 2048);
-                dma16(codes_base, lane16 + unit + ng + nf, wring_addr + slot * kWSlot + 3072);
+                dma16<NT>(codes_base, lane16 + unit, wring_addr + slot * kWSlot);
+                dma16<NT>(codes_base, lane16 + unit + nf, wring_addr + slot * kWSlot + 1024);
+                dma16<NT>(codes_base, lane16 + unit + ng, wring_addr + slot * kWSlot + 2048);
+                dma16<NT>(codes_base, lane16 + unit + ng + nf, wring_addr + slot * kWSlot + 3072);
             }
         }
         if (cleft > 1) {
@@ -1484,13 +1485,24 @@ void launch_stream(const GemmDev& p, bool fp16, dim3 grid, hipStream_t s)
 {
     // 64-token tiles: the LDS-staged kernel; smaller tiles: the register-streaming kernel (measured faster there:
     // its activation traffic shrinks with the tile while the staged kernel's per-iteration barriers do not)
+    const bool nt = weights_pass_by(p, grid, 96);
     if constexpr (MF >= 3) {
-        if (fp16) launch_gemm_kernel(stream_kernel<MF, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
-        else launch_gemm_kernel(stream_kernel<MF, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
+        if (fp16 && nt) launch_gemm_kernel(stream_kernel<MF, GROUP, OUT_FP16, true>, grid, kStreamThreads, s, p);
+        else if (fp16) launch_gemm_kernel(stream_kernel<MF, GROUP, OUT_FP16, false>, grid, kStreamThreads, s, p);
+        else launch_gemm_kernel(stream_kernel<MF, GROUP, OUT_I32, false>, grid, kStreamThreads, s, p);
     } else {
-        if (fp16) launch_gemm_kernel(rstream_kernel<MF, GROUP, OUT_FP16>, grid, kRsThreads, s, p);
-        else launch_gemm_kernel(rstream_kernel<MF, GROUP, OUT_I32>, grid, kRsThreads, s, p);
+        if (fp16 && nt) launch_gemm_kernel(rstream_kernel<MF, GROUP, OUT_FP16, true>, grid, kRsThreads, s, p);
+        else if (fp16) launch_gemm_kernel(rstream_kernel<MF, GROUP, OUT_FP16, false>, grid, kRsThreads, s, p);
+        else launch_gemm_kernel(rstream_kernel<MF, GROUP, OUT_I32, false>, grid, kRsThreads, s, p);
     }
+}
+
+template <int NB, int MF, bool GROUP>
+void launch_lockstep(const GemmDev& p, bool fp16, dim3 grid, hipStream_t s)
+{
+    if (fp16 && weights_pass_by(p, grid, 96)) launch_gemm_kernel(lockstep_kernel<NB, MF, GROUP, OUT_FP16, true>, grid, kStreamThreads, s, p);
+    else if (fp16) launch_gemm_kernel(lockstep_kernel<NB, MF, GROUP, OUT_FP16, false>, grid, kStreamThreads, s, p);
+    else launch_gemm_kernel(lockstep_kernel<NB, MF, GROUP, OUT_I32, false>, grid, kStreamThreads, s, p);
 }
 
 template <bool GROUP, int CF, int WM>
@@ -1517,24 +1529,18 @@ hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStrea
         return launch_astat(p, tile_m, nwg, GROUP, fp16, s);
     } else if (tile_m == 66) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 63) / 64));
-        if (three && fp16) launch_gemm_kernel(lockstep_kernel<4, 3, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
-        else if (three) launch_gemm_kernel(lockstep_kernel<4, 3, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
-        else if (fp16) launch_gemm_kernel(lockstep_kernel<4, 4, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
-        else launch_gemm_kernel(lockstep_kernel<4, 4, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
+        if (three) launch_lockstep<4, 3, GROUP>(p, fp16, grid, s);
+        else launch_lockstep<4, 4, GROUP>(p, fp16, grid, s);
     } else if (tile_m == 65) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 63) / 64));
-        if (three && fp16) launch_gemm_kernel(lockstep_kernel<2, 3, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
-        else if (three) launch_gemm_kernel(lockstep_kernel<2, 3, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
-        else if (fp16) launch_gemm_kernel(lockstep_kernel<2, 4, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
-        else launch_gemm_kernel(lockstep_kernel<2, 4, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
+        if (three) launch_lockstep<2, 3, GROUP>(p, fp16, grid, s);
+        else launch_lockstep<2, 4, GROUP>(p, fp16, grid, s);
     } else if (tile_m == 67) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 31) / 32));
-        if (fp16) launch_gemm_kernel(lockstep_kernel<2, 2, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
-        else launch_gemm_kernel(lockstep_kernel<2, 2, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
+        launch_lockstep<2, 2, GROUP>(p, fp16, grid, s);
     } else if (tile_m == 68) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + 15) / 16));
-        if (fp16) launch_gemm_kernel(lockstep_kernel<2, 1, GROUP, OUT_FP16>, grid, kStreamThreads, s, p);
-        else launch_gemm_kernel(lockstep_kernel<2, 1, GROUP, OUT_I32>, grid, kStreamThreads, s, p);
+        launch_lockstep<2, 1, GROUP>(p, fp16, grid, s);
     } else if (tile_m <= 64) {
         const dim3 grid((unsigned)nwg, (unsigned)((p.M + tile_m - 1) / tile_m));
         if (tile_m == 16) launch_stream<1, GROUP>(p, fp16, grid, s);

@@ -112,8 +112,8 @@ __device__ __forceinline__ void quantize_tokens(const GemmDev& p, const TokensIn
 }
 
 // W waves.  ROWS: tokens that the preload of a 16-token tile moves (8: half the staging, for up to eight tokens).  CHUNKS > 0: the
-// tokens come as FP16, so many chunks of them per thread.
-template <int W, int MF, int J, int R, bool GROUP, int OUT, int ROWS, int CHUNKS>
+// tokens come as FP16, so many chunks of them per thread.  NT: weights that no cache is worth keeping for (weights_pass_by).
+template <int W, int MF, int J, int R, bool GROUP, int OUT, int ROWS, int CHUNKS, bool NT>
 __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
 {
     constexpr bool FUSED = CHUNKS > 0;
@@ -156,14 +156,29 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
     auto group_of = [&](int j) __attribute__((always_inline)) { return min(g_lo + wave * jeff + min(j, jeff - 1), g_hi - 1); };
 
     // ---- weights: ring of D units per wave, filled ahead ----------------------------------------
+    // Fragments past the run (the refill at its end) and slots past the slice repeat valid addresses: those lines are in a cache.
+    // Non-temporal ones need not be, so there the loads are buffer loads, whose bounds check turns such places into no
+    // request at all (16 x 8192 x 10240 11.8 -> 11.2 us; as the only form 0.2 us slower where a workgroup has a fragment or two).
+    const int nfr = f1 - f0;
     uint4 w[D];
     uint32_t mt[D];
-    auto load_unit = [&](int slot, int j, int nf) __attribute__((always_inline)) {
-        const int g = group_of(j);
-        w[slot] = p.codes[((size_t)nf * G + g) * 64 + lane];
-        mt[slot] = GROUP ? (uint32_t)p.meta[((size_t)g * nf_total + nf) * 16 + ml] : 0u;
+    const __amdgpu_buffer_rsrc_t meta = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.meta), 0, G * nf_total * 32, 0x00020000);
+    auto window = [&](int fi) __attribute__((always_inline)) {     // codes of fragments fi ... fi + 2 R - 1 of the run, as far as it goes
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(p.codes) + (size_t)(f0 + fi) * G * 64, 0, min(nfr - fi, 2 * R) * G * 1024, 0x00020000);
     };
-    const int nfr = f1 - f0;
+    auto load_unit = [&](__amdgpu_buffer_rsrc_t codes, int slot, int j, int fi, int ahead) __attribute__((always_inline)) {   // fragment fi + ahead
+        if constexpr (NT) {
+            constexpr uint32_t kNowhere = 0x80000000u;   // past the end of either buffer, also with an offset added
+            const uint32_t g = (uint32_t)(g_lo + wave * jeff + j);
+            const uint32_t at_w = slot_valid(j) ? g * 1024u : kNowhere, at_m = slot_valid(j) ? (g * (uint32_t)nf_total + (uint32_t)f0) * 32u : kNowhere;
+            w[slot] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(codes, lane * 16 + (int)(at_w + (uint32_t)(ahead * G * 1024)), 0, 2));
+            mt[slot] = GROUP ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(meta, ml * 2 + (int)(at_m + (uint32_t)(fi + ahead) * 32u), 0, 0) : 0u;
+        } else {
+            const int g = group_of(j), nf = f0 + min(fi + ahead, nfr - 1);
+            w[slot] = p.codes[((size_t)nf * G + g) * 64 + lane];
+            mt[slot] = GROUP ? (uint32_t)p.meta[((size_t)g * nf_total + nf) * 16 + ml] : 0u;
+        }
+    };
 
     // ---- activations: loaded once, resident for the whole kernel ---------------------------------
     // lane (ml, q) holds, of every (group, m-fragment, k-step) operand, token row ml and the 16-byte k-chunk q.
@@ -174,6 +189,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
     // one or two passes, no barrier: the waves do not wait for one another.  Inside a row the 16-byte chunks are
     // stored XORed with the row number (64-bank LDS: the 16 lanes served together read the same chunk of 16
     // consecutive rows), which keeps the operand reads free of bank conflicts.
+    const __amdgpu_buffer_rsrc_t first = window(0);
     v4i a[J][MF][2];
 #pragma unroll
     for (int j = 0; j < J; ++j)
@@ -197,7 +213,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int j = 0; j < J; ++j) load_unit(r * J + j, j, f0 + min(r, nfr - 1));
+            for (int j = 0; j < J; ++j) load_unit(first, r * J + j, j, 0, r);
         __syncthreads();
         char* codes = lds_raw + kTokenLds;
         quantize_tokens(p, in, v, row, tr, per_row, want_sums, codes, s_amax, s_sum);
@@ -260,7 +276,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int j = 0; j < J; ++j) load_unit(r * J + j, j, f0 + min(r, nfr - 1));
+            for (int j = 0; j < J; ++j) load_unit(first, r * J + j, j, 0, r);
         asm volatile("; astat weight prologue end" ::: "memory");
         wait_vmcnt<kNW>();
         read_pass(0, 0);
@@ -306,12 +322,12 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
     // ---- main loop over the fragments, R per trip so that every ring slot is a compile-time constant -----------
     int buf = 0;
     for (int fi0 = 0; fi0 < nfr; fi0 += R) {
+        const __amdgpu_buffer_rsrc_t codes = window(fi0);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int fi = fi0 + r;
             if (fi >= nfr) break;                          // workgroup-uniform
             const int nf = f0 + fi;
-            const int nf_ahead = f0 + min(fi + R, nfr - 1);   // past the last fragment: reload it (valid memory, never used)
             uint2 c_s = make_uint2(0, 0);
             uint32_t c_z = 0;
             if (e_on && p.S == 1) {                        // epilogue constants: in flight during the fragment
@@ -338,7 +354,7 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
                         acc[mf] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w_op, a[j][mf][ks], acc[mf], 0, 0, 0);
                 }
                 // the slot's words are consumed: refill it with the same unit of the fragment R places ahead
-                load_unit(slot, j, nf_ahead);
+                load_unit(codes, slot, j, fi0, r + R);
                 // keep the units in program order: otherwise the compiler gathers the first touch of every slot at
                 // the top of the fragment and with it the waits for loads issued only a few hundred cycles earlier
                 __builtin_amdgcn_sched_barrier(0);
@@ -401,11 +417,11 @@ __device__ __forceinline__ void astat_run(const GemmDev& p, const TokensIn& in)
     }
 }
 
-template <int MF, int J, int R, bool GROUP, int OUT, int ROWS = 16>
+template <int MF, int J, int R, bool GROUP, int OUT, int ROWS, bool NT>
 __global__ __launch_bounds__(kAsThreads) void astat_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
     const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
-    astat_run<8, MF, J, R, GROUP, OUT, ROWS, 0>(p, TokensIn{});
+    astat_run<8, MF, J, R, GROUP, OUT, ROWS, 0, NT>(p, TokensIn{});
 }
 
 // Sixteen waves of 128 registers, for sixteen tokens and K between what eight waves hold and 14336 (seven groups per wave): one
@@ -413,41 +429,53 @@ __global__ __launch_bounds__(kAsThreads) void astat_kernel(QOQ_GEMM_PARAMS, Gemm
 // caches: about 2 us).  11008 x 4096 at one token 11.6 us -> 8.9, at sixteen 11.1 -> 10.3; 14336 x 4096 per channel 10.5 -> 8.2; 9216 x
 // 28672 per channel 35.5 -> 23.5.  Up to eight tokens need half the staging: all groups of a wave in one pass, not two one
 // after the other (8.9 and 9.9 us; eight waves, K = 8192 x 10240: 11.2 and 11.6).
-template <int J, bool GROUP, int OUT, int ROWS>
+template <int J, bool GROUP, int OUT, int ROWS, bool NT>
 __global__ __launch_bounds__(1024) void astat_deep_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
     const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
-    astat_run<16, 1, J, 1, GROUP, OUT, ROWS, 0>(p, TokensIn{});
+    astat_run<16, 1, J, 1, GROUP, OUT, ROWS, 0, NT>(p, TokensIn{});
 }
 
 // Up to sixteen FP16 tokens through the quantizer and the GEMM in one launch.
-template <int J, int R, bool GROUP, int CHUNKS>
+template <int J, int R, bool GROUP, int CHUNKS, bool NT>
 __global__ __launch_bounds__(kAsThreads) void astat_linear_kernel(QOQ_GEMM_PARAMS, GemmTail tail, TokensIn in)
 {
     const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
-    astat_run<8, 1, J, R, GROUP, OUT_FP16, 16, CHUNKS>(p, in);
+    astat_run<8, 1, J, R, GROUP, OUT_FP16, 16, CHUNKS, NT>(p, in);
 }
 
+template <int MF, int J, int R, bool GROUP, int OUT, int ROWS>
+void launch_nt(const GemmDev& p, dim3 grid, hipStream_t s)
+{
+    if (weights_pass_by(p, grid, p.S == 1 ? 40 : 96)) launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT, ROWS, true>, grid, kAsThreads, s, p);
+    else launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT, ROWS, false>, grid, kAsThreads, s, p);
+}
 template <int MF, int J, int R, bool GROUP>
 void launch_j(const GemmDev& p, dim3 grid, bool fp16, hipStream_t s)
 {
     if constexpr (MF == 1) {
         if (p.M <= 8) {
-            if (fp16) launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT_FP16, 8>, grid, kAsThreads, s, p);
-            else launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT_I32, 8>, grid, kAsThreads, s, p);
+            if (fp16) launch_nt<MF, J, R, GROUP, OUT_FP16, 8>(p, grid, s);
+            else launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT_I32, 8, false>, grid, kAsThreads, s, p);
             return;
         }
     }
-    if (fp16) launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT_FP16>, grid, kAsThreads, s, p);
-    else launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT_I32>, grid, kAsThreads, s, p);
+    if (fp16) launch_nt<MF, J, R, GROUP, OUT_FP16, 16>(p, grid, s);
+    else launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT_I32, 16, false>, grid, kAsThreads, s, p);
 }
 
 constexpr int kDeepGroups = 7 * 16;
+template <bool GROUP, int OUT, int ROWS, bool NT>
+void launch_deep_rows(const GemmDev& p, dim3 grid, hipStream_t s)
+{
+    if (p.gps <= 6 * 16) launch_gemm_kernel(astat_deep_kernel<6, GROUP, OUT, ROWS, NT>, grid, 1024, s, p);
+    else launch_gemm_kernel(astat_deep_kernel<7, GROUP, OUT, ROWS, NT>, grid, 1024, s, p);
+}
 template <bool GROUP, int OUT>
 void launch_deep(const GemmDev& p, dim3 grid, hipStream_t s)
 {
-    if (p.gps <= 6 * 16) p.M <= 8 ? launch_gemm_kernel(astat_deep_kernel<6, GROUP, OUT, 8>, grid, 1024, s, p) : launch_gemm_kernel(astat_deep_kernel<6, GROUP, OUT, 16>, grid, 1024, s, p);
-    else p.M <= 8 ? launch_gemm_kernel(astat_deep_kernel<7, GROUP, OUT, 8>, grid, 1024, s, p) : launch_gemm_kernel(astat_deep_kernel<7, GROUP, OUT, 16>, grid, 1024, s, p);
+    if (OUT == OUT_FP16 && weights_pass_by(p, grid, p.S == 1 ? 40 : 96)) p.M <= 8 ? launch_deep_rows<GROUP, OUT, 8, OUT == OUT_FP16>(p, grid, s) : launch_deep_rows<GROUP, OUT, 16, OUT == OUT_FP16>(p, grid, s);
+    else p.M <= 8 ? launch_deep_rows<GROUP, OUT, 8, false>(p, grid, s) : launch_deep_rows<GROUP, OUT, 16, false>(p, grid, s);
 }
 
 template <bool GROUP>
@@ -480,11 +508,16 @@ hipError_t launch_mode(const GemmDev& p, int tile, dim3 grid, bool fp16, hipStre
     return hipGetLastError();
 }
 
+template <bool GROUP, int CHUNKS, bool NT>
+void launch_linear_nt(const GemmDev& p, const TokensIn& in, dim3 grid, hipStream_t s)
+{
+    if ((p.G + kAsWaves - 1) / kAsWaves <= 4) launch_gemm_kernel(astat_linear_kernel<4, 2, GROUP, CHUNKS, NT>, grid, kAsThreads, s, p, in);
+    else launch_gemm_kernel(astat_linear_kernel<8, 1, GROUP, CHUNKS, NT>, grid, kAsThreads, s, p, in);
+}
 template <bool GROUP, int CHUNKS>
 void launch_linear(const GemmDev& p, const TokensIn& in, dim3 grid, hipStream_t s)
 {
-    if ((p.G + kAsWaves - 1) / kAsWaves <= 4) launch_gemm_kernel(astat_linear_kernel<4, 2, GROUP, CHUNKS>, grid, kAsThreads, s, p, in);
-    else launch_gemm_kernel(astat_linear_kernel<8, 1, GROUP, CHUNKS>, grid, kAsThreads, s, p, in);
+    weights_pass_by(p, grid, p.S == 1 ? 40 : 96) ? launch_linear_nt<GROUP, CHUNKS, true>(p, in, grid, s) : launch_linear_nt<GROUP, CHUNKS, false>(p, in, grid, s);
 }
 
 // Elements of M tokens of K, M rounded up to a power of two: what the threads of a workgroup share.

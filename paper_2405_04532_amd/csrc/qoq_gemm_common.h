@@ -59,6 +59,12 @@ __device__ __forceinline__ GemmDev gemm_dev(QOQ_GEMM_PARAMS, const GemmTail& t)
     p.counters = t.counters; p.parts = t.parts; p.token_sum = t.token_sum;
     return p;
 }
+// Weights that are read once, by one token tile, and are so many that the memory-side cache (256 MB) does not hold them
+// until the model's next step: loaded as non-temporal they leave it alone, which is faster (us from memory, before and after: 16 x 8192 x
+// 57344 47.8 -> 40.5, 37 51.8 -> 46, 8 x 28672 x 8192 26.9 -> 25.6).  Where a program's weights do fit, it is slower: the activation-
+// stationary kernels without slices by 2 to 5% (16 x 4096 x 22016 10.8 and 11.1; from memory 12.7 and 11.8), which therefore do it
+// from 40 MB on (below, 4096 x 12288 gains nothing either way), the others by up to 20%, which do it from 96 MB on.
+inline bool weights_pass_by(const GemmDev& p, dim3 grid, int megabytes) { return grid.y == 1 && (size_t)p.N * p.K / 2 >= (size_t)megabytes << 20; }
 // `more`: further arguments of the kernel, behind the structure.
 template <class Kernel, class... More>
 void launch_gemm_kernel(Kernel* kernel, dim3 grid, int threads, hipStream_t s, const GemmDev& p, const More&... more)
@@ -106,8 +112,14 @@ __device__ __forceinline__ const void* to_sgpr(const void* ptr)   // value is wa
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
     return reinterpret_cast<const void*>(((uint64_t)hi << 32) | lo);
 }
+template <bool NT = false>                               // non-temporal
 __device__ __forceinline__ void dma16(const void* base, uint32_t voff, uint32_t lds_addr)
 {
+    if constexpr (NT) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(to_sgpr(base)) : "memory");
+        return;
+    }
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(to_sgpr(base)) : "memory");
 }

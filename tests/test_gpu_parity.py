@@ -934,3 +934,23 @@ def test_captured_calls_in_one_workspace_and_without(api):
             assert torch.equal(out.view(torch.int16), want[M].view(torch.int16)), (rep, M)
         M = tokens[rep % 3]
         assert torch.equal(api.w4a8_gemm(qx[:M], sx[:M], blob, N, workspace=ws).view(torch.int16), want[M].view(torch.int16))
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M,K,N", [(1, 1152, 72896), (16, 1152, 72896), (32, 1152, 72896), (7, 4096, 20544), (64, 3456, 25600), (48, 2432, 36864),
+                                   (5, 11008, 8000), (16, 13952, 6208), (9, 16384, 12288), (32, 16512, 12288), (64, 16512, 12288),
+                                   (40, 8192, 25600), (60, 10240, 20480)])
+def test_gemm_weights_that_pass_by_the_caches(api, M, K, N, mode):
+    """Layers whose weights are loaded as non-temporal: groups that are no multiple of the waves, runs of fragments of uneven
+    length, every kernel that has that form.  Against the accumulators of the same call, which are loaded the other way and compared
+    with the oracle elsewhere, scaled in FP64: two FP32 roundings and one to FP16 lie between."""
+    g = torch.Generator(device=DEV).manual_seed(M + K + N)
+    blob = api.pack_weights(torch.randn((N, K), generator=g, device=DEV, dtype=torch.float16) * 0.02, mode)
+    x = torch.randn((M, K), generator=g, device=DEV, dtype=torch.float16)
+    qx, sx, rowsum, _ = api.quant_act_per_token(x)
+    rs = rowsum if mode else None
+    _, _, _, s = api.unpack_weights(blob, N, K, mode)
+    acc = api.w4a8_gemm_i32(qx, blob, N, mode, rowsum=rs)
+    want = acc.double() * sx.double()[:, None] * s.double()[None, :]
+    for got in (api.w4a8_gemm(qx, sx, blob, N, mode, rowsum=rs), api.w4a8_linear(x, blob, N, mode)[0]):
+        assert ((got.double() - want).abs() <= want.abs() * (2.0 ** -11 + 2.0 ** -22) + 2.0 ** -25).all()
