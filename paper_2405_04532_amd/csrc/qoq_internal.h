@@ -7,6 +7,13 @@
 
 namespace qoq {
 
+#ifdef __HIPCC__
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// 16 bytes that are not wanted in the caches afterwards
+__device__ __forceinline__ uint4 load_nontemporal(const uint4* p) { return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p))); }
+__device__ __forceinline__ void store_nontemporal(uint4* p, uint4 v) { __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4*>(p)); }
+#endif
+
 // qoq_pack.hip
 hipError_t launch_pack_weights(const void* w_fp16, const BlobLayout& L, uint8_t* blob, hipStream_t s);
 hipError_t launch_pack_quantized(const uint8_t* q, const uint8_t* s1, const uint8_t* z, const void* s_fp16,

@@ -291,7 +291,10 @@ constexpr int decode_lds_bytes(int waves, int columns) { return waves * columns 
 // would wait for that word to come from memory (4 x 200 tokens of 8 KV heads 4.4 -> 4.3 us, 1 x 8192 11.05 -> 10.7 in eight).  Not where
 // there are more workgroups than are resident: others then hide that wait, and chunks past the end are read in vain (64 x 128 of
 // 32 heads 11.5 us, 11.9 with them).
-template <int NW, int PK, bool SPLIT, bool EARLY>
+// NT: codes as non-temporal, for caches so large that the 256 MB memory-side cache cannot hold them until the next step (64 x 1024
+// tokens of 32 heads in a decoder layer 42 -> 32 us; 30 x 1500 of 8 heads, 49 MB, 1.1 us less, 20 x 300 of 32, 26 MB, 0.5, below that
+// nothing; repeated alone, where the cache does fit, up to 8% more).
+template <int NW, int PK, bool SPLIT, bool EARLY, bool NT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1 || NW == 8 ? 2 : 3))) void kv4_decode_kernel(
     const __half* __restrict__ q, const uint8_t* __restrict__ cache, const int32_t* __restrict__ seq_lens, __half* __restrict__ out,
     float* __restrict__ ws, int Hkv, int R, int S_max, int log_ns)
@@ -319,6 +322,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1
     const uint32_t off_kc = (uint32_t)(r16 * (kD / 2) + kb * 16), off_kz = (uint32_t)(kCodeBytes + r16 * 4);
     const uint32_t off_ks = (uint32_t)(kCodeBytes + kb * 16 + (second ? 64 : 0)), off_vc = (uint32_t)(kHalfPage + lane * 16);
     const uint32_t off_vp = (uint32_t)(kHalfPage + kCodeBytes + kb * 16);
+    auto code_words = [](const uint8_t* at) __attribute__((always_inline)) {
+        const uint4* p = reinterpret_cast<const uint4*>(at);
+        return NT ? load_nontemporal(p) : *p;
+    };
     auto load_chunk = [&](Chunk& c, int chunk) __attribute__((always_inline)) {
         const int t0 = __builtin_amdgcn_readfirstlane(chunk * kChunk);         // < n_pages * 64: inside the allocation
         const uint8_t* page = stream + (int64_t)(t0 / kPageTokens) * kPageBytes;
@@ -327,13 +334,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1
         const uint8_t* prm = page + tin * 4;             // (s, z) words of the chunk
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt) {
-            c.kc[tt] = *reinterpret_cast<const uint4*>(codes + tt * 1024 + off_kc);
+            c.kc[tt] = code_words(codes + tt * 1024 + off_kc);
             c.kz[tt] = *reinterpret_cast<const uint32_t*>(prm + tt * 64 + off_kz);
             if (tt < 2 / PK) c.ks[tt] = *reinterpret_cast<const uint4*>(prm + tt * 64 + off_ks);
         }
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt) {
-            c.vc[tt] = *reinterpret_cast<const uint4*>(codes + tt * 1024 + off_vc);
+            c.vc[tt] = code_words(codes + tt * 1024 + off_vc);
             c.vp[tt] = *reinterpret_cast<const uint4*>(prm + tt * 64 + off_vp);
         }
     };
@@ -644,14 +651,21 @@ size_t kv4_decode_workspace_least(int64_t B, int64_t H, int64_t Hkv, int64_t S_m
 // workgroup per compute unit).  Of the eight, shorter sequences use four.
 static int decode_waves(int64_t workgroups, int64_t tokens) { return workgroups <= 256 && tokens > kFewChunks * kChunk ? 8 : 4; }
 
-template <int PK, bool SPLIT>
-static void launch_decode(int waves, dim3 grid, const __half* q, const uint8_t* cache, const int32_t* seq_lens, int64_t Hkv, int R,
-                          int64_t S_max, __half* out, float* ws, int log_ns, hipStream_t s)
+template <int PK, bool SPLIT, bool NT>
+static void launch_decode_as(int waves, dim3 grid, const __half* q, const uint8_t* cache, const int32_t* seq_lens, int64_t Hkv, int R,
+                             int64_t S_max, __half* out, float* ws, int log_ns, hipStream_t s)
 {
     const size_t lds = (size_t)decode_lds_bytes(waves, PK * R);
-    if (waves == 8) kv4_decode_kernel<8, PK, SPLIT, true><<<grid, 512, lds, s>>>(q, cache, seq_lens, out, ws, (int)Hkv, R, (int)S_max, log_ns);
-    else if (SPLIT || grid.x <= 3 * 256) kv4_decode_kernel<4, PK, SPLIT, true><<<grid, 256, lds, s>>>(q, cache, seq_lens, out, ws, (int)Hkv, R, (int)S_max, log_ns);
-    else kv4_decode_kernel<4, PK, SPLIT, SPLIT><<<grid, 256, lds, s>>>(q, cache, seq_lens, out, ws, (int)Hkv, R, (int)S_max, log_ns);
+    auto* kernel = waves == 8 ? kv4_decode_kernel<8, PK, SPLIT, true, NT>
+                              : SPLIT || grid.x <= 3 * 256 ? kv4_decode_kernel<4, PK, SPLIT, true, NT> : kv4_decode_kernel<4, PK, SPLIT, SPLIT, NT>;
+    kernel<<<grid, 64 * waves, lds, s>>>(q, cache, seq_lens, out, ws, (int)Hkv, R, (int)S_max, log_ns);
+}
+
+template <int PK, bool SPLIT, class... Args>
+static void launch_decode(bool nt, Args... args)
+{
+    if (nt) launch_decode_as<PK, SPLIT, true>(args...);
+    else launch_decode_as<PK, SPLIT, false>(args...);
 }
 
 hipError_t launch_kv4_decode(const void* q, const uint8_t* cache, const int32_t* seq_lens, int64_t B, int64_t H, int64_t Hkv,
@@ -663,6 +677,7 @@ hipError_t launch_kv4_decode(const void* q, const uint8_t* cache, const int32_t*
     const int R = (int)(H / Hkv);
     if (R < 1 || R > kMaxRatio) return hipErrorInvalidValue;
     const int64_t pairs = B * Hkv;
+    const bool nt = kv4_cache_bytes(B, Hkv, S_max) >= (size_t)24 << 20;
     int log_ns = workspace ? decode_split_log(B, Hkv, S_max) : 0;
     while (log_ns > 0 && workspace_bytes < decode_workspace(B, H, (int64_t)1 << log_ns)) --log_ns;     // as many as there is room for
     if (log_ns > 0) {
@@ -670,15 +685,15 @@ hipError_t launch_kv4_decode(const void* q, const uint8_t* cache, const int32_t*
         const int ns = 1 << log_ns;
         const dim3 grid((unsigned)pairs, (unsigned)ns);
         const int waves = decode_waves(pairs * ns, S_max / ns);
-        if (R <= 8) launch_decode<2, true>(waves, grid, qh, cache, seq_lens, Hkv, R, S_max, oh, ws, log_ns, s);
-        else launch_decode<1, true>(waves, grid, qh, cache, seq_lens, Hkv, R, S_max, oh, ws, log_ns, s);
+        if (R <= 8) launch_decode<2, true>(nt, waves, grid, qh, cache, seq_lens, Hkv, R, S_max, oh, ws, log_ns, s);
+        else launch_decode<1, true>(nt, waves, grid, qh, cache, seq_lens, Hkv, R, S_max, oh, ws, log_ns, s);
         if (ns <= 8) kv4_combine_kernel<8><<<(unsigned)(B * H), kD, 0, s>>>(ws, oh, ns, R);
         else kv4_combine_kernel<kMaxSplits><<<(unsigned)(B * H), kD, 0, s>>>(ws, oh, ns, R);
         return hipGetLastError();
     }
     const int waves = decode_waves(pairs, S_max);
-    if (R <= 8) launch_decode<2, false>(waves, dim3((unsigned)pairs), qh, cache, seq_lens, Hkv, R, S_max, oh, nullptr, 0, s);
-    else launch_decode<1, false>(waves, dim3((unsigned)pairs), qh, cache, seq_lens, Hkv, R, S_max, oh, nullptr, 0, s);
+    if (R <= 8) launch_decode<2, false>(nt, waves, dim3((unsigned)pairs), qh, cache, seq_lens, Hkv, R, S_max, oh, nullptr, 0, s);
+    else launch_decode<1, false>(nt, waves, dim3((unsigned)pairs), qh, cache, seq_lens, Hkv, R, S_max, oh, nullptr, 0, s);
     return hipGetLastError();
 }
 

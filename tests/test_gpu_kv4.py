@@ -158,10 +158,10 @@ def test_attention_split_over_workgroups(H, Hkv):
 
 
 @pytest.mark.parametrize("B,H,Hkv,S,ways", [(2, 2, 1, 8192, 32), (2, 8, 4, 4100, 16), (4, 32, 8, 640, 4), (4, 32, 8, 768, 8),
-                                            (6, 8, 8, 2560, 8), (13, 8, 8, 1600, 4)])
+                                            (6, 8, 8, 2560, 8), (13, 8, 8, 1600, 4), (3, 24, 8, 8128, 8)])
 def test_attention_shared_by_workgroups(B, H, Hkv, S, ways):
     """Every number of workgroups to a sequence, lengths at the edges of chunks and of the shares; a workspace with room for
-    fewer of them is used as far as it goes, down to the smallest that is accepted."""
+    fewer of them is used as far as it goes, down to the smallest that is accepted.  The last cache is one of those read as non-temporal."""
     per_way = B * H * 130 * 4
     assert api.kv4_attention_workspace_bytes(B, H, Hkv, S) == ways * per_way
     lens = [S, 1, 32 * ways, 32 * ways + 1, 31, S - 31] + [S // 2 + 7 * i for i in range(B)]
