@@ -81,10 +81,14 @@ __device__ __forceinline__ float quarter_min(float v)
 //             every one; w * fl(1 / s0) is within 3e-5 of it, and pushed 1e-4 away from zero it lands on the same side
 //             (the argument of the activation quantizer).  Per-channel codes are the same quotient plus an integer.
 //   level 2   quotients of small integers by s1 <= 16 (by 15 for s1 itself): multiples of 1/32 (1/15), nudged by 1e-3.
+// PASS_BY (group mode, weights that fit the 256 MB memory-side cache): the codes go past it, so that it keeps the weights that a
+// rotation or reordering has just written (22016 x 4096 rotated and packed 145.6 -> 143.6 us, 10240 x 8192 reordered and packed 148.1 ->
+// 144.6, with the reads of those as non-temporal).  Larger weights are slower so (28672 x 14336 599 us, 604), per-channel ones of any
+// size (28672 x 8192 99.0, 102.2).
 // Bound by HBM: 22016 x 4096 in group mode in 54 us (226 MB, 4.2 TB/s; a copy moves them in 42 us).  One division of
 // doubles per weight and 4-byte stores 16 bytes apart kept one row per workgroup at 213 us, and it wrote the header by
 // a launch of its own.
-template <bool GROUP, int CH>
+template <bool GROUP, int CH, bool PASS_BY>
 __global__ __launch_bounds__(1024) void pack_kernel(const __half* __restrict__ w, BlobLayout L, uint8_t* __restrict__ blob)
 {
     __shared__ float s_lo[16][4], s_hi[16][4];
@@ -197,7 +201,11 @@ __global__ __launch_bounds__(1024) void pack_kernel(const __half* __restrict__ w
                 d[c] |= code << (8 * (t & 3) + 4 * (t >> 2));
             }
         }
-        if (g < G) codes[(nf * G + g) * 64 + kb * 16 + i] = make_uint4(d[0], d[1], d[2], d[3]);
+        if (g < G) {
+            uint4* at = codes + (nf * G + g) * 64 + kb * 16 + i;
+            if (PASS_BY) store_nontemporal(at, make_uint4(d[0], d[1], d[2], d[3]));
+            else *at = make_uint4(d[0], d[1], d[2], d[3]);
+        }
     };
     if constexpr (CH > 0) {
 #pragma unroll
@@ -286,23 +294,24 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(const uint8_t* __restr
 }  // namespace
 
 // As few groups per thread as 1024 threads allow (64 groups at a time): short rows then leave registers for more waves.
-template <bool GROUP>
+template <bool GROUP, bool PASS_BY>
 static void launch_pack(const __half* w, const BlobLayout& L, uint8_t* blob, hipStream_t s)
 {
     const int64_t per = L.G <= 64 ? 1 : L.G <= 128 ? 2 : 4;
     const int64_t groups = std::min<int64_t>(64, (L.G + per - 1) / per);
     const dim3 grid((unsigned)(L.N / 4)), block((unsigned)((groups * 16 + 63) / 64 * 64));
-    if (L.G <= 64) pack_kernel<GROUP, 1><<<grid, block, 0, s>>>(w, L, blob);
-    else if (L.G <= 128) pack_kernel<GROUP, 2><<<grid, block, 0, s>>>(w, L, blob);
-    else if (L.G <= 256) pack_kernel<GROUP, 4><<<grid, block, 0, s>>>(w, L, blob);
-    else pack_kernel<GROUP, 0><<<grid, block, 0, s>>>(w, L, blob);
+    if (L.G <= 64) pack_kernel<GROUP, 1, PASS_BY><<<grid, block, 0, s>>>(w, L, blob);
+    else if (L.G <= 128) pack_kernel<GROUP, 2, PASS_BY><<<grid, block, 0, s>>>(w, L, blob);
+    else if (L.G <= 256) pack_kernel<GROUP, 4, PASS_BY><<<grid, block, 0, s>>>(w, L, blob);
+    else pack_kernel<GROUP, 0, PASS_BY><<<grid, block, 0, s>>>(w, L, blob);
 }
 
 hipError_t launch_pack_weights(const void* w_fp16, const BlobLayout& L, uint8_t* blob, hipStream_t s)
 {
     const __half* w = static_cast<const __half*>(w_fp16);
-    if (L.mode == 0) launch_pack<true>(w, L, blob, s);
-    else launch_pack<false>(w, L, blob, s);
+    if (L.mode != 0) launch_pack<false, false>(w, L, blob, s);
+    else if (2 * L.N * L.K <= (int64_t)224 << 20) launch_pack<true, true>(w, L, blob, s);
+    else launch_pack<true, false>(w, L, blob, s);
     return hipGetLastError();
 }
 

@@ -171,10 +171,14 @@ __global__ __launch_bounds__(kRankThreads) void channel_order_kernel(const float
 // dst[r, j] = src[r, perm[j]].  A workgroup brings ROWS rows into LDS as whole lines and gathers there: thread t makes
 // 8 output channels at a time, whose indices it fetches once for all its rows.  Two-byte gathers from memory, the first
 // version, took 134 us for 4096 x 14336 (117 MB each way; a copy takes 44 us), this one 49 us.  Indices are clamped to
-// the row.
+// the row.  NT: what is read is not wanted again, what is written is (cache_for_output).
+// Where the result fits the 256 MB memory-side cache, the packing that follows finds it there if the source was read past it (see
+// pack_kernel); beyond, every byte of the source kept counts (28672 x 8192 rotated and packed 541 us, 547 with the source read past it).
+bool cache_for_output(int64_t elements) { return 2 * elements <= (int64_t)224 << 20; }
+
 constexpr int kGatherThreads = 512;
 constexpr int64_t kGatherLds = 64 << 10;
-template <int ROWS>
+template <int ROWS, bool NT>
 __global__ __launch_bounds__(kGatherThreads) void gather_channels_kernel(const uint4* __restrict__ src, const int4* __restrict__ perm,
                                                                          int64_t rows, int K, uint4* __restrict__ dst)
 {
@@ -182,7 +186,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_channels_kernel(const u
     const int chunks = K / 8;
     const int64_t r0 = (int64_t)blockIdx.x * ROWS;
     const int here = (int)min((int64_t)ROWS, rows - r0);
-    for (int c = threadIdx.x; c < here * chunks; c += kGatherThreads) reinterpret_cast<uint4*>(s_row)[c] = src[r0 * chunks + c];
+    for (int c = threadIdx.x; c < here * chunks; c += kGatherThreads) reinterpret_cast<uint4*>(s_row)[c] = NT ? load_nontemporal(src + r0 * chunks + c) : src[r0 * chunks + c];
     __syncthreads();
     for (int c = threadIdx.x; c < chunks; c += kGatherThreads) {
         const int4 p0 = perm[2 * c], p1 = perm[2 * c + 1];
@@ -359,7 +363,7 @@ __device__ __forceinline__ void hadamard_segment(T (&v)[CH][8], T* buf, int64_t 
 // in them: whole numbers have one zero, while FP64 sums of FP16 numbers are -0 only where a -0 went in (-0 - (x - x) = -0).  22016 x 4096: a single workgroup per
 // block with one LDS round trip and one barrier per stage, bound by LDS and barriers, took 863 us, these layouts in FP64 111 us
 // (bound by vector issue), in whole numbers 93 us (a copy of the tensor 67; conversions, butterflies and LDS each about half of that).
-template <int CH>
+template <int CH, bool NT>
 __global__ __launch_bounds__(256) void hadamard_kernel(const uint4* __restrict__ src, int64_t chunks, int n, double scale,
                                                        uint4* __restrict__ dst)
 {
@@ -372,7 +376,7 @@ __global__ __launch_bounds__(256) void hadamard_kernel(const uint4* __restrict__
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         const int64_t at = c0 + c * 256 + t;
-        raw[c] = at < chunks ? src[at] : make_uint4(0u, 0u, 0u, 0u);
+        raw[c] = at < chunks ? NT ? load_nontemporal(src + at) : src[at] : make_uint4(0u, 0u, 0u, 0u);
     }
     float x[CH][8];
 #pragma unroll
@@ -482,9 +486,11 @@ hipError_t launch_gather_channels(const void* src, const int32_t* perm, int64_t 
         const int4* p = reinterpret_cast<const int4*>(perm);
         uint4* to = static_cast<uint4*>(dst);
         auto blocks = [&](int per) { return dim3((unsigned)((rows + per - 1) / per)); };
-        if (8 * K <= kGatherLds && rows >= 2048) gather_channels_kernel<4><<<blocks(4), kGatherThreads, (size_t)K * 8, s>>>(from, p, rows, (int)K, to);
-        else if (4 * K <= kGatherLds && rows >= 512) gather_channels_kernel<2><<<blocks(2), kGatherThreads, (size_t)K * 4, s>>>(from, p, rows, (int)K, to);
-        else gather_channels_kernel<1><<<blocks(1), kGatherThreads, (size_t)K * 2, s>>>(from, p, rows, (int)K, to);
+        const bool nt = cache_for_output(rows * K);
+        auto launch = [&](auto* kernel, int per) { kernel<<<blocks(per), kGatherThreads, (size_t)K * 2 * per, s>>>(from, p, rows, (int)K, to); };
+        if (8 * K <= kGatherLds && rows >= 2048) launch(nt ? gather_channels_kernel<4, true> : gather_channels_kernel<4, false>, 4);
+        else if (4 * K <= kGatherLds && rows >= 512) launch(nt ? gather_channels_kernel<2, true> : gather_channels_kernel<2, false>, 2);
+        else launch(nt ? gather_channels_kernel<1, true> : gather_channels_kernel<1, false>, 1);
         return hipGetLastError();
     }
     const int64_t n = rows * (K / 8);
@@ -505,8 +511,10 @@ hipError_t launch_hadamard(const void* src, int64_t rows, int64_t K, int64_t blo
         const int64_t chunks = rows * K / 8;
         const uint4* from = static_cast<const uint4*>(src);
         uint4* to = static_cast<uint4*>(dst);
-        if (block <= 4096) hadamard_kernel<2><<<(unsigned)((chunks + 511) / 512), 256, 0, s>>>(from, chunks, (int)block, scale, to);
-        else hadamard_kernel<4><<<(unsigned)((chunks + 1023) / 1024), 256, 0, s>>>(from, chunks, (int)block, scale, to);
+        const bool nt = cache_for_output(rows * K);
+        auto launch = [&](auto* kernel, int per) { kernel<<<(unsigned)((chunks + per - 1) / per), 256, 0, s>>>(from, chunks, (int)block, scale, to); };
+        if (block <= 4096) launch(nt ? hadamard_kernel<2, true> : hadamard_kernel<2, false>, 512);
+        else launch(nt ? hadamard_kernel<4, true> : hadamard_kernel<4, false>, 1024);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)(K / block), (unsigned)rows);
