@@ -341,12 +341,7 @@ def channel_order(salience):
     DEVICE_ORDER_MAX channels; longer ones on the host.  A salience that is not finite raises QoqError either way."""
     if salience.is_cuda and 0 < salience.numel() <= DEVICE_ORDER_MAX:
         sal = salience.detach().to(torch.float32).contiguous()
-        perm = torch.empty(sal.numel(), dtype=torch.int32, device=sal.device)
-        nonfinite = torch.empty(1, dtype=torch.int32, device=sal.device)
-        _check(lib().qoq_channel_order(_ptr(sal), sal.numel(), _ptr(perm), _ptr(nonfinite), _stream(sal.device)))
-        if nonfinite.item():
-            _check(QOQ_ERR_SHAPE)
-        return perm
+        return (_native or _load_native()).channel_order(sal)
     host = salience.detach().to("cpu", torch.float32).contiguous()
     perm = torch.empty(host.numel(), dtype=torch.int32)
     _check(lib().qoq_channel_order_host(host.data_ptr(), host.numel(), perm.data_ptr()))

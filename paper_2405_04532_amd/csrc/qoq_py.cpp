@@ -6,7 +6,7 @@
 #include <Python.h>
 
 #include <algorithm>
-
+#include <chrono>
 
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
@@ -397,9 +397,46 @@ PyObject* set_raise_status(PyObject*, PyObject* f)
     Py_RETURN_NONE;
 }
 
+// The order of salient channels, and whether it is one: the kernel's first workgroup says so in pinned host memory, about when
+// the others begin to sort, so the caller's next launches are issued while they do (through a device tensor's value, copied
+// when the kernel was done: 28 us a call and 11 of them without work on the GPU).  Where the stream has other work in front the wait is
+// the stream's.
+PyObject* channel_order(PyObject*, PyObject* const* a, Py_ssize_t n)    // salience
+{
+    HANDLE_TH_ERRORS
+    if (!counted(n, 1)) return nullptr;
+    const at::Tensor* sal = dev_tensor(a[0], at::kFloat, "salience");
+    if (!sal) return nullptr;
+    const hipStream_t s = static_cast<hipStream_t>(stream_of(*sal));
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        PyErr_SetString(PyExc_RuntimeError, "channel_order reads a result on the host: not while the stream is being captured");
+        return nullptr;
+    }
+    const int64_t K = sal->numel();
+    at::Tensor perm = new_like(*sal, {K}, at::kInt);
+    at::Tensor pinned = at::empty({1}, at::TensorOptions().dtype(at::kInt).pinned_memory(true));
+    int32_t* verdict = static_cast<int32_t*>(pinned.data_ptr());
+    const float* sp = static_cast<const float*>(sal->data_ptr());
+    int32_t* pp = static_cast<int32_t*>(perm.data_ptr());
+    __atomic_store_n(verdict, -1, __ATOMIC_RELEASE);
+    if (!call([&] {
+            const int status = qoq_channel_order(sp, K, pp, verdict, s);
+            if (status != QOQ_OK) return status;
+            const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(100);
+            while (__atomic_load_n(verdict, __ATOMIC_ACQUIRE) < 0 && std::chrono::steady_clock::now() < until) {}
+            if (__atomic_load_n(verdict, __ATOMIC_ACQUIRE) < 0 && hipStreamSynchronize(s) != hipSuccess) return (int)QOQ_ERR_HIP;
+            const int v = __atomic_load_n(verdict, __ATOMIC_ACQUIRE);
+            return v == 0 ? (int)QOQ_OK : v > 0 ? (int)QOQ_ERR_SHAPE : (int)QOQ_ERR_HIP;
+        }))
+        return nullptr;
+    return THPVariable_Wrap(perm);
+    END_HANDLE_TH_ERRORS
+}
+
 #define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(name)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {FAST(quant_act), FAST(quant_act_reordered), FAST(rmsnorm_quant), FAST(silu_mul_quant), FAST(w4a8_gemm),
-                         FAST(w4a8_gemm_noalloc), FAST(w4a8_gemm_token_sum), FAST(w4a8_linear), FAST(kv4_append), FAST(kv4_attention_decode),
+                         FAST(w4a8_gemm_noalloc), FAST(w4a8_gemm_token_sum), FAST(w4a8_linear), FAST(kv4_append), FAST(kv4_attention_decode), FAST(channel_order),
                          {"set_raise_status", set_raise_status, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
 #undef FAST
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_qoq_py", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

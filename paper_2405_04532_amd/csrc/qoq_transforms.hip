@@ -106,20 +106,34 @@ __global__ __launch_bounds__(1024) void channel_absmax_columns_kernel(const uint
 // it comes before, and counts those numbers; the sums over the counts are the 64 ranks.  Seven steps per channel and workgroup
 // where comparing every pair took 64 (14336 channels: 25.5 us; a host sort with its copies 0.7 ms): 10.8 us, 19 if all are equal, which all
 // meet in one counter, for K <= kRankMaxK.
-// bad[0] = 1 if some salience is not finite (the order is then meaningless), else 0.
-constexpr int kRankMaxK = 32768, kRankThreads = 1024, kRankAhead = 8;
+// bad[0] = 1 if some salience is not finite (the order is then meaningless), else 0: the first workgroup's work, which it stores past
+// the caches as soon as it knows it.  A host that waits for it in pinned memory goes on while the others sort (4096 x 14336
+// reordered and packed 109.6 -> 95.7 us a pass).
+constexpr int kRankMaxK = 32768, kRankThreads = 1024, kRankAhead = 8, kCheckAhead = 16;
 __global__ __launch_bounds__(kRankThreads) void channel_order_kernel(const float* __restrict__ salience, int K, int32_t* __restrict__ perm,
                                                                      int32_t* __restrict__ bad)
 {
     __shared__ uint32_t s_sorted[64];                    // keys of the workgroup's channels, ascending
     __shared__ uint32_t s_count[64 + 1];                 // channels elsewhere that come before exactly so many of them
-    __shared__ int s_bad;
+    if (blockIdx.x == 0) {
+        bool finite = true;
+        for (int j0 = 0; j0 < K; j0 += kRankThreads * kCheckAhead) {
+            float f[kCheckAhead];
+#pragma unroll
+            for (int a = 0; a < kCheckAhead; ++a) f[a] = salience[min(j0 + a * kRankThreads + (int)threadIdx.x, K - 1)];
+#pragma unroll
+            for (int a = 0; a < kCheckAhead; ++a) finite &= fabsf(f[a]) < __builtin_inff();
+        }
+        const int all = __syncthreads_and(finite);
+        if (threadIdx.x == 0) __hip_atomic_store(bad, all ? 0 : 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        return;
+    }
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     auto key_of = [](float f) {                          // unsigned integers in the order of the floats, -0 = +0
         const uint32_t b = __float_as_uint(f + 0.0f);
         return b & 0x80000000u ? ~b : b | 0x80000000u;
     };
-    const int k0 = (int)blockIdx.x * 64, k = k0 + lane;
+    const int k0 = ((int)blockIdx.x - 1) * 64, k = k0 + lane;
     uint32_t before = 0;                                 // of the workgroup's own channels, those before this lane's (wave 0)
     if (wave == 0) {
         const uint32_t mine = k < K ? key_of(salience[k]) : 0u;              // past the end: behind every finite one
@@ -129,10 +143,9 @@ __global__ __launch_bounds__(kRankThreads) void channel_order_kernel(const float
         }
         s_sorted[63 - before] = mine;                    // (a permutation of 0 ... 63)
         s_count[lane] = 0;
-        if (lane == 0) { s_count[64] = 0; s_bad = 0; }
+        if (lane == 0) s_count[64] = 0;
     }
     __syncthreads();
-    bool nonfinite = false;
     for (int j0 = 0; j0 < K; j0 += kRankThreads * kRankAhead) {
         float f[kRankAhead];
 #pragma unroll
@@ -141,7 +154,6 @@ __global__ __launch_bounds__(kRankThreads) void channel_order_kernel(const float
 #pragma unroll
         for (int a = 0; a < kRankAhead; ++a) {
             const int j = j0 + a * kRankThreads + (int)threadIdx.x;
-            nonfinite |= !(fabsf(f[a]) < __builtin_inff());
             v[a] = key_of(f[a]) - (j < k0 ? 0u : 1u);    // ties: a channel in front comes before an equal one, one behind does not
             at[a] = 0;
         }
@@ -157,7 +169,6 @@ __global__ __launch_bounds__(kRankThreads) void channel_order_kernel(const float
             if (j < K && (uint32_t)(j - k0) >= 64u) atomicAdd(&s_count[at[a]], 1u);
         }
     }
-    if (nonfinite) s_bad = 1;
     __syncthreads();
     if (wave != 0) return;
     // channel at ascending place p: everybody that comes before more than p of the 64
@@ -165,7 +176,6 @@ __global__ __launch_bounds__(kRankThreads) void channel_order_kernel(const float
     uint32_t rank = before;
     for (int c = 1; c <= 64; ++c) rank += c > p ? s_count[c] : 0u;
     if (k < K) perm[min((int)rank, K - 1)] = k;          // (the bound only matters for NaNs)
-    if (blockIdx.x == 0 && lane == 0) bad[0] = s_bad;
 }
 
 // dst[r, j] = src[r, perm[j]].  A workgroup brings ROWS rows into LDS as whole lines and gathers there: thread t makes
@@ -469,7 +479,7 @@ int channel_order_max_k() { return kRankMaxK; }
 
 hipError_t launch_channel_order(const float* salience, int64_t K, int32_t* perm, int32_t* bad, hipStream_t s)
 {
-    channel_order_kernel<<<(unsigned)((K + 63) / 64), kRankThreads, 0, s>>>(salience, (int)K, perm, bad);
+    channel_order_kernel<<<(unsigned)((K + 63) / 64 + 1), kRankThreads, 0, s>>>(salience, (int)K, perm, bad);
     return hipGetLastError();
 }
 

@@ -48,6 +48,37 @@ def test_channel_order_on_the_device(K):
             api.channel_order(t.to(DEV))
 
 
+def test_channel_order_behind_other_work_and_under_capture():
+    """The verdict on the salience comes from the kernel while the host waits: behind work of milliseconds on a stream of its own, good
+    and bad in turn; a stream that is being captured cannot be waited for, and the capture goes on."""
+    s = torch.rand(5000, generator=torch.Generator().manual_seed(3))
+    bad = s.clone()
+    bad[4999] = float("nan")
+    ref = tr.channel_order(s.numpy())
+    good, worse = s.to(DEV), bad.to(DEV)
+    big = torch.ones(1 << 28, dtype=torch.float32, device=DEV)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        for _ in range(3):
+            for _ in range(4):
+                big.mul_(1.0)                                    # 2 GiB each: 0.4 ms
+            assert np.array_equal(api.channel_order(good).cpu().numpy(), ref)
+            big.mul_(1.0)
+            with pytest.raises(api.QoqError):
+                api.channel_order(worse)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        out = torch.zeros(8, device=DEV)
+        with torch.cuda.graph(graph, stream=side):
+            with pytest.raises(RuntimeError):
+                api.channel_order(good)
+            out += 1
+        graph.replay()
+    torch.cuda.synchronize()
+    assert (out == 1).all()
+
+
 @pytest.mark.parametrize("rows,K", [(1, 8), (5, 8192), (3, 8200), (7, 16392), (2, 32768), (2, 32776)])
 def test_gather_and_salience_edges(rows, K):
     """Four, two and one rows in LDS with a remainder, and rows that do not fit; row slabs of the salience."""
