@@ -366,6 +366,74 @@ __device__ __forceinline__ void hadamard_segment(T (&v)[CH][8], T* buf, int64_t 
     }
 }
 
+// The same for 4096 CH / 2 elements of which a workgroup exchanges the two halves of the FP64 numbers one after the other, in half the
+// LDS: twice the workgroups to a compute unit hide each other's barriers and loads (blocks of 8192: 8192 x 8192 119 -> 100 us, 2048 x
+// 8192 33.3 -> 31.3).  With 4096 elements, where the registers allow no more workgroups, it is no faster.
+template <int CH>
+__device__ __forceinline__ void hadamard_segment_halves(double (&v)[8 * CH], uint32_t* words, int64_t c0, int64_t chunks, int n, double scale,
+                                                        uint4* __restrict__ dst)
+{
+    constexpr int E = 8 * CH;
+    auto pos = [](int i) { return i + (i >> 3) + ((i >> 7) << 3); };
+    const int t = threadIdx.x;
+    auto butterfly = [](double& a, double& b) { const double s = a + b; b = a - b; a = s; };
+    // element number of a thread's j-th register in each layout
+    auto in_a = [&](int j) { return ((j >> 3) * 256 + t) * 8 + (j & 7); };
+    auto in_b = [&](int j) { return (t & 7) + (t >> 3) * 128 + (j >> 4) * 4096 + (j & 15) * 8; };
+    auto in_c = [&](int j) { return (t & 127) + (t >> 7) * 2048 + (j >> 4) * 4096 + (j & 15) * 128; };
+    auto exchange = [&](auto from, auto to) __attribute__((always_inline)) {
+        uint32_t low[E];
+#pragma unroll
+        for (int j = 0; j < E; ++j) words[pos(from(j))] = (uint32_t)__double2loint(v[j]);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < E; ++j) low[j] = words[pos(to(j))];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < E; ++j) words[pos(from(j))] = (uint32_t)__double2hiint(v[j]);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < E; ++j) v[j] = __hiloint2double((int)words[pos(to(j))], (int)low[j]);
+    };
+    // four stages on each sixteen registers, which are `step` elements apart
+    auto stages16 = [&](int step) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 1; h < 16; h <<= 1)
+            if (h * step < n)
+#pragma unroll
+                for (int j = 0; j < E; ++j)
+                    if (!(j & h)) butterfly(v[j], v[j | h]);
+    };
+    // ---- A
+#pragma unroll
+    for (int h = 1; h < 8; h <<= 1)
+        if (h < n)
+#pragma unroll
+            for (int j = 0; j < E; ++j)
+                if (!(j & h)) butterfly(v[j], v[j | h]);
+#pragma unroll
+    for (int h = 8; h < E; h <<= 1)
+        if (256 * h < n)
+#pragma unroll
+            for (int j = 0; j < E; ++j)
+                if (!(j & h)) butterfly(v[j], v[j | h]);
+    // ---- B and C (a thread writes where it has read: no barrier between)
+    exchange(in_a, in_b);
+    stages16(8);
+    exchange(in_b, in_c);
+    stages16(128);
+    __syncthreads();                                     // everybody has read: the buffer takes the results
+    unsigned short* out = reinterpret_cast<unsigned short*>(words);
+#pragma unroll
+    for (int j = 0; j < E; ++j) out[in_c(j)] = half_rne_by_odd(v[j] * scale);
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const int64_t at = c0 + c * 256 + t;
+        if (at < chunks) dst[at] = reinterpret_cast<const uint4*>(words)[c * 256 + t];
+    }
+}
+
 // An FP16 number is a whole multiple of 2^-24, so where the magnitudes of a segment add up to less than 128 every partial sum
 // fits 32-bit integers in that unit and the butterflies are integer additions: a quarter of the issue time of FP64 ones and half of
 // the LDS traffic, the same exact sums.  Weight rows are like that (4096 values of standard deviation 0.02 add up to 65);
@@ -374,11 +442,12 @@ __device__ __forceinline__ void hadamard_segment(T (&v)[CH][8], T* buf, int64_t 
 // block with one LDS round trip and one barrier per stage, bound by LDS and barriers, took 863 us, these layouts in FP64 111 us
 // (bound by vector issue), in whole numbers 93 us (a copy of the tensor 67; conversions, butterflies and LDS each about half of that).
 template <int CH, bool NT>
-__global__ __launch_bounds__(256) void hadamard_kernel(const uint4* __restrict__ src, int64_t chunks, int n, double scale,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void hadamard_kernel(const uint4* __restrict__ src, int64_t chunks, int n, double scale,
                                                        uint4* __restrict__ dst)
 {
     constexpr int kElems = 2048 * CH;
-    __shared__ double buf[kElems + kElems / 8 + kElems / 16];
+    using Word = std::conditional_t<CH == 2, double, uint32_t>;
+    __shared__ __attribute__((aligned(16))) Word buf[kElems + kElems / 8 + kElems / 16];
     __shared__ float s_sum[4];
     const int t = threadIdx.x;
     const int64_t c0 = (int64_t)blockIdx.x * (256 * CH);
@@ -422,12 +491,19 @@ __global__ __launch_bounds__(256) void hadamard_kernel(const uint4* __restrict__
             return;
         }
     }
-    double v[CH][8];
+    if constexpr (CH == 2) {
+        double v[CH][8];
 #pragma unroll
-    for (int c = 0; c < CH; ++c)
+        for (int c = 0; c < CH; ++c)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[c][e] = (double)x[c][e];
-    hadamard_segment(v, buf, c0, chunks, n, scale, dst);
+            for (int e = 0; e < 8; ++e) v[c][e] = (double)x[c][e];
+        hadamard_segment(v, buf, c0, chunks, n, scale, dst);
+    } else {
+        double v[8 * CH];
+#pragma unroll
+        for (int j = 0; j < 8 * CH; ++j) v[j] = (double)x[j >> 3][j & 7];
+        hadamard_segment_halves<CH>(v, buf, c0, chunks, n, scale, dst);
+    }
 }
 
 // The same for tensors that are no whole number of 16-byte chunks or not aligned to them, and for a few short blocks: one
