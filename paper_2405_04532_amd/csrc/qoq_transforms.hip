@@ -269,241 +269,217 @@ __device__ __forceinline__ float wave_sum_of(float v)
     return (lane(0) + lane(16)) + (lane(32) + lane(48));
 }
 
-// Blocks of rows * K contiguous elements are cut into segments of 2048 * CH elements, one workgroup of 256 threads each
-// (a segment holds whole blocks; CH = 4 only for n = 8192).  A thread keeps 8 * CH elements in registers and takes the
-// stages in three layouts, with two exchanges through LDS instead of one per stage:
+// Blocks of rows * K contiguous elements are cut into segments of 4096 elements (8192 for blocks of 8192), one workgroup of 256 threads
+// each; a segment holds whole blocks.  A thread keeps E = 16 (32) elements in registers and takes the stages in three layouts, with
+// two exchanges through LDS instead of one per stage:
 //     A  16-byte chunks as they are loaded: element bits 0..2, and 11.. (chunks 256 apart)
-//     B  element bits 3..6 in registers
-//     C  element bits 7..10 in registers
-// and the FP16 results go back to chunk order through LDS for 16-byte stores.  LDS position of element i: one element of padding
-// per 8 and eight more per 128, which spreads all three access patterns evenly over the 64 banks (two lanes to a bank at most).
-template <class T, int CH>
-__device__ __forceinline__ void hadamard_segment(T (&v)[CH][8], T* buf, int64_t c0, int64_t chunks, int n, double scale, uint4* __restrict__ dst)
+//     B  element bits 3..6 in registers, and 12
+//     C  element bits 7..10 in registers, and 12
+// and the FP16 results go back to chunk order through LDS for 16-byte stores.  LDS position of element i: i + i / 8 + 8 (i / 128),
+// which spreads all three access patterns evenly over the 64 banks (two lanes to a bank at most); a thread's places are a constant
+// distance apart in each layout, so one address serves them all.  The block size is known when the kernel is compiled: with stages
+// under conditions the compiler copied every register at each.
+struct HadamardPlaces {
+    int a, b, c;
+    __device__ __forceinline__ HadamardPlaces(int t) : a(9 * t + (t >> 4) * 8), b((t & 7) + (t >> 3) * 152), c((t & 127) + ((t & 127) >> 3) + (t >> 7) * 2432) {}
+    // of the thread's j-th register
+    __device__ __forceinline__ int in_a(int j) const { return a + (j >> 3) * 2432 + (j & 7); }
+    __device__ __forceinline__ int in_b(int j) const { return b + (j >> 4) * 4864 + (j & 15) * 9; }
+    __device__ __forceinline__ int in_c(int j) const { return c + (j >> 4) * 4864 + (j & 15) * 152; }
+};
+// the stages whose element bits FROM + i are register bits AT + i, i < BITS, as far as the block of 2^LOGN goes
+template <int LOGN, int E, int AT, int FROM, int BITS, class T>
+__device__ __forceinline__ void hadamard_stages(T (&v)[E])
 {
-    auto pos = [](int i) { return i + (i >> 3) + ((i >> 7) << 3); };
+#pragma unroll
+    for (int i = 0; i < BITS; ++i)
+        if (FROM + i < LOGN)
+#pragma unroll
+            for (int j = 0; j < E; ++j)
+                if (!(j & (1 << (AT + i)))) {
+                    const T s = v[j] + v[j | (1 << (AT + i))];
+                    v[j | (1 << (AT + i))] = v[j] - v[j | (1 << (AT + i))];
+                    v[j] = s;
+                }
+}
+// results of a thread, in layout C as pairs of FP16 numbers, to chunk order and to memory
+template <int E>
+__device__ __forceinline__ void hadamard_store(const uint32_t (&r)[E / 2], unsigned short* out, int64_t c0, int64_t chunks, uint4* __restrict__ dst)
+{
     const int t = threadIdx.x;
-    auto butterfly = [](T& a, T& b) { const T s = a + b; b = a - b; a = s; };
-    // ---- A
-#pragma unroll
-    for (int h = 1; h < 8; h <<= 1)
-        if (h < n)
-#pragma unroll
-            for (int c = 0; c < CH; ++c)
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (!(e & h)) butterfly(v[c][e], v[c][e | h]);
-#pragma unroll
-    for (int h = 1; h < CH; h <<= 1)
-        if (2048 * h < n)
-#pragma unroll
-            for (int c = 0; c < CH; ++c)
-                if (!(c & h))
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) butterfly(v[c][e], v[c | h][e]);
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) buf[pos((c * 256 + t) * 8 + e)] = v[c][e];
-    __syncthreads();
-    // ---- B and C: sixteen elements at a time, `step` elements apart, from element `first` on
-    auto stages16 = [&](int first, int step) __attribute__((always_inline)) {
-        T x[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) x[j] = buf[pos(first + j * step)];
-#pragma unroll
-        for (int h = 1; h < 16; h <<= 1)
-            if (h * step < n)
-#pragma unroll
-                for (int j = 0; j < 16; ++j)
-                    if (!(j & h)) butterfly(x[j], x[j | h]);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) v[j >> 3][j & 7] = x[j];
-    };
-#pragma unroll
-    for (int s = 0; s < CH / 2; ++s) {
-        const int first = (t & 7) + (t >> 3) * 128 + s * 4096;
-        stages16(first, 8);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) buf[pos(first + j * 8)] = v[j >> 3][j & 7];
-    }
-    __syncthreads();
-    uint32_t r[CH / 2][8];                               // pairs of FP16 results
-    const float below = (float)(scale * (1.0 - 4 * 0x1p-24)), above = (float)(scale * (1.0 + 4 * 0x1p-24));
-#pragma unroll
-    for (int s = 0; s < CH / 2; ++s) {
-        stages16((t & 127) + (t >> 7) * 2048 + s * 4096, 128);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const T x0 = v[j >> 2][2 * j & 7], x1 = v[j >> 2][(2 * j + 1) & 7];
-            if constexpr (std::is_same<T, int>::value) {
-                // x * scale from both sides in FP32: the conversion, the factor and the product are off by 2^-24 each, the factors'
-                // distance from the scale is 3.5 to 4.5 times that.  Rounding is monotonic: where both sides give the same FP16
-                // number the exact product does, else (1 element in 1000) FP64 decides.
-                typedef float f2 __attribute__((ext_vector_type(2)));
-                typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
-                const float f0 = (float)x0, f1 = (float)x1;
-                const uint32_t lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){f0 * below, f1 * below}, hv2));
-                const uint32_t hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){f0 * above, f1 * above}, hv2));
-                r[s][j] = lo;
-                if (lo != hi)
-                    r[s][j] = (uint32_t)half_rne_by_odd((double)x0 * scale) | ((uint32_t)half_rne_by_odd((double)x1 * scale) << 16);
-            } else {
-                r[s][j] = (uint32_t)half_rne_by_odd((double)x0 * scale) | ((uint32_t)half_rne_by_odd((double)x1 * scale) << 16);
-            }
-        }
-    }
     __syncthreads();                                     // everybody has read: the buffer takes the results
-    unsigned short* out = reinterpret_cast<unsigned short*>(buf);
 #pragma unroll
-    for (int s = 0; s < CH / 2; ++s)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) out[(t & 127) + (t >> 7) * 2048 + s * 4096 + j * 128] = (unsigned short)(r[s][j >> 1] >> (16 * (j & 1)));
+    for (int j = 0; j < E; ++j) out[(t & 127) + (t >> 7) * 2048 + (j >> 4) * 4096 + (j & 15) * 128] = (unsigned short)(r[j >> 1] >> (16 * (j & 1)));
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
+    for (int c = 0; c < E / 8; ++c) {
         const int64_t at = c0 + c * 256 + t;
-        if (at < chunks) dst[at] = reinterpret_cast<const uint4*>(buf)[c * 256 + t];
+        if (at < chunks) dst[at] = reinterpret_cast<const uint4*>(out)[c * 256 + t];
     }
 }
 
-// The same for 4096 CH / 2 elements of which a workgroup exchanges the two halves of the FP64 numbers one after the other, in half the
-// LDS: twice the workgroups to a compute unit hide each other's barriers and loads (blocks of 8192: 8192 x 8192 119 -> 100 us, 2048 x
-// 8192 33.3 -> 31.3).  With 4096 elements, where the registers allow no more workgroups, it is no faster.
-template <int CH>
-__device__ __forceinline__ void hadamard_segment_halves(double (&v)[8 * CH], uint32_t* words, int64_t c0, int64_t chunks, int n, double scale,
-                                                        uint4* __restrict__ dst)
+// Whole numbers in units of scale' = scale / 2^-24, the scale already divided.
+template <int LOGN>
+__device__ __forceinline__ void hadamard_whole(int (&v)[16], int* buf, int64_t c0, int64_t chunks, double scale, uint4* __restrict__ dst)
 {
-    constexpr int E = 8 * CH;
-    auto pos = [](int i) { return i + (i >> 3) + ((i >> 7) << 3); };
-    const int t = threadIdx.x;
-    auto butterfly = [](double& a, double& b) { const double s = a + b; b = a - b; a = s; };
-    // element number of a thread's j-th register in each layout
-    auto in_a = [&](int j) { return ((j >> 3) * 256 + t) * 8 + (j & 7); };
-    auto in_b = [&](int j) { return (t & 7) + (t >> 3) * 128 + (j >> 4) * 4096 + (j & 15) * 8; };
-    auto in_c = [&](int j) { return (t & 127) + (t >> 7) * 2048 + (j >> 4) * 4096 + (j & 15) * 128; };
-    auto exchange = [&](auto from, auto to) __attribute__((always_inline)) {
-        uint32_t low[E];
+    const HadamardPlaces at((int)threadIdx.x);
+    hadamard_stages<LOGN, 16, 0, 0, 3>(v);
+    hadamard_stages<LOGN, 16, 3, 11, 1>(v);
 #pragma unroll
-        for (int j = 0; j < E; ++j) words[pos(from(j))] = (uint32_t)__double2loint(v[j]);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < E; ++j) low[j] = words[pos(to(j))];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < E; ++j) words[pos(from(j))] = (uint32_t)__double2hiint(v[j]);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < E; ++j) v[j] = __hiloint2double((int)words[pos(to(j))], (int)low[j]);
-    };
-    // four stages on each sixteen registers, which are `step` elements apart
-    auto stages16 = [&](int step) __attribute__((always_inline)) {
-#pragma unroll
-        for (int h = 1; h < 16; h <<= 1)
-            if (h * step < n)
-#pragma unroll
-                for (int j = 0; j < E; ++j)
-                    if (!(j & h)) butterfly(v[j], v[j | h]);
-    };
-    // ---- A
-#pragma unroll
-    for (int h = 1; h < 8; h <<= 1)
-        if (h < n)
-#pragma unroll
-            for (int j = 0; j < E; ++j)
-                if (!(j & h)) butterfly(v[j], v[j | h]);
-#pragma unroll
-    for (int h = 8; h < E; h <<= 1)
-        if (256 * h < n)
-#pragma unroll
-            for (int j = 0; j < E; ++j)
-                if (!(j & h)) butterfly(v[j], v[j | h]);
-    // ---- B and C (a thread writes where it has read: no barrier between)
-    exchange(in_a, in_b);
-    stages16(8);
-    exchange(in_b, in_c);
-    stages16(128);
-    __syncthreads();                                     // everybody has read: the buffer takes the results
-    unsigned short* out = reinterpret_cast<unsigned short*>(words);
-#pragma unroll
-    for (int j = 0; j < E; ++j) out[in_c(j)] = half_rne_by_odd(v[j] * scale);
+    for (int j = 0; j < 16; ++j) buf[at.in_a(j)] = v[j];
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const int64_t at = c0 + c * 256 + t;
-        if (at < chunks) dst[at] = reinterpret_cast<const uint4*>(words)[c * 256 + t];
+    for (int j = 0; j < 16; ++j) v[j] = buf[at.in_b(j)];
+    hadamard_stages<LOGN, 16, 0, 3, 4>(v);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) buf[at.in_b(j)] = v[j];  // (where it has read: no barrier between)
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = buf[at.in_c(j)];
+    hadamard_stages<LOGN, 16, 0, 7, 4>(v);
+    // x * scale from both sides in FP32: the conversion, the factor and the product are off by 2^-24 each, the factors'
+    // distance from the scale is 3.5 to 4.5 times that.  Rounding is monotonic: where both sides give the same FP16
+    // number the exact product does, else (1 element in 1000) FP64 decides.
+    const float below = (float)(scale * (1.0 - 4 * 0x1p-24)), above = (float)(scale * (1.0 + 4 * 0x1p-24));
+    uint32_t r[8], undecided = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        typedef float f2 __attribute__((ext_vector_type(2)));
+        typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
+        const float f0 = (float)v[2 * j], f1 = (float)v[2 * j + 1];
+        r[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){f0 * below, f1 * below}, hv2));
+        const uint32_t hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2){f0 * above, f1 * above}, hv2));
+        undecided |= r[j] != hi ? 1u << j : 0u;
     }
+    if (undecided) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (undecided >> j & 1) r[j] = (uint32_t)half_rne_by_odd((double)v[2 * j] * scale) | ((uint32_t)half_rne_by_odd((double)v[2 * j + 1] * scale) << 16);
+    }
+    hadamard_store<16>(r, reinterpret_cast<unsigned short*>(buf), c0, chunks, dst);
+}
+
+template <int LOGN>
+__device__ __forceinline__ void hadamard_fp64(double (&v)[16], double* buf, int64_t c0, int64_t chunks, double scale, uint4* __restrict__ dst)
+{
+    const HadamardPlaces at((int)threadIdx.x);
+    hadamard_stages<LOGN, 16, 0, 0, 3>(v);
+    hadamard_stages<LOGN, 16, 3, 11, 1>(v);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) buf[at.in_a(j)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = buf[at.in_b(j)];
+    hadamard_stages<LOGN, 16, 0, 3, 4>(v);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) buf[at.in_b(j)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = buf[at.in_c(j)];
+    hadamard_stages<LOGN, 16, 0, 7, 4>(v);
+    uint32_t r[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) r[j] = (uint32_t)half_rne_by_odd(v[2 * j] * scale) | ((uint32_t)half_rne_by_odd(v[2 * j + 1] * scale) << 16);
+    hadamard_store<16>(r, reinterpret_cast<unsigned short*>(buf), c0, chunks, dst);
+}
+
+__device__ __forceinline__ uint4 hadamard_load(const uint4* __restrict__ src, int64_t at, int64_t chunks, bool nt)
+{
+    if (at >= chunks) return make_uint4(0u, 0u, 0u, 0u);
+    return nt ? load_nontemporal(src + at) : src[at];
 }
 
 // An FP16 number is a whole multiple of 2^-24, so where the magnitudes of a segment add up to less than 128 every partial sum
 // fits 32-bit integers in that unit and the butterflies are integer additions: a quarter of the issue time of FP64 ones and half of
 // the LDS traffic, the same exact sums.  Weight rows are like that (4096 values of standard deviation 0.02 add up to 65);
 // other segments, infinities and NaN among them, and blocks of less than eight or of 8192 take FP64, and so do segments with a -0
-// in them: whole numbers have one zero, while FP64 sums of FP16 numbers are -0 only where a -0 went in (-0 - (x - x) = -0).  22016 x 4096: a single workgroup per
-// block with one LDS round trip and one barrier per stage, bound by LDS and barriers, took 863 us, these layouts in FP64 111 us
-// (bound by vector issue), in whole numbers 93 us (a copy of the tensor 67; conversions, butterflies and LDS each about half of that).
-template <int CH, bool NT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void hadamard_kernel(const uint4* __restrict__ src, int64_t chunks, int n, double scale,
-                                                       uint4* __restrict__ dst)
+// in them: whole numbers have one zero, while FP64 sums of FP16 numbers are -0 only where a -0 went in (-0 - (x - x) = -0).
+// 22016 x 4096: a single workgroup per block with one LDS round trip and one barrier per stage, bound by LDS and barriers, took 863 us,
+// these layouts 108 (a copy of the tensor 69) while they were bound by 40 vector instructions per element, half of them
+// addresses and copies of registers.
+template <int LOGN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void hadamard_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t chunks,
+                                                                                                 double scale, bool nt)
 {
-    constexpr int kElems = 2048 * CH;
-    using Word = std::conditional_t<CH == 2, double, uint32_t>;
-    __shared__ __attribute__((aligned(16))) Word buf[kElems + kElems / 8 + kElems / 16];
+    constexpr int kElems = 4096;
+    __shared__ __attribute__((aligned(16))) double buf[kElems + kElems / 8 + kElems / 16];
     __shared__ float s_sum[4];
+    typedef short s2 __attribute__((ext_vector_type(2)));
+    typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
     const int t = threadIdx.x;
-    const int64_t c0 = (int64_t)blockIdx.x * (256 * CH);
-    uint4 raw[CH];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const int64_t at = c0 + c * 256 + t;
-        raw[c] = at < chunks ? NT ? load_nontemporal(src + at) : src[at] : make_uint4(0u, 0u, 0u, 0u);
-    }
-    float x[CH][8];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const uint32_t w[4] = {raw[c].x, raw[c].y, raw[c].z, raw[c].w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[c][e] = __half2float(__ushort_as_half((unsigned short)(w[e >> 1] >> (16 * (e & 1)))));
-    }
-    if constexpr (CH == 2) {                             // (8192 weights of the usual size add up to more than 128)
-        typedef short s2 __attribute__((ext_vector_type(2)));
-        float sum = n < 8 ? __builtin_inff() : 0.f;
+    const int64_t c0 = (int64_t)blockIdx.x * 512;
+    const uint4 raw[2] = {hadamard_load(src, c0 + t, chunks, nt), hadamard_load(src, c0 + 256 + t, chunks, nt)};
+    const uint32_t w[8] = {raw[0].x, raw[0].y, raw[0].z, raw[0].w, raw[1].x, raw[1].y, raw[1].z, raw[1].w};
+    if constexpr (LOGN >= 3) {
+        float sum = 0.f;
         s2 lowest = {0, 0};                              // of the bits as 16-bit integers, among which those of -0 are the lowest
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const uint32_t w[4] = {raw[c].x, raw[c].y, raw[c].z, raw[c].w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) lowest = __builtin_elementwise_min(lowest, __builtin_bit_cast(s2, w[i]));
-#pragma unroll
-            for (int e = 0; e < 8; ++e) sum += fabsf(x[c][e]);
+        for (int i = 0; i < 8; ++i) {
+            lowest = __builtin_elementwise_min(lowest, __builtin_bit_cast(s2, w[i]));
+            sum = __builtin_amdgcn_fdot2(__builtin_bit_cast(hv2, w[i] & 0x7FFF7FFFu), (hv2){(_Float16)1.f, (_Float16)1.f}, sum, false);
         }
         if (min(lowest.x, lowest.y) == -32768) sum = __builtin_inff();
         sum = wave_sum_of(sum);
         if ((t & 63) == 0) s_sum[t >> 6] = sum;
         __syncthreads();
-        // the FP32 sum is off by less than 2^-16 of itself
-        if ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]) < 127.9f) {
-            int whole[CH][8];                            // in units of 2^-24
+        // the FP32 sum is off by less than 2^-16 of itself, and by the subnormal numbers, 4096 of less than 2^-14, if the
+        // instruction takes them for zeros
+        if ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]) < 127.5f) {
+            int whole[16];                               // in units of 2^-24
 #pragma unroll
-            for (int c = 0; c < CH; ++c)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) whole[c][e] = (int)(x[c][e] * 0x1p24f);
-            hadamard_segment(whole, reinterpret_cast<int*>(buf), c0, chunks, n, scale * 0x1p-24, dst);
+            for (int j = 0; j < 16; ++j) whole[j] = (int)(__half2float(__ushort_as_half((unsigned short)(w[j >> 1] >> (16 * (j & 1))))) * 0x1p24f);
+            hadamard_whole<LOGN>(whole, reinterpret_cast<int*>(buf), c0, chunks, scale * 0x1p-24, dst);
             return;
         }
     }
-    if constexpr (CH == 2) {
-        double v[CH][8];
+    double v[16];
 #pragma unroll
-        for (int c = 0; c < CH; ++c)
+    for (int j = 0; j < 16; ++j) v[j] = (double)__half2float(__ushort_as_half((unsigned short)(w[j >> 1] >> (16 * (j & 1)))));
+    hadamard_fp64<LOGN>(v, buf, c0, chunks, scale, dst);
+}
+
+// Blocks of 8192 (weights of the usual size then add up to more than 128): the two halves of the FP64 numbers are exchanged one after
+// the other, in half the LDS, which makes four workgroups to a compute unit, not two, and they hide each other's barriers and
+// loads (8192 x 8192 119 -> 100 us, 2048 x 8192 33.3 -> 31.3).
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void hadamard_8192_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t chunks,
+                                                                                                      double scale, bool nt)
+{
+    constexpr int kElems = 8192, E = 32;
+    __shared__ __attribute__((aligned(16))) uint32_t words[kElems + kElems / 8 + kElems / 16];
+    const HadamardPlaces at((int)threadIdx.x);
+    const int64_t c0 = (int64_t)blockIdx.x * 1024;
+    double v[E];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[c][e] = (double)x[c][e];
-        hadamard_segment(v, buf, c0, chunks, n, scale, dst);
-    } else {
-        double v[8 * CH];
+    for (int c = 0; c < 4; ++c) {
+        const uint4 raw = hadamard_load(src, c0 + c * 256 + (int)threadIdx.x, chunks, nt);
+        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
-        for (int j = 0; j < 8 * CH; ++j) v[j] = (double)x[j >> 3][j & 7];
-        hadamard_segment_halves<CH>(v, buf, c0, chunks, n, scale, dst);
+        for (int e = 0; e < 8; ++e) v[8 * c + e] = (double)__half2float(__ushort_as_half((unsigned short)(w[e >> 1] >> (16 * (e & 1)))));
     }
+    auto exchange = [&](auto from, auto to) __attribute__((always_inline)) {
+        uint32_t low[E];
+#pragma unroll
+        for (int j = 0; j < E; ++j) words[from(j)] = (uint32_t)__double2loint(v[j]);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < E; ++j) low[j] = words[to(j)];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < E; ++j) words[from(j)] = (uint32_t)__double2hiint(v[j]);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < E; ++j) v[j] = __hiloint2double((int)words[to(j)], (int)low[j]);
+    };
+    hadamard_stages<13, E, 0, 0, 3>(v);
+    hadamard_stages<13, E, 3, 11, 2>(v);
+    exchange([&](int j) { return at.in_a(j); }, [&](int j) { return at.in_b(j); });
+    hadamard_stages<13, E, 0, 3, 4>(v);
+    exchange([&](int j) { return at.in_b(j); }, [&](int j) { return at.in_c(j); });
+    hadamard_stages<13, E, 0, 7, 4>(v);
+    uint32_t r[E / 2];
+#pragma unroll
+    for (int j = 0; j < E / 2; ++j) r[j] = (uint32_t)half_rne_by_odd(v[2 * j] * scale) | ((uint32_t)half_rne_by_odd(v[2 * j + 1] * scale) << 16);
+    hadamard_store<E>(r, reinterpret_cast<unsigned short*>(words), c0, chunks, dst);
 }
 
 // The same for tensors that are no whole number of 16-byte chunks or not aligned to them, and for a few short blocks: one
@@ -598,9 +574,24 @@ hipError_t launch_hadamard(const void* src, int64_t rows, int64_t K, int64_t blo
         const uint4* from = static_cast<const uint4*>(src);
         uint4* to = static_cast<uint4*>(dst);
         const bool nt = cache_for_output(rows * K);
-        auto launch = [&](auto* kernel, int per) { kernel<<<(unsigned)((chunks + per - 1) / per), 256, 0, s>>>(from, chunks, (int)block, scale, to); };
-        if (block <= 4096) launch(nt ? hadamard_kernel<2, true> : hadamard_kernel<2, false>, 512);
-        else launch(nt ? hadamard_kernel<4, true> : hadamard_kernel<4, false>, 1024);
+        auto launch = [&](auto* kernel, int per) { kernel<<<(unsigned)((chunks + per - 1) / per), 256, 0, s>>>(from, to, chunks, scale, nt); };
+        switch (block) {
+            case 1: launch(hadamard_kernel<0>, 512); break;
+            case 2: launch(hadamard_kernel<1>, 512); break;
+            case 4: launch(hadamard_kernel<2>, 512); break;
+            case 8: launch(hadamard_kernel<3>, 512); break;
+            case 16: launch(hadamard_kernel<4>, 512); break;
+            case 32: launch(hadamard_kernel<5>, 512); break;
+            case 64: launch(hadamard_kernel<6>, 512); break;
+            case 128: launch(hadamard_kernel<7>, 512); break;
+            case 256: launch(hadamard_kernel<8>, 512); break;
+            case 512: launch(hadamard_kernel<9>, 512); break;
+            case 1024: launch(hadamard_kernel<10>, 512); break;
+            case 2048: launch(hadamard_kernel<11>, 512); break;
+            case 4096: launch(hadamard_kernel<12>, 512); break;
+            case kMaxHadamard: launch(hadamard_8192_kernel, 1024); break;
+            default: return hipErrorInvalidValue;
+        }
         return hipGetLastError();
     }
     const dim3 grid((unsigned)(K / block), (unsigned)rows);
