@@ -359,23 +359,33 @@ __device__ __forceinline__ void hadamard_whole(int (&v)[16], int* buf, int64_t c
     hadamard_store<16>(r, reinterpret_cast<unsigned short*>(buf), c0, chunks, dst);
 }
 
+// A thread's FP64 numbers from one layout to the other, the two halves one after the other through space for one.
+template <int E, class From, class To>
+__device__ __forceinline__ void exchange_halves(double (&v)[E], uint32_t* words, From from, To to)
+{
+    uint32_t low[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) words[from(j)] = (uint32_t)__double2loint(v[j]);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < E; ++j) low[j] = words[to(j)];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < E; ++j) words[from(j)] = (uint32_t)__double2hiint(v[j]);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[j] = __hiloint2double((int)words[to(j)], (int)low[j]);
+}
+
 template <int LOGN>
-__device__ __forceinline__ void hadamard_fp64(double (&v)[16], double* buf, int64_t c0, int64_t chunks, double scale, uint4* __restrict__ dst)
+__device__ __forceinline__ void hadamard_fp64(double (&v)[16], uint32_t* buf, int64_t c0, int64_t chunks, double scale, uint4* __restrict__ dst)
 {
     const HadamardPlaces at((int)threadIdx.x);
     hadamard_stages<LOGN, 16, 0, 0, 3>(v);
     hadamard_stages<LOGN, 16, 3, 11, 1>(v);
-#pragma unroll
-    for (int j = 0; j < 16; ++j) buf[at.in_a(j)] = v[j];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 16; ++j) v[j] = buf[at.in_b(j)];
+    exchange_halves(v, buf, [&](int j) { return at.in_a(j); }, [&](int j) { return at.in_b(j); });
     hadamard_stages<LOGN, 16, 0, 3, 4>(v);
-#pragma unroll
-    for (int j = 0; j < 16; ++j) buf[at.in_b(j)] = v[j];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 16; ++j) v[j] = buf[at.in_c(j)];
+    exchange_halves(v, buf, [&](int j) { return at.in_b(j); }, [&](int j) { return at.in_c(j); });
     hadamard_stages<LOGN, 16, 0, 7, 4>(v);
     uint32_t r[8];
 #pragma unroll
@@ -396,13 +406,13 @@ __device__ __forceinline__ uint4 hadamard_load(const uint4* __restrict__ src, in
 // in them: whole numbers have one zero, while FP64 sums of FP16 numbers are -0 only where a -0 went in (-0 - (x - x) = -0).
 // 22016 x 4096: a single workgroup per block with one LDS round trip and one barrier per stage, bound by LDS and barriers, took 863 us,
 // these layouts 108 (a copy of the tensor 69) while they were bound by 40 vector instructions per element, half of them
-// addresses and copies of registers.
+// addresses and copies of registers, and 90 with LDS for whole FP64 numbers, four workgroups to a compute unit.  Now 78, with eight.
 template <int LOGN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void hadamard_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t chunks,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void hadamard_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t chunks,
                                                                                                  double scale, bool nt)
 {
     constexpr int kElems = 4096;
-    __shared__ __attribute__((aligned(16))) double buf[kElems + kElems / 8 + kElems / 16];
+    __shared__ __attribute__((aligned(16))) uint32_t buf[kElems + kElems / 8 + kElems / 16];
     __shared__ float s_sum[4];
     typedef short s2 __attribute__((ext_vector_type(2)));
     typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
@@ -456,25 +466,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void h
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[8 * c + e] = (double)__half2float(__ushort_as_half((unsigned short)(w[e >> 1] >> (16 * (e & 1)))));
     }
-    auto exchange = [&](auto from, auto to) __attribute__((always_inline)) {
-        uint32_t low[E];
-#pragma unroll
-        for (int j = 0; j < E; ++j) words[from(j)] = (uint32_t)__double2loint(v[j]);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < E; ++j) low[j] = words[to(j)];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < E; ++j) words[from(j)] = (uint32_t)__double2hiint(v[j]);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < E; ++j) v[j] = __hiloint2double((int)words[to(j)], (int)low[j]);
-    };
     hadamard_stages<13, E, 0, 0, 3>(v);
     hadamard_stages<13, E, 3, 11, 2>(v);
-    exchange([&](int j) { return at.in_a(j); }, [&](int j) { return at.in_b(j); });
+    exchange_halves(v, words, [&](int j) { return at.in_a(j); }, [&](int j) { return at.in_b(j); });
     hadamard_stages<13, E, 0, 3, 4>(v);
-    exchange([&](int j) { return at.in_b(j); }, [&](int j) { return at.in_c(j); });
+    exchange_halves(v, words, [&](int j) { return at.in_b(j); }, [&](int j) { return at.in_c(j); });
     hadamard_stages<13, E, 0, 7, 4>(v);
     uint32_t r[E / 2];
 #pragma unroll
