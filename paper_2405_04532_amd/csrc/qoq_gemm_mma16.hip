@@ -39,9 +39,8 @@ namespace {
 
 constexpr int kMmaThreads = 256;
 constexpr int kMSlotBytes = 1024;                   // metadata: 256 B per copying wave
-constexpr int kTileM = 128, kTileN = 256;           // tokens, channels
+constexpr int kTileM = 128;                         // tokens
 constexpr int kDepth = 2;                           // slabs of the rings: small enough for two workgroups per compute unit
-constexpr int kNF = 4;                              // 16-channel fragments of a wave = blocks of eight chunks per half-stage
 
 // f(integral_constant 0), f(1), ... f(N - 1): a loop that is unrolled whatever its size
 template <class F, int... I>
@@ -49,12 +48,13 @@ __device__ __forceinline__ void unrolled_over(F&& f, std::integer_sequence<int, 
 template <int N, class F>
 __device__ __forceinline__ void unrolled(F&& f) { unrolled_over(f, std::make_integer_sequence<int, N>()); }
 
-template <bool GROUP, int OUT>
+// kNF: 16-channel fragments of a wave = blocks of eight chunks per half-stage; 4 = tiles of 256 channels, 3 = of 192
+template <bool GROUP, int OUT, int kNF>
 __global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
     const GemmDev p = gemm_dev(QOQ_GEMM_ARGS, tail);
     constexpr int kASlots = kDepth, kWSlots = kDepth;
-    constexpr int TMt = kTileM, TNt = kTileN;       // tile: tokens x channels
+    constexpr int TMt = kTileM, TNt = 64 * kNF;     // tile: tokens x channels
     constexpr int kABlocks = TMt / 16;              // 1 KiB blocks (16 tokens x 64 k) per activation slab
     constexpr int kUnits = TNt / 16;                // 1 KiB weight units per slab
     constexpr int kASlotBytes = 2 * kABlocks * 1024, kWSlotBytes = kUnits * 1024;   // a group of a tile: 128 B per token
@@ -195,15 +195,17 @@ __global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(QOQ_GEMM_PARAMS, 
     uint32_t a_rd[2];
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) a_rd[hf] = (uint32_t)(r16 * 128 + (((4 * hf + kb) ^ row_swizzle(r16)) * 16));
-    const uint32_t w_rd = (uint32_t)(wave * kNF * 1024 + lane * 16);
+    // A wave's fragments: the four of a 64-channel block, or with 192 channels its place in each of the three blocks.
+    auto unit_of = [&](int f) { return kNF == 4 ? wave * 4 + f : f * 4 + wave; };
+    const uint32_t w_rd = (uint32_t)(unit_of(0) * 1024 + lane * 16);
     auto lds_a = [&](uint32_t slab, int hf, int tf) {
         return as_v4i(*reinterpret_cast<const uint4*>(aring + slab + a_rd[hf] + tf * 2048));
     };
     auto lds_w = [&](uint32_t slab, int f) {
-        return *reinterpret_cast<const uint4*>(wring + slab + w_rd + f * 1024);
+        return *reinterpret_cast<const uint4*>(wring + slab + w_rd + f * (kNF == 4 ? 1024 : 4096));
     };
     auto lds_m = [&](uint32_t slab, int f) {
-        const int u = wave * kNF + f;
+        const int u = unit_of(f);
         return (uint32_t)*reinterpret_cast<const uint16_t*>(mring + slab + (u / kWCopies) * 256 + (u % kWCopies) * 32 + r16 * 2);
     };
     const uint32_t nib_mask = 0x0F0F0F0Fu, sign = 0x80808080u;
@@ -280,10 +282,12 @@ __global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(QOQ_GEMM_PARAMS, 
                     // lane words of the next group: 0 and 1 are free since the barrier, 2 and 3 once their own block has begun
                     if constexpr (L < 2) rq[L] = lds_w(w_next, L);
                     else if constexpr (tf == 0) rq[b] = lds_w(w_next, b);
-                    if constexpr (GROUP && L >= 2 && L < 6) mt[L - 2] = lds_m(m_nxt, L - 2);
-                    if constexpr (L >= 3 && L < 19 && (L & 1)) at[0][(L - 3) >> 1] = lds_a(a_nxt, 0, (L - 3) >> 1);
-                    // level-2 constants of the next group, each after the last use of the old one (block f - 1, step 6)
-                    constexpr int pf = c == 21 ? 0 : c == 22 ? 1 : c == 23 ? 2 : c == 27 ? 3 : -1;
+                    if constexpr (GROUP && L >= 2 && L < 2 + kNF) mt[L - 2] = lds_m(m_nxt, L - 2);
+                    if constexpr (kNF == 4 && L >= 3 && L < 19 && (L & 1)) at[0][(L - 3) >> 1] = lds_a(a_nxt, 0, (L - 3) >> 1);
+                    if constexpr (kNF == 3 && L >= 5 && L != 8 && L < 14) at[0][L - (L < 8 ? 5 : 6)] = lds_a(a_nxt, 0, L - (L < 8 ? 5 : 6));
+                    // level-2 constants of the next group, each after the last use of the old one (block f - 1, step 6) and
+                    // before its own (the last block's steps make the next half-stage's first operand)
+                    constexpr int pf = kNF == 4 ? (c == 21 ? 0 : c == 22 ? 1 : c == 23 ? 2 : c == 27 ? 3 : -1) : (c == 15 ? 0 : c == 17 ? 1 : c == 18 ? 2 : -1);
                     if constexpr (GROUP && pf >= 0) {
                         S[pf] = __builtin_amdgcn_perm(mt[pf], mt[pf], 0x0c000c00u);
                         B[pf] = __builtin_amdgcn_perm(mt[pf], mt[pf], 0x01010101u);
@@ -324,12 +328,12 @@ __global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(QOQ_GEMM_PARAMS, 
             if (s2 == slice) continue;
             const int4* theirs = p.parts + ((size_t)(tile_id * p.S + s2) * NJ) * kMmaThreads + threadIdx.x;
 #pragma unroll
-            for (int j0 = 0; j0 < NJ; j0 += 16) {          // four loads in flight: no plan cuts this kernel, only a forced one
-                v4i t[16];
+            for (int j0 = 0; j0 < NJ; j0 += 8) {           // four loads in flight: no plan cuts this kernel, only a forced one
+                v4i t[8];
 #pragma unroll
-                for (int x = 0; x < 16; x += 4) load_sc1_and_wait(&t[x], theirs + (size_t)(j0 + x) * kMmaThreads, kMmaThreads);
+                for (int x = 0; x < 8; x += 4) load_sc1_and_wait(&t[x], theirs + (size_t)(j0 + x) * kMmaThreads, kMmaThreads);
 #pragma unroll
-                for (int x = 0; x < 16; ++x) acc[(j0 + x) >> 3][(j0 + x) & 7] += t[x];
+                for (int x = 0; x < 8; ++x) acc[j0 >> 3][x] += t[x];
             }
         }
     }
@@ -339,6 +343,26 @@ __global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(QOQ_GEMM_PARAMS, 
     const int* e_rs = reinterpret_cast<const int*>(ering + 1024);
     const uint8_t* e_zn = reinterpret_cast<const uint8_t*>(ering + 2048);
 
+    if constexpr (kNF == 3) {
+        // ---- epilogue, 192 channels: fragment f of a lane (token r16, row quad kb) holds logical channels 16 kb + 4 wave + v of
+        // the tile's f-th block of 64.
+#pragma unroll
+        for (int f = 0; f < kNF; ++f) {
+            const int nl = f * 64 + 16 * kb + 4 * wave, n0 = n_base + nl;
+            if (n0 >= p.N) break;                        // N % 64 == 0: a block is all in or all out
+            float sn[4];
+            int zn[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) { sn[x] = OUT == OUT_FP16 ? __half2float(e_sn[nl + x]) : 0.f; zn[x] = GROUP ? 0 : (int)e_zn[nl + x]; }
+#pragma unroll
+            for (int tf = 0; tf < 8; ++tf) {
+                const int ml = tf * 16 + r16, m = m_base + ml;
+                if (m >= p.M) continue;
+                finish4<GROUP, OUT>(p, m, n0, acc[f][tf], sn, zn, OUT == OUT_FP16 ? __half2float(e_sx[ml]) : 0.f, GROUP ? 0 : e_rs[ml]);
+            }
+        }
+        return;
+    }
     // ---- epilogue.  Lane (token r16, row quad kb) of fragment f holds physical rows 4 kb .. 4 kb + 3, i.e. logical
     // channels 16 kb + 4 f + v of the wave's 64: 16 consecutive channels of a token, one row segment of 32 bytes.
     const int nl = wave * 64 + 16 * kb, n0 = n_base + nl;  // first channel inside the tile, and of all
@@ -388,12 +412,14 @@ __global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(QOQ_GEMM_PARAMS, 
 
 }  // namespace
 
-hipError_t launch_mma16(const GemmDev& p, bool group, bool fp16, hipStream_t s)
+hipError_t launch_mma16(const GemmDev& p, int channels, bool group, bool fp16, hipStream_t s)
 {
-    const dim3 grid((unsigned)(((p.N + kTileN - 1) / kTileN) * ((p.M + kTileM - 1) / kTileM)), (unsigned)p.S);
-    auto* kern = group ? (fp16 ? mma16_kernel<true, OUT_FP16> : mma16_kernel<true, OUT_I32>)
-                       : (fp16 ? mma16_kernel<false, OUT_FP16> : mma16_kernel<false, OUT_I32>);
-    launch_gemm_kernel(kern, grid, kMmaThreads, s, p);
+    const dim3 grid((unsigned)(((p.N + channels - 1) / channels) * ((p.M + kTileM - 1) / kTileM)), (unsigned)p.S);
+    auto* wide = group ? (fp16 ? mma16_kernel<true, OUT_FP16, 4> : mma16_kernel<true, OUT_I32, 4>)
+                       : (fp16 ? mma16_kernel<false, OUT_FP16, 4> : mma16_kernel<false, OUT_I32, 4>);
+    auto* narrow = group ? (fp16 ? mma16_kernel<true, OUT_FP16, 3> : mma16_kernel<true, OUT_I32, 3>)
+                         : (fp16 ? mma16_kernel<false, OUT_FP16, 3> : mma16_kernel<false, OUT_I32, 3>);
+    launch_gemm_kernel(channels == 256 ? wide : narrow, grid, kMmaThreads, s, p);
     return hipGetLastError();
 }
 

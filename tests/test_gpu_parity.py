@@ -954,3 +954,27 @@ def test_gemm_weights_that_pass_by_the_caches(api, M, K, N, mode):
     want = acc.double() * sx.double()[:, None] * s.double()[None, :]
     for got in (api.w4a8_gemm(qx, sx, blob, N, mode, rowsum=rs), api.w4a8_linear(x, blob, N, mode)[0]):
         assert ((got.double() - want).abs() <= want.abs() * (2.0 ** -11 + 2.0 ** -22) + 2.0 ** -25).all()
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(1, 64, 128), (127, 192, 128), (128, 256, 256), (129, 320, 384), (300, 832, 1152), (65, 448, 512), (385, 128, 640)])
+def test_gemm_tiles_of_192_channels_two_per_compute_unit(api, M, N, K, mode):
+    """128 x 192 tiles: one token past a tile, channels that end in the first, second and third block of a tile, one group, two and odd
+    numbers of them.  Accumulators exact, FP16 within the tolerance of the other kernels, token sums as well."""
+    w, x = rand_inputs(M, N, K, seed=7 * M + N + K)
+    blob = api.pack_weights(w, mode)
+    qx, sx, rowsum, tx = api.quant_act_per_token(x, want_tx=True)
+    ref = (ogemm.forward_per_channel if mode else ogemm.forward_group)(_np(w), _np(x))
+    api.set_gemm_config(131, 1)
+    try:
+        acc = api.w4a8_gemm_i32(qx, blob, N, mode, rowsum=rowsum if mode else None)
+        out = api.w4a8_gemm(qx, sx, blob, N, mode, rowsum=rowsum if mode else None)
+        sums = api.w4a8_gemm_token_sum(qx, sx, tx, blob, N) if mode else None
+    finally:
+        api.set_gemm_config(0, 0)
+    assert (_np(acc).astype(np.int64) == ref["acc"]).all()
+    check_fp16(out, ref["out64"])
+    if mode:
+        # the same FP32 formula in another kernel: a product may be fused with the subtraction or not, 2^-23 of its two terms
+        other = api.w4a8_gemm_token_sum(qx, sx, tx, blob, N).double()
+        assert ((sums.double() - other).abs() <= other.abs() * 2.0 ** -10 + 2.0 ** -21 * other.abs().max()).all()
