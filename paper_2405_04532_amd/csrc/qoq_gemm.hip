@@ -1515,10 +1515,11 @@ void launch_mma(const GemmDev& p, bool fp16, hipStream_t s)
 }
 
 bool two_per_cu_narrow(int64_t M, int64_t N, int64_t G, int mode);
+int two_per_cu_channels(int64_t M, int64_t N, int64_t G, int mode);
 
 // tile_m selects the kernel and its shape: 16 / 32 / 64 = streaming kernel with that many tokens per tile;
-// 128 = compute-bound kernel, 256 tokens x 256 channels; 129 = 128 tokens x 256 channels; 131 = 256 x 192; 132 = 128 x 256,
-// two workgroups per compute unit; 130 = eight waves on up to 144 tokens x 128 or 256 channels.  The error of a launch is read, and thereby cleared,
+// 128 = compute-bound kernel, 256 tokens x 256 channels; 129 = 128 tokens x 256 channels; 131 = 192 channels, 256 tokens or, without
+// slices, 128 and two workgroups per compute unit; 132 = 128 tokens, two per compute unit, 256 channels or 192 without slices; 130 = eight waves on up to 144 tokens x 128 or 256 channels.  The error of a launch is read, and thereby cleared,
 // once: by the launcher of another file that made it, or here.
 template <bool GROUP>
 hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStream_t s)
@@ -1559,7 +1560,7 @@ hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStrea
         if (p.S == 1 && two_per_cu_narrow(p.M, p.N, p.G, GROUP ? 0 : 1)) return launch_mma16(p, 192, GROUP, fp16, s);
         launch_mma<GROUP, 3, 2>(p, fp16, s);
     } else if (tile_m == 132) {
-        return launch_mma16(p, 256, GROUP, fp16, s);
+        return launch_mma16(p, p.S == 1 ? two_per_cu_channels(p.M, p.N, p.G, GROUP ? 0 : 1) : 256, GROUP, fp16, s);
     } else {
         launch_mma<GROUP, 4, 2>(p, fp16, s);
     }
@@ -1858,6 +1859,12 @@ bool two_per_cu_narrow(int64_t M, int64_t N, int64_t G, int mode)
     const double one = (double)rounds * (8.0 + 0.92 * (1.0 + 0.45 * load * load) * (double)G);
     return two_per_cu_cost(M, N, G, mode, 192) < 0.94 * measured_cost(N, G, 131, mode, one);
 }
+
+// Channels of the tiles of a plan that says two per compute unit (132): 192 where they are estimated 3% ahead.
+int two_per_cu_channels(int64_t M, int64_t N, int64_t G, int mode)
+{
+    return two_per_cu_cost(M, N, G, mode, 192) < 0.97 * two_per_cu_cost(M, N, G, mode, 256) ? 192 : 256;
+}
 }  // namespace
 
 // Eight-wave kernels (tile_m 130): the cheapest number of k-slices, and with it the width, in microseconds: a start, more for every
@@ -2008,10 +2015,9 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
     double cost;
     pick_other_config(M, N, K, mode, forced, tile_m, split_k, cost);
     if (forced.tile_m || M <= 64) return;
-    auto narrow_instead = [&] {                              // of the other four-wave tiles
-        if ((tile_m != 129 && tile_m != 132 && !(tile_m == 128 && mode != 0)) || split_k > 1) return;
-        const double other = tile_m == 132 ? two_per_cu_cost(M, N, K / kGroup, mode, 256) : cost;
-        if (two_per_cu_cost(M, N, K / kGroup, mode, 192) < 0.97 * other) { tile_m = 131; split_k = 1; }
+    auto narrow_instead = [&] {                              // of four-wave tiles with one workgroup per compute unit
+        if ((tile_m != 129 && !(tile_m == 128 && mode != 0)) || split_k > 1) return;
+        if (two_per_cu_cost(M, N, K / kGroup, mode, 192) < 0.97 * cost) { tile_m = 131; split_k = 1; }
     };
     if (!eight_waves || N * K >= ((int64_t)1 << 33)) return narrow_instead();
     // Taken where the estimate is ahead by a share of the other plan's that depends on how far off that one's estimate is: by

@@ -239,8 +239,8 @@ int astat_deep_groups();
 bool astat_linear_takes(int64_t M, int64_t K);
 hipError_t launch_astat_linear(const GemmDev& p, const void* x, int8_t* qx, void* sx, int32_t* rowsum, bool group, hipStream_t s);
 
-// qoq_gemm_mma16.hip: the compute-bound kernel with 16x16x64 matrix instructions, tiles of 128 tokens x 256 (tile_m code 132) or 192
-// channels (code 131 without k-slices).
+// qoq_gemm_mma16.hip: the compute-bound kernel with 16x16x64 matrix instructions, tiles of 128 tokens x 256 or 192 channels
+// (tile_m code 132, and 131 without k-slices).
 hipError_t launch_mma16(const GemmDev& p, int channels, bool group, bool fp16, hipStream_t s);
 
 // qoq_gemm_mma8.h: eight waves on one output tile of 256 or 128 channels and 16 mf tokens (tile_m code 130); one
