@@ -288,7 +288,7 @@ constexpr int decode_lds_bytes(int waves, int columns) { return waves * columns 
 // 2^log_ns workgroups share a sequence, the y-th takes chunks y, y + 2^log_ns, ..., and their (unnormalised sums, maximum,
 // weight sum) go to the workspace for kv4_combine_kernel; used when there are too few (sequence, KV head) pairs to fill
 // the chip.  EARLY: every wave's first chunk is known before the length is, so its loads go out at once, where they
-// would wait for that word to come from memory (4 x 200 tokens of 8 KV heads 4.4 -> 4.3 us, 1 x 8192 11.05 -> 10.7 in eight).  Not where
+// would wait for that word to come from memory (4 x 256 tokens of 8 KV heads 4.42 -> 4.35 us, 1 x 8192 in eight 11.2 -> 10.8).  Not where
 // there are more workgroups than are resident: others then hide that wait, and chunks past the end are read in vain (64 x 128 of
 // 32 heads 11.5 us, 11.9 with them).
 // NT: codes as non-temporal, for caches so large that the 256 MB memory-side cache cannot hold them until the next step (64 x 1024

@@ -410,6 +410,7 @@ PyObject* channel_order(PyObject*, PyObject* const* a, Py_ssize_t n)    // salie
     const hipStream_t s = static_cast<hipStream_t>(stream_of(*sal));
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();                // (the default stream beside a capture: not the next launch's error)
         PyErr_SetString(PyExc_RuntimeError, "channel_order reads a result on the host: not while the stream is being captured");
         return nullptr;
     }
