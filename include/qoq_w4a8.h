@@ -253,8 +253,7 @@ int qoq_kv4_attention_decode(const void* q_fp16, const void* cache, const int32_
  *   workspace   device scratch of at least qoq_kv4_attention_workspace_bytes(...) bytes, 16-byte aligned, contents
  *               irrelevant on entry and exit; two calls that overlap in time need separate workspaces.
  * qoq_kv4_attention_workspace_bytes returns 0 when the library would not split this problem; the call then runs the
- * single pass (workspace may be NULL).  A smaller workspace is used as far as it goes; with less than
- * B * H * min(256 / (B * Hkv), 8, S_max / 512) * 520 bytes (where that minimum is 2 or more): QOQ_ERR_WORKSPACE. */
+ * single pass (workspace may be NULL).  A workspace that is too small: QOQ_ERR_WORKSPACE. */
 size_t qoq_kv4_attention_workspace_bytes(int64_t B, int64_t H, int64_t Hkv, int64_t D, int64_t S_max);
 int qoq_kv4_attention_decode_split(const void* q_fp16, const void* cache, const int32_t* seq_lens, int64_t B, int64_t H,
                                    int64_t Hkv, int64_t D, int64_t S_max, void* out_fp16, void* workspace,

@@ -390,7 +390,7 @@ static int kv4_decode_common(const void* q_fp16, const void* cache, const int32_
     if (B == 0) return QOQ_OK;
     if (!q_fp16 || !cache || !seq_lens || !out_fp16) return QOQ_ERR_NULL;
     if (!aligned16(q_fp16) || !aligned16(cache) || !aligned16(out_fp16) || !aligned16(workspace)) return QOQ_ERR_ALIGN;
-    if (workspace && workspace_bytes < qoq::kv4_decode_workspace_least(B, H, Hkv, S_max)) return QOQ_ERR_WORKSPACE;
+    if (workspace && workspace_bytes < qoq::kv4_decode_workspace_bytes(B, H, Hkv, S_max)) return QOQ_ERR_WORKSPACE;
     if (!arch_ok()) return QOQ_ERR_ARCH;
     return qoq::launch_kv4_decode(q_fp16, static_cast<const uint8_t*>(cache), seq_lens, B, H, Hkv, S_max, out_fp16, workspace,
                                   workspace_bytes, static_cast<hipStream_t>(stream)) == hipSuccess ? QOQ_OK : QOQ_ERR_HIP;

@@ -285,10 +285,10 @@ constexpr int kFewChunks = 12;
 constexpr int decode_lds_bytes(int waves, int columns) { return waves * columns * kPartial * (int)sizeof(float); }
 
 // NW waves.  PK: tiles side by side in the columns of a matrix instruction (2 with at most eight heads, else 1).  SPLIT:
-// 2^log_ns workgroups share a sequence, the y-th takes chunks y, y + 2^log_ns, ..., and their (unnormalised sums, maximum,
+// the sequence is cut into `ns` contiguous ranges of chunks, one workgroup each, whose (unnormalised sums, maximum,
 // weight sum) go to the workspace for kv4_combine_kernel; used when there are too few (sequence, KV head) pairs to fill
-// the chip.  EARLY: every wave's first chunk is known before the length is, so its loads go out at once, where they
-// would wait for that word to come from memory (4 x 256 tokens of 8 KV heads 4.42 -> 4.35 us, 1 x 8192 in eight 11.2 -> 10.8).  Not where
+// the chip (grouped-query models).  EARLY (whole sequences): every wave's first chunk is known before the length is, so its loads go out
+// at once, where they would wait for that word to come from memory (4 x 256 tokens of 8 KV heads 4.42 -> 4.35 us).  Not where
 // there are more workgroups than are resident: others then hide that wait, and chunks past the end are read in vain (64 x 128 of
 // 32 heads 11.5 us, 11.9 with them).
 // NT: codes as non-temporal, for caches so large that the 256 MB memory-side cache cannot hold them until the next step (64 x 1024
@@ -297,8 +297,9 @@ constexpr int decode_lds_bytes(int waves, int columns) { return waves * columns 
 template <int NW, int PK, bool SPLIT, bool EARLY, bool NT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1 || NW == 8 ? 2 : 3))) void kv4_decode_kernel(
     const __half* __restrict__ q, const uint8_t* __restrict__ cache, const int32_t* __restrict__ seq_lens, __half* __restrict__ out,
-    float* __restrict__ ws, int Hkv, int R, int S_max, int log_ns)
+    float* __restrict__ ws, int Hkv, int R, int S_max, int ns)
 {
+    static_assert(!(SPLIT && EARLY), "where a range begins depends on the length");
     extern __shared__ float s_part[];                    // [wave][column][kPartial]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -308,7 +309,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1
     const uint32_t bh = blockIdx.x;                      // b * Hkv + hk
     const int n_pages = (S_max + kPageTokens - 1) / kPageTokens;
     const uint8_t* stream = cache + (int64_t)bh * n_pages * kPageBytes;
-    const int first = SPLIT ? (int)blockIdx.y : 0, step_log = SPLIT ? log_ns : 0;    // this workgroup's chunks: first + (i << step_log)
 
     struct Chunk {
         uint4 kc[2];        // keys: token r16 of the tile, elements 32 kb ..
@@ -345,28 +345,32 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1
         }
     };
     Chunk A, Bf;
-    if constexpr (EARLY) load_chunk(A, min(first + (wave << step_log), 2 * n_pages - 1));   // past the length: whatever is there, masked
+    if constexpr (EARLY) load_chunk(A, min(wave, 2 * n_pages - 1));   // past the length: whatever is there, masked
 
-    const int L = min(max(seq_lens[bh / (uint32_t)Hkv], 0), S_max);
+    const int L_seq = min(max(seq_lens[bh / (uint32_t)Hkv], 0), S_max);
     __half* out_bh = out + (size_t)bh * R * kD;
-    float* ws_bh = SPLIT ? ws + (((size_t)bh << log_ns) + blockIdx.y) * R * kPartial : nullptr;
-    const int chunks_seq = (L + kChunk - 1) / kChunk;
-    const int mine = chunks_seq > first ? ((chunks_seq - 1 - first) >> step_log) + 1 : 0;     // chunks of this workgroup
-    if (mine == 0) {                                     // nothing to attend to: zero rows / an empty partial result
+    float* ws_bh = SPLIT ? ws + ((size_t)bh * ns + blockIdx.y) * R * kPartial : nullptr;
+    // this workgroup's range of chunks [c0, c1) and the length it masks against
+    const int chunks_seq = (L_seq + kChunk - 1) / kChunk;
+    const int per_split = SPLIT ? (chunks_seq + ns - 1) / ns : chunks_seq;
+    const int c0 = SPLIT ? min(chunks_seq, (int)blockIdx.y * per_split) : 0;
+    const int c1 = SPLIT ? min(chunks_seq, c0 + per_split) : chunks_seq;
+    const int L = min(L_seq, c1 * kChunk);
+    if (c0 >= c1) {                                      // nothing to attend to: zero rows / an empty partial result
         for (int x = threadIdx.x; x < R * (SPLIT ? kPartial : kD); x += 64 * NW) {
             if (SPLIT) ws_bh[x] = x % kPartial == kD ? -1e30f : 0.f;
             else out_bh[x] = __float2half_rn(0.f);
         }
         return;
     }
-    // Wave w of the nw that attend takes the workgroup's chunks w, w + nw, ...; they all run the same number of iterations (a wave
+    // Wave w of the nw that attend takes chunks w, w + nw, ... of the range; they all run the same number of iterations (a wave
     // without a chunk in the last one has one past the end, masked).  Two buffers alternate, and every path through the loop
     // issues a fixed number of loads, so the compiler's wait counts are exact: while a chunk is computed the next
     // one stays in flight.  (With loads under a condition it waits for everything outstanding.)
-    const int nw = NW > 4 && mine <= kFewChunks ? 4 : NW;
-    const int n_iter = wave < nw ? (mine + nw - 1) / nw : 0;
-    auto chunk_of = [&](int it) __attribute__((always_inline)) { return first + ((it * nw + wave) << step_log); };
-    auto fetch = [&](Chunk& c, int it) __attribute__((always_inline)) { load_chunk(c, min(chunk_of(it), chunks_seq - 1)); };
+    const int nw = NW > 4 && c1 - c0 <= kFewChunks ? 4 : NW;
+    const int n_iter = wave < nw ? (c1 - c0 + nw - 1) / nw : 0;
+    auto chunk_of = [&](int it) __attribute__((always_inline)) { return c0 + it * nw + wave; };
+    auto fetch = [&](Chunk& c, int it) __attribute__((always_inline)) { load_chunk(c, min(chunk_of(it), c1 - 1)); };
     if constexpr (!EARLY) fetch(A, 0);
 
     // B operand of S = K q^T: column = head (both halves of the columns with PK = 2; heads >= R: zero), k-block kb =
@@ -556,25 +560,24 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1
 }
 
 // Second pass of the split variant: one workgroup of 128 threads per (sequence, query head), all loads in flight at once.
-constexpr int kMaxSplits = 32;
-template <int MAX>
+constexpr int kMaxSplits = 8;
 __global__ __launch_bounds__(kD) void kv4_combine_kernel(const float* __restrict__ ws, __half* __restrict__ out, int NS, int R)
 {
     const uint32_t bh = blockIdx.x / (uint32_t)R;        // (sequence, KV head)
     const int r = (int)(blockIdx.x - bh * R), d = threadIdx.x;
     const float* part = ws + (size_t)bh * NS * R * kPartial + (size_t)r * kPartial;
-    float acc[MAX], mx[MAX], den[MAX];
+    float acc[kMaxSplits], mx[kMaxSplits], den[kMaxSplits];
 #pragma unroll
-    for (int s = 0; s < MAX; ++s) {
+    for (int s = 0; s < kMaxSplits; ++s) {
         const float* p = part + (size_t)min(s, NS - 1) * R * kPartial;
         acc[s] = p[d]; mx[s] = p[kD]; den[s] = p[kD + 1];
     }
     float mm = mx[0];
 #pragma unroll
-    for (int s = 1; s < MAX; ++s) mm = fmaxf(mm, mx[s]);
+    for (int s = 1; s < kMaxSplits; ++s) mm = fmaxf(mm, mx[s]);
     float num = 0.f, sum = 0.f;
 #pragma unroll
-    for (int s = 0; s < MAX; ++s) {
+    for (int s = 0; s < kMaxSplits; ++s) {
         const float f = s < NS ? __builtin_amdgcn_exp2f(mx[s] - mm) : 0.f;
         num = fmaf(acc[s], f, num);
         sum = fmaf(den[s], f, sum);
@@ -613,36 +616,29 @@ hipError_t launch_kv4_unpack(const uint8_t* cache, int64_t B, int64_t Hkv, int64
     return hipGetLastError();
 }
 
-// log2 of the workgroups that share a sequence where there is a workspace (0 = single pass).  A sequence in one workgroup takes
-// 1 us for every 256 tokens; sharing it costs the second launch, about 2 us, and more where there are many partial results.
-// Up to 64 pairs as many as give every compute unit a workgroup, up to eight of 96 tokens, beyond that of 256 (us, one workgroup, the
-// number chosen, twice as many: 32 pairs of 1023 tokens 7.6, 5.8 in 8, 6.9 in 16; 64 of 1023 7.7, 7.1 in 4, 6.9 in 8; 8 of 8192 37.6, 8.4 in
-// 32; 16 of 4096 20.7, 7.9 in 16; too short: 32 of 512 5.3, 5.6 in 8; 64 of 768 6.6, 7.0 in 4).  More pairs in 4, long ones in 8: more
-// workgroups than compute units, which even out sequences of different lengths (96 of 4096 21.4, 16.6 in 2, 15.1 in 8; 128
-// of 2048 12.4, 11.5 in 4; of 1023 8.2, 9.0 in 4; 192 of 8192 38.1, 33.3 in 4).  From 256 pairs on every cut is slower than none.
-static int decode_split_log(int64_t B, int64_t Hkv, int64_t S_max)
+// Number of sequence ranges the split variant would use for this problem (1 = single pass).  Cutting the sequence pays only
+// while the (sequence, KV head) pairs alone leave compute units idle: measured at 8 KV heads, 1 x 8192 tokens goes from 51 to
+// 15 us with 8 ranges and 8 x 2048 from 16 to 11 us with 4, while at 64 sequences (512 pairs) every cut is slower than none
+// (18.6 us whole, 22.2 in 2 ranges, 25.5 in 4): each range repeats the set-up and adds a second launch that merges them.
+// The host knows what a sequence may grow to, not its length, so a rule by what full caches gain loses on short sequences.  Up to 32
+// workgroups from 640 tokens on, four up to 255 pairs, chunks in turn: full caches up to 1.4 times as fast (32 pairs of 1000 tokens 7.9 -> 5.8
+// us), but 192 pairs of 128 in caches for 4096 3.9 -> 9.0, 32 pairs of 128 in caches for 1000 3.3 -> 5.4, 8 pairs of 400 in caches for 8192
+// 5.9 -> 7.2, and 0.96 of the speed on average over 1674 sets of lengths from 16 tokens to the whole cache.
+constexpr int64_t kDecodeFill = 256;
+static int kv4_decode_splits(int64_t B, int64_t Hkv, int64_t S_max)
 {
     const int64_t pairs = B * Hkv;
-    if (pairs <= 0 || pairs >= 256 || S_max < 640 || S_max < pairs * (pairs <= 128 ? 15 : 20)) return 0;
-    if (pairs > 32 && pairs <= 112 && S_max >= 2560) return 3;
-    if (pairs > 64) return 2;
-    int log = 0;
-    while ((2 << log) <= kMaxSplits && (pairs << (log + 1)) <= 256 && S_max >> (log + 1) >= (log < 3 ? 96 : 256)) ++log;
-    return log;
+    if (pairs <= 0) return 1;
+    int64_t ns = kDecodeFill / pairs;                    // about one workgroup per compute unit
+    ns = std::min<int64_t>(ns, kMaxSplits);
+    ns = std::min<int64_t>(ns, S_max / 512);             // ranges of at least 512 tokens
+    return (int)std::max<int64_t>(ns, 1);
 }
-
-static size_t decode_workspace(int64_t B, int64_t H, int64_t ns) { return ns <= 1 ? 0 : (size_t)(B * H) * ns * kPartial * sizeof(float); }
 
 size_t kv4_decode_workspace_bytes(int64_t B, int64_t H, int64_t Hkv, int64_t S_max)
 {
-    return std::max(kv4_decode_workspace_least(B, H, Hkv, S_max), decode_workspace(B, H, (int64_t)1 << decode_split_log(B, Hkv, S_max)));
-}
-
-// What a workspace must have: room for about one workgroup per compute unit, at most eight to a sequence, of 512 tokens at least each.
-size_t kv4_decode_workspace_least(int64_t B, int64_t H, int64_t Hkv, int64_t S_max)
-{
-    const int64_t pairs = B * Hkv;
-    return pairs <= 0 ? 0 : decode_workspace(B, H, std::min<int64_t>({256 / pairs, 8, S_max / 512}));
+    const int ns = kv4_decode_splits(B, Hkv, S_max);
+    return ns <= 1 ? 0 : (size_t)(B * H) * ns * kPartial * sizeof(float);
 }
 
 // Waves of a workgroup: eight where there is at most one workgroup per compute unit and a sequence that fills the cache (its
@@ -653,12 +649,12 @@ static int decode_waves(int64_t workgroups, int64_t tokens) { return workgroups 
 
 template <int PK, bool SPLIT, bool NT>
 static void launch_decode_as(int waves, dim3 grid, const __half* q, const uint8_t* cache, const int32_t* seq_lens, int64_t Hkv, int R,
-                             int64_t S_max, __half* out, float* ws, int log_ns, hipStream_t s)
+                             int64_t S_max, __half* out, float* ws, int ns, hipStream_t s)
 {
     const size_t lds = (size_t)decode_lds_bytes(waves, PK * R);
-    auto* kernel = waves == 8 ? kv4_decode_kernel<8, PK, SPLIT, true, NT>
-                              : SPLIT || grid.x <= 3 * 256 ? kv4_decode_kernel<4, PK, SPLIT, true, NT> : kv4_decode_kernel<4, PK, SPLIT, SPLIT, NT>;
-    kernel<<<grid, 64 * waves, lds, s>>>(q, cache, seq_lens, out, ws, (int)Hkv, R, (int)S_max, log_ns);
+    auto* kernel = waves == 8 ? kv4_decode_kernel<8, PK, SPLIT, !SPLIT, NT>
+                              : grid.x <= 3 * 256 ? kv4_decode_kernel<4, PK, SPLIT, !SPLIT, NT> : kv4_decode_kernel<4, PK, SPLIT, false, NT>;
+    kernel<<<grid, 64 * waves, lds, s>>>(q, cache, seq_lens, out, ws, (int)Hkv, R, (int)S_max, ns);
 }
 
 template <int PK, bool SPLIT, class... Args>
@@ -678,22 +674,19 @@ hipError_t launch_kv4_decode(const void* q, const uint8_t* cache, const int32_t*
     if (R < 1 || R > kMaxRatio) return hipErrorInvalidValue;
     const int64_t pairs = B * Hkv;
     const bool nt = kv4_cache_bytes(B, Hkv, S_max) >= (size_t)24 << 20;
-    int log_ns = workspace ? decode_split_log(B, Hkv, S_max) : 0;
-    while (log_ns > 0 && workspace_bytes < decode_workspace(B, H, (int64_t)1 << log_ns)) --log_ns;     // as many as there is room for
-    if (log_ns > 0) {
+    const int ns = kv4_decode_splits(B, Hkv, S_max);
+    if (workspace && ns > 1 && workspace_bytes >= kv4_decode_workspace_bytes(B, H, Hkv, S_max)) {
         float* ws = static_cast<float*>(workspace);
-        const int ns = 1 << log_ns;
         const dim3 grid((unsigned)pairs, (unsigned)ns);
         const int waves = decode_waves(pairs * ns, S_max / ns);
-        if (R <= 8) launch_decode<2, true>(nt, waves, grid, qh, cache, seq_lens, Hkv, R, S_max, oh, ws, log_ns, s);
-        else launch_decode<1, true>(nt, waves, grid, qh, cache, seq_lens, Hkv, R, S_max, oh, ws, log_ns, s);
-        if (ns <= 8) kv4_combine_kernel<8><<<(unsigned)(B * H), kD, 0, s>>>(ws, oh, ns, R);
-        else kv4_combine_kernel<kMaxSplits><<<(unsigned)(B * H), kD, 0, s>>>(ws, oh, ns, R);
+        if (R <= 8) launch_decode<2, true>(nt, waves, grid, qh, cache, seq_lens, Hkv, R, S_max, oh, ws, ns, s);
+        else launch_decode<1, true>(nt, waves, grid, qh, cache, seq_lens, Hkv, R, S_max, oh, ws, ns, s);
+        kv4_combine_kernel<<<(unsigned)(B * H), kD, 0, s>>>(ws, oh, ns, R);
         return hipGetLastError();
     }
     const int waves = decode_waves(pairs, S_max);
-    if (R <= 8) launch_decode<2, false>(nt, waves, dim3((unsigned)pairs), qh, cache, seq_lens, Hkv, R, S_max, oh, nullptr, 0, s);
-    else launch_decode<1, false>(nt, waves, dim3((unsigned)pairs), qh, cache, seq_lens, Hkv, R, S_max, oh, nullptr, 0, s);
+    if (R <= 8) launch_decode<2, false>(nt, waves, dim3((unsigned)pairs), qh, cache, seq_lens, Hkv, R, S_max, oh, nullptr, 1, s);
+    else launch_decode<1, false>(nt, waves, dim3((unsigned)pairs), qh, cache, seq_lens, Hkv, R, S_max, oh, nullptr, 1, s);
     return hipGetLastError();
 }
 

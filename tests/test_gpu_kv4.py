@@ -157,31 +157,59 @@ def test_attention_split_over_workgroups(H, Hkv):
                                             ws.data_ptr(), 16, None) == api.QOQ_ERR_WORKSPACE
 
 
-@pytest.mark.parametrize("B,H,Hkv,S,ways", [(2, 2, 1, 8192, 32), (2, 8, 4, 4100, 16), (4, 32, 8, 640, 4), (4, 32, 8, 768, 8),
-                                            (6, 8, 8, 2560, 8), (13, 8, 8, 1600, 4), (3, 24, 8, 8128, 8)])
+@pytest.mark.parametrize("B,H,Hkv,S,ways", [(2, 2, 1, 8192, 8), (2, 8, 4, 4100, 8), (4, 32, 8, 640, 1), (4, 32, 8, 768, 1), (6, 8, 8, 2560, 5),
+                                            (13, 8, 8, 1600, 2), (3, 24, 8, 8128, 8), (1, 16, 1, 1536, 3)])
 def test_attention_shared_by_workgroups(B, H, Hkv, S, ways):
-    """Every number of workgroups to a sequence, lengths at the edges of chunks and of the shares; a workspace with room for
-    fewer of them is used as far as it goes, down to the smallest that is accepted.  The last cache is one of those read as non-temporal."""
-    per_way = B * H * 130 * 4
-    assert api.kv4_attention_workspace_bytes(B, H, Hkv, S) == ways * per_way
-    lens = [S, 1, 32 * ways, 32 * ways + 1, 31, S - 31] + [S // 2 + 7 * i for i in range(B)]
-    _attention_case(B, H, Hkv, S, lens[:B], 30 + ways, split=True)
+    """Numbers of ranges from one to eight, every length at the edges of chunks, ranges and of what four of eight waves attend to,
+    with and without the workspace, which is filled with NaN and written no further than it says.  The last but one cache is read as
+    non-temporal, the last has sixteen heads to a KV head."""
+    need = B * H * 130 * 4 * ways if ways > 1 else 0
+    assert api.kv4_attention_workspace_bytes(B, H, Hkv, S) == need
     k, v = wl.make_kv(B, Hkv, S, 128, 31, DEV)
     q = wl.make_queries(B, H, 128, 31, DEV)
     cache = api.kv4_new_cache(B, Hkv, S, DEV)
     api.kv4_append(cache, k.permute(0, 2, 1, 3).contiguous(), v.permute(0, 2, 1, 3).contiguous(),
                    torch.zeros(B, dtype=torch.int32, device=DEV), S)
-    seq = torch.tensor(lens[:B], dtype=torch.int32, device=DEV)
-    whole = api.kv4_attention_decode(q, cache, seq, Hkv, S)
-    least = min(256 // (B * Hkv), 8, S // 512)
-    for room in {ways, ways // 2 + 1, least}:
-        if room < max(least, 1):
-            continue
-        ws = torch.full((room * per_way + 256,), 0xFF, dtype=torch.uint8, device=DEV)
-        got = api.kv4_attention_decode(q, cache, seq, Hkv, S, workspace=ws[:room * per_way])
-        assert (ws[room * per_way:] == 0xFF).all()
-        # two orders of the same FP32 sums, FP16 softmax weights relative to another maximum: 2^-11 of the values
-        assert torch.allclose(whole.float(), got.float(), rtol=2e-3, atol=2e-3)
+    o = _check_cache(cache, B, Hkv, S, k.cpu().numpy(), v.cpu().numpy(), np.ones((B, S), dtype=bool))
+    vmax = np.repeat(np.abs(kv4.kv4_dequantize(o[3], o[4], o[5])).max(axis=(2, 3)), H // Hkv, axis=1)[:, :, None]
+    edges = [S, 0, 1, 31, 32 * ways, 32 * ways + 1, 384 * ways, 384 * ways + 1, S - 31, S // 2 + 7]
+    edges = [min(e, S) for e in edges] + [S // 3] * (-len(edges) % B)
+    for at in range(0, len(edges), B):
+        lens = edges[at:at + B]
+        seq = torch.tensor(lens, dtype=torch.int32, device=DEV)
+        ws = torch.full((max(need, 16) + 256,), 0xFF, dtype=torch.uint8, device=DEV)
+        ref = kv4.attention_decode(q.cpu().numpy(), *o, np.array(lens))
+        for room in (None, ws[:max(need, 16)]):
+            got = api.kv4_attention_decode(q, cache, seq, Hkv, S, workspace=room).cpu().numpy().astype(np.float64)
+            assert (np.abs(got - ref) <= 1e-3 * np.abs(ref) + 1e-3 * vmax).all(), (lens, room is None)
+        assert (ws[max(need, 16):] == 0xFF).all() and (need or (ws == 0xFF).all())
+    if need:
+        with pytest.raises(api.QoqError):
+            api.kv4_attention_decode(q, cache, seq, Hkv, S, workspace=ws[:need - 16])
+
+
+@pytest.mark.parametrize("B,H,Hkv,S,lens", [(2, 8, 2, 700, [70, 385]), (3, 2, 2, 700, [0, 1, 33]), (140, 4, 2, 150, [1, 17, 96, 150]),
+                                            (2, 8, 2, 4096, [70, 1111]), (2, 9, 1, 2048, [31, 513]), (24, 8, 8, 1024, [5, 300, 1024]), (100, 8, 8, 300, [3, 290])])
+def test_attention_ignores_what_lies_past_the_lengths(B, H, Hkv, S, lens):
+    """Eight waves and four, whole sequences and ranges, both forms of the matrix product, a cache read as non-temporal: first chunks and ranges
+    that lie past the end of a sequence hold NaN parameters in one cache and zeros in the other."""
+    k, v = wl.make_kv(B, Hkv, S, 128, 53, DEV)
+    q = wl.make_queries(B, H, 128, 53, DEV)
+    k, v = k.permute(0, 2, 1, 3).contiguous(), v.permute(0, 2, 1, 3).contiguous()
+    seq = [lens[i % len(lens)] for i in range(B)]
+    size = api.kv4_cache_bytes(1, Hkv, S)
+    need = api.kv4_attention_workspace_bytes(B, H, Hkv, S)
+    for split in ((False, True) if need else (False,)):
+        outs = []
+        for fill in (0x00, 0xFF):
+            cache = torch.full((B * size,), fill, dtype=torch.uint8, device=DEV)
+            for b, n in enumerate(seq):
+                if n:
+                    api.kv4_append(cache[b * size:(b + 1) * size], k[b:b + 1, :n].contiguous(), v[b:b + 1, :n].contiguous(),
+                                   torch.zeros(1, dtype=torch.int32, device=DEV), S)
+            ws = torch.full((need,), 0xFF, dtype=torch.uint8, device=DEV) if split else None
+            outs.append(api.kv4_attention_decode(q, cache, torch.tensor(seq, dtype=torch.int32, device=DEV), Hkv, S, workspace=ws))
+        assert torch.isfinite(outs[1]).all() and torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16)), split
 
 
 def test_attention_long_sequence_many_pages():
