@@ -290,10 +290,11 @@ constexpr int decode_lds_bytes(int waves, int columns) { return waves * columns 
 // the chip (grouped-query models).  EARLY (whole sequences): every wave's first chunk is known before the length is, so its loads go out
 // at once, where they would wait for that word to come from memory (4 x 256 tokens of 8 KV heads 4.42 -> 4.35 us).  Not where
 // there are more workgroups than are resident: others then hide that wait, and chunks past the end are read in vain (64 x 128 of
-// 32 heads 11.5 us, 11.9 with them).
-// NT: codes as non-temporal, for caches so large that the 256 MB memory-side cache cannot hold them until the next step (64 x 1024
-// tokens of 32 heads in a decoder layer 42 -> 32 us; 30 x 1500 of 8 heads, 49 MB, 1.1 us less, 20 x 300 of 32, 26 MB, 0.5, below that
-// nothing; repeated alone, where the cache does fit, up to 8% more).
+// 32 heads 11.5 us, 11.9 with them).  Nor with NT, where what is read in vain comes from memory each time (192 pairs of 64 tokens in caches
+// for 1000 3.5 us, 3.9 with them; longer ones gain 1% at most).
+// NT: codes as non-temporal, for caches so large that the 256 MB memory-side cache cannot hold them until the next step (one call after
+// 400 MB of other data: 64 x 1024 tokens of 32 heads 99 -> 62 us, of which 400 tokens each are live 47 -> 32, 31 x 2000 of 8 heads 31 -> 21;
+// the same cache again and again, where its live part does fit, up to 7% more: 1024 pairs of 1000 tokens 24.5 and 26.2 us).
 template <int NW, int PK, bool SPLIT, bool EARLY, bool NT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(PK == 1 || NW == 8 ? 2 : 3))) void kv4_decode_kernel(
     const __half* __restrict__ q, const uint8_t* __restrict__ cache, const int32_t* __restrict__ seq_lens, __half* __restrict__ out,
@@ -652,8 +653,9 @@ static void launch_decode_as(int waves, dim3 grid, const __half* q, const uint8_
                              int64_t S_max, __half* out, float* ws, int ns, hipStream_t s)
 {
     const size_t lds = (size_t)decode_lds_bytes(waves, PK * R);
-    auto* kernel = waves == 8 ? kv4_decode_kernel<8, PK, SPLIT, !SPLIT, NT>
-                              : grid.x <= 3 * 256 ? kv4_decode_kernel<4, PK, SPLIT, !SPLIT, NT> : kv4_decode_kernel<4, PK, SPLIT, false, NT>;
+    constexpr bool early = !SPLIT && !NT;
+    auto* kernel = waves == 8 ? kv4_decode_kernel<8, PK, SPLIT, early, NT>
+                              : grid.x <= 3 * 256 ? kv4_decode_kernel<4, PK, SPLIT, early, NT> : kv4_decode_kernel<4, PK, SPLIT, false, NT>;
     kernel<<<grid, 64 * waves, lds, s>>>(q, cache, seq_lens, out, ws, (int)Hkv, R, (int)S_max, ns);
 }
 
