@@ -269,8 +269,8 @@ int qoq_kv4_unpack(const void* cache, int64_t B, int64_t Hkv, int64_t S_max, int
  * 69, 70, 71 = activation-stationary kernel with 16 / 32 / 64 tokens per tile (activations resident in registers,
  * only weights streamed; K beyond what a workgroup holds is cut into slices that meet in the workspace; as 16 / 32 / 64 where
  * that would take more than 65536 arrival counters);
- * 128, 129, 131 = compute-bound kernel with tiles of 256 x 256, 128 x 256, 256 x 192 (tokens x channels; 131 without slices also
- * 128 x 192 with two workgroups per compute unit); 132 = two workgroups per compute unit, 128 x 256 (without slices also 128 x 192); 130 = eight waves per tile of 128 or 256 channels and equal shares of at most 144 tokens.
+ * 128, 129, 131 = compute-bound kernel with tiles of 256 x 256, 128 x 256, 256 x 192 (tokens x channels; 131 per channel without
+ * slices is 128 x 192 with two workgroups per compute unit); 132 = two workgroups per compute unit, 128 x 256 (without slices also 128 x 192); 130 = eight waves per tile of 128 or 256 channels and equal shares of at most 144 tokens.
  * split_k >= 0 (0 = auto): for the compute-bound kernel the number of k-slices per output tile (one with more than 65536 tiles), for the
  * streaming kernels the number of workgroups the stream of work units is dealt to (activation-stationary kernels:
  * workgroups per token tile and k-slice that share the layer's 16-channel fragments).

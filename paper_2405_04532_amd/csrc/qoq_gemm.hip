@@ -40,6 +40,7 @@
 
 #include "qoq_internal.h"
 #include "qoq_gemm_common.h"
+#include "qoq_tiles.h"
 #include "qoq_walk.h"
 #include "qoq_workspace.h"
 
@@ -1514,12 +1515,9 @@ void launch_mma(const GemmDev& p, bool fp16, hipStream_t s)
     else launch_gemm_kernel(mma_kernel<GROUP, OUT_I32, CF, WM>, grid, kMmaThreads, s, p);
 }
 
-bool two_per_cu_narrow(int64_t M, int64_t N, int64_t G, int mode);
-int two_per_cu_channels(int64_t M, int64_t N, int64_t G, int mode);
-
 // tile_m selects the kernel and its shape: 16 / 32 / 64 = streaming kernel with that many tokens per tile;
-// 128 = compute-bound kernel, 256 tokens x 256 channels; 129 = 128 tokens x 256 channels; 131 = 192 channels, 256 tokens or, without
-// slices, 128 and two workgroups per compute unit; 132 = 128 tokens, two per compute unit, 256 channels or 192 without slices; 130 = eight waves on up to 144 tokens x 128 or 256 channels.  The error of a launch is read, and thereby cleared,
+// 128 = compute-bound kernel, 256 tokens x 256 channels; 129 = 128 tokens x 256 channels; 131 = 192 channels, 256 tokens or, per channel
+// without slices, 128 and two workgroups per compute unit; 132 = 128 tokens, two per compute unit, 256 channels or 192 without slices; 130 = eight waves on up to 144 tokens x 128 or 256 channels.  The error of a launch is read, and thereby cleared,
 // once: by the launcher of another file that made it, or here.
 template <bool GROUP>
 hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStream_t s)
@@ -1557,7 +1555,7 @@ hipError_t launch_any(const GemmDev& p, int tile_m, int nwg, bool fp16, hipStrea
         if (eight_wave_width(p.M, p.N, p.S) == 128) return GROUP ? launch_mma8_group_128(p, mf, s) : launch_mma8_channel_128(p, mf, s);
         return GROUP ? launch_mma8_group_256(p, mf, s) : launch_mma8_channel_256(p, mf, s);
     } else if (tile_m == 131) {
-        if (p.S == 1 && two_per_cu_narrow(p.M, p.N, p.G, GROUP ? 0 : 1)) return launch_mma16(p, 192, GROUP, fp16, s);
+        if (p.S == 1 && two_per_cu_narrow(GROUP ? 0 : 1)) return launch_mma16(p, 192, GROUP, fp16, s);
         launch_mma<GROUP, 3, 2>(p, fp16, s);
     } else if (tile_m == 132) {
         return launch_mma16(p, p.S == 1 ? two_per_cu_channels(p.M, p.N, p.G, GROUP ? 0 : 1) : 256, GROUP, fp16, s);
@@ -1632,26 +1630,6 @@ static double mma_cost(int64_t M, int64_t N, int64_t G, int tile_m, int& S)
     const double per_group = light * (1.0 + 0.45 * load * load);
     return (double)rounds * (8.0 + per_group * (double)((G + S - 1) / S)) +
            (S > 1 ? (tile_m == 128 ? 30.0 : tile_m == 131 ? 22.0 : 9.0) : 0.0);
-}
-
-// Times of the two-per-CU tiles, 128 tokens x 192 (tile_m 131 without slices) or 256 channels (132), in microseconds: whole rounds of 512
-// workgroups, what is left over two per compute unit or alone, each at a pace that grows with the share of the compute units that are
-// busy.  Fitted to 18500 times of drawn shapes (129 ... 3000 tokens, K = 1024 ... 14336 and 28672, weights mostly from memory; standard
-// deviation 4 to 8%).  Where the plan had been 256 channels the narrow tile is taken for a fifth of the shapes, which run 8% (per
-// channel 11%) faster, 4 of 630 more than 2% slower, by 4%: 4096 x 22016 at 700 tokens 83 -> 75 us, 4096 x 12288 at 1500 82.9 -> 77,
-// per channel at 1024 tokens (256 x 192 tiles of one workgroup per compute unit) 52.8 -> 46.5.
-static double two_per_cu_cost(int64_t M, int64_t N, int64_t G, int mode, int64_t channels)
-{
-    struct Fit { double start, round, pair, alone, share, per_mb, half; };
-    static const Fit fits[2][2] = {                          // [channels][mode]
-        {{0.41, 7.66, 1.269, 0.740, 0.242, 0.0226, 0.604}, {0.84, 7.15, 1.063, 0.641, 0.255, 0.0347, 0.664}},
-        {{1.21, 5.92, 1.574, 0.874, 0.230, 0.0109, 0.638}, {2.41, 6.53, 1.315, 0.758, 0.231, 0.0211, 0.672}}};
-    const Fit& t = fits[channels == 256][mode != 0];
-    const int64_t tiles = ((M + 127) / 128) * ((N + channels - 1) / channels), full = tiles / 512, rem = tiles - full * 512;
-    double c = t.start + (double)full * (t.pair * (double)G + t.round);
-    if (rem > 256) c += (t.alone + (t.pair - t.alone) * (t.half + (1.0 - t.half) * (double)(rem - 256) / 256.0)) * (double)G + t.round;
-    else if (rem > 0) c += t.alone * (double)G * (1.0 - t.share + t.share * (double)rem / 256.0) + (full == 0 ? t.round : 0.0);
-    return c + t.per_mb * (double)N * (double)G * (double)kGroup / 2.0e6;
 }
 
 // Streaming kernels: partition and cost of running `tile`-token tiles, in microseconds (fitted to measurements of the
@@ -1847,26 +1825,6 @@ static double measured_cost(int64_t N, int64_t G, int tile_m, int mode, double e
     return t.start + t.scale * estimate + t.per_mb * (double)N * (double)G * (double)kGroup / 2.0e6;
 }
 
-// Tiles of 192 channels without slices: two of 128 tokens per compute unit, or one of 256.  Per channel always two (0.99 to 1.9 of the
-// other's speed over 92 shapes, 1.17 on average); in groups where they are estimated ahead, which is where they have fewer rows of no token or
-// a better last round (4096 x 12288 at 1500 tokens 90 and 77 us, at 1024 53.0 and 52.7; 1280 x 3776 at 2971 22.2 and 25.0).
-namespace {
-bool two_per_cu_narrow(int64_t M, int64_t N, int64_t G, int mode)
-{
-    if (mode != 0) return true;
-    const int64_t wgs = ((M + 255) / 256) * ((N + 191) / 192), rounds = (wgs + 255) / 256;
-    const double load = (double)wgs / (double)(rounds * 256);
-    const double one = (double)rounds * (8.0 + 0.92 * (1.0 + 0.45 * load * load) * (double)G);
-    return two_per_cu_cost(M, N, G, mode, 192) < 0.94 * measured_cost(N, G, 131, mode, one);
-}
-
-// Channels of the tiles of a plan that says two per compute unit (132): 192 where they are estimated 3% ahead.
-int two_per_cu_channels(int64_t M, int64_t N, int64_t G, int mode)
-{
-    return two_per_cu_cost(M, N, G, mode, 192) < 0.97 * two_per_cu_cost(M, N, G, mode, 256) ? 192 : 256;
-}
-}  // namespace
-
 // Eight-wave kernels (tile_m 130): the cheapest number of k-slices, and with it the width, in microseconds: a start, more for every
 // further round of 256 workgroups, per group of a slice a time that grows with the token fragments and with the share of the
 // compute units that are busy, the hand-over of slices, and the weights' way from memory.  Fitted to times half from memory, half
@@ -2015,8 +1973,10 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
     double cost;
     pick_other_config(M, N, K, mode, forced, tile_m, split_k, cost);
     if (forced.tile_m || M <= 64) return;
-    auto narrow_instead = [&] {                              // of four-wave tiles with one workgroup per compute unit
-        if ((tile_m != 129 && !(tile_m == 128 && mode != 0)) || split_k > 1) return;
+    // In place of four-wave tiles with one workgroup per compute unit, per channel: where the plan had been 256 tokens x 256 channels 1.15 to
+    // 1.5 times as fast over 55 shapes, 128 x 256 1.16 on average over 40 (964 x 4864 x 26112 139 -> 121 us, 1206 x 1152 x 4480 16.4 -> 13.4).
+    auto narrow_instead = [&] {
+        if (!two_per_cu_narrow(mode) || (tile_m != 129 && tile_m != 128) || split_k > 1) return;
         if (two_per_cu_cost(M, N, K / kGroup, mode, 192) < 0.97 * cost) { tile_m = 131; split_k = 1; }
     };
     if (!eight_waves || N * K >= ((int64_t)1 << 33)) return narrow_instead();
