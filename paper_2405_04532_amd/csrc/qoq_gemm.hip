@@ -1973,11 +1973,8 @@ void pick_gemm_config(int64_t M, int64_t N, int64_t K, int mode, const GemmTunin
     double cost;
     pick_other_config(M, N, K, mode, forced, tile_m, split_k, cost);
     if (forced.tile_m || M <= 64) return;
-    // In place of four-wave tiles with one workgroup per compute unit, per channel: where the plan had been 256 tokens x 256 channels 1.15 to
-    // 1.5 times as fast over 55 shapes, 128 x 256 1.16 on average over 40 (964 x 4864 x 26112 139 -> 121 us, 1206 x 1152 x 4480 16.4 -> 13.4).
     auto narrow_instead = [&] {
-        if (!two_per_cu_narrow(mode) || (tile_m != 129 && tile_m != 128) || split_k > 1) return;
-        if (two_per_cu_cost(M, N, K / kGroup, mode, 192) < 0.97 * cost) { tile_m = 131; split_k = 1; }
+        if (split_k <= 1 && narrow_instead_of(tile_m, M, N, K / kGroup, mode, cost)) { tile_m = 131; split_k = 1; }
     };
     if (!eight_waves || N * K >= ((int64_t)1 << 33)) return narrow_instead();
     // Taken where the estimate is ahead by a share of the other plan's that depends on how far off that one's estimate is: by

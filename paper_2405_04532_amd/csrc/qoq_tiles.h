@@ -24,15 +24,33 @@ inline double two_per_cu_cost(int64_t M, int64_t N, int64_t G, int mode, int64_t
 }
 
 // Tiles of 192 channels without slices (131): per channel two of 128 tokens per compute unit (1.0 to 1.3 of the speed of one of 256
-// tokens over 142 shapes from 291 tokens on, 1.17 on average), in groups one of 256 tokens.  There the dequantizer has twice the work per
+// tokens over 142 shapes from 291 tokens on, 1.18 on average), in groups one of 256 tokens.  There the dequantizer has twice the work per
 // weight, which the taller tile spreads over twice the tokens: where the estimates had two of them 6% ahead they took 0.954 of the speed
 // over 71 shapes, 60 of them below 0.98 (2221 x 256 x 5248 13.3 and 14.7 us, 1500 x 4096 x 12288 86.9 and 85.9).
 inline bool two_per_cu_narrow(int mode) { return mode != 0; }
 
-// Channels of the tiles of a plan that says two per compute unit (132, without slices): 192 where they are estimated 3% ahead.
+// Channels of the tiles of a plan that says two per compute unit (132, without slices): 192 where they are estimated 3% ahead, from ten groups
+// on (per channel five).  Shorter rows lie outside of what the estimates were fitted to; there the third more workgroups, each with a start
+// and an epilogue, cost what the last round saves: at 5 to 9 groups 0.975 of the speed on average over 33 shapes, 20 of them below 0.98 (1586 x 768 x 11200
+// 25.9 and 27.5 us), from 10 on 1.08 over 150, 1 below; per channel at two to four 1.0 over 39, 7 below (623 x 256 x 19520 13.0 and 14.3), from
+// five on 1.11 over 175, 2 below (328 x 13696 x 27584 150 and 126).
 inline int two_per_cu_channels(int64_t M, int64_t N, int64_t G, int mode)
 {
+    if (G < (mode == 0 ? 10 : 5)) return 256;
     return two_per_cu_cost(M, N, G, mode, 192) < 0.97 * two_per_cu_cost(M, N, G, mode, 256) ? 192 : 256;
+}
+
+// Whether a per-channel plan of four-wave tiles with one workgroup per compute unit (128 or 129, no slices, `cost` estimated) is better off with two
+// of 128 x 192.  In place of 256 x 256 they are 1.15 to 1.5 times as fast over 55 shapes.  In place of 128 x 256, 1.2 times (160, none
+// below 0.98), with two exceptions: rows of five groups or less where they are more than 256 and the wider ones were not, so that the compute units' second workgroup
+// comes on top (0.96 of the speed over 31 shapes, 1920 x 384 x 3648 12.4 and 13.1 us), and layers from 28 MB on, whose weights come from
+// memory to few token tiles, where more and narrower workgroups do not help (0.963 over 23, 256 x 4736 x 18752 32.1 and 35.8; 1.03 to
+// 1.08 over 9 of 20 to 25 MB).
+inline bool narrow_instead_of(int tile_m, int64_t M, int64_t N, int64_t G, int mode, double cost)
+{
+    if (!two_per_cu_narrow(mode) || (tile_m != 128 && tile_m != 129)) return false;
+    if (tile_m == 129 && ((G < 6 && ((M + 127) / 128) * ((N + 191) / 192) > 256) || N * G * (kGroup / 2) >= 28000000)) return false;
+    return two_per_cu_cost(M, N, G, mode, 192) < 0.97 * cost;
 }
 
 // Tokens and channels of the workgroups' tiles that a plan of a compute-bound kernel (128, 129, 131, 132) with S slices runs.

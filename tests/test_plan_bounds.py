@@ -503,3 +503,18 @@ def test_group_mode_keeps_the_tall_narrow_tile(tiles_of):
     assert set(tiles_of([(*s, 0, 131, 1) for s in shapes])) == {(256, 192)}
     assert set(tiles_of([(*s, 1, 131, 1) for s in shapes])) == {(128, 192)}
     assert set(tiles_of([(*s, m, 131, 2) for s in shapes for m in (0, 1)])) == {(256, 192)}
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(1920, 3648, 384, 129), (2735, 2240, 512, 129), (852, 9152, 640, 129), (227, 21888, 3456, 129), (256, 18752, 4736, 129),
+                                        (370, 15808, 5120, 129), (1657, 2816, 512, 131), (945, 5952, 640, 131), (478, 11904, 2816, 131), (1992, 21248, 896, 131)])
+def test_narrow_tiles_only_where_they_are_ahead(M, N, K, tile):
+    """Per channel, in place of 128 x 256 and 256 x 256 tiles: not where the compute units' second workgroup comes on top of short rows, nor
+    where few token tiles wait for many weights."""
+    from paper_2405_04532_amd import api
+    assert api.query_gemm_config(M, N, K, 1) == (tile, 1)
+
+
+def test_two_per_compute_unit_keep_256_channels_for_short_rows(tiles_of):
+    wide = [(1586, 11200, 768, 0), (3464, 5184, 640, 0), (763, 24384, 1024, 0), (2562, 4544, 1152, 0), (623, 19520, 256, 1), (861, 12416, 256, 1), (1063, 10688, 512, 1)]
+    narrow = [(548, 16832, 7168, 0), (1382, 8576, 1280, 0), (328, 27584, 13696, 1), (300, 25600, 640, 1)]
+    assert tiles_of([(*s, 132, 1) for s in wide + narrow]) == [(128, 256)] * len(wide) + [(128, 192)] * len(narrow)
