@@ -126,12 +126,19 @@ __device__ __forceinline__ void finish_shared_blocks(const GemmDev& p, int npart
     for (int x = 0; x < 2 * kRounds * kBatch; ++x) t[x] = (v4i){0, 0, 0, 0};
     bool mine[2];
     int blk[2], wf[2], wl[2];
+    // Workgroup-uniform, and in scalar registers: of quotients of kernel arguments that come in registers the compiler knows that they are
+    // uniform, drops a plain readfirstlane and keeps them in vector ones, with an exec mask around each load below
+    // (15 x 6272 x 512 14.6 us so, 13.7 with the loads behind scalar branches).
+    auto scalar = [](int v) __attribute__((always_inline)) {
+        asm("" : "+v"(v));
+        return __builtin_amdgcn_readfirstlane(v);
+    };
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         mine[k] = k < npart && s_flag[k];                                  // everything here is workgroup-uniform
-        blk[k] = __builtin_amdgcn_readfirstlane(k == 0 ? part_block0 : part_block1);
-        wf[k] = __builtin_amdgcn_readfirstlane((blk[k] * G) / p.upw);
-        wl[k] = __builtin_amdgcn_readfirstlane((blk[k] * G + G - 1) / p.upw);
+        blk[k] = scalar(k == 0 ? part_block0 : part_block1);
+        wf[k] = scalar((blk[k] * G) / p.upw);
+        wl[k] = scalar((blk[k] * G + G - 1) / p.upw);
     }
     // a contributor's partial tile of block blk[k] is its first one iff its run starts inside that block
     auto first_partial = [&](int ww, int k) __attribute__((always_inline)) {
