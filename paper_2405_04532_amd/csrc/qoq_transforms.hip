@@ -182,9 +182,11 @@ __global__ __launch_bounds__(kRankThreads) void channel_order_kernel(const float
 // 8 output channels at a time, whose indices it fetches once for all its rows.  Two-byte gathers from memory, the first
 // version, took 134 us for 4096 x 14336 (117 MB each way; a copy takes 44 us), this one 49 us.  Indices are clamped to
 // the row.  NT: what is read is not wanted again, what is written is (cache_for_output).
-// Where the result fits the 256 MB memory-side cache, the packing that follows finds it there if the source was read past it (see
-// pack_kernel); beyond, every byte of the source kept counts (28672 x 8192 rotated and packed 541 us, 547 with the source read past it).
-bool cache_for_output(int64_t elements) { return 2 * elements <= (int64_t)224 << 20; }
+// Where the 256 MB memory-side cache holds the result and not the source beside it, the packing that follows finds the result there if the source
+// was read past it (22016 x 4096 reordered and packed 110 -> 107 us; see pack_kernel).  Beyond, every byte of the source kept counts (28672 x
+// 8192 rotated and packed 541 us, 547 with the source read past it), and smaller sources lie there already more often than not: 1152 x 15360
+// reordered and packed again and again 37.6 us, 44.2 past the cache, 4096 x 4096 25.0 and 26.9; 4096 x 8192 from memory 50.9 and 49.4.
+bool cache_for_output(int64_t elements) { return 2 * elements > (int64_t)128 << 20 && 2 * elements <= (int64_t)224 << 20; }
 
 constexpr int kGatherThreads = 512;
 constexpr int64_t kGatherLds = 64 << 10;
