@@ -200,7 +200,8 @@ int qoq_w4a8_linear(const void* x_fp16, const void* packed, int64_t M, int64_t N
  *                          Every salience must be finite (a NaN has no place in an order): else QOQ_ERR_SHAPE.
  *   qoq_channel_order      the same order computed on the device: salience [K] FP32 device -> perm [K] INT32 device,
  *                          K <= 32768; nonfinite [1] INT32, device or pinned host memory, receives 1 if some salience is
- *                          not finite (perm is then meaningless), else 0; in host memory it can be seen before perm is complete.
+ *                          not finite (perm is then meaningless), else 0; in host memory it can be seen before perm is complete, so wait for the
+ *                          stream and not for the word.
  *   qoq_gather_channels    dst[r, j] = src[r, perm[j]], FP16 [rows, K] device, perm [K] INT32 device, not in place.
  *   qoq_quant_act_per_token_reordered   qoq_quant_act_per_token of x[:, perm] in one pass (K <= 32768).
  * perm entries outside [0, K) are clamped (a kernel cannot report them).

@@ -338,7 +338,8 @@ def channel_absmax(x):
 
 def channel_order(salience):
     """Permutation (INT32, on the device of `salience`): most salient channel first.  Sorted where `salience` is, up to
-    DEVICE_ORDER_MAX channels; longer ones on the host.  A salience that is not finite raises QoqError either way."""
+    DEVICE_ORDER_MAX channels; longer ones on the host.  A salience that is not finite raises QoqError either way.  Waits for
+    the current stream: the permutation is complete when the call returns, for any stream."""
     if salience.is_cuda and 0 < salience.numel() <= DEVICE_ORDER_MAX:
         sal = salience.detach().to(torch.float32).contiguous()
         return (_native or _load_native()).channel_order(sal)

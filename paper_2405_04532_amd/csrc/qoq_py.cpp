@@ -6,7 +6,6 @@
 #include <Python.h>
 
 #include <algorithm>
-#include <chrono>
 
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
@@ -397,10 +396,10 @@ PyObject* set_raise_status(PyObject*, PyObject* f)
     Py_RETURN_NONE;
 }
 
-// The order of salient channels, and whether it is one: the kernel's first workgroup says so in pinned host memory, about when
-// the others begin to sort, so the caller's next launches are issued while they do (through a device tensor's value, copied
-// when the kernel was done: 28 us a call and 11 of them without work on the GPU).  Where the stream has other work in front the wait is
-// the stream's.
+// The order of salient channels, and whether it is one: the kernel says so in pinned host memory.  The call returns when the order is complete,
+// which callers may then use, and salience reuse, on any stream.  (Returning with the verdict, which is there when the others begin to
+// sort, 4096 x 14336 reordered and packed takes 96 us a pass and not 109, but other streams then read an order that is not there yet.  Flags that
+// the sorting workgroups set when their parts are in memory, polled in place of the stream, 108; with a system-wide fence each 113.)
 PyObject* channel_order(PyObject*, PyObject* const* a, Py_ssize_t n)    // salience
 {
     HANDLE_TH_ERRORS
@@ -424,9 +423,7 @@ PyObject* channel_order(PyObject*, PyObject* const* a, Py_ssize_t n)    // salie
     if (!call([&] {
             const int status = qoq_channel_order(sp, K, pp, verdict, s);
             if (status != QOQ_OK) return status;
-            const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(100);
-            while (__atomic_load_n(verdict, __ATOMIC_ACQUIRE) < 0 && std::chrono::steady_clock::now() < until) {}
-            if (__atomic_load_n(verdict, __ATOMIC_ACQUIRE) < 0 && hipStreamSynchronize(s) != hipSuccess) return (int)QOQ_ERR_HIP;
+            if (hipStreamSynchronize(s) != hipSuccess) return (int)QOQ_ERR_HIP;
             const int v = __atomic_load_n(verdict, __ATOMIC_ACQUIRE);
             return v == 0 ? (int)QOQ_OK : v > 0 ? (int)QOQ_ERR_SHAPE : (int)QOQ_ERR_HIP;
         }))

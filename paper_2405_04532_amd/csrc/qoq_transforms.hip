@@ -107,8 +107,7 @@ __global__ __launch_bounds__(1024) void channel_absmax_columns_kernel(const uint
 // where comparing every pair took 64 (14336 channels: 25.5 us; a host sort with its copies 0.7 ms): 10.8 us, 19 if all are equal, which all
 // meet in one counter, for K <= kRankMaxK.
 // bad[0] = 1 if some salience is not finite (the order is then meaningless), else 0: the first workgroup's work, which it stores past
-// the caches as soon as it knows it.  A host that waits for it in pinned memory goes on while the others sort (4096 x 14336
-// reordered and packed 109.6 -> 95.7 us a pass).
+// the caches, so that it may lie in pinned host memory.
 constexpr int kRankMaxK = 32768, kRankThreads = 1024, kRankAhead = 8, kCheckAhead = 16;
 __global__ __launch_bounds__(kRankThreads) void channel_order_kernel(const float* __restrict__ salience, int K, int32_t* __restrict__ perm,
                                                                      int32_t* __restrict__ bad)

@@ -1,6 +1,7 @@
 """GPU parity of the data-free offline transforms (channel salience, order, gather, reordered activation
 quantizer, Hadamard rotation) against the CPU oracle, through the C ABI.  Everything here is exact: indices,
 FP16 bit patterns, INT8 codes, INT32 accumulators."""
+import ctypes
 import math
 
 import numpy as np
@@ -77,6 +78,60 @@ def test_channel_order_behind_other_work_and_under_capture():
         graph.replay()
     torch.cuda.synchronize()
     assert (out == 1).all()
+
+
+def test_channel_order_is_complete_when_the_call_returns():
+    """Read on another stream without an event between, and salience overwritten there: 32768 channels of one value, which all meet in one counter
+    and take the sort longest, so that its verdict on the salience is there long before the order is; the order's memory held other values."""
+    K = 32768
+    want = torch.arange(K, dtype=torch.int32)
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    for _ in range(4):
+        with torch.cuda.stream(side):
+            sal = torch.full((K,), 2.5, device=DEV)
+            stale = torch.full((K,), -1, dtype=torch.int32, device=DEV)
+            side.synchronize()
+            del stale
+            perm = api.channel_order(sal)
+        with torch.cuda.stream(other):
+            sal.fill_(float("nan"))
+            seen = perm.clone()
+        other.synchronize()
+        assert torch.equal(seen.cpu(), want)
+
+
+@pytest.mark.parametrize("blocking", [False, True])
+def test_channel_order_on_the_default_stream_beside_a_capture(blocking):
+    """While another stream is captured: beside one that the default stream does not wait for, the order; beside one that it does, an error before
+    anything is launched.  Neither the capture nor the next launch is the worse for it."""
+    sal = torch.rand(300, device=DEV)
+    want = torch.argsort(sal, descending=True, stable=True).to(torch.int32)
+    out = torch.zeros(8, device=DEV)
+    handle = ctypes.c_ulonglong(0)
+    if blocking:
+        assert int(torch.cuda.cudart().cudaStreamCreate(ctypes.addressof(handle))) == 0
+    side = torch.cuda.ExternalStream(handle.value) if blocking else torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    assert torch.equal(api.channel_order(sal), want)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        out += 1
+        with torch.cuda.stream(torch.cuda.default_stream()):
+            if blocking:
+                with pytest.raises(RuntimeError):
+                    api.channel_order(sal)
+            else:
+                order = api.channel_order(sal)
+        out += 2
+    for n in range(1, 4):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (out == 3 * n).all()
+        assert torch.equal(api.channel_order(sal), want) and (blocking or torch.equal(order, want))
+    torch.cuda.synchronize()
+    del graph
+    if blocking:
+        assert int(torch.cuda.cudart().cudaStreamDestroy(handle.value)) == 0
 
 
 @pytest.mark.parametrize("rows,K", [(1, 8), (5, 8192), (3, 8200), (7, 16392), (2, 32768), (2, 32776)])
