@@ -1493,7 +1493,7 @@ void launch_stream(const GemmDev& p, bool fp16, dim3 grid, hipStream_t s)
 {
     // 64-token tiles: the LDS-staged kernel; smaller tiles: the register-streaming kernel (measured faster there:
     // its activation traffic shrinks with the tile while the staged kernel's per-iteration barriers do not)
-    const bool nt = weights_pass_by(p, grid, 96);
+    const bool nt = weights_pass_by(p, grid, kPassBy);
     if constexpr (MF >= 3) {
         if (fp16 && nt) launch_gemm_kernel(stream_kernel<MF, GROUP, OUT_FP16, true>, grid, kStreamThreads, s, p);
         else if (fp16) launch_gemm_kernel(stream_kernel<MF, GROUP, OUT_FP16, false>, grid, kStreamThreads, s, p);
@@ -1508,7 +1508,7 @@ void launch_stream(const GemmDev& p, bool fp16, dim3 grid, hipStream_t s)
 template <int NB, int MF, bool GROUP>
 void launch_lockstep(const GemmDev& p, bool fp16, dim3 grid, hipStream_t s)
 {
-    if (fp16 && weights_pass_by(p, grid, 96)) launch_gemm_kernel(lockstep_kernel<NB, MF, GROUP, OUT_FP16, true>, grid, kStreamThreads, s, p);
+    if (fp16 && weights_pass_by(p, grid, kPassBy)) launch_gemm_kernel(lockstep_kernel<NB, MF, GROUP, OUT_FP16, true>, grid, kStreamThreads, s, p);
     else if (fp16) launch_gemm_kernel(lockstep_kernel<NB, MF, GROUP, OUT_FP16, false>, grid, kStreamThreads, s, p);
     else launch_gemm_kernel(lockstep_kernel<NB, MF, GROUP, OUT_I32, false>, grid, kStreamThreads, s, p);
 }

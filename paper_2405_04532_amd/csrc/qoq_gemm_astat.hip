@@ -447,7 +447,7 @@ __global__ __launch_bounds__(kAsThreads) void astat_linear_kernel(QOQ_GEMM_PARAM
 template <int MF, int J, int R, bool GROUP, int OUT, int ROWS>
 void launch_nt(const GemmDev& p, dim3 grid, hipStream_t s)
 {
-    if (weights_pass_by(p, grid, p.S == 1 ? 40 : 96)) launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT, ROWS, true>, grid, kAsThreads, s, p);
+    if (weights_pass_by(p, grid, p.S == 1 ? kPassByWhole : kPassBy)) launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT, ROWS, true>, grid, kAsThreads, s, p);
     else launch_gemm_kernel(astat_kernel<MF, J, R, GROUP, OUT, ROWS, false>, grid, kAsThreads, s, p);
 }
 template <int MF, int J, int R, bool GROUP>
@@ -474,7 +474,7 @@ void launch_deep_rows(const GemmDev& p, dim3 grid, hipStream_t s)
 template <bool GROUP, int OUT>
 void launch_deep(const GemmDev& p, dim3 grid, hipStream_t s)
 {
-    if (OUT == OUT_FP16 && weights_pass_by(p, grid, p.S == 1 ? 40 : 96)) p.M <= 8 ? launch_deep_rows<GROUP, OUT, 8, OUT == OUT_FP16>(p, grid, s) : launch_deep_rows<GROUP, OUT, 16, OUT == OUT_FP16>(p, grid, s);
+    if (OUT == OUT_FP16 && weights_pass_by(p, grid, kPassByWhole)) p.M <= 8 ? launch_deep_rows<GROUP, OUT, 8, OUT == OUT_FP16>(p, grid, s) : launch_deep_rows<GROUP, OUT, 16, OUT == OUT_FP16>(p, grid, s);
     else p.M <= 8 ? launch_deep_rows<GROUP, OUT, 8, false>(p, grid, s) : launch_deep_rows<GROUP, OUT, 16, false>(p, grid, s);
 }
 
@@ -517,7 +517,7 @@ void launch_linear_nt(const GemmDev& p, const TokensIn& in, dim3 grid, hipStream
 template <bool GROUP, int CHUNKS>
 void launch_linear(const GemmDev& p, const TokensIn& in, dim3 grid, hipStream_t s)
 {
-    weights_pass_by(p, grid, p.S == 1 ? 40 : 96) ? launch_linear_nt<GROUP, CHUNKS, true>(p, in, grid, s) : launch_linear_nt<GROUP, CHUNKS, false>(p, in, grid, s);
+    weights_pass_by(p, grid, kPassByWhole) ? launch_linear_nt<GROUP, CHUNKS, true>(p, in, grid, s) : launch_linear_nt<GROUP, CHUNKS, false>(p, in, grid, s);
 }
 
 // Elements of M tokens of K, M rounded up to a power of two: what the threads of a workgroup share.

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "qoq_tiles.h"
+
 namespace qoq {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -59,12 +61,7 @@ __device__ __forceinline__ GemmDev gemm_dev(QOQ_GEMM_PARAMS, const GemmTail& t)
     p.counters = t.counters; p.parts = t.parts; p.token_sum = t.token_sum;
     return p;
 }
-// Weights that are read once, by one token tile, and are so many that the memory-side cache (256 MB) does not hold them
-// until the model's next step: loaded as non-temporal they leave it alone, which is faster (us from memory, before and after: 16 x 8192 x
-// 57344 47.8 -> 40.5, 37 51.8 -> 46, 8 x 28672 x 8192 26.9 -> 25.6).  Where a program's weights do fit, it is slower: the activation-
-// stationary kernels without slices by 2 to 5% (16 x 4096 x 22016 10.8 and 11.1; from memory 12.7 and 11.8), which therefore do it
-// from 40 MB on (below, 4096 x 12288 gains nothing either way), the others by up to 20%, which do it from 96 MB on.
-inline bool weights_pass_by(const GemmDev& p, dim3 grid, int megabytes) { return grid.y == 1 && (size_t)p.N * p.K / 2 >= (size_t)megabytes << 20; }
+inline bool weights_pass_by(const GemmDev& p, dim3 grid, int64_t least) { return weights_pass_by(p.N, p.K, grid.y, least); }
 // `more`: further arguments of the kernel, behind the structure.
 template <class Kernel, class... More>
 void launch_gemm_kernel(Kernel* kernel, dim3 grid, int threads, hipStream_t s, const GemmDev& p, const More&... more)

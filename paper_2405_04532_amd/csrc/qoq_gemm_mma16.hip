@@ -48,7 +48,8 @@ __device__ __forceinline__ void unrolled_over(F&& f, std::integer_sequence<int, 
 template <int N, class F>
 __device__ __forceinline__ void unrolled(F&& f) { unrolled_over(f, std::make_integer_sequence<int, N>()); }
 
-// kNF: 16-channel fragments of a wave = blocks of eight chunks per half-stage; 4 = tiles of 256 channels, 3 = of 192
+// kNF: 16-channel fragments of a wave = blocks of eight chunks per half-stage; 4 = tiles of 256 channels, 3 = of 192, which are never cut
+// into k-slices
 template <bool GROUP, int OUT, int kNF>
 __global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(QOQ_GEMM_PARAMS, GemmTail tail)
 {
@@ -307,6 +308,7 @@ __global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(QOQ_GEMM_PARAMS, 
     // ---- split-k: every slice writes its partial tile through to memory and bumps the tile's counter; the last
     // one to arrive adds the others' (integer sums: exact, order independent) and alone runs the epilogue.
     // Same fence-free hand-over as in the streaming kernels; the counter is left at zero for the next launch.
+    if constexpr (kNF == 4)
     if (p.S > 1) {
         constexpr int NJ = kNF * 8;                      // int4 per thread in a partial tile
         const int tile_id = tm * n_tiles + tn;
@@ -414,6 +416,7 @@ __global__ __launch_bounds__(kMmaThreads, 2) void mma16_kernel(QOQ_GEMM_PARAMS, 
 
 hipError_t launch_mma16(const GemmDev& p, int channels, bool group, bool fp16, hipStream_t s)
 {
+    if (channels != 256 && (channels != 192 || p.S != 1)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(((p.N + channels - 1) / channels) * ((p.M + kTileM - 1) / kTileM)), (unsigned)p.S);
     auto* wide = group ? (fp16 ? mma16_kernel<true, OUT_FP16, 4> : mma16_kernel<true, OUT_I32, 4>)
                        : (fp16 ? mma16_kernel<false, OUT_FP16, 4> : mma16_kernel<false, OUT_I32, 4>);

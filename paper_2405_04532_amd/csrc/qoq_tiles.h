@@ -1,5 +1,5 @@
-// Which kernel a launch plan's code stands for where that depends on the shape (internal to the library; the host check of the
-// plans reads the same rules).
+// Which kernel a launch plan's code stands for where that depends on the shape, and in which form it loads its weights (internal to the
+// library; the host check of the plans reads the same rules).
 #pragma once
 #include "qoq_layout.h"
 
@@ -60,5 +60,14 @@ inline void compute_bound_tile(int64_t M, int64_t N, int64_t G, int mode, int ti
     tokens = tile_m == 129 || tile_m == 132 || narrow ? 128 : 256;
     channels = tile_m == 131 ? 192 : tile_m == 132 && S == 1 ? two_per_cu_channels(M, N, G, mode) : 256;
 }
+
+// Weights that are read once, by one token tile, and are so many that the memory-side cache (256 MB) does not hold them
+// until the model's next step: loaded as non-temporal they leave it alone, which is faster (us from memory, before and after: 16 x 8192 x
+// 57344 47.8 -> 40.5, 37 51.8 -> 46, 8 x 28672 x 8192 26.9 -> 25.6).  Where a program's weights do fit, it is slower: the activation-
+// stationary kernels without slices by 2 to 5% (16 x 4096 x 22016 10.8 and 11.1; from memory 12.7 and 11.8), which therefore do it
+// from 40 MB on (below, 4096 x 12288 gains nothing either way), the others by up to 20%, which do it from 96 MB on (46 x 11136 x
+// 18688, 104 MB again and again, 34.4 and 37.8).
+constexpr int64_t kPassByWhole = (int64_t)40 << 20, kPassBy = (int64_t)96 << 20;
+inline bool weights_pass_by(int64_t N, int64_t K, int64_t token_tiles, int64_t least) { return token_tiles == 1 && N * K / 2 >= least; }
 
 }  // namespace qoq
