@@ -941,8 +941,9 @@ def test_captured_calls_in_one_workspace_and_without(api):
                                    (5, 11008, 8000), (16, 13952, 6208), (9, 16384, 12288), (32, 16512, 12288), (64, 16512, 12288),
                                    (40, 8192, 25600), (60, 10240, 20480)])
 def test_gemm_weights_that_pass_by_the_caches(api, M, K, N, mode):
-    """Layers whose weights are loaded as non-temporal: groups that are no multiple of the waves, runs of fragments of uneven
-    length, every kernel that has that form.  Against the accumulators of the same call, which are loaded the other way and compared
+    """Layers whose weights are loaded as non-temporal, as they are planned (activation-stationary kernels of all widths, with slices and in one
+    launch with the quantizer, two and four token fragments of the streaming kernels, pairs): groups that are no multiple of the waves, runs
+    of fragments of uneven length.  Against the accumulators of the same call, which are loaded the other way and compared
     with the oracle elsewhere, scaled in FP64: two FP32 roundings and one to FP16 lie between."""
     g = torch.Generator(device=DEV).manual_seed(M + K + N)
     blob = api.pack_weights(torch.randn((N, K), generator=g, device=DEV, dtype=torch.float16) * 0.02, mode)
@@ -956,10 +957,54 @@ def test_gemm_weights_that_pass_by_the_caches(api, M, K, N, mode):
         assert ((got.double() - want).abs() <= want.abs() * (2.0 ** -11 + 2.0 ** -22) + 2.0 ** -25).all()
 
 
+# streaming kernel with 16, 32, 48 and 64 tokens; quads, pairs of 48 and 64, of 32 and 16 tokens
+PASS_BY_FORMS = [(16, 1), (16, 13), (32, 25), (64, 40), (64, 64), (66, 33), (66, 48), (66, 49), (65, 37), (65, 60), (67, 30), (68, 10)]
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_every_streaming_kernel_loads_weights_that_pass_by(api, mode):
+    """Each streaming and lockstep kernel on a layer of 96 MB, the least that they load as non-temporal, 57 groups (an odd number, no multiple of the
+    waves); the plan is forced and asked for.  Bounds of the test above."""
+    K, N = 7296, 27648
+    assert 96 << 20 <= N * K // 2 < 97 << 20
+    g = torch.Generator(device=DEV).manual_seed(K + mode)
+    blob = api.pack_weights(torch.randn((N, K), generator=g, device=DEV, dtype=torch.float16) * 0.02, mode)
+    s = api.unpack_weights(blob, N, K, mode)[3].double()
+    for code, M in PASS_BY_FORMS:
+        x = torch.randn((M, K), generator=g, device=DEV, dtype=torch.float16)
+        qx, sx, rowsum, _ = api.quant_act_per_token(x)
+        rs = rowsum if mode else None
+        want = api.w4a8_gemm_i32(qx, blob, N, mode, rowsum=rs).double() * sx.double()[:, None] * s[None, :]
+        api.set_gemm_config(code, 0)
+        try:
+            assert api.query_gemm_config(M, N, K, mode)[0] == code
+            got = api.w4a8_gemm(qx, sx, blob, N, mode, rowsum=rs).double()
+        finally:
+            api.set_gemm_config(0, 0)
+        assert ((got - want).abs() <= want.abs() * (2.0 ** -11 + 2.0 ** -22) + 2.0 ** -25).all(), (code, M)
+
+
+@pytest.mark.parametrize("M,N,K,mode", [(129, 320, 5120, 0), (300, 832, 5120, 0), (257, 448, 5248, 0), (129, 320, 5120, 1)])
+def test_gemm_two_per_compute_unit_with_192_channels(api, M, N, K, mode):
+    """Tiles of 128 x 192 where a plan says two per compute unit, in group mode too (test_plan_bounds.py asks the rule for these shapes)."""
+    w, x = rand_inputs(M, N, K, seed=3 * M + N)
+    blob = api.pack_weights(w, mode)
+    qx, sx, rowsum, _ = api.quant_act_per_token(x)
+    ref = (ogemm.forward_per_channel if mode else ogemm.forward_group)(_np(w), _np(x))
+    api.set_gemm_config(132, 1)
+    try:
+        acc = api.w4a8_gemm_i32(qx, blob, N, mode, rowsum=rowsum if mode else None)
+        out = api.w4a8_gemm(qx, sx, blob, N, mode, rowsum=rowsum if mode else None)
+    finally:
+        api.set_gemm_config(0, 0)
+    assert (_np(acc).astype(np.int64) == ref["acc"]).all()
+    check_fp16(out, ref["out64"])
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("M,N,K", [(1, 64, 128), (127, 192, 128), (128, 256, 256), (129, 320, 384), (300, 832, 1152), (65, 448, 512), (385, 128, 640)])
 def test_gemm_tiles_of_192_channels_two_per_compute_unit(api, M, N, K, mode):
-    """128 x 192 tiles: one token past a tile, channels that end in the first, second and third block of a tile, one group, two and odd
+    """Tiles of 192 channels without slices, per channel two of 128 tokens per compute unit: one token past a tile, channels that end in the first, second and third block of a tile, one group, two and odd
     numbers of them.  Accumulators exact, FP16 within the tolerance of the other kernels, token sums as well."""
     w, x = rand_inputs(M, N, K, seed=7 * M + N + K)
     blob = api.pack_weights(w, mode)

@@ -114,13 +114,35 @@ static void check_lockstep(int NB, int MF) {
 }
 
 // ---- activation-stationary kernels ---------------------------------------------------------------------------------
-// Weights, constants and partial tiles of a workgroup's fragments: `waves` waves of jeff groups each, kEl int4 per tile.
-static void check_fragments(ll nwg, ll waves, ll S, ll gps, ll m_tiles, ll kEl) {
+// Non-temporal weights come by buffer loads through a window of the codes of 2 R fragments of the run and one of all metadata: what a wave needs
+// is inside, at the unit's own place, and what it does not (slots past the slice, fragments past the run) past the end of the window.
+static void check_windows(ll f0, ll nfr, ll g_lo, ll g_hi, ll waves, ll jeff, ll J, ll R) {
+    const ll nowhere = 0x80000000ll, nf_total = N / 16, whole = G * nf_total * 32;
+    if (whole >= nowhere) { fail = "metadata window"; return; }
+    for (ll fi0 = 0; fi0 < nfr; fi0 += R) {
+        const ll window = std::min(nfr - fi0, 2 * R) * G * 1024;
+        chk("codes", (f0 + fi0) * G * 1024, window, n_codes);
+        for (int w = 0; w < waves; ++w) for (ll j = 0; j < J; ++j) for (ll ahead = fi0 == 0 ? 0 : R; ahead < 2 * R; ++ahead) {
+            const ll g = g_lo + w * jeff + j;
+            const bool valid = j < jeff && g < g_hi, needed = valid && fi0 + ahead < nfr;
+            const ll at = (valid ? g * 1024 : nowhere) + ahead * G * 1024, at_m = (valid ? (g * nf_total + f0) * 32 : nowhere) + (fi0 + ahead) * 32;
+            if (needed ? at + 1024 > window || (f0 + fi0) * G * 1024 + at != ((f0 + fi0 + ahead) * G + g) * 1024 : at < window) { fail = "codes window"; return; }
+            if (at + 1024 > (ll)1 << 32 || at_m + 32 > (ll)1 << 32) { fail = "window offset"; return; }
+            if (mode == 0 && needed) chk("meta", at_m, 32, n_meta);
+            if (!valid && at_m < whole) { fail = "metadata window"; return; }
+        }
+    }
+}
+// Weights, constants and partial tiles of a workgroup's fragments: `waves` waves of jeff groups each (J as compiled, R fragments ahead), kEl int4
+// per tile.
+static void check_fragments(ll nwg, ll waves, ll S, ll gps, ll m_tiles, ll kEl, ll J, ll R) {
+    const bool pass_by = weights_pass_by(N, K, m_tiles, S == 1 ? kPassByWhole : kPassBy);
     const ll nf_total = N / 16, base = nf_total / nwg, rem = nf_total - base * nwg, jeff = cdiv(gps, waves);
     for (ll mt = 0; mt < m_tiles; ++mt) for (ll sl = 0; sl < S; ++sl) for (ll wg = 0; wg < nwg; ++wg) {
         const ll f0 = wg * base + std::min(wg, rem), f1 = f0 + base + (wg < rem ? 1 : 0), g_lo = sl * gps, g_hi = std::min(G, g_lo + gps);
         if (g_lo >= g_hi) { fail = "astat empty slice"; return; }
         if (S > 1 && f1 - f0 > 128) { fail = "astat fragments"; return; }
+        if (pass_by) check_windows(f0, f1 - f0, g_lo, g_hi, waves, jeff, J, R);
         for (ll nf = f0; nf < f1; ++nf) {
             for (int w = 0; w < waves; ++w) for (ll j = 0; j < jeff + 3; ++j) {   // slots past jeff re-read the last group
                 const ll g = std::min(g_lo + w * jeff + std::min(j, jeff - 1), g_hi - 1);
@@ -173,7 +195,7 @@ static void check_astat(int tl) {
             }
         }
     }
-    check_fragments(split, waves, S, gps, m_tiles, MF * 64);
+    check_fragments(split, waves, S, gps, m_tiles, MF * 64, J, deep || J == 8 ? 1 : 2);
 }
 // Few short tokens, quantized by every workgroup in front of its first fragment (512 threads).
 static void check_linear() {
@@ -196,7 +218,7 @@ static void check_linear() {
         const ll row = std::min<ll>(lane & 15, M - 1);
         chk("LDS codes", row * K + ((((w * jeff + j) * 8 + ks * 4 + (lane >> 4)) ^ (row & 7)) * 16), 16, M * K);
     }
-    check_fragments(std::min<ll>(N / 16, 256), 8, 1, G, 1, 64);
+    check_fragments(std::min<ll>(N / 16, 256), 8, 1, G, 1, 64, jeff <= 4 ? 4 : 8, jeff <= 4 ? 2 : 1);
 }
 
 // ---- eight waves on equal token tiles ------------------------------------------------------------------------------
@@ -278,6 +300,15 @@ static void check_mma() {
     const ll n_tiles = cdiv(N, tn), m_tiles = cdiv(M, tm), S = split, gps = cdiv(G, S), nf_total = N / 16;
     const ll kACopies = tm / 64, kUnits = tn / 16, kWCopies = kUnits / 4, tiles = n_tiles * m_tiles;
     if (cdiv(G, gps) != S) { fail = "mma slices"; return; }
+    if (tile == 132 || (tile == 131 && tm == 128)) {           // two per compute unit: a wave's fragments in LDS, places of the three blocks with 192 channels
+        std::vector<char> unit(kUnits);
+        for (int wave = 0; wave < 4; ++wave) for (int f = 0; f < tn / 64; ++f) {
+            const ll u = tn == 256 ? wave * 4 + f : f * 4 + wave;
+            chk("LDS weights", (tn == 256 ? wave * 4 : wave) * 1024 + f * (tn == 256 ? 1024 : 4096), 1024, kUnits * 1024);
+            chk("LDS metadata", u / kWCopies * 256 + u % kWCopies * 32, 32, 1024);
+            if (!fail && unit[u]++) { fail = "a unit twice"; return; }
+        }
+    }
     for (ll t = 0; t < tiles; ++t) for (ll sl = 0; sl < S; ++sl) {
         const ll tmi = t / n_tiles, tni = t % n_tiles, m_base = tmi * tm, n_base = tni * tn, nf_base = tni * kUnits;
         const ll g_first = sl * gps, Gs = std::min(G - g_first, gps), g_last = g_first + Gs - 1;
@@ -408,7 +439,11 @@ def test_every_launch_plan_stays_inside_its_buffers(tmp_path):
     # 48 tokens: the second pass read in full
     ("if (rows == 16 && rp * RP + i * 8 / JP >= MF * 16) continue;", "if (rp * RP + i * 8 / JP >= 32) continue;", "48 64 2048 0 71 4 0 1"),
     # tokens of one launch: a row that takes more chunks than its threads hold
-    ("rows * K <= 2 * 8 * 512 ? 2 : 8", "2", "16 64 2048 0 0 0 0 0")])
+    ("rows * K <= 2 * 8 * 512 ? 2 : 8", "2", "16 64 2048 0 0 0 0 0"),
+    # a window that ends with the fragments that are multiplied, not with those ahead of them
+    ("const ll window = std::min(nfr - fi0, 2 * R) * G * 1024;", "const ll window = std::min(nfr - fi0, R) * G * 1024;", "16 24576 4096 0 69 256 0 1"),
+    # 192 channels: units of the wide tile
+    ("const ll u = tn == 256 ? wave * 4 + f : f * 4 + wave;", "const ll u = wave * 4 + f;", "300 832 1152 1 131 1 0 1")])
 def test_the_checker_catches_a_planted_overrun(tmp_path, right, wrong, plan):
     """Mistakes planted in the host model, the first of which once faulted on the GPU, must be reported."""
     assert CHECKER.count(right) == 1
@@ -419,7 +454,7 @@ def test_the_checker_catches_a_planted_overrun(tmp_path, right, wrong, plan):
         src.write_text(source)
         subprocess.check_call(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2405_04532_amd", "csrc"), str(src), "-o", str(exe)])
         out = subprocess.run([str(exe), str(listing)], capture_output=True, text=True)
-        assert out.returncode == status and ("outside" in out.stdout or "left out" in out.stdout) == bool(status), out.stdout
+        assert out.returncode == status and ("outside" in out.stdout or "left out" in out.stdout or "window" in out.stdout) == bool(status), out.stdout
 
 
 @pytest.mark.parametrize("M,N,K,mode,tile,nwg", [(130, 12288, 4096, 0, 71, 80), (65, 10240, 8192, 0, 70, 80), (100, 10240, 8192, 1, 70, 64),
@@ -516,5 +551,6 @@ def test_narrow_tiles_only_where_they_are_ahead(M, N, K, tile):
 
 def test_two_per_compute_unit_keep_256_channels_for_short_rows(tiles_of):
     wide = [(1586, 11200, 768, 0), (3464, 5184, 640, 0), (763, 24384, 1024, 0), (2562, 4544, 1152, 0), (623, 19520, 256, 1), (861, 12416, 256, 1), (1063, 10688, 512, 1)]
-    narrow = [(548, 16832, 7168, 0), (1382, 8576, 1280, 0), (328, 27584, 13696, 1), (300, 25600, 640, 1)]
+    narrow = [(548, 16832, 7168, 0), (1382, 8576, 1280, 0), (328, 27584, 13696, 1), (300, 25600, 640, 1),
+              (129, 320, 5120, 0), (300, 832, 5120, 0), (257, 448, 5248, 0), (129, 320, 5120, 1)]
     assert tiles_of([(*s, 132, 1) for s in wide + narrow]) == [(128, 256)] * len(wide) + [(128, 192)] * len(narrow)
