@@ -38,7 +38,7 @@ struct GemmDev {
 // How a GemmDev reaches a kernel.  The first fourteen dwords of a kernel's arguments, where they are plain values, arrive in
 // scalar registers with the wave (build.py asks for it): what the first loads need is there when the kernel starts.  A structure
 // does not, and fetching it took every kernel about 0.3 us before its first load went out (the one-token Llama-2-7B decoder
-// layer, ten kernels, 59.5 -> 55.5 us; 16 x 256 x 256 in one launch 4.46 -> 4.09); what only the epilogue needs still comes that way, behind the loads.
+// layer, ten kernels, 59.5 -> 55.5 us; 16 x 256 x 256 in one launch 4.21 -> 4.11); what only the epilogue needs still comes that way, behind the loads.
 struct GemmTail {
     const __half* scales;
     const uint8_t* zeros;

@@ -618,9 +618,10 @@ hipError_t launch_kv4_unpack(const uint8_t* cache, int64_t B, int64_t Hkv, int64
 }
 
 // Number of sequence ranges the split variant would use for this problem (1 = single pass).  Cutting the sequence pays only
-// while the (sequence, KV head) pairs alone leave compute units idle: measured at 8 KV heads, 1 x 8192 tokens goes from 51 to
-// 15 us with 8 ranges and 8 x 2048 from 16 to 11 us with 4, while at 64 sequences (512 pairs) every cut is slower than none
-// (18.6 us whole, 22.2 in 2 ranges, 25.5 in 4): each range repeats the set-up and adds a second launch that merges them.
+// while the (sequence, KV head) pairs alone leave compute units idle: measured at 8 KV heads, 1 x 8192 tokens goes from 37.3 to
+// 10.7 us with 8 ranges and 8 x 2048 from 12.4 to 9.1 us with 4, while at 64 sequences (512 pairs) every cut is slower than none
+// (18.6 us whole, 22.2 in 2 ranges, 25.5 in 4): each range repeats the set-up and adds a second launch that merges them, 2.4 us, which
+// is all that short sequences see (16 tokens 3.6 and 6.0 us; two ranges of 512 are not ahead either, 1 x 1024 of 32 heads 7.6 and 7.9).
 // The host knows what a sequence may grow to, not its length, so a rule by what full caches gain loses on short sequences.  Up to 32
 // workgroups from 640 tokens on, four up to 255 pairs, chunks in turn: full caches up to 1.4 times as fast (32 pairs of 1000 tokens 7.9 -> 5.8
 // us), but 192 pairs of 128 in caches for 4096 3.9 -> 9.0, 32 pairs of 128 in caches for 1000 3.3 -> 5.4, 8 pairs of 400 in caches for 8192

@@ -82,8 +82,8 @@ __device__ __forceinline__ float quarter_min(float v)
 //             (the argument of the activation quantizer).  Per-channel codes are the same quotient plus an integer.
 //   level 2   quotients of small integers by s1 <= 16 (by 15 for s1 itself): multiples of 1/32 (1/15), nudged by 1e-3.
 // PASS_BY (group mode, weights that fit the 256 MB memory-side cache): the codes go past it, so that it keeps the weights that a
-// rotation or reordering has just written (22016 x 4096 rotated and packed 145.6 -> 143.6 us, 10240 x 8192 reordered and packed 148.1 ->
-// 144.6, with the reads of those as non-temporal).  Larger weights are slower so (28672 x 14336 599 us, 604), per-channel ones of any
+// rotation or reordering has just written (22016 x 4096 rotated and packed 145.6 -> 143.6 us when the rotation took 90, 10240 x 8192 reordered
+// and packed 148.1 -> 144.6, with the reads of those as non-temporal).  Larger weights are slower so (28672 x 14336 599 us, 604), per-channel ones of any
 // size (28672 x 8192 99.0, 102.2).
 // Bound by HBM: 22016 x 4096 in group mode in 54 us (226 MB, 4.2 TB/s; a copy moves them in 42 us).  One division of
 // doubles per weight and 4-byte stores 16 bytes apart kept one row per workgroup at 213 us, and it wrote the header by

@@ -407,7 +407,7 @@ __device__ __forceinline__ uint4 hadamard_load(const uint4* __restrict__ src, in
 // in them: whole numbers have one zero, while FP64 sums of FP16 numbers are -0 only where a -0 went in (-0 - (x - x) = -0).
 // 22016 x 4096: a single workgroup per block with one LDS round trip and one barrier per stage, bound by LDS and barriers, took 863 us,
 // these layouts 108 (a copy of the tensor 69) while they were bound by 40 vector instructions per element, half of them
-// addresses and copies of registers, and 90 with LDS for whole FP64 numbers, four workgroups to a compute unit.  Now 78, with eight.
+// addresses and copies of registers, and 90 with LDS for whole FP64 numbers, four workgroups to a compute unit.  Now 72 (in FP64 92), with eight.
 template <int LOGN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void hadamard_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t chunks,
                                                                                                  double scale, bool nt)
@@ -451,7 +451,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void h
 
 // Blocks of 8192 (weights of the usual size then add up to more than 128): the two halves of the FP64 numbers are exchanged one after
 // the other, in half the LDS, which makes four workgroups to a compute unit, not two, and they hide each other's barriers and
-// loads (8192 x 8192 119 -> 100 us, 2048 x 8192 33.3 -> 31.3).
+// loads (8192 x 8192 from memory 119 -> 76 us with the kernel for this one size, 2048 x 8192 33.7 -> 24.5).
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void hadamard_8192_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t chunks,
                                                                                                       double scale, bool nt)
 {
